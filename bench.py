@@ -10,11 +10,13 @@ value = (3 * |E| per step) / (wall time per step): undirected edges per second
 of solve time with the graph resident in HBM.  The result of every eps is
 compared with the CPU oracle and the line reports whether all match exactly.
 
-roofline: the dominant kernel is the similarity/core kernel of the degree
-bucket with the most device time; its algorithmic bytes per launch are
-sum over intersected edges of (4 * smaller-list elements consumed + 8 bytes of
-endpoints + 1 byte of edge state), divided by its launch duration measured
-with HIP events on the library's stream, against 8 TB/s.
+roofline: the cores phase (the count and close kernels of the triangle path),
+which is nearly all of a solve; its algorithmic bytes are 2 per row entry
+looked up and, per edge, 16 of in-edge record, 4 of count, written and read,
+and 4 of neighbour, divided by its duration measured with HIP events on the
+library's stream, against 8 TB/s.  A graph outside that path reports the
+edge-list kernel of the degree bucket with the most device time: 4 bytes per
+smaller-list element consumed and 9 per intersected edge.
 
 cpu_baseline: the oracle (not tuned) on the host cores, on the same graph at
 eps = 1/2, mu = 5: closed counts of every edge plus clustering.
@@ -188,10 +190,18 @@ def main():
     read_gbps = read_bytes / (read_ms * 1e-3) / 1e9
     log(f"streaming copy {args.copy_mib} MiB: {copy_ms:.3f} ms -> {copy_gbps:.0f} GB/s; "
         f"read-only stream {read_bytes >> 20} MiB: {read_ms:.3f} ms -> {read_gbps:.0f} GB/s")
+    launch_ms, alg_bytes = ms_b[dom] / launches, bytes_b[dom] / launches
     dom_kernel = "k_hub<0>" if dom == nb - 1 else f"k_group<0, *> (bucket {dom})"
+    dom_name = f"{dom_kernel}: cores pass, degree bucket {dom}"
+    if ms_b.sum() == 0:  # no pass per bucket: the triangle path
+        launch_ms = sum(st["ms_phase"]["cores"] for st in stats) / launches
+        alg_bytes = sum(2.0 * st["probes"]["cores"] + 28.0 * m for st in stats) / launches
+        achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
+        dom_kernel = "k_tri_block"
+        dom_name = "k_tri_block, k_tri_wave and k_tri_close: cores phase"
     traffic = _traffic_from_profile(dom_kernel)
     byte_models = solve_byte_models(g, stats[-len(EPS_SET):], traffic,
-                                    float(bytes_b[dom] / launches) if launches else None)
+                                    float(alg_bytes) if launches else None)
     log(f"byte models: {byte_models}")
     # every bucket's kernel against the same roofline, and the whole cores pass
     # (the intersection bytes above, and beside them the same plus the classification stream:
@@ -210,7 +220,7 @@ def main():
                         "bytes_incl_classify_per_launch": float(cls_l),
                         "frac_incl_classify": float(cls_l / (ms_l * 1e-3) / 1e9 / HBM_PEAK_GBS) if ms_l > 0 else 0.0})
     cores_ms = sum(st["ms_phase"]["cores"] for st in stats) / launches
-    cores_alg = float(bytes_b.sum() / launches)
+    cores_alg = float(bytes_b.sum() / launches) if ms_b.sum() else float(alg_bytes)
     cores_pass = {"launch_ms": cores_ms, "alg_bytes_per_launch": cores_alg,
                   "frac": cores_alg / (cores_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if cores_ms > 0 else 0.0}
     # the non-degenerate point of this graph (eps = 1/10 has cores and clusters), timed beside the step
@@ -308,10 +318,10 @@ def main():
         "exact_match": exact,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": f"{dom_kernel}: cores pass, degree bucket {dom}",
+                     "kernel": dom_name,
                      "copy_gbps": copy_gbps, "read_gbps": read_gbps,
-                     "launch_ms": float(ms_b[dom] / launches),
-                     "alg_bytes_per_launch": float(bytes_b[dom] / launches)},
+                     "launch_ms": float(launch_ms),
+                     "alg_bytes_per_launch": float(alg_bytes)},
         "cpu_baseline": cpu,
         "pcie_inclusive_edges_per_s": e2e_rate,
         "scan_similarity_ms": sim_ms,

@@ -54,6 +54,10 @@ void release_extra(ExtraRun& x) {
 
 void release(scan_graph* g) {
   part_release(g);
+  tri_release(g->tri);
+  tri_release_scratch(g->tri_s);
+  tri_release_scratch(g->tri_na);
+  if (g->tri_ev) hipEventDestroy(g->tri_ev);
   for (auto& x : g->extra) {
     if (x->stream) hipStreamSynchronize(x->stream);
     release_extra(*x);
@@ -158,6 +162,36 @@ void scan::enqueue_clustering(scan_graph* g, EdgeArgs& A, int32_t* d_labels, uin
   mark(8);
 }
 
+void scan::enqueue_tri(scan_graph* g, const TriScratch& S, int64_t p, int64_t q, int32_t mu, int32_t* d_labels,
+                       uint8_t* d_roles, hipStream_t s, const RunState& R, hipEvent_t* events) {
+  auto mark = [&](int k) {
+    if (events) (void)hipEventRecord(events[k], s);
+  };
+  const TriLayout& T = g->tri;
+  TriArgs a;
+  a.p = (uint64_t)p;
+  a.q = (uint64_t)q;
+  a.mu = mu;
+  const int32_t split = g->opts.hub_outlier ? 1 : 0;
+  mark(0);
+  tri_init(s, T, S, R.lower, R.parent, R.label, R.role);
+  mark(1);
+  tri_count(s, T, S);
+  tri_close(s, T, S, a, R.lower);
+  // the counts are exact: nothing is left to finalise, to merge or to flatten
+  mark(2);
+  mark(3);
+  tri_hook(s, T, S, mu, R.lower, R.parent);
+  mark(4);
+  mark(5);
+  mark(6);
+  tri_attach(s, T, S, mu, R.lower, R.parent, R.label);
+  mark(7);
+  if (split) tri_hub_outlier(s, T, S, mu, R.lower, R.parent, R.label, R.upper, R.role);
+  tri_output(s, T, mu, R.lower, R.parent, R.label, R.role, d_labels, d_roles, split);
+  mark(8);
+}
+
 // Reads the statistics counters and event times of the last enqueued run.
 void scan::set_last(scan_graph* g, const scan_stats& L) {
   std::lock_guard<std::mutex> lk(g->stats_lock);
@@ -171,8 +205,16 @@ int scan::collect_stats(scan_graph* g, hipStream_t s, bool timing) {
 int scan::collect_stats(scan_graph* g, hipStream_t s, bool timing, const RunState& R, hipEvent_t* ev) {
   const int64_t m = g->m;
   HIP_TRY(hipGetLastError(), "kernel launch");
-  unsigned long long st[ST_COUNT];
-  HIP_TRY(hipMemcpyAsync(st, R.stats, sizeof(st), hipMemcpyDeviceToHost, s), "stats copy");
+  unsigned long long st[ST_COUNT] = {0};
+  if (g->has_tri) {  // every edge's count, from the candidates of its row
+    for (int k = 0; k < kNumBuckets; ++k) {
+      st[ST_BUCKET_EVAL + k] = (unsigned long long)(g->bucket_off[k + 1] - g->bucket_off[k]);
+      st[ST_EVAL + MODE_CORES] += st[ST_BUCKET_EVAL + k];
+    }
+    st[ST_PROBES + MODE_CORES] = (unsigned long long)g->tri.steps * kTriLine;  // entries looked up
+  } else {
+    HIP_TRY(hipMemcpyAsync(st, R.stats, sizeof(st), hipMemcpyDeviceToHost, s), "stats copy");
+  }
   HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
   scan_stats L;
   memset(&L, 0, sizeof(L));
@@ -197,7 +239,7 @@ int scan::collect_stats(scan_graph* g, hipStream_t s, bool timing, const RunStat
     }
     hipEventElapsedTime(&ms, ev[0], ev[SCAN_NUM_PHASES]);
     L.ms_total = ms;
-    for (int k = 0; k < kNumBuckets; ++k) {
+    for (int k = 0; k < kNumBuckets && !g->has_tri; ++k) {  // (the triangle path has no pass per bucket)
       hipEventElapsedTime(&ms, ev[k == 0 ? 1 : SCAN_NUM_PHASES + k], ev[SCAN_NUM_PHASES + 1 + k]);
       L.ms_cores_bucket[k] = ms;
     }
@@ -218,6 +260,9 @@ uint64_t scan::graph_device_bytes(const scan_graph* g) {
 uint64_t scan::graph_layout_bytes(const scan_graph* g) {
   const uint64_t n = (uint64_t)g->n, nnz = (uint64_t)g->nnz, m = (uint64_t)g->m;
   const uint64_t b6 = (uint64_t)(g->bucket_off[kNumBuckets] - g->bucket_off[kNumBuckets - 1]);
+  if (g->has_tri)
+    return 8 * (n + 1) + 4 * (nnz + kColPad) + 17 * n + tri_layout_bytes(g->tri) + tri_scratch_bytes(g->tri) +
+           (g->tri_na.cnt ? tri_scratch_bytes(g->tri) : 0);
   uint64_t b = 8 * (n + 1) + 4 * (nnz + kColPad) + 8 * m + (g->d_edeg ? 8 * m : 0) + sizeof(HubJob) * (uint64_t)g->hub_jobs + 4 * b6 +
                4 * (uint64_t)g->wtab_entries;
   if (g->d_hci) b += 4 * (nnz + kColPad);
@@ -242,12 +287,51 @@ int scan::check_params(const scan_graph* g, int64_t& p, int64_t& q, int32_t mu) 
 
 namespace {
 
+// The graph's triangle scratch on stream s for the life of this object: work
+// enqueued on s meanwhile starts after the work of the calls that hold it now.
+// (A call waits for its stream before it lets go, so that without overlapping
+// calls nothing is recorded or waited for.)
+class TriTurn {
+ public:
+  TriTurn(scan_graph* g, hipStream_t s) : g_(g), lk_(g->tri_lock) {
+    if (g->tri_inflight > 0 && g->tri_stream != s) {
+      err_ = hipEventRecord(g->tri_ev, g->tri_stream);
+      if (err_ == hipSuccess) err_ = hipStreamWaitEvent(s, g->tri_ev, 0);
+    }
+    g->tri_stream = s;
+    ++g->tri_inflight;
+  }
+  hipError_t error() const { return err_; }
+  void enqueued() { lk_.unlock(); }  // everything is on the stream
+  ~TriTurn() {
+    if (!lk_.owns_lock()) lk_.lock();
+    --g_->tri_inflight;
+  }
+
+ private:
+  scan_graph* g_;
+  std::unique_lock<std::mutex> lk_;
+  hipError_t err_ = hipSuccess;
+};
+
+// One clustering through the triangle path, in R, waited for.
+int run_tri(scan_graph* g, int64_t p, int64_t q, int32_t mu, int32_t* d_labels, uint8_t* d_roles, hipStream_t s,
+            const RunState& R, hipEvent_t* ev) {
+  const bool timing = g->opts.timing != 0;
+  TriTurn turn(g, s);
+  if (turn.error() != hipSuccess) return fail_hip(turn.error(), "wait for an overlapping call");
+  enqueue_tri(g, g->tri_s, p, q, mu, d_labels, d_roles, s, R, timing ? ev : nullptr);
+  turn.enqueued();
+  return collect_stats(g, s, timing, R, ev);
+}
+
 // Validates eps and mu and runs the in-memory or partitioned clustering.
 int run_clustering(scan_graph* g, int64_t p, int64_t q, int32_t mu, int32_t* d_labels,
                    uint8_t* d_roles, hipStream_t s) {
   const int rc = check_params(g, p, q, mu);
   if (rc != SCAN_OK) return rc;
   if (g->partitioned) return part_run(g, (uint64_t)p, (uint64_t)q, mu, d_labels, d_roles, s);
+  if (g->has_tri) return run_tri(g, p, q, mu, d_labels, d_roles, s, graph_state(g), g->ev);
   EdgeArgs A{};
   A.p = (uint64_t)p;
   A.q = (uint64_t)q;
@@ -345,15 +429,22 @@ int run_extra(scan_graph* g, ExtraRun* x, int64_t p, int64_t q, int32_t mu, int3
     return fail_hip(e, "buffers for an overlapping call");
   }
   hipStream_t s = caller ? caller : x->stream;
-  EdgeArgs A{};
-  A.p = (uint64_t)p;
-  A.q = (uint64_t)q;
-  A.mu = mu;
-  A.pruning = g->opts.pruning;
-  const bool timing = g->opts.timing != 0;
-  enqueue_clustering(g, A, host ? x->d_out_labels : d_labels, host ? x->d_out_roles : d_roles, nullptr, s, timing,
-                     nullptr, &x->R, x->ev);
-  rc = collect_stats(g, s, timing, x->R, x->ev);
+  if (host) {
+    d_labels = x->d_out_labels;
+    d_roles = x->d_out_roles;
+  }
+  if (g->has_tri) {
+    rc = run_tri(g, p, q, mu, d_labels, d_roles, s, x->R, x->ev);
+  } else {
+    EdgeArgs A{};
+    A.p = (uint64_t)p;
+    A.q = (uint64_t)q;
+    A.mu = mu;
+    A.pruning = g->opts.pruning;
+    const bool timing = g->opts.timing != 0;
+    enqueue_clustering(g, A, d_labels, d_roles, nullptr, s, timing, nullptr, &x->R, x->ev);
+    rc = collect_stats(g, s, timing, x->R, x->ev);
+  }
   if (rc == SCAN_OK && host && g->n > 0) {
     hipError_t c = hipMemcpyAsync(h_labels, x->d_out_labels, sizeof(int32_t) * (size_t)g->n, hipMemcpyDeviceToHost, s);
     if (c == hipSuccess) c = hipMemcpyAsync(h_roles, x->d_out_roles, (size_t)g->n, hipMemcpyDeviceToHost, s);
@@ -368,6 +459,32 @@ int run_extra(scan_graph* g, ExtraRun* x, int64_t p, int64_t q, int32_t mu, int3
 
 int scan::run_counts(scan_graph* g, int32_t* d_counts_arc, int32_t* d_counts_edge, hipStream_t s) {
   const bool timing = g->opts.timing != 0;
+  if (g->has_tri) {
+    TriTurn turn(g, s);
+    if (turn.error() != hipSuccess) return fail_hip(turn.error(), "wait for an overlapping call");
+    if (timing) hipEventRecord(g->ev[0], s);
+    tri_init(s, g->tri, g->tri_s, nullptr, nullptr, nullptr, nullptr);
+    tri_count(s, g->tri, g->tri_s);
+    tri_close(s, g->tri, g->tri_s, TriArgs{}, nullptr);
+    if (d_counts_arc) tri_arc_counts(s, g->tri, g->tri_s, g->d_rp, g->d_ci, d_counts_arc);
+    if (timing) hipEventRecord(g->ev[1], s);
+    turn.enqueued();
+    HIP_TRY(hipGetLastError(), "kernel launch");
+    HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    scan_stats L;
+    memset(&L, 0, sizeof(L));
+    L.edges = L.evaluated[SCAN_PHASE_CORES] = g->m;
+    L.probes[SCAN_PHASE_CORES] = g->tri.steps * kTriLine;
+    for (int k = 0; k < kNumBuckets; ++k) L.bucket_edges[k] = g->bucket_off[k + 1] - g->bucket_off[k];
+    if (timing) {
+      float ms = 0;
+      hipEventElapsedTime(&ms, g->ev[0], g->ev[1]);
+      L.ms_total = ms;
+      L.ms_phase[SCAN_PHASE_CORES] = ms;
+    }
+    set_last(g, L);
+    return SCAN_OK;
+  }
   HIP_TRY(hipMemsetAsync(g->d_stats, 0, sizeof(unsigned long long) * ST_COUNT, s), "hipMemsetAsync");
   launch_zero_u64(s, g->d_counters, kCounters);
   if (timing) hipEventRecord(g->ev[0], s);
@@ -432,6 +549,13 @@ int64_t scan_eps_threshold(int64_t p, int64_t q, int64_t a, int64_t b) {
 
 int scan_graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx,
                       const scan_opts* opts, scan_graph** out) {
+  return graph_create(n, nnz, row_ptr, col_idx, opts, true, out);
+}
+
+}  // extern "C"
+
+int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx,
+                       const scan_opts* opts, bool tri, scan_graph** out) {
   g_error.clear();
   if (!out) return fail(SCAN_E_INVAL, "out is NULL");
   *out = nullptr;
@@ -452,6 +576,7 @@ int scan_graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int3
   std::vector<HubJob> jobs;
   std::vector<uint32_t> wtab;
   std::vector<int32_t> ranked;
+  int32_t* d_src = nullptr;
 #define CTRY(call, what)                         \
   do {                                           \
     e = (call);                                  \
@@ -495,8 +620,52 @@ int scan_graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int3
   if (nnz > 0)
     CTRY(hipMemcpyAsync(g->d_ci, col_idx, sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice, g->stream),
          "copy col_idx");
-  CTRY(build_layout(g->stream, n, nnz, row_ptr, col_idx, g->d_rp, g->d_ci, g->opts.validate, &g->d_edges,
-                    &jobs, &lay), "layout");
+  CTRY(check_csr(g->stream, n, nnz, g->d_rp, g->d_ci, g->opts.validate, &d_src, &lay), "layout");
+  // The triangle path, unless the options ask for the exhaustive or the
+  // binary-search kernels, or bound the device memory (its scratch grows with
+  // the pairs of row entries, which scan_graph_footprint cannot know).
+  if (tri && !lay.error && g->opts.pruning && g->opts.strategy == 0 && !g->opts.device_budget_bytes) {
+    int64_t be[kNumBuckets];
+    int ok = 0;
+    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, &g->tri, be, &ok);
+    if (e == hipSuccess && ok) e = tri_alloc_scratch(g->tri, &g->tri_s);
+    if (e == hipSuccess && ok) {
+      g->has_tri = true;
+      for (int k = 0; k < kNumBuckets; ++k) g->bucket_off[k + 1] = g->bucket_off[k] + be[k];
+      g->m = g->bucket_off[kNumBuckets];
+      if (noalloc_bytes(g) <= kNoallocScratch) e = tri_alloc_scratch(g->tri, &g->tri_na);
+    }
+    if (e == hipErrorOutOfMemory) {  // no room: the edge list takes less
+      (void)hipGetLastError();
+      tri_release(g->tri);
+      tri_release_scratch(g->tri_s);
+      g->has_tri = false;
+      e = hipSuccess;
+    }
+    CTRY(e, "triangle layout");
+  }
+  if (g->has_tri) {
+    (void)hipFree(d_src);
+    d_src = nullptr;
+    g->max_degree = lay.max_degree;
+    if (g->opts.validate && g->m * 2 != nnz) {
+      rc = fail(SCAN_E_GRAPH, "edge count %lld does not match nnz/2", (long long)g->m);
+      goto error;
+    }
+    CTRY(dalloc(&g->d_lower, n), "hipMalloc");
+    CTRY(dalloc(&g->d_upper, n), "hipMalloc");
+    CTRY(dalloc(&g->d_role, n), "hipMalloc");
+    CTRY(dalloc(&g->d_parent, n), "hipMalloc");
+    CTRY(dalloc(&g->d_label, n), "hipMalloc");
+    for (auto& ev : g->ev) CTRY(hipEventCreate(&ev), "hipEventCreate");
+    CTRY(hipEventCreateWithFlags(&g->tri_ev, hipEventDisableTiming), "hipEventCreate");
+    *out = g;
+    return SCAN_OK;
+  }
+  CTRY(build_layout(g->stream, n, nnz, row_ptr, col_idx, g->d_rp, g->d_ci, d_src, &g->d_edges, &jobs, &lay),
+       "layout");
+  (void)hipFree(d_src);
+  d_src = nullptr;
   if (lay.error) {
     rc = fail(SCAN_E_GRAPH, "CSR rejected (flags 0x%x: 1 offsets, 2 id range, 4 self-loop, "
               "8 row order/duplicate, 16 missing reverse arc, 32 inconsistent layout)", lay.error);
@@ -548,11 +717,14 @@ int scan_graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int3
   *out = g;
   return SCAN_OK;
 error:
+  if (d_src) (void)hipFree(d_src);
   release(g);
   delete g;
 #undef CTRY
   return rc;
 }
+
+extern "C" {
 
 int scan_graph_destroy(scan_graph* g) {
   if (!g) return SCAN_OK;

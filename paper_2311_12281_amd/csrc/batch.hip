@@ -388,7 +388,7 @@ int scan_batch_create(const scan_batch* b, const scan_opts* opts, scan_batch_gra
     else scan_opts_default(&o);
     o.device_budget_bytes = 0;
     o.hub_ranked = 0;  // the batch kernel reads the rows as given
-    rc = scan_graph_create(N, nnz, rp.data(), ci.data(), &o, &B->g);
+    rc = graph_create(N, nnz, rp.data(), ci.data(), &o, false, &B->g);
     if (rc != SCAN_OK) {
       delete B;
       return rc;

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "scan_internal.h"
+#include "tri.h"
 #include "../../include/scan.h"
 
 #include <atomic>
@@ -126,6 +127,16 @@ struct scan_graph {
   int32_t* d_out_labels = nullptr;  // staging for the host-output entry points
   uint8_t* d_out_roles = nullptr;
   int32_t* d_counts = nullptr;      // staging for scan_similarity
+  // triangle path (tri.lines > 0 or no edges): replaces the edge list, jobs,
+  // windows, ranked rows, samples, degree pairs and worklist above
+  bool has_tri = false;
+  TriLayout tri;
+  TriScratch tri_s;                 // of the calls on the graph's own and pooled buffer sets, in turn
+  TriScratch tri_na;                // of scan_run_device_noalloc
+  std::mutex tri_lock;              // the three below
+  int tri_inflight = 0;             // calls using tri_s
+  hipStream_t tri_stream = nullptr; // stream of the last of them
+  hipEvent_t tri_ev = nullptr;
   hipEvent_t ev[SCAN_NUM_PHASES + kNumBuckets + 2] = {};
   std::mutex lock;  // the graph's own per-run buffers, staging and events (one call at a time)
   // buffer sets of calls that find the graph's own ones in use
@@ -162,6 +173,16 @@ void launch_bucket(scan_graph* g, hipStream_t s, int mode, int k, EdgeArgs& A, c
 void enqueue_clustering(scan_graph* g, EdgeArgs& A, int32_t* d_labels, uint8_t* d_roles,
                         const int32_t* gbase, hipStream_t s, bool timing, const RunConfig* cfg,
                         const RunState* R = nullptr, hipEvent_t* ev = nullptr);
+// The same through the triangle path, in scratch S (kernel launches only).
+void enqueue_tri(scan_graph* g, const TriScratch& S, int64_t p, int64_t q, int32_t mu, int32_t* d_labels,
+                 uint8_t* d_roles, hipStream_t s, const RunState& R, hipEvent_t* events);
+// scan_graph_create; tri: whether the graph may take the triangle path (else
+// it has the edge list that the batch and the server read).
+int graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx, const scan_opts* opts,
+                 bool tri, scan_graph** out);
+// Device bytes a noalloc call's per-run buffers take in the static scratch.
+uint64_t noalloc_bytes(const scan_graph* g);
+constexpr uint64_t kNoallocScratch = 64ull << 20;
 // Checks eps = p/q and mu against the graph (Def 2.3, Def 2.4, the 64-bit
 // range of the test) and reduces p/q; SCAN_OK or the error code.
 int check_params(const scan_graph* g, int64_t& p, int64_t& q, int32_t mu);

@@ -182,6 +182,8 @@ __global__ void k_scan_add(int64_t* data, int64_t n, const int64_t* add) {
   if (i < n) data[i] += add[i / kTile];
 }
 
+}  // namespace
+
 hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + kTile - 1) / kTile;
@@ -202,9 +204,6 @@ hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_
   hipFree(sums);
   return e != hipSuccess ? e : f;
 }
-
-
-}  // namespace
 
 int64_t hub_windows(const int32_t* row, int64_t dv, std::vector<uint32_t>& out) {
   // The same windows the LDS-hash kernel would find: a bitmap of the ids
@@ -295,26 +294,16 @@ hipError_t build_ranked_rows(hipStream_t s, int32_t n, int64_t nnz, const int64_
   return e;
 }
 
-hipError_t build_layout(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
-                        const int32_t* h_ci, const int64_t* d_rp, const int32_t* d_ci, int validate,
-                        int2** d_edges_out, std::vector<HubJob>* jobs_out, LayoutResult* out) {
+#define LTRY(x) do { e = (x); if (e != hipSuccess) goto done; } while (0)
+hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
+                     int32_t** d_src_out, LayoutResult* out) {
   hipError_t e = hipSuccess;
-  jobs_out->clear();
-  out->hub_jobs = 0;
   int32_t* d_flags = nullptr;  // [0] = error bits, [1] = max degree
   int32_t* d_src = nullptr;
-  int64_t* d_cnt = nullptr;
-  int2* d_edges = nullptr;
-  const int64_t nblocks = (nnz + kTile - 1) / kTile;
-  const int64_t ncnt = nblocks * kNumBuckets;
   int32_t h_flags[2] = {0, 0};
-  int64_t h_off[kNumBuckets];
-  int64_t h_last[2] = {0, 0};
-  *d_edges_out = nullptr;
-  for (int k = 0; k <= kNumBuckets; ++k) out->bucket_off[k] = 0;
+  *d_src_out = nullptr;
   out->error = 0;
   out->max_degree = 0;
-#define LTRY(x) do { e = (x); if (e != hipSuccess) goto done; } while (0)
   LTRY(hipMalloc((void**)&d_flags, sizeof(int32_t) * 2));
   LTRY(hipMemsetAsync(d_flags, 0, sizeof(int32_t) * 2, s));
   k_check_offsets<<<(unsigned)((n + 1 + 255) / 256), 256, 0, s>>>(n, nnz, d_rp, d_flags, d_flags + 1);
@@ -335,6 +324,30 @@ hipError_t build_layout(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_
   LTRY(hipStreamSynchronize(s));
   out->error = h_flags[0];
   if (h_flags[0] != 0) goto done;
+  *d_src_out = d_src;
+  d_src = nullptr;
+done:
+  hipStreamSynchronize(s);
+  if (d_src) hipFree(d_src);
+  if (d_flags) hipFree(d_flags);
+  return e;
+}
+
+hipError_t build_layout(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
+                        const int32_t* h_ci, const int64_t* d_rp, const int32_t* d_ci, const int32_t* d_src,
+                        int2** d_edges_out, std::vector<HubJob>* jobs_out, LayoutResult* out) {
+  hipError_t e = hipSuccess;
+  jobs_out->clear();
+  out->hub_jobs = 0;
+  int64_t* d_cnt = nullptr;
+  int2* d_edges = nullptr;
+  const int64_t nblocks = (nnz + kTile - 1) / kTile;
+  const int64_t ncnt = nblocks * kNumBuckets;
+  int64_t h_off[kNumBuckets];
+  int64_t h_last[2] = {0, 0};
+  *d_edges_out = nullptr;
+  for (int k = 0; k <= kNumBuckets; ++k) out->bucket_off[k] = 0;
+  if (out->error || nnz == 0) return hipSuccess;  // rejected by check_csr, or no edges
   LTRY(hipMalloc((void**)&d_cnt, sizeof(int64_t) * ncnt * 2));
   k_bucket_counts<<<(unsigned)nblocks, kBlock, 0, s>>>(nnz, d_rp, d_ci, d_src, nblocks, d_cnt);
   LTRY(hipGetLastError());
@@ -434,8 +447,6 @@ done:
   hipStreamSynchronize(s);
   if (d_edges) hipFree(d_edges);
   if (d_cnt) hipFree(d_cnt);
-  if (d_src) hipFree(d_src);
-  if (d_flags) hipFree(d_flags);
 #undef LTRY
   return e;
 }

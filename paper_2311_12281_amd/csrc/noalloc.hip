@@ -20,7 +20,7 @@
 
 namespace {
 
-constexpr uint64_t kScratchBytes = 64ull << 20;
+constexpr uint64_t kScratchBytes = kNoallocScratch;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -75,6 +75,8 @@ uint64_t layout_state(const scan_graph* g, unsigned char* base, RunState* R) {
 
 }  // namespace
 
+uint64_t scan::noalloc_bytes(const scan_graph* g) { return layout_state(g, nullptr, nullptr); }
+
 extern "C" {
 
 int scan_run_device_noalloc(scan_graph* g, int64_t eps_num, int64_t eps_den, int32_t mu, int32_t* d_labels,
@@ -100,13 +102,17 @@ int scan_run_device_noalloc(scan_graph* g, int64_t eps_num, int64_t eps_den, int
   if (rc != SCAN_OK) return rc;
   RunState R{};
   layout_state(g, base, &R);
-  EdgeArgs A{};
-  A.p = (uint64_t)p;
-  A.q = (uint64_t)q;
-  A.mu = mu;
-  A.pruning = g->opts.pruning;
   hipStream_t s = stream ? (hipStream_t)stream : g->stream;
-  enqueue_clustering(g, A, d_labels, d_roles, nullptr, s, false, nullptr, &R);
+  if (g->has_tri) {
+    enqueue_tri(g, g->tri_na, p, q, mu, d_labels, d_roles, s, R, nullptr);
+  } else {
+    EdgeArgs A{};
+    A.p = (uint64_t)p;
+    A.q = (uint64_t)q;
+    A.mu = mu;
+    A.pruning = g->opts.pruning;
+    enqueue_clustering(g, A, d_labels, d_roles, nullptr, s, false, nullptr, &R);
+  }
   HIP_TRY(hipGetLastError(), "kernel launch");
   // on the caller's stream the run stays stream-ordered (the caller
   // synchronises); on the graph's own stream the outputs are ready on return

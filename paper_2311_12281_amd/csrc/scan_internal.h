@@ -274,13 +274,19 @@ struct LayoutResult {
   int32_t max_degree;
   int32_t error;  // 0 or bit mask of validation failures
 };
-// Validates the CSR and builds the oriented, bucketed edge list and the job
+// Validates the CSR (out->error, out->max_degree); *d_src: the row of every
+// arc, allocated here (null when the CSR is rejected or has no arcs).
+hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
+                     int32_t** d_src, LayoutResult* out);
+// Exclusive prefix sum of n int64 on the device (synchronises for more than one block).
+hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n);
+// Builds the oriented, bucketed edge list and the job
 // table of the last bucket, both allocated here (caller frees):
 //   *d_edges: bucket_off[kNumBuckets] entries, *d_jobs: hub_jobs entries.
 // The job table is returned on the host (jobs), to be completed with the
 // windows and uploaded by the caller.
 hipError_t build_layout(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
-                        const int32_t* h_ci, const int64_t* d_rp, const int32_t* d_ci, int validate,
+                        const int32_t* h_ci, const int64_t* d_rp, const int32_t* d_ci, const int32_t* d_src,
                         int2** d_edges, std::vector<HubJob>* jobs, LayoutResult* out);
 // Fills d_hci (nnz entries) with the rows of the CSR with every vertex renamed
 // to its rank in order of increasing degree (ties by id), each row sorted

@@ -1,0 +1,118 @@
+// Internal: the triangle path, which computes the closed counts of all edges
+// at once from the triangles of the graph (tri.hip) instead of intersecting
+// the neighbour lists of one edge after another.
+#pragma once
+
+#include "scan_internal.h"
+
+namespace scan {
+
+// Vertices are renamed by decreasing degree (ties by id): h = 0 is the vertex
+// of the highest degree.  Every edge is kept once, in the row of its endpoint
+// with the larger h: row u lists the neighbours v of u with h(v) < h(u), in
+// decreasing order.  No row is longer than about sqrt(2 m).
+//
+// Rows are cut into lines of 32 entries, aligned to lines; an entry holds h + 1
+// of its neighbour, 0 where the last line has none.
+// An entry is addressed by its place 32 * line + column everywhere: its
+// neighbour (oc), its count (cnt), and one bit of simw[line].
+constexpr int kTriLine = 32;
+constexpr int kTriMaxRow = 4096;  // longest row the kernels take
+constexpr int kTriBlock = 512;    // threads of the block kernel
+constexpr int kTriJob = 1024;     // in-edges per job of the block kernel
+constexpr int kTriDirect = 16384; // h below this: table of row positions indexed by h
+constexpr int kTriShort = 65534;  // h below this: 16-bit entries (oc16) and a bitmap table
+constexpr int kTriWaveRow = 128;  // rows up to this, with few in-edges, go one per wave
+constexpr int kTriWaveSlots = 256;
+constexpr int64_t kTriWaveWords = 512;  // words of in-edges a wave takes on
+
+// One in-edge (u, v) of a vertex v: the columns of row u after v's entry are
+// the w to look up in row v.
+struct TriRec {
+  uint32_t line;  // line of v's entry in row u
+  uint32_t word;  // bit word of row u's columns from that line on
+  uint32_t nw;    // lines from there to the end of row u (0: nothing after v)
+  uint32_t pad;
+};
+
+struct TriJob {
+  int32_t v;
+  uint32_t rbeg, rcnt;  // in-edge records
+  uint32_t single;      // 1: the only job of v (its counts are stored, not added)
+};
+
+// A vertex of the wave kernel.
+struct TriWave {
+  int32_t v;
+  uint32_t line, rbeg;  // of its row, of its in-edge records
+  uint32_t shape;       // row length | records << 8
+};
+
+// Read-only after creation.
+struct TriLayout {
+  int32_t n = 0;
+  int64_t lines = 0, words = 0, recs = 0, steps = 0;
+  int64_t jobs = 0, wave_rows = 0;
+  int32_t max_row = 0, max_hash_row = 0;
+  int32_t* hof = nullptr;     // [n] id -> h
+  int32_t* idof = nullptr;    // [n] h -> id
+  int32_t* deg = nullptr;     // [n] degree, by h
+  int32_t* row = nullptr;     // [n] entries of a row, by h
+  uint32_t* oline = nullptr;  // [n + 1] first line of a row
+  uint32_t* wbase = nullptr;  // [n + 1] first bit word of a row
+  uint32_t* inoff = nullptr;  // [n + 1] first in-edge record
+  int32_t* lu = nullptr;      // [lines] h of the line's row
+  int32_t* oc = nullptr;      // [32 lines + pad] h + 1 of the neighbour, or 0
+  uint16_t* oc16 = nullptr;   // the same in 16 bits, 0xFFFF for h >= kTriShort
+  TriRec* rec = nullptr;      // [recs]
+  TriJob* job = nullptr;      // [jobs], hubs first
+  TriWave* wrow = nullptr;    // [wave_rows]
+};
+
+// Written by every run.
+struct TriScratch {
+  int32_t* cnt = nullptr;     // [32 lines] common neighbours, then closed counts
+  uint32_t* bits = nullptr;   // [words]
+  uint32_t* simw = nullptr;   // [lines] similar entries
+  int32_t* flag = nullptr;    // [1] some vertex is a core
+};
+
+// Device bytes of the layout and of one scratch.
+uint64_t tri_layout_bytes(const TriLayout& T);
+uint64_t tri_scratch_bytes(const TriLayout& T);
+
+// Builds the layout from a validated CSR on the device (h_rp: the caller's
+// offsets).  *ok = 0 with hipSuccess when the graph is outside the path's
+// limits (nothing stays allocated).  bucket_edges: edges per degree bucket.
+hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
+                     const int32_t* d_ci, TriLayout* T, int64_t* bucket_edges, int* ok);
+void tri_release(TriLayout& T);
+hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S);
+void tri_release_scratch(TriScratch& S);
+
+// What a run does with the counts: eps and mu, or (eps_den == 0) nothing but
+// the closed counts, left in S.cnt.
+struct TriArgs {
+  uint64_t p = 0, q = 0;
+  int32_t mu = 2;
+};
+
+// Kernel launches of the phases, in this order.
+void tri_init(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* lower, int32_t* parent,
+              int32_t* label, uint8_t* role);
+void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S);
+void tri_close(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower);
+void tri_hook(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+              int32_t* parent);
+void tri_attach(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+                int32_t* parent, int32_t* label);
+// Hub marks (Def 2.7): role[id] = ROLE_HUB; first is scratch of n entries.
+void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+                     int32_t* parent, int32_t* label, int32_t* first, uint8_t* role);
+void tri_output(hipStream_t s, const TriLayout& T, int32_t mu, const int32_t* lower, int32_t* parent,
+                const int32_t* label, const uint8_t* role, int32_t* out_labels, uint8_t* out_roles, int32_t split);
+// Closed counts of every arc in CSR order from S.cnt (after tri_close).
+void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, const int64_t* rp, const int32_t* ci,
+                    int32_t* counts);
+
+}  // namespace scan

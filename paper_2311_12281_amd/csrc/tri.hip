@@ -1,0 +1,1260 @@
+// Closed counts of all edges from the triangles of the graph, and the
+// clustering steps that follow from exact counts.
+//
+// With the vertices ordered by degree and every edge (u, v) kept in the row of
+// its lower-degree endpoint u, a triangle is one u with two entries v, w of
+// its row that are adjacent, so the pairs of entries of all rows are the only
+// candidates: sum of D(D-1)/2 over rows of length D, where the intersections
+// of kernels.hip read sum of min(d(u), d(v)) elements (R-MAT scale 22: 7.2 G
+// against 43 G for exact counts, and 28.9 / 11.1 / 3.3 G with every early
+// exit at eps = 1/5, 1/2, 4/5).
+//
+// A triangle u, v, w (in order of the columns of u and v) counts for three
+// edges, and none of the three needs an atomic per triangle on global memory:
+//   (v, w)  count kernels: row v is held in LDS with a counter per entry; the
+//           columns of every in-edge (u, v) after v's own are looked up in it,
+//           a hit adds to the entry's counter, and the counters of a job are
+//           added to row v of cnt once;
+//   (u, v), (u, w)  the same lookups, as one bit per column, are written to
+//           row u's triangle of bits (0.9 GB for the 7.2 G pairs).  The close
+//           kernel adds, for every entry of row u, the bits of its row and of
+//           its column.
+#include "tri.h"
+#include "device.h"
+
+#include <algorithm>
+#include <climits>
+#include <type_traits>
+#include <vector>
+
+namespace scan {
+namespace {
+
+__host__ __device__ inline uint32_t tri_lines(int32_t D) { return (uint32_t)(D + kTriLine - 1) / kTriLine; }
+
+// Words of row u's bits before those of column i (rows of W lines: column i
+// keeps the words of lines i / 32 .. W - 1).
+__host__ __device__ inline uint32_t tri_word(uint32_t W, uint32_t i) {
+  const uint32_t b = i >> 5;
+  return i * W - (32 * (b * (b - 1) / 2) + (i & 31) * b);
+}
+
+// ---------------------------------------------------------------------------
+// Layout
+
+__device__ __forceinline__ uint64_t lanes_below(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
+
+// deg[h], and the length of every row; one wave per vertex, or (h < nbig, the
+// highest degrees) one block.
+__global__ __launch_bounds__(1024) void k_row_len_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
+                                                        const int32_t* hof, const int32_t* idof, int32_t* deg,
+                                                        int32_t* row) {
+  __shared__ int32_t sum;
+  const int32_t h = blockIdx.x;
+  if (h >= nbig) return;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  int32_t c = 0;
+  for (int64_t k = b + threadIdx.x; k < e; k += 1024) c += hof[ci[k]] < h ? 1 : 0;
+  c = (int32_t)wave_sum((unsigned long long)c);
+  if ((threadIdx.x & 63) == 0 && c) atomicAdd(&sum, c);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    deg[h] = (int32_t)(e - b);
+    row[h] = sum;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_row_len_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
+                                                      const int32_t* hof, const int32_t* idof, int32_t* deg,
+                                                      int32_t* row) {
+  const int lane = threadIdx.x & 63;
+  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  if (h >= n) return;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  int32_t c = 0;
+  for (int64_t k = b + lane; k < e; k += 64) c += hof[ci[k]] < h ? 1 : 0;
+  c = (int32_t)wave_sum((unsigned long long)c);
+  if (lane == 0) {
+    deg[h] = (int32_t)(e - b);
+    row[h] = c;
+  }
+}
+
+// Per vertex: lines and bit words of its row, in-edges, longest row.
+__global__ void k_row_sizes(int32_t n, const int32_t* deg, const int32_t* row, int64_t* nline, int64_t* nword,
+                            int64_t* nin, int32_t* max_row) {
+  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t D = h < n ? row[h] : 0;
+  const uint32_t W = tri_lines(D);
+  if (h <= n) {
+    nline[h] = W;
+    nword[h] = D <= kTriMaxRow ? tri_word(W, (uint32_t)D) : 0;
+    nin[h] = h < n ? deg[h] - D : 0;
+  }
+  int32_t m = D;
+  for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d, 64));
+  if ((threadIdx.x & 63) == 0 && m > 0) atomicMax(max_row, m);
+}
+
+__global__ void k_narrow(int32_t n, const int64_t* a, const int64_t* b, const int64_t* c, uint32_t* x, uint32_t* y,
+                         uint32_t* z) {
+  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (h > n) return;
+  x[h] = (uint32_t)a[h];
+  y[h] = (uint32_t)b[h];
+  z[h] = (uint32_t)c[h];
+}
+
+// Entries of every row, in the order of the CSR (sorted afterwards).
+__global__ __launch_bounds__(1024) void k_row_fill_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
+                                                         const int32_t* hof, const int32_t* idof,
+                                                         const uint32_t* oline, const int32_t* row, int32_t* oc) {
+  __shared__ int32_t at;
+  const int32_t h = blockIdx.x;
+  if (h >= nbig) return;
+  const int lane = threadIdx.x & 63;
+  const int32_t x = idof[h], D = row[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  int32_t* out = oc + (int64_t)oline[h] * kTriLine;
+  if (threadIdx.x == 0) at = 0;
+  __syncthreads();
+  for (int64_t k0 = b; k0 < e; k0 += 1024) {
+    const int64_t k = k0 + threadIdx.x;
+    const int32_t y = k < e ? hof[ci[k]] : INT_MAX;
+    const bool keep = y < h;
+    const uint64_t mask = __ballot(keep);
+    int32_t base = 0;
+    if (lane == 0 && mask) base = atomicAdd(&at, (int32_t)__popcll(mask));
+    base = __shfl(base, 0, 64);
+    const int32_t p = base + (int32_t)__popcll(mask & lanes_below(lane));
+    if (keep && p < D) out[p] = y + 1;
+  }
+  for (int32_t p = D + threadIdx.x; p < (int32_t)tri_lines(D) * kTriLine; p += 1024) out[p] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_row_fill_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
+                                                       const int32_t* hof, const int32_t* idof,
+                                                       const uint32_t* oline, const int32_t* row, int32_t* oc) {
+  const int lane = threadIdx.x & 63;
+  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  if (h >= n) return;
+  const int32_t D = row[h];
+  if (D == 0) return;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  int32_t* out = oc + (int64_t)oline[h] * kTriLine;
+  int32_t at = 0;
+  for (int64_t k0 = b; k0 < e; k0 += 64) {
+    const int64_t k = k0 + lane;
+    const int32_t y = k < e ? hof[ci[k]] : INT_MAX;
+    const bool keep = y < h;
+    const uint64_t mask = __ballot(keep);
+    const int32_t p = at + (int32_t)__popcll(mask & lanes_below(lane));
+    if (keep && p < D) out[p] = y + 1;
+    at += (int32_t)__popcll(mask);
+  }
+  for (int32_t p = D + lane; p < (int32_t)tri_lines(D) * kTriLine; p += 64) out[p] = 0;
+}
+
+__device__ __forceinline__ uint16_t tri_short(int32_t x) {
+  return x <= kTriShort ? (uint16_t)x : (uint16_t)0xFFFF;
+}
+
+// Rows in decreasing order of h: up to 64 entries in the registers of a wave
+// (bitonic network over the lanes); longer ones are listed for the block kernel.
+__global__ __launch_bounds__(256) void k_row_sort_wave(int32_t n, const uint32_t* oline, const int32_t* row,
+                                                       int32_t* oc, uint16_t* oc16, int32_t* lu, int32_t* longer,
+                                                       int32_t* nlonger) {
+  const int lane = threadIdx.x & 63;
+  const int64_t h = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+  if (h >= n) return;
+  const int32_t D = row[h];
+  if (D == 0) return;
+  const uint32_t W = tri_lines(D), l0 = oline[h];
+  for (uint32_t l = lane; l < W; l += 64) lu[l0 + l] = (int32_t)h;
+  if (D > 64) {
+    if (lane == 0) longer[atomicAdd(nlonger, 1)] = (int32_t)h;
+    return;
+  }
+  int32_t* out = oc + (int64_t)l0 * kTriLine;
+  const bool in = lane < (int)(W * kTriLine);
+  int32_t x = in ? out[lane] : 0;
+  for (int k = 2; k <= 64; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      const int32_t y = __shfl_xor(x, j, 64);
+      const bool up = (lane & k) != 0;            // ascending part
+      const bool low = (lane & j) == 0;
+      x = (low != up) ? max(x, y) : min(x, y);
+    }
+  if (in) {
+    out[lane] = x;
+    oc16[(int64_t)l0 * kTriLine + lane] = tri_short(x);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_row_sort_block(const int32_t* longer, const int32_t* nlonger,
+                                                        const uint32_t* oline, const int32_t* row, int32_t* oc,
+                                                        uint16_t* oc16) {
+  __shared__ int32_t a[kTriMaxRow];
+  const int32_t cnt = *nlonger;
+  for (int32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
+    const int32_t h = longer[r], D = row[h];
+    const int64_t base = (int64_t)oline[h] * kTriLine;
+    int32_t P = 128;
+    while (P < D) P <<= 1;
+    for (int32_t k = threadIdx.x; k < P; k += 256) a[k] = k < D ? oc[base + k] : 0;
+    __syncthreads();
+    for (int32_t k = 2; k <= P; k <<= 1)
+      for (int32_t j = k >> 1; j > 0; j >>= 1) {
+        for (int32_t t = threadIdx.x; t < P / 2; t += 256) {
+          const int32_t i = 2 * t - (t & (j - 1)), l = i + j;
+          const int32_t p = a[i], q = a[l];
+          const bool down = (i & k) == 0;  // decreasing part
+          if (down ? p < q : p > q) {
+            a[i] = q;
+            a[l] = p;
+          }
+        }
+        __syncthreads();
+      }
+    for (int32_t k = threadIdx.x; k < (int32_t)tri_lines(D) * kTriLine; k += 256) {
+      const int32_t x = k < D ? a[k] : 0;
+      oc[base + k] = x;
+      oc16[base + k] = tri_short(x);
+    }
+    __syncthreads();
+  }
+}
+
+// Column of v in row u (decreasing), or -1.
+__device__ __forceinline__ int32_t tri_find(const int32_t* r, int32_t D, int32_t v) {
+  int32_t lo = 0, hi = D;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (r[mid] > v + 1) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo < D && r[lo] == v + 1 ? lo : -1;
+}
+
+__device__ __forceinline__ TriRec tri_rec(int32_t u, int32_t v, const uint32_t* oline, const uint32_t* wbase,
+                                          const int32_t* row, const int32_t* oc) {
+  TriRec r{};
+  const int32_t D = row[u];
+  const uint32_t l0 = oline[u];
+  const int32_t i = tri_find(oc + (int64_t)l0 * kTriLine, D, v);
+  if (i < 0 || i == D - 1) return r;
+  const uint32_t W = tri_lines(D);
+  r.line = l0 + ((uint32_t)i >> 5);
+  r.word = wbase[u] + tri_word(W, (uint32_t)i);
+  r.nw = W - ((uint32_t)i >> 5);
+  return r;
+}
+
+// In-edge records of every vertex, and the words its in-edges hold.
+__global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
+                                                     const int32_t* hof, const int32_t* idof, const uint32_t* oline,
+                                                     const uint32_t* wbase, const int32_t* row, const int32_t* oc,
+                                                     const uint32_t* inoff, TriRec* rec, int64_t* steps) {
+  __shared__ int32_t at;
+  __shared__ unsigned long long sum;
+  const int32_t h = blockIdx.x;
+  if (h >= nbig) return;
+  const int lane = threadIdx.x & 63;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  const uint32_t r0 = inoff[h], rn = inoff[h + 1] - r0;
+  if (threadIdx.x == 0) {
+    at = 0;
+    sum = 0;
+  }
+  __syncthreads();
+  unsigned long long st = 0;
+  for (int64_t k0 = b; k0 < e; k0 += 1024) {
+    const int64_t k = k0 + threadIdx.x;
+    const int32_t u = k < e ? hof[ci[k]] : -1;
+    const bool keep = u > h;
+    const uint64_t mask = __ballot(keep);
+    int32_t base = 0;
+    if (lane == 0 && mask) base = atomicAdd(&at, (int32_t)__popcll(mask));
+    base = __shfl(base, 0, 64);
+    const uint32_t p = (uint32_t)base + (uint32_t)__popcll(mask & lanes_below(lane));
+    if (keep && p < rn) {
+      const TriRec r = tri_rec(u, h, oline, wbase, row, oc);
+      rec[r0 + p] = r;
+      st += r.nw;
+    }
+  }
+  st = wave_sum(st);
+  if (lane == 0 && st) atomicAdd(&sum, st);
+  __syncthreads();
+  if (threadIdx.x == 0) steps[h] = (int64_t)sum;
+}
+
+__global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
+                                                   const int32_t* hof, const int32_t* idof, const uint32_t* oline,
+                                                   const uint32_t* wbase, const int32_t* row, const int32_t* oc,
+                                                   const uint32_t* inoff, TriRec* rec, int64_t* steps) {
+  const int lane = threadIdx.x & 63;
+  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  if (h >= n) return;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  const uint32_t r0 = inoff[h], rn = inoff[h + 1] - r0;
+  uint32_t at = 0;
+  unsigned long long st = 0;
+  for (int64_t k0 = b; k0 < e; k0 += 64) {
+    const int64_t k = k0 + lane;
+    const int32_t u = k < e ? hof[ci[k]] : -1;
+    const bool keep = u > h;
+    const uint64_t mask = __ballot(keep);
+    const uint32_t p = at + (uint32_t)__popcll(mask & lanes_below(lane));
+    if (keep && p < rn) {
+      const TriRec r = tri_rec(u, (int32_t)h, oline, wbase, row, oc);
+      rec[r0 + p] = r;
+      st += r.nw;
+    }
+    at += (uint32_t)__popcll(mask);
+  }
+  st = wave_sum(st);
+  if (lane == 0) steps[h] = (int64_t)st;
+}
+
+__device__ __forceinline__ bool tri_wave_row(int32_t D, uint32_t nin, int64_t steps) {
+  return D <= kTriWaveRow && steps <= kTriWaveWords && nin < (1u << 24);
+}
+
+// Work of every vertex: jobs of the block kernel, or a place in the wave
+// kernel's list; the sum of all words and the longest hash-table row.
+__global__ void k_job_counts(int32_t n, const int32_t* row, const uint32_t* inoff, const int64_t* steps,
+                             int64_t* njob, int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
+  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t j = 0, w = 0;
+  unsigned long long st = 0;
+  if (h < n && steps[h] > 0) {
+    st = (unsigned long long)steps[h];
+    if (tri_wave_row(row[h], inoff[h + 1] - inoff[h], steps[h])) {
+      w = 1;
+    } else {
+      j = (inoff[h + 1] - inoff[h] + kTriJob - 1) / kTriJob;
+      if (h >= kTriShort) atomicMax(max_hash, row[h]);
+    }
+  }
+  if (h <= n) {
+    njob[h] = j;
+    nwave[h] = w;
+  }
+  st = wave_sum(st);
+  if ((threadIdx.x & 63) == 0 && st) atomicAdd(total, st);
+}
+
+__global__ void k_job_fill(int32_t n, const uint32_t* inoff, const uint32_t* oline, const int32_t* row,
+                           const int64_t* job_at, const int64_t* wave_at, TriJob* job, TriWave* wrow) {
+  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (h >= n) return;
+  const int64_t j0 = job_at[h], nj = job_at[h + 1] - j0;
+  const uint32_t r0 = inoff[h], r1 = inoff[h + 1];
+  if (wave_at[h + 1] > wave_at[h]) wrow[wave_at[h]] = TriWave{(int32_t)h, oline[h], r0, (uint32_t)row[h] | (r1 - r0) << 8};
+  for (int64_t j = 0; j < nj; ++j) {
+    TriJob J;
+    J.v = (int32_t)h;
+    J.rbeg = r0 + (uint32_t)(j * kTriJob);
+    J.rcnt = min((uint32_t)kTriJob, r1 - J.rbeg);
+    J.single = nj == 1;
+    job[j0 + j] = J;
+  }
+}
+
+// Edges per degree bucket (lane per entry, smaller side = the row's vertex).
+__global__ __launch_bounds__(256) void k_tri_buckets(int64_t lines, const int32_t* lu, const int32_t* oc,
+                                                     const int32_t* deg, unsigned long long* out) {
+  __shared__ uint32_t c[kNumBuckets];
+  if (threadIdx.x < kNumBuckets) c[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < lines * kTriLine; i += stride) {
+    const int32_t x = oc[i] - 1;
+    int b = -1;
+    if (x >= 0) {
+      b = bucket_of(deg[lu[i >> 5]]);
+      if (b == 5 && deg[x] > kHubMinDegree) b = 6;
+    }
+    for (int k = 0; k < kNumBuckets; ++k) {
+      const uint64_t m = __ballot(b == k);
+      if (m && (threadIdx.x & 63) == 0) atomicAdd(&c[k], (uint32_t)__popcll(m));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kNumBuckets && c[threadIdx.x]) atomicAdd(out + threadIdx.x, (unsigned long long)c[threadIdx.x]);
+}
+
+// ---------------------------------------------------------------------------
+// Counting
+
+// w of lane `to` = x (x and `to` uniform).
+__device__ __forceinline__ void set_lane(uint32_t& w, uint32_t x, const int to) {
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(w) : "s"(x), "i"(to));
+}
+
+// Loads through a buffer descriptor whose size is the rest of the row: entries
+// past it read as 0 (no entry) without touching memory.
+constexpr int kBufferFlags = 0x00027000;  // raw 32-bit data, gfx9 layout
+__device__ __forceinline__ uint16_t buffer_entry(const uint16_t*, __amdgpu_buffer_rsrc_t b, int lane, int k) {
+  return __builtin_amdgcn_raw_buffer_load_b16(b, 2 * lane + 128 * k, 0, 0);
+}
+__device__ __forceinline__ uint32_t buffer_entry(const uint32_t*, __amdgpu_buffer_rsrc_t b, int lane, int k) {
+  return __builtin_amdgcn_raw_buffer_load_b32(b, 4 * lane + 256 * k, 0, 0);
+}
+
+using LdsCounter = __attribute__((address_space(3))) int32_t;
+
+// Columns of one job's in-edges through a lookup: find(x) is the LDS address
+// of x's counter, or 0.  A wave takes a run of the in-edges, one at a time and
+// 64 columns a step, so that the record (read from the lane that loaded it),
+// the row's address and the loop are scalar and a ballot is two words of bits.
+// The columns of four steps, of this in-edge or the next, are loaded while the
+// four before them are looked up; all four loads are always issued, since a
+// load under a branch would make the compiler wait for every load in flight.
+// Columns up to v's own are in no table of v (h(w) >= h(v)) and need no mask.
+template <typename E, typename F>
+__device__ __forceinline__ void tri_stream(const E* __restrict__ cols, const TriRec* __restrict__ rec, uint32_t cnt,
+                                           uint32_t wave, int lane, uint32_t* __restrict__ bits, F find) {
+  constexpr uint32_t kAhead = 8;  // lines per chunk
+  struct Cols {
+    E c0, c1, c2, c3;  // (named: an array is kept as one vector, which waits for all of it)
+  };
+  struct Chunk {
+    uint32_t i, line, word, left;  // record, next line and word, lines left
+  };
+  // (two clamped ends: written as a saturating difference, the compiler drops
+  // the saturation of the scalar subtraction)
+  const uint32_t per = (cnt + kTriBlock / 64 - 1) / (kTriBlock / 64);
+  const uint32_t first = min(wave * per, cnt), n = min(wave * per + per, cnt) - first;
+  for (uint32_t b0 = 0; b0 < n; b0 += 64) {
+    const uint32_t nb = min(64u, n - b0);
+    const TriRec mine = (uint32_t)lane < nb ? rec[first + b0 + lane] : TriRec{};
+    auto at = [&](uint32_t i) {
+      Chunk c;
+      c.i = i;
+      c.line = (uint32_t)__builtin_amdgcn_readlane((int)mine.line, (int)(i & 63));
+      c.word = (uint32_t)__builtin_amdgcn_readlane((int)mine.word, (int)(i & 63));
+      c.left = (uint32_t)__builtin_amdgcn_readlane((int)mine.nw, (int)(i & 63));
+      return c;
+    };
+    auto after = [&](const Chunk& c) {
+      if (c.left <= kAhead) return at(c.i + 1);
+      Chunk d = c;
+      d.line += kAhead;
+      d.word += kAhead;
+      d.left -= kAhead;
+      return d;
+    };
+    auto load = [&](Cols& y, const Chunk& c) {
+      const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<E*>(cols + (uint64_t)c.line * kTriLine), 0, (int)(c.left * (kTriLine * sizeof(E))), kBufferFlags);
+      y.c0 = buffer_entry(cols, b, lane, 0);
+      y.c1 = buffer_entry(cols, b, lane, 1);
+      y.c2 = buffer_entry(cols, b, lane, 2);
+      y.c3 = buffer_entry(cols, b, lane, 3);
+    };
+    auto look = [&](const Cols& x, const Chunk& c) {
+      uint32_t w = 0;
+      auto step = [&](E col, auto k) {
+        constexpr int kAt = decltype(k)::value;
+        const uint32_t place = find(col);
+        const bool hit = place != 0;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+        if (hit) __hip_atomic_fetch_add((LdsCounter*)place, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        set_lane(w, (uint32_t)m, 2 * kAt);
+        set_lane(w, (uint32_t)(m >> 32), 2 * kAt + 1);
+      };
+      if (c.left > 0) {
+        step(x.c0, std::integral_constant<int, 0>{});
+        if (c.left > 2) {
+          step(x.c1, std::integral_constant<int, 1>{});
+          if (c.left > 4) {
+            step(x.c2, std::integral_constant<int, 2>{});
+            if (c.left > 6) step(x.c3, std::integral_constant<int, 3>{});
+          }
+        }
+      }
+      const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(
+          bits + c.word, 0, (int)(min(c.left, kAhead) * 4), kBufferFlags);
+      __builtin_amdgcn_raw_buffer_store_b32(w, b, 4 * lane, 0, 0);
+    };
+    Cols x, y;
+    Chunk c = at(0);
+    load(x, c);
+    while (true) {
+      const Chunk d = after(c);
+      load(y, d);
+      look(x, c);
+      if (d.i >= nb) break;
+      c = after(d);
+      load(x, c);
+      look(y, d);
+      if (c.i >= nb) break;
+    }
+  }
+}
+
+__host__ __device__ inline uint32_t tri_hash_slots(int32_t D) {
+  uint32_t s = 64;
+  while (s < 2u * (uint32_t)D) s <<= 1;
+  return s;
+}
+
+__device__ __forceinline__ uint32_t tri_hash(int32_t x) { return (uint32_t)x * 0x9E3779B1u >> 12; }
+
+// One job: row v into LDS, its in-edges streamed past it.  Three tables:
+//   h(v) < kTriDirect  16 bits per h below h(v): the address of the entry's counter;
+//   h(v) < kTriShort   a bit per h and, per 32 of them, the places before;
+//   above              a hash set of the entries, linear probing, at most half full.
+// The first two read the 16-bit columns.  Block-uniform choice.
+__global__ __launch_bounds__(kTriBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec, const int32_t* __restrict__ row,
+                 const uint32_t* __restrict__ oline, const int32_t* __restrict__ oc,
+                 const uint16_t* __restrict__ oc16, uint32_t* __restrict__ bits, int32_t* __restrict__ cnt,
+                 uint32_t acc_cap) {
+  extern __shared__ __align__(16) int32_t tri_lds[];
+  const TriJob J = jobs[blockIdx.x];
+  const int32_t v = J.v, D = row[v];
+  const int64_t base = (int64_t)oline[v] * kTriLine;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lds = (uint32_t)(uintptr_t)(LdsCounter*)tri_lds;  // LDS address of the counters
+  const TriRec* recs = rec + J.rbeg;
+  auto put = [&](int32_t j, int32_t c) {
+    if (!c) return;
+    if (J.single) cnt[base + j] = c;
+    else atomicAdd(cnt + base + j, c);
+  };
+  int32_t* acc = tri_lds;
+  int32_t* tab = tri_lds + acc_cap;
+  if (v < kTriShort) {
+    for (int32_t k = tid; k <= D; k += kTriBlock) acc[k] = 0;
+    if (v < kTriDirect) {
+      uint16_t* t16 = reinterpret_cast<uint16_t*>(tab);
+      for (int32_t k = tid; k < (v + 1) / 8 + 1; k += kTriBlock)
+        reinterpret_cast<int4*>(tab)[k] = make_int4(0, 0, 0, 0);
+      __syncthreads();
+      static_assert(4 * (kTriMaxRow + 1) <= 0xFFFF, "addresses in 16 bits");
+      for (int32_t j = tid; j < D; j += kTriBlock) t16[oc[base + j]] = (uint16_t)(lds + 4 * (j + 1));
+      __syncthreads();
+      // entry v + 1 (and 0, no entry) stays 0
+      tri_stream(oc16, recs, J.rcnt, wave, lane, bits, [&](uint16_t x) -> uint32_t {
+        uint32_t p = t16[min(x, (uint16_t)(v + 1))];
+        asm("" : "+v"(p));  // a 32-bit value from here on (the load extends it)
+        return p;
+      });
+      __syncthreads();
+      for (int32_t j = tid; j < D; j += kTriBlock) put(j, acc[j + 1]);
+    } else {
+      uint2* tb = reinterpret_cast<uint2*>(tab);
+      const int32_t nt = ((v + 1) >> 5) + 1;
+      for (int32_t k = tid; k < nt; k += kTriBlock) tb[k] = make_uint2(0, 0);
+      __syncthreads();
+      for (int32_t j = tid; j < D; j += kTriBlock) {
+        const int32_t x = oc[base + j];
+        atomicOr(&tb[x >> 5].x, 1u << (x & 31));
+      }
+      __syncthreads();
+      // entries before each word: one wave, 64 words a step
+      if (tid < 64) {
+        uint32_t before = 0;
+        for (int32_t k0 = 0; k0 < nt; k0 += 64) {
+          const int32_t k = k0 + lane;
+          const uint32_t c = k < nt ? (uint32_t)__popc(tb[k].x) : 0;
+          uint32_t incl = c;
+          for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
+          }
+          if (k < nt) tb[k].y = before + incl - c;
+          before += __shfl(incl, 63, 64);
+        }
+      }
+      __syncthreads();
+      auto find = [&](uint16_t x) -> uint32_t {
+        const uint32_t o = min(x, (uint16_t)(v + 1));  // bits 0 (no entry) and v + 1 are not set
+        const uint2 t = tb[o >> 5];
+        const uint32_t upto = t.x << (~o & 31);
+        return (int32_t)upto < 0 ? lds + 4 * (t.y + (uint32_t)__popc(upto)) : 0;
+      };
+      tri_stream(oc16, recs, J.rcnt, wave, lane, bits, find);
+      __syncthreads();
+      for (int32_t j = tid; j < D; j += kTriBlock) put(j, acc[(find((uint16_t)oc[base + j]) - lds) / 4]);
+    }
+  } else {
+    const uint32_t slots = tri_hash_slots(D), mask = slots - 1;
+    int32_t* key = tri_lds;
+    int32_t* hits = tri_lds + slots;
+    for (uint32_t k = tid; k < slots; k += kTriBlock) {
+      key[k] = -1;
+      hits[k] = 0;
+    }
+    __syncthreads();
+    for (int32_t j = tid; j < D; j += kTriBlock) {
+      const int32_t x = oc[base + j];
+      uint32_t t = tri_hash(x) & mask;
+      while (atomicCAS(key + t, -1, x) != -1) t = (t + 1) & mask;
+    }
+    __syncthreads();
+    auto find = [&](uint32_t x) -> uint32_t {
+      if (x - 1 >= (uint32_t)v) return 0;  // no entry included
+      uint32_t t = tri_hash((int32_t)x) & mask;
+      while (true) {
+        const int32_t y = key[t];
+        if (y == (int32_t)x) return lds + 4 * (slots + t);
+        if (y == -1) return 0;
+        t = (t + 1) & mask;
+      }
+    };
+    tri_stream(reinterpret_cast<const uint32_t*>(oc), recs, J.rcnt, wave, lane, bits, find);
+    __syncthreads();
+    for (int32_t j = tid; j < D; j += kTriBlock) put(j, tri_lds[(find((uint32_t)oc[base + j]) - lds) / 4]);
+  }
+}
+
+// Vertices with a short row and few in-edges: one per wave.  Each half of the
+// wave takes every other in-edge, a line of columns a step; the next four lines
+// (of this in-edge or the ones after) are loaded while four are looked up.
+__global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* __restrict__ wrow,
+                                                  const TriRec* __restrict__ rec, const int32_t* __restrict__ oc,
+                                                  uint32_t* __restrict__ bits, int32_t* __restrict__ cnt) {
+  __shared__ __align__(16) int32_t keys[4][kTriWaveSlots];
+  __shared__ __align__(16) int32_t hits[4][kTriWaveSlots];
+  constexpr uint32_t kMask = kTriWaveSlots - 1;
+  const int lane = threadIdx.x & 63, half = lane >> 5, sub = lane & 31;
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= nrow) return;
+  int32_t* key = keys[threadIdx.x >> 6];
+  int32_t* hit = hits[threadIdx.x >> 6];
+  const TriWave V = wrow[i];
+  const uint32_t D = V.shape & 0xFFu, rc = V.shape >> 8;
+  const int64_t base = (int64_t)V.line * kTriLine;
+  const int32_t e0 = (uint32_t)lane < D ? oc[base + lane] : 0, e1 = (uint32_t)lane + 64 < D ? oc[base + 64 + lane] : 0;
+  TriRec r = (uint32_t)lane < rc ? rec[V.rbeg + lane] : TriRec{};
+  static_assert(kTriWaveSlots == 256 && kTriWaveRow <= 128, "four slots per lane, two entries per lane");
+  reinterpret_cast<int4*>(key)[lane] = make_int4(-1, -1, -1, -1);
+  reinterpret_cast<int4*>(hit)[lane] = make_int4(0, 0, 0, 0);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  auto insert = [&](int32_t x) -> uint32_t {
+    uint32_t t = tri_hash(x) & kMask;
+    while (atomicCAS(key + t, -1, x) != -1) t = (t + 1) & kMask;
+    return t;
+  };
+  const uint32_t t0 = e0 ? insert(e0) : 0, t1 = e1 ? insert(e1) : 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t b0 = 0; b0 < rc; b0 += 64) {
+    if (b0) r = b0 + lane < rc ? rec[V.rbeg + b0 + lane] : TriRec{};
+    const uint32_t nb = min(64u, rc - b0);
+    struct Group {
+      int32_t x0, x1, x2, x3;      // columns (0: none)
+      uint32_t w0, w1, w2, w3;     // words their bits go to (~0: none)
+    };
+    uint32_t at = (uint32_t)half, line = 0, word = 0, left = 0;
+    auto fetch = [&]() {  // record `at` of this half (lanes past nb hold empty ones)
+      const int src = (int)min(at, 63u);
+      line = __shfl(r.line, src, 64);
+      word = __shfl(r.word, src, 64);
+      left = __shfl(r.nw, src, 64);
+      if (at >= nb) left = 0;
+    };
+    auto next = [&](int32_t& x, uint32_t& w) {
+      const bool in = left > 0;
+      w = in ? word : ~0u;
+      x = in ? oc[(int64_t)line * kTriLine + sub] : 0;
+      ++line;
+      ++word;
+      if (left > 1) {
+        --left;
+      } else {
+        at += 2;
+        left = 0;
+      }
+      if (__ballot(left == 0)) {
+        const uint32_t l = line, d = word, f = left;
+        fetch();
+        if (f) {
+          line = l;
+          word = d;
+          left = f;
+        }
+      }
+    };
+    auto load = [&](Group& g) {
+      next(g.x0, g.w0);
+      next(g.x1, g.w1);
+      next(g.x2, g.w2);
+      next(g.x3, g.w3);
+    };
+    auto look = [&](int32_t x, uint32_t w) {
+      bool found = false;
+      uint32_t t = tri_hash(x) & kMask;
+      if ((uint32_t)(x - 1) < (uint32_t)V.v) {
+        while (true) {
+          const int32_t y = key[t];
+          if (y == x) {
+            found = true;
+            break;
+          }
+          if (y == -1) break;
+          t = (t + 1) & kMask;
+        }
+      }
+      if (found) atomicAdd(hit + t, 1);
+      const uint64_t m = __ballot(found);
+      if (sub == 0 && w != ~0u) bits[w] = half ? (uint32_t)(m >> 32) : (uint32_t)m;
+    };
+    auto look4 = [&](const Group& g) {
+      look(g.x0, g.w0);
+      look(g.x1, g.w1);
+      look(g.x2, g.w2);
+      look(g.x3, g.w3);
+    };
+    Group g, h;
+    fetch();
+    load(g);
+    while (true) {
+      const bool more = __ballot(at < nb) != 0;
+      if (more) load(h);
+      look4(g);
+      if (!more) break;
+      const bool more2 = __ballot(at < nb) != 0;
+      if (more2) load(g);
+      look4(h);
+      if (!more2) break;
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (e0) cnt[base + lane] = hit[t0];
+  if (e1) cnt[base + 64 + lane] = hit[t1];
+}
+
+// ---------------------------------------------------------------------------
+// From counts to clusters
+
+__global__ void k_tri_init(int64_t ncnt4, int4* cnt, int32_t n, int32_t* lower, int32_t* parent, int32_t* label,
+                           uint8_t* role, int32_t* flag) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = i0; i < ncnt4; i += stride) cnt[i] = make_int4(0, 0, 0, 0);
+  if (i0 == 0) *flag = 0;
+  if (!lower) return;
+  for (int64_t u = i0; u < n; u += stride) {
+    lower[u] = 1;  // u itself is in N_eps[u]
+    parent[u] = (int32_t)u;
+    label[u] = INT_MAX;
+    role[u] = 0;
+  }
+}
+
+// 32 x 32 bits across the lanes of a half wave: lane j's word becomes column j.
+__device__ __forceinline__ uint32_t tri_transpose(uint32_t w, int sub) {
+  uint32_t m = 0x0000FFFFu;
+#pragma unroll
+  for (int s = 16; s >= 1; s >>= 1) {
+    const uint32_t y = (uint32_t)__shfl_xor((int32_t)w, s, 64);
+    w = (sub & s) ? (w & ~m) | ((y & ~m) >> s) : (w & m) | ((y & m) << s);
+    m ^= m << (s >> 1);
+  }
+  return w;
+}
+
+// One line per half wave: closed counts of its entries, and with eps the
+// similar ones, which are counted on both endpoints.
+template <bool kEps>
+__global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const int32_t* __restrict__ lu,
+                                                   const uint32_t* __restrict__ oline,
+                                                   const uint32_t* __restrict__ wbase,
+                                                   const int32_t* __restrict__ row, const int32_t* __restrict__ deg,
+                                                   const int32_t* __restrict__ oc, const uint32_t* __restrict__ bits,
+                                                   int32_t* __restrict__ cnt, TriArgs a, uint32_t* __restrict__ simw,
+                                                   int32_t* __restrict__ lower, int32_t* __restrict__ flag) {
+  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
+  if (t >= lines) return;
+  const int sub = threadIdx.x & 31;
+  const int32_t u = lu[t];
+  const uint32_t l0 = oline[u], W = oline[u + 1] - l0, c = (uint32_t)t - l0;
+  const int32_t D = row[u];
+  const uint32_t wb = wbase[u];
+  const int32_t x = oc[t * kTriLine + sub] - 1;
+  int32_t closed = cnt[t * kTriLine + sub] + 2;
+  const int32_t i = (int32_t)(c * kTriLine) + sub;
+  // the row's own bits (the last column has none after it and was not written)
+  if (i < D - 1) {
+    const uint32_t* mine = bits + wb + tri_word(W, (uint32_t)i);
+    for (uint32_t k = 0; k < W - c; ++k) closed += __popc(mine[k]);
+  }
+  // the bits of its column
+  for (uint32_t b = 0; b <= c; ++b) {
+    const int32_t k = (int32_t)(b * kTriLine) + sub;
+    const uint32_t w = k < D - 1 ? bits[wb + tri_word(W, (uint32_t)k) + (c - b)] : 0;
+    closed += __popc(tri_transpose(w, sub));
+  }
+  if (!kEps) {
+    cnt[t * kTriLine + sub] = closed;
+    return;
+  }
+  bool sim = false;
+  if (x >= 0) {
+    const uint64_t ab = ((uint64_t)deg[u] + 1) * ((uint64_t)deg[x] + 1);
+    const uint64_t cq = (uint64_t)closed * a.q;
+    sim = cq * cq >= (a.p * a.p) * ab;
+  }
+  const uint64_t m = __ballot(sim);
+  const uint32_t mine = (threadIdx.x & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
+  if (sub == 0) simw[t] = mine;
+  if (!m) return;
+  bool core = false;
+  if (sim) core = atomicAdd(lower + x, 1) + 1 >= a.mu;
+  if (sub == 0 && mine) core = (atomicAdd(lower + u, (int32_t)__popc(mine)) + (int32_t)__popc(mine) >= a.mu) || core;
+  if (__ballot(core) && (threadIdx.x & 63) == 0) *flag = 1;
+}
+
+// A parent as the caches have it: some ancestor, maybe not the newest.
+__device__ __forceinline__ int32_t ld_near(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Minimum over a half wave.
+__device__ __forceinline__ int32_t half_min(int32_t x) {
+#pragma unroll
+  for (int d = 16; d >= 1; d >>= 1) x = min(x, __shfl_xor(x, d, 64));
+  return x;
+}
+
+// First step of the clustering: every core points at the least core id that a
+// line joins it to.  A parent is a smaller core of the same cluster, so this is
+// a forest, got with one atomicMin per similar entry at most and no retries,
+// and in a dense cluster it leaves few roots for k_tri_hook, where unions of
+// single edges from the start compete for the same roots.
+__global__ __launch_bounds__(256) void k_tri_link(int64_t lines, const int32_t* __restrict__ lu,
+                                                  const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
+                                                  const int32_t* __restrict__ lower, const int32_t* __restrict__ idof,
+                                                  int32_t mu, int32_t* parent, const int32_t* __restrict__ flag) {
+  if (!*flag) return;
+  const int sub = threadIdx.x & 31;
+  const int64_t stride = (int64_t)gridDim.x * 8;
+  for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
+    const uint32_t w = simw[t];
+    if (!w) continue;
+    const int32_t u = lu[t];
+    if (lower[u] < mu) continue;
+    const int32_t x = oc[t * kTriLine + sub] - 1;
+    const bool in = ((w >> sub) & 1u) && lower[x] >= mu;
+    const int32_t a = idof[u], b = in ? idof[x] : a;
+    const int32_t least = half_min(min(a, b));
+    if (in && least < b && ld_near(parent + b) > least) atomicMin(parent + b, least);
+    if (sub == 0 && least < a && ld_near(parent + a) > least) atomicMin(parent + a, least);
+  }
+}
+
+__global__ void k_tri_compress(int32_t n, int32_t* parent, const int32_t* __restrict__ flag) {
+  if (!*flag) return;
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= n) return;
+  const int32_t p = ld_i32(parent + x);
+  if (p == (int32_t)x) return;
+  const int32_t r = uf_find(parent, p);
+  if (r != p) st_i32(parent + x, r);
+}
+
+// The rest of the unions: the roots that a line's entries found are hooked
+// below the least of them, each by one lane.
+__global__ __launch_bounds__(256) void k_tri_hook(int64_t lines, const int32_t* __restrict__ lu,
+                                                  const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
+                                                  const int32_t* __restrict__ lower, const int32_t* __restrict__ idof,
+                                                  int32_t mu, int32_t* parent, const int32_t* __restrict__ flag) {
+  if (!*flag) return;
+  const int lane = threadIdx.x & 63, half = lane >> 5, sub = lane & 31;
+  const int64_t stride = (int64_t)gridDim.x * 8;
+  for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
+    const uint32_t w = simw[t];
+    if (!w) continue;
+    const int32_t u = lu[t];
+    if (lower[u] < mu) continue;
+    const int32_t x = oc[t * kTriLine + sub] - 1;
+    const bool in = ((w >> sub) & 1u) && lower[x] >= mu;
+    const int32_t a = idof[u], b = in ? idof[x] : a;
+    // most lines are one tree already
+    const int32_t na = ld_near(parent + a), nb = in ? ld_near(parent + b) : na;
+    const uint64_t differ = __ballot(na != nb);
+    if (!(half ? (uint32_t)(differ >> 32) : (uint32_t)differ)) continue;
+    int32_t ra = uf_find(parent, na);
+    int32_t rb = in ? uf_find(parent, nb) : ra;
+    while (true) {
+      const int32_t least = half_min(min(ra, rb));
+      // u's root, held by the whole half, and the entries' other roots: one
+      // lane hooks each, for all lanes that hold it
+      int32_t r = rb != least ? rb : ra;
+      bool todo = r != least;
+      bool again = false;
+      while (__ballot(todo)) {
+        const uint64_t m = __ballot(todo);
+        const uint32_t mine = half ? (uint32_t)(m >> 32) : (uint32_t)m;
+        const int lead = mine ? (half << 5) + __ffs((int)mine) - 1 : lane;
+        const int32_t v = __shfl(r, lead, 64);
+        int32_t to = v;
+        if (todo && lane == lead) {
+          to = least;
+          if (ld_i32(parent + v) != v || atomicCAS(parent + v, v, least) != v) to = uf_find(parent, v);
+        }
+        to = __shfl(to, lead, 64);
+        if (todo && r == v) {
+          todo = false;
+          again = to != least;
+        }
+        if (mine && ra == v) ra = to;
+        if (mine && rb == v) rb = to;
+      }
+      const uint64_t any = __ballot(again || ra != rb || ra != least);
+      if (!(half ? (uint32_t)(any >> 32) : (uint32_t)any)) break;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_tri_attach(int64_t lines, const int32_t* __restrict__ lu,
+                                                    const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
+                                                    const int32_t* __restrict__ lower,
+                                                    const int32_t* __restrict__ idof, int32_t mu, int32_t* parent,
+                                                    int32_t* label, const int32_t* __restrict__ flag) {
+  if (!*flag) return;
+  const int sub = threadIdx.x & 31;
+  const int64_t stride = (int64_t)gridDim.x * 8;
+  for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
+    if (!((simw[t] >> sub) & 1u)) continue;
+    const int32_t u = lu[t], x = oc[t * kTriLine + sub] - 1;
+    const bool cu = lower[u] >= mu, cx = lower[x] >= mu;
+    if (cu == cx) continue;
+    atomicMin(label + idof[cu ? x : u], uf_find(parent, idof[cu ? u : x]));
+  }
+}
+
+// Labels of the cores (needed before hub marks, which read every label).
+__global__ void k_tri_core_labels(int32_t n, const int32_t* hof, const int32_t* lower, int32_t mu, int32_t* parent,
+                                  int32_t* label, int32_t* first) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= n) return;
+  if (lower[hof[x]] >= mu) label[x] = uf_find(parent, (int32_t)x);
+  first[x] = -1;
+}
+
+// Def 2.7, one entry per lane: see k_hub_outlier.
+__global__ __launch_bounds__(256) void k_tri_hub(int64_t lines, const int32_t* __restrict__ lu,
+                                                 const int32_t* __restrict__ oc, const int32_t* __restrict__ idof,
+                                                 const int32_t* __restrict__ label, int32_t* first, uint8_t* role,
+                                                 const int32_t* __restrict__ flag) {
+  if (!*flag) return;
+  const int sub = threadIdx.x & 31;
+  const int64_t stride = (int64_t)gridDim.x * 8;
+  for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
+    const int32_t h = oc[t * kTriLine + sub] - 1;
+    if (h < 0) continue;
+    const int32_t a = idof[lu[t]], b = idof[h];
+    const int32_t la = label[a], lb = label[b];
+    if ((la == INT_MAX) == (lb == INT_MAX)) continue;
+    const int32_t x = (la == INT_MAX) ? a : b;
+    const int32_t L = (la == INT_MAX) ? lb : la;
+    const int32_t seen = ld_i32(first + x);
+    if (seen == L) continue;
+    const int32_t old = (seen == -1) ? atomicCAS(first + x, -1, L) : seen;
+    if (old != -1 && old != L) role[x] = ROLE_HUB;
+  }
+}
+
+__global__ void k_tri_output(int32_t n, const int32_t* __restrict__ hof, const int32_t* __restrict__ lower, int32_t mu,
+                             int32_t* parent, const int32_t* __restrict__ label, const uint8_t* __restrict__ role,
+                             int32_t* __restrict__ out_labels, uint8_t* __restrict__ out_roles, int32_t split) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= n) return;
+  if (lower[hof[x]] >= mu) {
+    out_roles[x] = 1;
+    out_labels[x] = uf_find(parent, (int32_t)x);
+    return;
+  }
+  const int32_t l = label[x];
+  out_labels[x] = l == INT_MAX ? -1 : l;
+  out_roles[x] = l != INT_MAX ? 2 : split ? (role[x] == ROLE_HUB ? 3 : 4) : 0;
+}
+
+// Counts in CSR order: one wave per row; the entry of an arc is found in the
+// row of its endpoint with the larger h.
+__global__ __launch_bounds__(256) void k_tri_arcs(int32_t n, const int64_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ ci, const int32_t* __restrict__ hof,
+                                                  const uint32_t* __restrict__ oline, const int32_t* __restrict__ row,
+                                                  const int32_t* __restrict__ oc, const int32_t* __restrict__ cnt,
+                                                  int32_t* __restrict__ counts) {
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = ((int64_t)gridDim.x * 256) >> 6;
+  for (int64_t x = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6; x < n; x += nw) {
+    const int32_t hx = hof[x];
+    for (int64_t k = rp[x] + lane; k < rp[x + 1]; k += 64) {
+      const int32_t hy = hof[ci[k]];
+      const int32_t u = max(hx, hy), v = min(hx, hy);
+      const int64_t base = (int64_t)oline[u] * kTriLine;
+      const int32_t j = tri_find(oc + base, row[u], v);
+      if (j >= 0) counts[k] = cnt[base + j];
+    }
+  }
+}
+
+inline unsigned grid_for(int64_t items, int64_t per_block) {
+  const int64_t b = (items + per_block - 1) / per_block;
+  return (unsigned)(b < 1 ? 1 : b);
+}
+
+uint32_t tri_acc_cap(const TriLayout& T) { return ((uint32_t)T.max_row + 2 + 3) & ~3u; }
+
+// Dynamic LDS of the block kernel: counters, then the largest table of the graph.
+size_t tri_lds_bytes(const TriLayout& T) {
+  const size_t acc = 4 * (size_t)tri_acc_cap(T);
+  size_t b = acc + 2 * ((size_t)std::min(T.n, kTriDirect) + 24);
+  if (T.n > kTriDirect) b = std::max(b, acc + 8 * ((size_t)std::min(T.n, kTriShort) / 32 + 3));
+  if (T.max_hash_row > 0) b = std::max(b, 8 * (size_t)tri_hash_slots(T.max_hash_row));
+  return (b + 15) & ~(size_t)15;
+}
+
+template <typename T>
+hipError_t dnew(T** p, int64_t count) {
+  return hipMalloc((void**)p, sizeof(T) * (size_t)(count > 0 ? count : 1));
+}
+
+}  // namespace
+
+uint64_t tri_layout_bytes(const TriLayout& T) {
+  const uint64_t n = (uint64_t)T.n, L = (uint64_t)T.lines;
+  return 16 * n + 12 * (n + 1) + 4 * L + 6 * (L * kTriLine + 2 * kTriLine) + sizeof(TriRec) * (uint64_t)T.recs +
+         sizeof(TriJob) * (uint64_t)T.jobs + sizeof(TriWave) * (uint64_t)T.wave_rows;
+}
+
+uint64_t tri_scratch_bytes(const TriLayout& T) {
+  return 4 * ((uint64_t)T.lines * kTriLine + (uint64_t)T.words + (uint64_t)T.lines + 1);
+}
+
+void tri_release(TriLayout& T) {
+  void* p[] = {T.hof, T.idof, T.deg, T.row, T.oline, T.wbase, T.inoff, T.lu, T.oc, T.oc16, T.rec, T.job, T.wrow};
+  for (void* x : p)
+    if (x) (void)hipFree(x);
+  T = TriLayout();
+}
+
+void tri_release_scratch(TriScratch& S) {
+  void* p[] = {S.cnt, S.bits, S.simw, S.flag};
+  for (void* x : p)
+    if (x) (void)hipFree(x);
+  S = TriScratch();
+}
+
+hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S) {
+  hipError_t e = dnew(&S->cnt, T.lines * kTriLine);
+  if (e == hipSuccess) e = dnew(&S->bits, T.words);
+  if (e == hipSuccess) e = dnew(&S->simw, T.lines);
+  if (e == hipSuccess) e = dnew(&S->flag, 1);
+  if (e != hipSuccess) tri_release_scratch(*S);
+  return e;
+}
+
+hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
+                     const int32_t* d_ci, TriLayout* out, int64_t* bucket_edges, int* ok) {
+  *ok = 0;
+  if (n <= 0 || nnz <= 0 || nnz / 2 >= (int64_t)1 << 31) return hipSuccess;
+  TriLayout T;
+  T.n = n;
+  T.recs = nnz / 2;
+  hipError_t e = hipSuccess;
+  int64_t *nline = nullptr, *nword = nullptr, *nin = nullptr, *at0 = nullptr, *at1 = nullptr, *at2 = nullptr;
+  int32_t *ctl = nullptr, *longer = nullptr;
+  unsigned long long* sums = nullptr;
+  int64_t tot[3] = {0, 0, 0};
+  int32_t h_ctl[4] = {0, 0, 0, 0};
+  unsigned long long h_sums[1 + kNumBuckets] = {0};
+  const unsigned gv = grid_for((int64_t)n + 1, 256);
+  int32_t nbig = 0;
+#define TTRY(x)                        \
+  do {                                 \
+    e = (x);                           \
+    if (e != hipSuccess) goto done;    \
+  } while (0)
+  {
+    // h: counting sort by decreasing degree, ties by id
+    int64_t maxd = 0;
+    for (int32_t v = 0; v < n; ++v) maxd = std::max(maxd, h_rp[v + 1] - h_rp[v]);
+    std::vector<int32_t> first((size_t)maxd + 2, 0), hof((size_t)n), idof((size_t)n);
+    for (int32_t v = 0; v < n; ++v) ++first[(size_t)(h_rp[v + 1] - h_rp[v])];
+    int32_t acc = 0;
+    for (int64_t d = maxd; d >= 0; --d) {
+      const int32_t t = first[(size_t)d];
+      first[(size_t)d] = acc;
+      acc += t;
+      if (d > 2048) nbig = acc;
+    }
+    for (int32_t v = 0; v < n; ++v) {
+      const int32_t h = first[(size_t)(h_rp[v + 1] - h_rp[v])]++;
+      hof[(size_t)v] = h;
+      idof[(size_t)h] = v;
+    }
+    TTRY(dnew(&T.hof, n));
+    TTRY(dnew(&T.idof, n));
+    TTRY(hipMemcpyAsync(T.hof, hof.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s));
+    TTRY(hipMemcpyAsync(T.idof, idof.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s));
+    TTRY(hipStreamSynchronize(s));
+  }
+  TTRY(dnew(&T.deg, n));
+  TTRY(dnew(&T.row, n));
+  TTRY(dnew(&ctl, 4));   // longest row, rows for the block sort, longest hash row
+  TTRY(dnew(&sums, 1 + kNumBuckets));
+  TTRY(hipMemsetAsync(ctl, 0, 16, s));
+  TTRY(hipMemsetAsync(sums, 0, 8 * (1 + kNumBuckets), s));
+  if (nbig > 0) k_row_len_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.deg, T.row);
+  if (n > nbig) k_row_len_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.deg, T.row);
+  TTRY(hipGetLastError());
+  TTRY(dnew(&nline, (int64_t)n + 1));
+  TTRY(dnew(&nword, (int64_t)n + 1));
+  TTRY(dnew(&nin, (int64_t)n + 1));
+  TTRY(dnew(&at0, (int64_t)n + 1));
+  TTRY(dnew(&at1, (int64_t)n + 1));
+  TTRY(dnew(&at2, (int64_t)n + 1));
+  k_row_sizes<<<gv, 256, 0, s>>>(n, T.deg, T.row, nline, nword, nin, ctl);
+  TTRY(hipGetLastError());
+  TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1));
+  TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1));
+  TTRY(exclusive_scan(s, nin, at2, (int64_t)n + 1));
+  TTRY(hipMemcpyAsync(tot + 0, at0 + n, 8, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(tot + 1, at1 + n, 8, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(tot + 2, at2 + n, 8, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(h_ctl, ctl, 16, hipMemcpyDeviceToHost, s));
+  TTRY(hipStreamSynchronize(s));
+  T.max_row = h_ctl[0];
+  T.lines = tot[0];
+  T.words = tot[1];
+  if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 31 || T.words >= (int64_t)1 << 32 || tot[2] != T.recs)
+    goto done;  // outside the limits, or not a symmetric CSR
+  TTRY(dnew(&T.oline, (int64_t)n + 1));
+  TTRY(dnew(&T.wbase, (int64_t)n + 1));
+  TTRY(dnew(&T.inoff, (int64_t)n + 1));
+  k_narrow<<<gv, 256, 0, s>>>(n, at0, at1, at2, T.oline, T.wbase, T.inoff);
+  TTRY(dnew(&T.lu, T.lines));
+  // steps of 64 entries may start on a row's last line
+  TTRY(dnew(&T.oc, (T.lines + 2) * kTriLine));
+  TTRY(dnew(&T.oc16, (T.lines + 2) * kTriLine));
+  TTRY(dnew(&longer, n));
+  if (nbig > 0) k_row_fill_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
+  if (n > nbig)
+    k_row_fill_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
+  k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.oc, T.oc16, T.lu, longer, ctl + 1);
+  k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.oc, T.oc16);
+  TTRY(hipGetLastError());
+  TTRY(dnew(&T.rec, T.recs));
+  if (nbig > 0)
+    k_recs_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row, T.oc, T.inoff, T.rec,
+                                       nin);
+  if (n > nbig)
+    k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
+                                                      T.oc, T.inoff, T.rec, nin);
+  k_job_counts<<<gv, 256, 0, s>>>(n, T.row, T.inoff, nin, nline, nword, sums, ctl + 2);
+  k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
+                                                                                               T.deg, sums + 1);
+  TTRY(hipGetLastError());
+  TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1));
+  TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1));
+  TTRY(hipMemcpyAsync(tot + 0, at0 + n, 8, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(tot + 1, at1 + n, 8, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(h_ctl, ctl, 16, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(h_sums, sums, sizeof(h_sums), hipMemcpyDeviceToHost, s));
+  TTRY(hipStreamSynchronize(s));
+  T.jobs = tot[0];
+  T.wave_rows = tot[1];
+  T.max_hash_row = h_ctl[2];
+  T.steps = (int64_t)h_sums[0];
+  for (int k = 0; k < kNumBuckets; ++k) bucket_edges[k] = (int64_t)h_sums[1 + k];
+  TTRY(dnew(&T.job, T.jobs));
+  TTRY(dnew(&T.wrow, T.wave_rows));
+  k_job_fill<<<gv, 256, 0, s>>>(n, T.inoff, T.oline, T.row, at0, at1, T.job, T.wrow);
+  TTRY(hipGetLastError());
+  TTRY(hipStreamSynchronize(s));
+  *out = T;
+  *ok = 1;
+done:
+  (void)hipStreamSynchronize(s);
+  void* tmp[] = {nline, nword, nin, at0, at1, at2, ctl, longer, sums};
+  for (void* x : tmp)
+    if (x) (void)hipFree(x);
+  if (!*ok) tri_release(T);
+#undef TTRY
+  return e;
+}
+
+void tri_init(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* lower, int32_t* parent,
+              int32_t* label, uint8_t* role) {
+  const int64_t ncnt4 = T.lines * (kTriLine / 4);
+  const unsigned grid = (unsigned)std::min<int64_t>(grid_for(std::max<int64_t>(ncnt4, T.n), 256), 8192);
+  k_tri_init<<<grid, 256, 0, s>>>(ncnt4, reinterpret_cast<int4*>(S.cnt), T.n, lower, parent, label, role, S.flag);
+}
+
+void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
+  if (T.jobs > 0)
+    k_tri_block<<<(unsigned)T.jobs, kTriBlock, tri_lds_bytes(T), s>>>(T.job, T.rec, T.row, T.oline, T.oc, T.oc16,
+                                                                     S.bits, S.cnt, tri_acc_cap(T));
+  if (T.wave_rows > 0)
+    k_tri_wave<<<grid_for(T.wave_rows, 4), 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc, S.bits, S.cnt);
+}
+
+void tri_close(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower) {
+  if (T.lines <= 0) return;
+  const unsigned grid = grid_for(T.lines, 8);
+  if (a.q)
+    k_tri_close<true><<<grid, 256, 0, s>>>(T.lines, T.lu, T.oline, T.wbase, T.row, T.deg, T.oc, S.bits, S.cnt, a,
+                                           S.simw, lower, S.flag);
+  else
+    k_tri_close<false><<<grid, 256, 0, s>>>(T.lines, T.lu, T.oline, T.wbase, T.row, T.deg, T.oc, S.bits, S.cnt, a,
+                                            S.simw, nullptr, S.flag);
+}
+
+namespace {
+unsigned line_grid(const TriLayout& T) { return (unsigned)std::min<int64_t>(grid_for(T.lines, 8), 1 << 16); }
+}  // namespace
+
+void tri_hook(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+              int32_t* parent) {
+  if (T.lines <= 0) return;
+  k_tri_link<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, mu, parent, S.flag);
+  k_tri_compress<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, parent, S.flag);
+  k_tri_hook<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, mu, parent, S.flag);
+}
+
+void tri_attach(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+                int32_t* parent, int32_t* label) {
+  if (T.lines > 0)
+    k_tri_attach<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, mu, parent, label, S.flag);
+}
+
+void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+                     int32_t* parent, int32_t* label, int32_t* first, uint8_t* role) {
+  k_tri_core_labels<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, T.hof, lower, mu, parent, label, first);
+  if (T.lines > 0)
+    k_tri_hub<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, T.idof, label, first, role, S.flag);
+}
+
+void tri_output(hipStream_t s, const TriLayout& T, int32_t mu, const int32_t* lower, int32_t* parent,
+                const int32_t* label, const uint8_t* role, int32_t* out_labels, uint8_t* out_roles, int32_t split) {
+  if (T.n > 0)
+    k_tri_output<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, T.hof, lower, mu, parent, label, role, out_labels, out_roles,
+                                                    split);
+}
+
+void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, const int64_t* rp, const int32_t* ci,
+                    int32_t* counts) {
+  const unsigned grid = (unsigned)std::min<int64_t>(grid_for(T.n, 4), 1 << 16);
+  k_tri_arcs<<<grid, 256, 0, s>>>(T.n, rp, ci, T.hof, T.oline, T.row, T.oc, S.cnt, counts);
+}
+
+}  // namespace scan
