@@ -19,19 +19,20 @@ namespace scan {
 constexpr int kTriLine = 32;
 constexpr int kTriMaxRow = 4096;  // longest row the kernels take
 constexpr int kTriBlock = 512;    // threads of the block kernel
-constexpr int kTriJob = 1024;     // in-edges per job of the block kernel
+constexpr int kTriRecLines = 8;   // lines per in-edge record
+constexpr int kTriJob = 1024;     // records per job of the block kernel
 constexpr int kTriDirect = 16384; // h below this: table of row positions indexed by h
 constexpr int kTriShort = 65534;  // h below this: 16-bit entries (oc16) and a bitmap table
 constexpr int kTriWaveRow = 128;  // rows up to this, with few in-edges, go one per wave
 constexpr int kTriWaveSlots = 256;
 constexpr int64_t kTriWaveWords = 512;  // words of in-edges a wave takes on
 
-// One in-edge (u, v) of a vertex v: the columns of row u after v's entry are
-// the w to look up in row v.
+// Up to kTriRecLines lines of one in-edge (u, v) of a vertex v: the columns of
+// row u after v's entry are the w to look up in row v.
 struct TriRec {
-  uint32_t line;  // line of v's entry in row u
-  uint32_t word;  // bit word of row u's columns from that line on
-  uint32_t nw;    // lines from there to the end of row u (0: nothing after v)
+  uint32_t line;  // first line (of v's entry in row u, or a later one)
+  uint32_t word;  // bit word of that line
+  uint32_t nw;    // lines
   uint32_t pad;
 };
 
@@ -60,11 +61,10 @@ struct TriLayout {
   int32_t* row = nullptr;     // [n] entries of a row, by h
   uint32_t* oline = nullptr;  // [n + 1] first line of a row
   uint32_t* wbase = nullptr;  // [n + 1] first bit word of a row
-  uint32_t* inoff = nullptr;  // [n + 1] first in-edge record
   int32_t* lu = nullptr;      // [lines] h of the line's row
   int32_t* oc = nullptr;      // [32 lines + pad] h + 1 of the neighbour, or 0
   uint16_t* oc16 = nullptr;   // the same in 16 bits, 0xFFFF for h >= kTriShort
-  TriRec* rec = nullptr;      // [recs]
+  TriRec* rec = nullptr;      // [recs] a vertex's records, then unused ones
   TriJob* job = nullptr;      // [jobs], hubs first
   TriWave* wrow = nullptr;    // [wave_rows]
 };

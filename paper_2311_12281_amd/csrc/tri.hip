@@ -84,29 +84,71 @@ __global__ __launch_bounds__(256) void k_row_len_wave(int32_t h0, int32_t n, con
   }
 }
 
-// Per vertex: lines and bit words of its row, in-edges, longest row.
-__global__ void k_row_sizes(int32_t n, const int32_t* deg, const int32_t* row, int64_t* nline, int64_t* nword,
-                            int64_t* nin, int32_t* max_row) {
+// In-edge records of (u, v) at most, whatever v's column: kTriRecLines lines each.
+__device__ __forceinline__ int32_t tri_recs_of(int32_t D) {
+  return D < 2 ? 0 : ((int32_t)tri_lines(D) + kTriRecLines - 1) / kTriRecLines;
+}
+
+__global__ __launch_bounds__(1024) void k_in_bound_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
+                                                         const int32_t* hof, const int32_t* idof, const int32_t* row,
+                                                         int64_t* nin) {
+  __shared__ unsigned long long sum;
+  const int32_t h = blockIdx.x;
+  if (h >= nbig) return;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  unsigned long long c = 0;
+  for (int64_t k = b + threadIdx.x; k < e; k += 1024) {
+    const int32_t u = hof[ci[k]];
+    if (u > h) c += tri_recs_of(row[u]);
+  }
+  c = wave_sum(c);
+  if ((threadIdx.x & 63) == 0 && c) atomicAdd(&sum, c);
+  __syncthreads();
+  if (threadIdx.x == 0) nin[h] = (int64_t)sum;
+}
+
+__global__ __launch_bounds__(256) void k_in_bound_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
+                                                       const int32_t* hof, const int32_t* idof, const int32_t* row,
+                                                       int64_t* nin) {
+  const int lane = threadIdx.x & 63;
+  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  if (h >= n) return;
+  const int32_t x = idof[h];
+  const int64_t b = rp[x], e = rp[x + 1];
+  unsigned long long c = 0;
+  for (int64_t k = b + lane; k < e; k += 64) {
+    const int32_t u = hof[ci[k]];
+    if (u > h) c += tri_recs_of(row[u]);
+  }
+  c = wave_sum(c);
+  if (lane == 0) nin[h] = (int64_t)c;
+}
+
+// Per vertex: lines and bit words of its row; all entries, and the longest row.
+__global__ void k_row_sizes(int32_t n, const int32_t* row, int64_t* nline, int64_t* nword, unsigned long long* entries,
+                            int32_t* max_row) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int32_t D = h < n ? row[h] : 0;
   const uint32_t W = tri_lines(D);
   if (h <= n) {
     nline[h] = W;
     nword[h] = D <= kTriMaxRow ? tri_word(W, (uint32_t)D) : 0;
-    nin[h] = h < n ? deg[h] - D : 0;
   }
+  const unsigned long long all = wave_sum((unsigned long long)D);
+  if ((threadIdx.x & 63) == 0 && all) atomicAdd(entries, all);
   int32_t m = D;
   for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d, 64));
   if ((threadIdx.x & 63) == 0 && m > 0) atomicMax(max_row, m);
 }
 
-__global__ void k_narrow(int32_t n, const int64_t* a, const int64_t* b, const int64_t* c, uint32_t* x, uint32_t* y,
-                         uint32_t* z) {
+__global__ void k_narrow(int32_t n, const int64_t* a, const int64_t* b, uint32_t* x, uint32_t* y) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (h > n) return;
   x[h] = (uint32_t)a[h];
   y[h] = (uint32_t)b[h];
-  z[h] = (uint32_t)c[h];
 }
 
 // Entries of every row, in the order of the CSR (sorted afterwards).
@@ -255,19 +297,41 @@ __device__ __forceinline__ TriRec tri_rec(int32_t u, int32_t v, const uint32_t* 
   return r;
 }
 
-// In-edge records of every vertex, and the words its in-edges hold.
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, int lane) {
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+  }
+  return x;
+}
+
+__device__ __forceinline__ void tri_put_recs(TriRec r, TriRec* out, uint32_t p, uint32_t end) {
+  for (; r.nw > 0 && p < end; ++p) {
+    TriRec c = r;
+    c.nw = min(r.nw, (uint32_t)kTriRecLines);
+    out[p] = c;
+    r.line += c.nw;
+    r.word += c.nw;
+    r.nw -= c.nw;
+  }
+}
+
+// In-edge records of every vertex: their number and the words they hold.
 __global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
                                                      const int32_t* hof, const int32_t* idof, const uint32_t* oline,
                                                      const uint32_t* wbase, const int32_t* row, const int32_t* oc,
-                                                     const uint32_t* inoff, TriRec* rec, int64_t* steps) {
-  __shared__ int32_t at;
+                                                     const int64_t* inoff, TriRec* rec, uint32_t* inlen,
+                                                     int64_t* steps) {
+  __shared__ uint32_t at;
   __shared__ unsigned long long sum;
   const int32_t h = blockIdx.x;
   if (h >= nbig) return;
   const int lane = threadIdx.x & 63;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
-  const uint32_t r0 = inoff[h], rn = inoff[h + 1] - r0;
+  const uint32_t rn = (uint32_t)(inoff[h + 1] - inoff[h]);
+  TriRec* out = rec + inoff[h];
   if (threadIdx.x == 0) {
     at = 0;
     sum = 0;
@@ -277,51 +341,53 @@ __global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t
   for (int64_t k0 = b; k0 < e; k0 += 1024) {
     const int64_t k = k0 + threadIdx.x;
     const int32_t u = k < e ? hof[ci[k]] : -1;
-    const bool keep = u > h;
-    const uint64_t mask = __ballot(keep);
-    int32_t base = 0;
-    if (lane == 0 && mask) base = atomicAdd(&at, (int32_t)__popcll(mask));
+    const TriRec r = u > h ? tri_rec(u, h, oline, wbase, row, oc) : TriRec{};
+    const uint32_t c = (r.nw + kTriRecLines - 1) / kTriRecLines;
+    const uint32_t incl = wave_scan(c, lane), all = __shfl(incl, 63, 64);
+    uint32_t base = 0;
+    if (lane == 0 && all) base = atomicAdd(&at, all);
     base = __shfl(base, 0, 64);
-    const uint32_t p = (uint32_t)base + (uint32_t)__popcll(mask & lanes_below(lane));
-    if (keep && p < rn) {
-      const TriRec r = tri_rec(u, h, oline, wbase, row, oc);
-      rec[r0 + p] = r;
-      st += r.nw;
-    }
+    tri_put_recs(r, out, base + incl - c, rn);
+    st += r.nw;
   }
   st = wave_sum(st);
   if (lane == 0 && st) atomicAdd(&sum, st);
   __syncthreads();
-  if (threadIdx.x == 0) steps[h] = (int64_t)sum;
+  if (threadIdx.x == 0) {
+    inlen[h] = min(at, rn);
+    steps[h] = (int64_t)sum;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                    const int32_t* hof, const int32_t* idof, const uint32_t* oline,
                                                    const uint32_t* wbase, const int32_t* row, const int32_t* oc,
-                                                   const uint32_t* inoff, TriRec* rec, int64_t* steps) {
+                                                   const int64_t* inoff, TriRec* rec, uint32_t* inlen,
+                                                   int64_t* steps) {
   const int lane = threadIdx.x & 63;
   const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
   if (h >= n) return;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
-  const uint32_t r0 = inoff[h], rn = inoff[h + 1] - r0;
+  const uint32_t rn = (uint32_t)(inoff[h + 1] - inoff[h]);
+  TriRec* out = rec + inoff[h];
   uint32_t at = 0;
   unsigned long long st = 0;
   for (int64_t k0 = b; k0 < e; k0 += 64) {
     const int64_t k = k0 + lane;
     const int32_t u = k < e ? hof[ci[k]] : -1;
-    const bool keep = u > h;
-    const uint64_t mask = __ballot(keep);
-    const uint32_t p = at + (uint32_t)__popcll(mask & lanes_below(lane));
-    if (keep && p < rn) {
-      const TriRec r = tri_rec(u, (int32_t)h, oline, wbase, row, oc);
-      rec[r0 + p] = r;
-      st += r.nw;
-    }
-    at += (uint32_t)__popcll(mask);
+    const TriRec r = u > (int32_t)h ? tri_rec(u, (int32_t)h, oline, wbase, row, oc) : TriRec{};
+    const uint32_t c = (r.nw + kTriRecLines - 1) / kTriRecLines;
+    const uint32_t incl = wave_scan(c, lane);
+    tri_put_recs(r, out, at + incl - c, rn);
+    at += __shfl(incl, 63, 64);
+    st += r.nw;
   }
   st = wave_sum(st);
-  if (lane == 0) steps[h] = (int64_t)st;
+  if (lane == 0) {
+    inlen[h] = min(at, rn);
+    steps[h] = (int64_t)st;
+  }
 }
 
 __device__ __forceinline__ bool tri_wave_row(int32_t D, uint32_t nin, int64_t steps) {
@@ -330,17 +396,17 @@ __device__ __forceinline__ bool tri_wave_row(int32_t D, uint32_t nin, int64_t st
 
 // Work of every vertex: jobs of the block kernel, or a place in the wave
 // kernel's list; the sum of all words and the longest hash-table row.
-__global__ void k_job_counts(int32_t n, const int32_t* row, const uint32_t* inoff, const int64_t* steps,
+__global__ void k_job_counts(int32_t n, const int32_t* row, const uint32_t* inlen, const int64_t* steps,
                              int64_t* njob, int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t j = 0, w = 0;
   unsigned long long st = 0;
   if (h < n && steps[h] > 0) {
     st = (unsigned long long)steps[h];
-    if (tri_wave_row(row[h], inoff[h + 1] - inoff[h], steps[h])) {
+    if (tri_wave_row(row[h], inlen[h], steps[h])) {
       w = 1;
     } else {
-      j = (inoff[h + 1] - inoff[h] + kTriJob - 1) / kTriJob;
+      j = (inlen[h] + kTriJob - 1) / kTriJob;
       if (h >= kTriShort) atomicMax(max_hash, row[h]);
     }
   }
@@ -352,12 +418,12 @@ __global__ void k_job_counts(int32_t n, const int32_t* row, const uint32_t* inof
   if ((threadIdx.x & 63) == 0 && st) atomicAdd(total, st);
 }
 
-__global__ void k_job_fill(int32_t n, const uint32_t* inoff, const uint32_t* oline, const int32_t* row,
+__global__ void k_job_fill(int32_t n, const int64_t* inoff, const uint32_t* inlen, const uint32_t* oline, const int32_t* row,
                            const int64_t* job_at, const int64_t* wave_at, TriJob* job, TriWave* wrow) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (h >= n) return;
   const int64_t j0 = job_at[h], nj = job_at[h + 1] - j0;
-  const uint32_t r0 = inoff[h], r1 = inoff[h + 1];
+  const uint32_t r0 = (uint32_t)inoff[h], r1 = r0 + inlen[h];
   if (wave_at[h + 1] > wave_at[h]) wrow[wave_at[h]] = TriWave{(int32_t)h, oline[h], r0, (uint32_t)row[h] | (r1 - r0) << 8};
   for (int64_t j = 0; j < nj; ++j) {
     TriJob J;
@@ -400,104 +466,90 @@ __device__ __forceinline__ void set_lane(uint32_t& w, uint32_t x, const int to) 
   asm("v_writelane_b32 %0, %1, %2" : "+v"(w) : "s"(x), "i"(to));
 }
 
-// Loads through a buffer descriptor whose size is the rest of the row: entries
-// past it read as 0 (no entry) without touching memory.
-constexpr int kBufferFlags = 0x00027000;  // raw 32-bit data, gfx9 layout
-__device__ __forceinline__ uint16_t buffer_entry(const uint16_t*, __amdgpu_buffer_rsrc_t b, int lane, int k) {
-  return __builtin_amdgcn_raw_buffer_load_b16(b, 2 * lane + 128 * k, 0, 0);
+// Accesses through a buffer descriptor that ends where the record ends: loads
+// past it give 0 (no entry) and stores nothing, without touching memory.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_upto(const void* base, uint32_t end) {
+  constexpr int kFlags = 0x00027000;  // raw 32-bit data
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)end, kFlags);
 }
-__device__ __forceinline__ uint32_t buffer_entry(const uint32_t*, __amdgpu_buffer_rsrc_t b, int lane, int k) {
-  return __builtin_amdgcn_raw_buffer_load_b32(b, 4 * lane + 256 * k, 0, 0);
+__device__ __forceinline__ uint16_t buffer_entry(const uint16_t*, __amdgpu_buffer_rsrc_t b, uint32_t at) {
+  return __builtin_amdgcn_raw_buffer_load_b16(b, (int)at, 0, 0);
+}
+__device__ __forceinline__ uint32_t buffer_entry(const uint32_t*, __amdgpu_buffer_rsrc_t b, uint32_t at) {
+  return __builtin_amdgcn_raw_buffer_load_b32(b, (int)at, 0, 0);
 }
 
 using LdsCounter = __attribute__((address_space(3))) int32_t;
 
 // Columns of one job's in-edges through a lookup: find(x) is the LDS address
-// of x's counter, or 0.  A wave takes a run of the in-edges, one at a time and
-// 64 columns a step, so that the record (read from the lane that loaded it),
-// the row's address and the loop are scalar and a ballot is two words of bits.
-// The columns of four steps, of this in-edge or the next, are loaded while the
-// four before them are looked up; all four loads are always issued, since a
-// load under a branch would make the compiler wait for every load in flight.
+// of x's counter, or 0.  A wave takes a run of the records, one at a time (up
+// to 8 lines) and 64 columns a step, so that addresses and loop are scalar and
+// a ballot is two words of bits.  Each lane works out the offsets of one record
+// of 64, read back one after the other: scalar instructions, of which a compute
+// unit issues one a cycle for all its waves, bounded the loop when every record
+// was decoded in scalar code (R-MAT scale 22: 6.6 ms).  The next record is loaded
+// while this one is looked up; all four loads are always issued, since a load
+// under a branch would make the compiler wait for every load in flight.
 // Columns up to v's own are in no table of v (h(w) >= h(v)) and need no mask.
 template <typename E, typename F>
 __device__ __forceinline__ void tri_stream(const E* __restrict__ cols, const TriRec* __restrict__ rec, uint32_t cnt,
                                            uint32_t wave, int lane, uint32_t* __restrict__ bits, F find) {
-  constexpr uint32_t kAhead = 8;  // lines per chunk
+  static_assert(kTriRecLines == 8, "four steps of two lines");
+  constexpr uint32_t kLineBytes = kTriLine * sizeof(E), kStep = 64 * sizeof(E);
   struct Cols {
     E c0, c1, c2, c3;  // (named: an array is kept as one vector, which waits for all of it)
-  };
-  struct Chunk {
-    uint32_t i, line, word, left;  // record, next line and word, lines left
   };
   // (two clamped ends: written as a saturating difference, the compiler drops
   // the saturation of the scalar subtraction)
   const uint32_t per = (cnt + kTriBlock / 64 - 1) / (kTriBlock / 64);
   const uint32_t first = min(wave * per, cnt), n = min(wave * per + per, cnt) - first;
+  const uint32_t at = (uint32_t)lane * sizeof(E), wat = (uint32_t)lane * 4;
   for (uint32_t b0 = 0; b0 < n; b0 += 64) {
     const uint32_t nb = min(64u, n - b0);
-    const TriRec mine = (uint32_t)lane < nb ? rec[first + b0 + lane] : TriRec{};
-    auto at = [&](uint32_t i) {
-      Chunk c;
-      c.i = i;
-      c.line = (uint32_t)__builtin_amdgcn_readlane((int)mine.line, (int)(i & 63));
-      c.word = (uint32_t)__builtin_amdgcn_readlane((int)mine.word, (int)(i & 63));
-      c.left = (uint32_t)__builtin_amdgcn_readlane((int)mine.nw, (int)(i & 63));
-      return c;
+    const TriRec r = (uint32_t)lane < nb ? rec[first + b0 + lane] : TriRec{};
+    const int off = (int)(r.line * kLineBytes), end = (int)((r.line + r.nw) * kLineBytes);
+    const int woff = (int)(r.word * 4), wend = (int)((r.word + r.nw) * 4);
+    auto load = [&](Cols& y, uint32_t i) {  // i = 64: record 0 again, not used
+      const uint32_t o = at + (uint32_t)__builtin_amdgcn_readlane(off, (int)(i & 63));
+      const __amdgpu_buffer_rsrc_t b = buffer_upto(cols, (uint32_t)__builtin_amdgcn_readlane(end, (int)(i & 63)));
+      y.c0 = buffer_entry(cols, b, o);
+      y.c1 = buffer_entry(cols, b, o + kStep);
+      y.c2 = buffer_entry(cols, b, o + 2 * kStep);
+      y.c3 = buffer_entry(cols, b, o + 3 * kStep);
     };
-    auto after = [&](const Chunk& c) {
-      if (c.left <= kAhead) return at(c.i + 1);
-      Chunk d = c;
-      d.line += kAhead;
-      d.word += kAhead;
-      d.left -= kAhead;
-      return d;
-    };
-    auto load = [&](Cols& y, const Chunk& c) {
-      const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<E*>(cols + (uint64_t)c.line * kTriLine), 0, (int)(c.left * (kTriLine * sizeof(E))), kBufferFlags);
-      y.c0 = buffer_entry(cols, b, lane, 0);
-      y.c1 = buffer_entry(cols, b, lane, 1);
-      y.c2 = buffer_entry(cols, b, lane, 2);
-      y.c3 = buffer_entry(cols, b, lane, 3);
-    };
-    auto look = [&](const Cols& x, const Chunk& c) {
+    auto look = [&](const Cols& x, uint32_t i) {
+      const uint32_t so = (uint32_t)__builtin_amdgcn_readlane(woff, (int)i);
+      const uint32_t se = (uint32_t)__builtin_amdgcn_readlane(wend, (int)i);
+      const uint32_t left = se - so;  // bytes of bits: 4 per line
       uint32_t w = 0;
       auto step = [&](E col, auto k) {
         constexpr int kAt = decltype(k)::value;
         const uint32_t place = find(col);
         const bool hit = place != 0;
         const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
-        if (hit) __hip_atomic_fetch_add((LdsCounter*)place, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (hit) __hip_atomic_fetch_add((LdsCounter*)(uintptr_t)place, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         set_lane(w, (uint32_t)m, 2 * kAt);
         set_lane(w, (uint32_t)(m >> 32), 2 * kAt + 1);
       };
-      if (c.left > 0) {
+      if (left > 0) {
         step(x.c0, std::integral_constant<int, 0>{});
-        if (c.left > 2) {
+        if (left > 8) {
           step(x.c1, std::integral_constant<int, 1>{});
-          if (c.left > 4) {
+          if (left > 16) {
             step(x.c2, std::integral_constant<int, 2>{});
-            if (c.left > 6) step(x.c3, std::integral_constant<int, 3>{});
+            if (left > 24) step(x.c3, std::integral_constant<int, 3>{});
           }
         }
       }
-      const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc(
-          bits + c.word, 0, (int)(min(c.left, kAhead) * 4), kBufferFlags);
-      __builtin_amdgcn_raw_buffer_store_b32(w, b, 4 * lane, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(w, buffer_upto(bits, se), (int)(wat + so), 0, 0);
     };
     Cols x, y;
-    Chunk c = at(0);
-    load(x, c);
-    while (true) {
-      const Chunk d = after(c);
-      load(y, d);
-      look(x, c);
-      if (d.i >= nb) break;
-      c = after(d);
-      load(x, c);
-      look(y, d);
-      if (c.i >= nb) break;
+    load(x, 0);
+    for (uint32_t i = 0; i < nb; i += 2) {
+      load(y, i + 1);
+      look(x, i);
+      load(x, i + 2);
+      look(y, i + 1);
     }
   }
 }
@@ -1032,7 +1084,7 @@ hipError_t dnew(T** p, int64_t count) {
 
 uint64_t tri_layout_bytes(const TriLayout& T) {
   const uint64_t n = (uint64_t)T.n, L = (uint64_t)T.lines;
-  return 16 * n + 12 * (n + 1) + 4 * L + 6 * (L * kTriLine + 2 * kTriLine) + sizeof(TriRec) * (uint64_t)T.recs +
+  return 16 * n + 8 * (n + 1) + 4 * L + 6 * (L * kTriLine + 2 * kTriLine) + sizeof(TriRec) * (uint64_t)T.recs +
          sizeof(TriJob) * (uint64_t)T.jobs + sizeof(TriWave) * (uint64_t)T.wave_rows;
 }
 
@@ -1041,7 +1093,7 @@ uint64_t tri_scratch_bytes(const TriLayout& T) {
 }
 
 void tri_release(TriLayout& T) {
-  void* p[] = {T.hof, T.idof, T.deg, T.row, T.oline, T.wbase, T.inoff, T.lu, T.oc, T.oc16, T.rec, T.job, T.wrow};
+  void* p[] = {T.hof, T.idof, T.deg, T.row, T.oline, T.wbase, T.lu, T.oc, T.oc16, T.rec, T.job, T.wrow};
   for (void* x : p)
     if (x) (void)hipFree(x);
   T = TriLayout();
@@ -1069,14 +1121,14 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (n <= 0 || nnz <= 0 || nnz / 2 >= (int64_t)1 << 31) return hipSuccess;
   TriLayout T;
   T.n = n;
-  T.recs = nnz / 2;
   hipError_t e = hipSuccess;
   int64_t *nline = nullptr, *nword = nullptr, *nin = nullptr, *at0 = nullptr, *at1 = nullptr, *at2 = nullptr;
+  uint32_t* inlen = nullptr;
   int32_t *ctl = nullptr, *longer = nullptr;
   unsigned long long* sums = nullptr;
   int64_t tot[3] = {0, 0, 0};
   int32_t h_ctl[4] = {0, 0, 0, 0};
-  unsigned long long h_sums[1 + kNumBuckets] = {0};
+  unsigned long long h_sums[2 + kNumBuckets] = {0};
   const unsigned gv = grid_for((int64_t)n + 1, 256);
   int32_t nbig = 0;
 #define TTRY(x)                        \
@@ -1111,9 +1163,9 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(dnew(&T.deg, n));
   TTRY(dnew(&T.row, n));
   TTRY(dnew(&ctl, 4));   // longest row, rows for the block sort, longest hash row
-  TTRY(dnew(&sums, 1 + kNumBuckets));
+  TTRY(dnew(&sums, 2 + kNumBuckets));  // words, edges per bucket, entries
   TTRY(hipMemsetAsync(ctl, 0, 16, s));
-  TTRY(hipMemsetAsync(sums, 0, 8 * (1 + kNumBuckets), s));
+  TTRY(hipMemsetAsync(sums, 0, sizeof(h_sums), s));
   if (nbig > 0) k_row_len_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.deg, T.row);
   if (n > nbig) k_row_len_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.deg, T.row);
   TTRY(hipGetLastError());
@@ -1123,7 +1175,11 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(dnew(&at0, (int64_t)n + 1));
   TTRY(dnew(&at1, (int64_t)n + 1));
   TTRY(dnew(&at2, (int64_t)n + 1));
-  k_row_sizes<<<gv, 256, 0, s>>>(n, T.deg, T.row, nline, nword, nin, ctl);
+  TTRY(dnew(&inlen, n));
+  k_row_sizes<<<gv, 256, 0, s>>>(n, T.row, nline, nword, sums + 1 + kNumBuckets, ctl);
+  if (nbig > 0) k_in_bound_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.row, nin);
+  if (n > nbig) k_in_bound_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row, nin);
+  TTRY(hipMemsetAsync(nin + n, 0, 8, s));
   TTRY(hipGetLastError());
   TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1));
   TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1));
@@ -1132,16 +1188,19 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(hipMemcpyAsync(tot + 1, at1 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(tot + 2, at2 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(h_ctl, ctl, 16, hipMemcpyDeviceToHost, s));
+  TTRY(hipMemcpyAsync(h_sums, sums, sizeof(h_sums), hipMemcpyDeviceToHost, s));
   TTRY(hipStreamSynchronize(s));
   T.max_row = h_ctl[0];
   T.lines = tot[0];
   T.words = tot[1];
-  if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 31 || T.words >= (int64_t)1 << 32 || tot[2] != T.recs)
-    goto done;  // outside the limits, or not a symmetric CSR
+  T.recs = tot[2];
+  // outside the limits (32-bit byte offsets of entries and bits), or not a symmetric CSR
+  if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 25 || T.words >= (int64_t)1 << 30 ||
+      T.recs >= (int64_t)1 << 32 || (int64_t)h_sums[1 + kNumBuckets] != nnz / 2)
+    goto done;
   TTRY(dnew(&T.oline, (int64_t)n + 1));
   TTRY(dnew(&T.wbase, (int64_t)n + 1));
-  TTRY(dnew(&T.inoff, (int64_t)n + 1));
-  k_narrow<<<gv, 256, 0, s>>>(n, at0, at1, at2, T.oline, T.wbase, T.inoff);
+  k_narrow<<<gv, 256, 0, s>>>(n, at0, at1, T.oline, T.wbase);
   TTRY(dnew(&T.lu, T.lines));
   // steps of 64 entries may start on a row's last line
   TTRY(dnew(&T.oc, (T.lines + 2) * kTriLine));
@@ -1155,12 +1214,12 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(hipGetLastError());
   TTRY(dnew(&T.rec, T.recs));
   if (nbig > 0)
-    k_recs_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row, T.oc, T.inoff, T.rec,
-                                       nin);
+    k_recs_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row, T.oc, at2, T.rec,
+                                       inlen, nin);
   if (n > nbig)
     k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
-                                                      T.oc, T.inoff, T.rec, nin);
-  k_job_counts<<<gv, 256, 0, s>>>(n, T.row, T.inoff, nin, nline, nword, sums, ctl + 2);
+                                                      T.oc, at2, T.rec, inlen, nin);
+  k_job_counts<<<gv, 256, 0, s>>>(n, T.row, inlen, nin, nline, nword, sums, ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
   TTRY(hipGetLastError());
@@ -1178,14 +1237,14 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   for (int k = 0; k < kNumBuckets; ++k) bucket_edges[k] = (int64_t)h_sums[1 + k];
   TTRY(dnew(&T.job, T.jobs));
   TTRY(dnew(&T.wrow, T.wave_rows));
-  k_job_fill<<<gv, 256, 0, s>>>(n, T.inoff, T.oline, T.row, at0, at1, T.job, T.wrow);
+  k_job_fill<<<gv, 256, 0, s>>>(n, at2, inlen, T.oline, T.row, at0, at1, T.job, T.wrow);
   TTRY(hipGetLastError());
   TTRY(hipStreamSynchronize(s));
   *out = T;
   *ok = 1;
 done:
   (void)hipStreamSynchronize(s);
-  void* tmp[] = {nline, nword, nin, at0, at1, at2, ctl, longer, sums};
+  void* tmp[] = {nline, nword, nin, at0, at1, at2, inlen, ctl, longer, sums};
   for (void* x : tmp)
     if (x) (void)hipFree(x);
   if (!*ok) tri_release(T);
