@@ -162,16 +162,12 @@ void scan::enqueue_clustering(scan_graph* g, EdgeArgs& A, int32_t* d_labels, uin
   mark(8);
 }
 
-void scan::enqueue_tri(scan_graph* g, const TriScratch& S, int64_t p, int64_t q, int32_t mu, int32_t* d_labels,
-                       uint8_t* d_roles, hipStream_t s, const RunState& R, hipEvent_t* events) {
+void scan::enqueue_tri(scan_graph* g, const TriScratch& S, const TriArgs& a, int32_t* d_labels, uint8_t* d_roles,
+                       hipStream_t s, const RunState& R, hipEvent_t* events) {
   auto mark = [&](int k) {
     if (events) (void)hipEventRecord(events[k], s);
   };
   const TriLayout& T = g->tri;
-  TriArgs a;
-  a.p = (uint64_t)p;
-  a.q = (uint64_t)q;
-  a.mu = mu;
   const int32_t split = g->opts.hub_outlier ? 1 : 0;
   mark(0);
   tri_init(s, T, S, R.lower, R.parent, R.label, R.role);
@@ -181,14 +177,14 @@ void scan::enqueue_tri(scan_graph* g, const TriScratch& S, int64_t p, int64_t q,
   // the counts are exact: nothing is left to finalise, to merge or to flatten
   mark(2);
   mark(3);
-  tri_hook(s, T, S, mu, R.lower, R.parent);
+  tri_hook(s, T, S, a, R.lower, R.parent);
   mark(4);
   mark(5);
   mark(6);
-  tri_attach(s, T, S, mu, R.lower, R.parent, R.label);
+  tri_attach(s, T, S, a, R.lower, R.parent, R.label);
   mark(7);
-  if (split) tri_hub_outlier(s, T, S, mu, R.lower, R.parent, R.label, R.upper, R.role);
-  tri_output(s, T, mu, R.lower, R.parent, R.label, R.role, d_labels, d_roles, split);
+  if (split) tri_hub_outlier(s, T, S, a, R.lower, R.parent, R.label, R.upper, R.role);
+  tri_output(s, T, a, R.lower, R.parent, R.label, R.role, d_labels, d_roles, split);
   mark(8);
 }
 
@@ -320,7 +316,11 @@ int run_tri(scan_graph* g, int64_t p, int64_t q, int32_t mu, int32_t* d_labels, 
   const bool timing = g->opts.timing != 0;
   TriTurn turn(g, s);
   if (turn.error() != hipSuccess) return fail_hip(turn.error(), "wait for an overlapping call");
-  enqueue_tri(g, g->tri_s, p, q, mu, d_labels, d_roles, s, R, timing ? ev : nullptr);
+  TriArgs a;
+  a.p = (uint64_t)p;
+  a.q = (uint64_t)q;
+  a.mu = mu;
+  enqueue_tri(g, g->tri_s, a, d_labels, d_roles, s, R, timing ? ev : nullptr);
   turn.enqueued();
   return collect_stats(g, s, timing, R, ev);
 }
@@ -549,13 +549,13 @@ int64_t scan_eps_threshold(int64_t p, int64_t q, int64_t a, int64_t b) {
 
 int scan_graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx,
                       const scan_opts* opts, scan_graph** out) {
-  return graph_create(n, nnz, row_ptr, col_idx, opts, true, out);
+  return graph_create(n, nnz, row_ptr, col_idx, opts, true, nullptr, out);
 }
 
 }  // extern "C"
 
 int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx,
-                       const scan_opts* opts, bool tri, scan_graph** out) {
+                       const scan_opts* opts, bool tri, const TriGroups* groups, scan_graph** out) {
   g_error.clear();
   if (!out) return fail(SCAN_E_INVAL, "out is NULL");
   *out = nullptr;
@@ -627,13 +627,13 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
   if (tri && !lay.error && g->opts.pruning && g->opts.strategy == 0 && !g->opts.device_budget_bytes) {
     int64_t be[kNumBuckets];
     int ok = 0;
-    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, &g->tri, be, &ok);
+    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, groups, &g->tri, be, &ok);
     if (e == hipSuccess && ok) e = tri_alloc_scratch(g->tri, &g->tri_s);
     if (e == hipSuccess && ok) {
       g->has_tri = true;
       for (int k = 0; k < kNumBuckets; ++k) g->bucket_off[k + 1] = g->bucket_off[k] + be[k];
       g->m = g->bucket_off[kNumBuckets];
-      if (noalloc_bytes(g) <= kNoallocScratch) e = tri_alloc_scratch(g->tri, &g->tri_na);
+      if (!groups && noalloc_bytes(g) <= kNoallocScratch) e = tri_alloc_scratch(g->tri, &g->tri_na);
     }
     if (e == hipErrorOutOfMemory) {  // no room: the edge list takes less
       (void)hipGetLastError();

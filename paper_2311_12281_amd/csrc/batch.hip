@@ -8,6 +8,11 @@
 // capture).  Labels (minimum core ids) are turned back into graph-local ids on
 // output.
 //
+// The union takes the triangle path (tri.hip), whose kernels look the graph's
+// parameters up the same way; every graph is renamed by degree in its own range
+// of vertices.  Where that path cannot hold the union (its limits, or memory),
+// or the options or SCAN_BATCH_WATCHDOG_US ask for the queue:
+//
 // One persistent kernel clusters the whole batch: its blocks take (graph,
 // phase, tile) items from a device queue, and every graph moves through the
 // phases of Algorithm 1 (with Algorithms 2 and 3) on its own, with a per-graph
@@ -156,11 +161,26 @@ int batch_prepare(scan_batch_graph* B) {
   return SCAN_OK;
 }
 
+// Kernel launches of one run.
+void batch_enqueue(scan_batch_graph* B, hipStream_t s) {
+  scan_graph* g = B->g;
+  if (!g->has_tri) {
+    launch_batch(s, B->args, B->grid);
+    return;
+  }
+  TriArgs a;
+  a.gid = B->d_gid;
+  a.gp = B->d_gp;
+  a.gq = B->d_gq;
+  a.gmu = B->d_gmu;
+  enqueue_tri(g, g->tri_s, a, B->d_labels, B->d_roles, s, graph_state(g), nullptr);
+}
+
 // Runs the batch once on the graph's stream (eagerly); device time in ms.
 int batch_run_eager(scan_batch_graph* B, float* ms) {
   hipStream_t s = B->g->stream;
   HIP_TRY(hipEventRecord(B->ev0, s), "hipEventRecord");
-  launch_batch(s, B->args, B->grid);
+  batch_enqueue(B, s);
   HIP_TRY(hipEventRecord(B->ev1, s), "hipEventRecord");
   HIP_TRY(hipGetLastError(), "batch launch");
   HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
@@ -171,8 +191,8 @@ int batch_run_eager(scan_batch_graph* B, float* ms) {
 // Reads the run's statistics and the queue's error flag.
 int batch_collect(scan_batch_graph* B) {
   scan_graph* g = B->g;
-  unsigned long long ctl[4];
-  HIP_TRY(hipMemcpy(ctl, B->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost), "copy queue counters");
+  unsigned long long ctl[4] = {0, 0, 0, 0};
+  if (!g->has_tri) HIP_TRY(hipMemcpy(ctl, B->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost), "copy queue counters");
   if (ctl[2]) return fail(SCAN_E_DEVICE, "batched run abandoned: a block waited too long for its work item");
   const int rc = collect_stats(g, g->stream, false);
   g->last.ms_total = B->last_ms;
@@ -274,7 +294,7 @@ int autotune(scan_batch_graph* B) {
 }
 
 int capture(scan_batch_graph* B) {
-  int rc = batch_prepare(B);
+  int rc = B->g->has_tri ? SCAN_OK : batch_prepare(B);
   if (rc != SCAN_OK) return rc;
   if (B->exec) {
     (void)hipGraphExecDestroy(B->exec);
@@ -286,7 +306,7 @@ int capture(scan_batch_graph* B) {
   }
   hipStream_t s = B->g->stream;
   HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-  launch_batch(s, B->args, B->grid);
+  batch_enqueue(B, s);
   hipGraph_t graph = nullptr;
   HIP_TRY(hipStreamEndCapture(s, &graph), "hipStreamEndCapture");
   B->graph = graph;
@@ -388,16 +408,20 @@ int scan_batch_create(const scan_batch* b, const scan_opts* opts, scan_batch_gra
     else scan_opts_default(&o);
     o.device_budget_bytes = 0;
     o.hub_ranked = 0;  // the batch kernel reads the rows as given
-    rc = graph_create(N, nnz, rp.data(), ci.data(), &o, false, &B->g);
-    if (rc != SCAN_OK) {
-      delete B;
-      return rc;
-    }
     const size_t NN = (size_t)(N > 0 ? N : 1);
     hipError_t e = hipMalloc((void**)&B->d_gid, 4 * NN);
     if (e == hipSuccess) e = hipMemcpy(B->d_gid, gid.data(), 4 * NN, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      rc = fail_hip(e, "graph ids");
+    if (e == hipSuccess) e = hipMalloc((void**)&B->d_vtx_off, 8 * ((size_t)G + 1));
+    if (e == hipSuccess) e = hipMemcpy(B->d_vtx_off, b->vtx_off, 8 * ((size_t)G + 1), hipMemcpyHostToDevice);
+    if (e != hipSuccess) rc = fail_hip(e, "graph ids");
+    TriGroups groups;
+    groups.count = G;
+    groups.h_vtx_off = b->vtx_off;
+    groups.vtx_off = B->d_vtx_off;
+    groups.gid = B->d_gid;
+    if (rc == SCAN_OK)
+      rc = graph_create(N, nnz, rp.data(), ci.data(), &o, !getenv("SCAN_BATCH_WATCHDOG_US"), &groups, &B->g);
+    if (rc != SCAN_OK) {
       batch_release(B);
       delete B;
       return rc;
@@ -411,19 +435,23 @@ int scan_batch_create(const scan_batch* b, const scan_opts* opts, scan_batch_gra
   BTRY(hipMalloc((void**)&B->d_gp, 8 * GG), "hipMalloc");
   BTRY(hipMalloc((void**)&B->d_gq, 8 * GG), "hipMalloc");
   BTRY(hipMalloc((void**)&B->d_gmu, 4 * GG), "hipMalloc");
-  BTRY(hipMalloc((void**)&B->d_vtx_off, 8 * G1), "hipMalloc");
+  BTRY(hipMalloc((void**)&B->d_labels, 4 * (size_t)(N > 0 ? N : 1)), "hipMalloc");
+  BTRY(hipMalloc((void**)&B->d_roles, (size_t)(N > 0 ? N : 1)), "hipMalloc");
+  BTRY(hipEventCreate(&B->ev0), "hipEventCreate");
+  BTRY(hipEventCreate(&B->ev1), "hipEventCreate");
+  rc = upload_params(B, b->eps_num, b->eps_den, b->mu);
+  if (rc != SCAN_OK) goto error;
+  if (g->has_tri) {  // nothing to tune: no lane widths, no tiles
+    rc = capture(B);
+    if (rc != SCAN_OK) goto error;
+    *out = B;
+    return SCAN_OK;
+  }
   BTRY(hipMalloc((void**)&B->d_eoff, 8 * G1 * kNumBuckets), "hipMalloc");
   BTRY(hipMalloc((void**)&B->d_init_prefix, 8 * G1), "hipMalloc");
   BTRY(hipMalloc((void**)&B->d_remaining, 4 * GG), "hipMalloc");
   BTRY(hipMalloc((void**)&B->d_ncores, 8 * GG), "hipMalloc");
   BTRY(hipMalloc((void**)&B->d_ctl, 8 * 4), "hipMalloc");
-  BTRY(hipMalloc((void**)&B->d_labels, 4 * (size_t)(N > 0 ? N : 1)), "hipMalloc");
-  BTRY(hipMalloc((void**)&B->d_roles, (size_t)(N > 0 ? N : 1)), "hipMalloc");
-  BTRY(hipEventCreate(&B->ev0), "hipEventCreate");
-  BTRY(hipEventCreate(&B->ev1), "hipEventCreate");
-  BTRY(hipMemcpy(B->d_vtx_off, b->vtx_off, 8 * G1, hipMemcpyHostToDevice), "copy");
-  rc = upload_params(B, b->eps_num, b->eps_den, b->mu);
-  if (rc != SCAN_OK) goto error;
   // each graph's edge range in every bucket
   launch_batch_edge_offsets(g->stream, G, B->d_vtx_off, g->d_edges, g->bucket_off, B->d_eoff);
   BTRY(hipGetLastError(), "edge offsets");

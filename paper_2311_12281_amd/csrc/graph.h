@@ -174,12 +174,13 @@ void enqueue_clustering(scan_graph* g, EdgeArgs& A, int32_t* d_labels, uint8_t* 
                         const int32_t* gbase, hipStream_t s, bool timing, const RunConfig* cfg,
                         const RunState* R = nullptr, hipEvent_t* ev = nullptr);
 // The same through the triangle path, in scratch S (kernel launches only).
-void enqueue_tri(scan_graph* g, const TriScratch& S, int64_t p, int64_t q, int32_t mu, int32_t* d_labels,
-                 uint8_t* d_roles, hipStream_t s, const RunState& R, hipEvent_t* events);
+void enqueue_tri(scan_graph* g, const TriScratch& S, const TriArgs& a, int32_t* d_labels, uint8_t* d_roles,
+                 hipStream_t s, const RunState& R, hipEvent_t* events);
 // scan_graph_create; tri: whether the graph may take the triangle path (else
-// it has the edge list that the batch and the server read).
+// it has the edge list that the server and the batch kernel read); groups:
+// the graphs of a batch.
 int graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx, const scan_opts* opts,
-                 bool tri, scan_graph** out);
+                 bool tri, const TriGroups* groups, scan_graph** out);
 // Device bytes a noalloc call's per-run buffers take in the static scratch.
 uint64_t noalloc_bytes(const scan_graph* g);
 constexpr uint64_t kNoallocScratch = 64ull << 20;

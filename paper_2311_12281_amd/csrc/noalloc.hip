@@ -104,7 +104,11 @@ int scan_run_device_noalloc(scan_graph* g, int64_t eps_num, int64_t eps_den, int
   layout_state(g, base, &R);
   hipStream_t s = stream ? (hipStream_t)stream : g->stream;
   if (g->has_tri) {
-    enqueue_tri(g, g->tri_na, p, q, mu, d_labels, d_roles, s, R, nullptr);
+    TriArgs a;
+    a.p = (uint64_t)p;
+    a.q = (uint64_t)q;
+    a.mu = mu;
+    enqueue_tri(g, g->tri_na, a, d_labels, d_roles, s, R, nullptr);
   } else {
     EdgeArgs A{};
     A.p = (uint64_t)p;

@@ -472,7 +472,7 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
     scan_opts o = S->opts;
     o.device_budget_bytes = 0;
     scan_graph* g = nullptr;
-    int rc = graph_create(n, nnz, row_ptr, col_idx, &o, false, &g);
+    int rc = graph_create(n, nnz, row_ptr, col_idx, &o, false, nullptr, &g);
     G->g = g;
     if (rc == SCAN_OK && g->m > 0) {
       hipError_t e = hipMalloc((void**)&G->d_ecount, sizeof(int32_t) * (size_t)g->m);

@@ -8,7 +8,8 @@
 namespace scan {
 
 // Vertices are renamed by decreasing degree (ties by id): h = 0 is the vertex
-// of the highest degree.  Every edge is kept once, in the row of its endpoint
+// of the highest degree.  In a batch (a disjoint union) every graph keeps its
+// range of ids and is renamed inside it, so that its rows stay together.  Every edge is kept once, in the row of its endpoint
 // with the larger h: row u lists the neighbours v of u with h(v) < h(u), in
 // decreasing order.  No row is longer than about sqrt(2 m).
 //
@@ -49,9 +50,21 @@ struct TriWave {
   uint32_t shape;       // row length | records << 8
 };
 
+// The graphs of a batch: vertices vtx_off[k] .. vtx_off[k + 1] - 1, and the
+// graph of every vertex (the same array by id and by h).  All null for one graph.
+struct TriGroups {
+  int32_t count = 0;
+  const int64_t* h_vtx_off = nullptr;  // host
+  const int64_t* vtx_off = nullptr;    // device
+  const int32_t* gid = nullptr;        // device
+};
+
 // Read-only after creation.
 struct TriLayout {
   int32_t n = 0;
+  int32_t span = 0;           // vertices of the largest graph
+  const int64_t* vtx_off = nullptr;  // TriGroups (not owned)
+  const int32_t* gid = nullptr;
   int64_t lines = 0, words = 0, recs = 0, steps = 0;
   int64_t jobs = 0, wave_rows = 0;
   int32_t max_row = 0, max_hash_row = 0;
@@ -63,7 +76,7 @@ struct TriLayout {
   uint32_t* wbase = nullptr;  // [n + 1] first bit word of a row
   int32_t* lu = nullptr;      // [lines] h of the line's row
   int32_t* oc = nullptr;      // [32 lines + pad] h + 1 of the neighbour, or 0
-  uint16_t* oc16 = nullptr;   // the same in 16 bits, 0xFFFF for h >= kTriShort
+  uint16_t* oc16 = nullptr;   // the same within the graph in 16 bits, 0xFFFF for h >= kTriShort
   TriRec* rec = nullptr;      // [recs] a vertex's records, then unused ones
   TriJob* job = nullptr;      // [jobs], hubs first
   TriWave* wrow = nullptr;    // [wave_rows]
@@ -85,16 +98,20 @@ uint64_t tri_scratch_bytes(const TriLayout& T);
 // offsets).  *ok = 0 with hipSuccess when the graph is outside the path's
 // limits (nothing stays allocated).  bucket_edges: edges per degree bucket.
 hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
-                     const int32_t* d_ci, TriLayout* T, int64_t* bucket_edges, int* ok);
+                     const int32_t* d_ci, const TriGroups* groups, TriLayout* T, int64_t* bucket_edges, int* ok);
 void tri_release(TriLayout& T);
 hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S);
 void tri_release_scratch(TriScratch& S);
 
-// What a run does with the counts: eps and mu, or (eps_den == 0) nothing but
-// the closed counts, left in S.cnt.
+// eps = p/q and mu of a run, or of every graph of a batch (q == 0 and no gq:
+// only the closed counts, left in S.cnt).
 struct TriArgs {
   uint64_t p = 0, q = 0;
   int32_t mu = 2;
+  const int32_t* gid = nullptr;  // null: one graph
+  const uint64_t* gp = nullptr;
+  const uint64_t* gq = nullptr;
+  const int32_t* gmu = nullptr;
 };
 
 // Kernel launches of the phases, in this order.
@@ -102,14 +119,14 @@ void tri_init(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* l
               int32_t* label, uint8_t* role);
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S);
 void tri_close(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower);
-void tri_hook(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+void tri_hook(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, const int32_t* lower,
               int32_t* parent);
-void tri_attach(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+void tri_attach(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, const int32_t* lower,
                 int32_t* parent, int32_t* label);
 // Hub marks (Def 2.7): role[id] = ROLE_HUB; first is scratch of n entries.
-void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, const int32_t* lower,
                      int32_t* parent, int32_t* label, int32_t* first, uint8_t* role);
-void tri_output(hipStream_t s, const TriLayout& T, int32_t mu, const int32_t* lower, int32_t* parent,
+void tri_output(hipStream_t s, const TriLayout& T, const TriArgs& a, const int32_t* lower, int32_t* parent,
                 const int32_t* label, const uint8_t* role, int32_t* out_labels, uint8_t* out_roles, int32_t split);
 // Closed counts of every arc in CSR order from S.cnt (after tri_close).
 void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, const int64_t* rp, const int32_t* ci,

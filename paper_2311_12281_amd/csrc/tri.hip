@@ -202,14 +202,21 @@ __global__ __launch_bounds__(256) void k_row_fill_wave(int32_t h0, int32_t n, co
   for (int32_t p = D + lane; p < (int32_t)tri_lines(D) * kTriLine; p += 64) out[p] = 0;
 }
 
-__device__ __forceinline__ uint16_t tri_short(int32_t x) {
-  return x <= kTriShort ? (uint16_t)x : (uint16_t)0xFFFF;
+// First h of the graph of h.
+__device__ __forceinline__ int32_t tri_base(const int32_t* gid, const int64_t* vtx_off, int64_t h) {
+  return gid ? (int32_t)vtx_off[gid[h]] : 0;
+}
+
+// 16-bit form of entry x of a graph that starts at base.
+__device__ __forceinline__ uint16_t tri_short(int32_t x, int32_t base) {
+  return x == 0 ? (uint16_t)0 : x - base <= kTriShort ? (uint16_t)(x - base) : (uint16_t)0xFFFF;
 }
 
 // Rows in decreasing order of h: up to 64 entries in the registers of a wave
 // (bitonic network over the lanes); longer ones are listed for the block kernel.
 __global__ __launch_bounds__(256) void k_row_sort_wave(int32_t n, const uint32_t* oline, const int32_t* row,
-                                                       int32_t* oc, uint16_t* oc16, int32_t* lu, int32_t* longer,
+                                                       const int32_t* gid, const int64_t* vtx_off, int32_t* oc,
+                                                       uint16_t* oc16, int32_t* lu, int32_t* longer,
                                                        int32_t* nlonger) {
   const int lane = threadIdx.x & 63;
   const int64_t h = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
@@ -234,18 +241,20 @@ __global__ __launch_bounds__(256) void k_row_sort_wave(int32_t n, const uint32_t
     }
   if (in) {
     out[lane] = x;
-    oc16[(int64_t)l0 * kTriLine + lane] = tri_short(x);
+    oc16[(int64_t)l0 * kTriLine + lane] = tri_short(x, tri_base(gid, vtx_off, h));
   }
 }
 
 __global__ __launch_bounds__(256) void k_row_sort_block(const int32_t* longer, const int32_t* nlonger,
-                                                        const uint32_t* oline, const int32_t* row, int32_t* oc,
+                                                        const uint32_t* oline, const int32_t* row,
+                                                        const int32_t* gid, const int64_t* vtx_off, int32_t* oc,
                                                         uint16_t* oc16) {
   __shared__ int32_t a[kTriMaxRow];
   const int32_t cnt = *nlonger;
   for (int32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
     const int32_t h = longer[r], D = row[h];
     const int64_t base = (int64_t)oline[h] * kTriLine;
+    const int32_t h0 = tri_base(gid, vtx_off, h);
     int32_t P = 128;
     while (P < D) P <<= 1;
     for (int32_t k = threadIdx.x; k < P; k += 256) a[k] = k < D ? oc[base + k] : 0;
@@ -266,7 +275,7 @@ __global__ __launch_bounds__(256) void k_row_sort_block(const int32_t* longer, c
     for (int32_t k = threadIdx.x; k < (int32_t)tri_lines(D) * kTriLine; k += 256) {
       const int32_t x = k < D ? a[k] : 0;
       oc[base + k] = x;
-      oc16[base + k] = tri_short(x);
+      oc16[base + k] = tri_short(x, h0);
     }
     __syncthreads();
   }
@@ -396,7 +405,8 @@ __device__ __forceinline__ bool tri_wave_row(int32_t D, uint32_t nin, int64_t st
 
 // Work of every vertex: jobs of the block kernel, or a place in the wave
 // kernel's list; the sum of all words and the longest hash-table row.
-__global__ void k_job_counts(int32_t n, const int32_t* row, const uint32_t* inlen, const int64_t* steps,
+__global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_off, const int32_t* row,
+                             const uint32_t* inlen, const int64_t* steps,
                              int64_t* njob, int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t j = 0, w = 0;
@@ -407,7 +417,7 @@ __global__ void k_job_counts(int32_t n, const int32_t* row, const uint32_t* inle
       w = 1;
     } else {
       j = (inlen[h] + kTriJob - 1) / kTriJob;
-      if (h >= kTriShort) atomicMax(max_hash, row[h]);
+      if (h - tri_base(gid, vtx_off, h) >= kTriShort) atomicMax(max_hash, row[h]);
     }
   }
   if (h <= n) {
@@ -507,11 +517,17 @@ __device__ __forceinline__ void tri_stream(const E* __restrict__ cols, const Tri
   for (uint32_t b0 = 0; b0 < n; b0 += 64) {
     const uint32_t nb = min(64u, n - b0);
     const TriRec r = (uint32_t)lane < nb ? rec[first + b0 + lane] : TriRec{};
-    const int off = (int)(r.line * kLineBytes), end = (int)((r.line + r.nw) * kLineBytes);
+    // 16-bit entries: byte offsets of the record; 32-bit ones, which would pass
+    // 32 bits on the largest graphs: its line, and its length
+    const int off = (int)(sizeof(E) == 2 ? r.line * kLineBytes : r.line);
+    const int end = (int)((sizeof(E) == 2 ? r.line + r.nw : r.nw) * kLineBytes);
     const int woff = (int)(r.word * 4), wend = (int)((r.word + r.nw) * 4);
     auto load = [&](Cols& y, uint32_t i) {  // i = 64: record 0 again, not used
-      const uint32_t o = at + (uint32_t)__builtin_amdgcn_readlane(off, (int)(i & 63));
-      const __amdgpu_buffer_rsrc_t b = buffer_upto(cols, (uint32_t)__builtin_amdgcn_readlane(end, (int)(i & 63)));
+      uint32_t o = at, upto = (uint32_t)__builtin_amdgcn_readlane(end, (int)(i & 63));
+      const E* from = cols;
+      if (sizeof(E) == 2) o += (uint32_t)__builtin_amdgcn_readlane(off, (int)(i & 63));
+      else from += (uint64_t)(uint32_t)__builtin_amdgcn_readlane(off, (int)(i & 63)) * kTriLine;
+      const __amdgpu_buffer_rsrc_t b = buffer_upto(from, upto);
       y.c0 = buffer_entry(cols, b, o);
       y.c1 = buffer_entry(cols, b, o + kStep);
       y.c2 = buffer_entry(cols, b, o + 2 * kStep);
@@ -569,13 +585,14 @@ __device__ __forceinline__ uint32_t tri_hash(int32_t x) { return (uint32_t)x * 0
 // The first two read the 16-bit columns.  Block-uniform choice.
 __global__ __launch_bounds__(kTriBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec, const int32_t* __restrict__ row,
-                 const uint32_t* __restrict__ oline, const int32_t* __restrict__ oc,
+                 const uint32_t* __restrict__ oline, const int32_t* __restrict__ gid,
+                 const int64_t* __restrict__ vtx_off, const int32_t* __restrict__ oc,
                  const uint16_t* __restrict__ oc16, uint32_t* __restrict__ bits, int32_t* __restrict__ cnt,
                  uint32_t acc_cap) {
   extern __shared__ __align__(16) int32_t tri_lds[];
   const TriJob J = jobs[blockIdx.x];
-  const int32_t v = J.v, D = row[v];
-  const int64_t base = (int64_t)oline[v] * kTriLine;
+  const int32_t D = row[J.v], h0 = tri_base(gid, vtx_off, J.v), v = J.v - h0;  // v within its graph
+  const int64_t base = (int64_t)oline[J.v] * kTriLine;
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t lds = (uint32_t)(uintptr_t)(LdsCounter*)tri_lds;  // LDS address of the counters
@@ -595,7 +612,7 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
         reinterpret_cast<int4*>(tab)[k] = make_int4(0, 0, 0, 0);
       __syncthreads();
       static_assert(4 * (kTriMaxRow + 1) <= 0xFFFF, "addresses in 16 bits");
-      for (int32_t j = tid; j < D; j += kTriBlock) t16[oc[base + j]] = (uint16_t)(lds + 4 * (j + 1));
+      for (int32_t j = tid; j < D; j += kTriBlock) t16[oc[base + j] - h0] = (uint16_t)(lds + 4 * (j + 1));
       __syncthreads();
       // entry v + 1 (and 0, no entry) stays 0
       tri_stream(oc16, recs, J.rcnt, wave, lane, bits, [&](uint16_t x) -> uint32_t {
@@ -611,7 +628,7 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
       for (int32_t k = tid; k < nt; k += kTriBlock) tb[k] = make_uint2(0, 0);
       __syncthreads();
       for (int32_t j = tid; j < D; j += kTriBlock) {
-        const int32_t x = oc[base + j];
+        const int32_t x = oc[base + j] - h0;
         atomicOr(&tb[x >> 5].x, 1u << (x & 31));
       }
       __syncthreads();
@@ -639,7 +656,7 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
       };
       tri_stream(oc16, recs, J.rcnt, wave, lane, bits, find);
       __syncthreads();
-      for (int32_t j = tid; j < D; j += kTriBlock) put(j, acc[(find((uint16_t)oc[base + j]) - lds) / 4]);
+      for (int32_t j = tid; j < D; j += kTriBlock) put(j, acc[(find((uint16_t)(oc[base + j] - h0)) - lds) / 4]);
     }
   } else {
     const uint32_t slots = tri_hash_slots(D), mask = slots - 1;
@@ -657,7 +674,7 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
     }
     __syncthreads();
     auto find = [&](uint32_t x) -> uint32_t {
-      if (x - 1 >= (uint32_t)v) return 0;  // no entry included
+      if (x - 1 >= (uint32_t)J.v) return 0;  // no entry included
       uint32_t t = tri_hash((int32_t)x) & mask;
       while (true) {
         const int32_t y = key[t];
@@ -809,6 +826,8 @@ __global__ void k_tri_init(int64_t ncnt4, int4* cnt, int32_t n, int32_t* lower, 
   }
 }
 
+__device__ __forceinline__ int32_t tri_mu(const TriArgs& a, int64_t h) { return a.gid ? a.gmu[a.gid[h]] : a.mu; }
+
 // 32 x 32 bits across the lanes of a half wave: lane j's word becomes column j.
 __device__ __forceinline__ uint32_t tri_transpose(uint32_t w, int sub) {
   uint32_t m = 0x0000FFFFu;
@@ -856,6 +875,12 @@ __global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const int32_t*
     cnt[t * kTriLine + sub] = closed;
     return;
   }
+  if (a.gid) {
+    const int32_t g = a.gid[u];
+    a.p = a.gp[g];
+    a.q = a.gq[g];
+    a.mu = a.gmu[g];
+  }
   bool sim = false;
   if (x >= 0) {
     const uint64_t ab = ((uint64_t)deg[u] + 1) * ((uint64_t)deg[x] + 1);
@@ -892,14 +917,14 @@ __device__ __forceinline__ int32_t half_min(int32_t x) {
 __global__ __launch_bounds__(256) void k_tri_link(int64_t lines, const int32_t* __restrict__ lu,
                                                   const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
                                                   const int32_t* __restrict__ lower, const int32_t* __restrict__ idof,
-                                                  int32_t mu, int32_t* parent, const int32_t* __restrict__ flag) {
+                                                  TriArgs a_, int32_t* parent, const int32_t* __restrict__ flag) {
   if (!*flag) return;
   const int sub = threadIdx.x & 31;
   const int64_t stride = (int64_t)gridDim.x * 8;
   for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
     const uint32_t w = simw[t];
     if (!w) continue;
-    const int32_t u = lu[t];
+    const int32_t u = lu[t], mu = tri_mu(a_, u);
     if (lower[u] < mu) continue;
     const int32_t x = oc[t * kTriLine + sub] - 1;
     const bool in = ((w >> sub) & 1u) && lower[x] >= mu;
@@ -925,14 +950,14 @@ __global__ void k_tri_compress(int32_t n, int32_t* parent, const int32_t* __rest
 __global__ __launch_bounds__(256) void k_tri_hook(int64_t lines, const int32_t* __restrict__ lu,
                                                   const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
                                                   const int32_t* __restrict__ lower, const int32_t* __restrict__ idof,
-                                                  int32_t mu, int32_t* parent, const int32_t* __restrict__ flag) {
+                                                  TriArgs a_, int32_t* parent, const int32_t* __restrict__ flag) {
   if (!*flag) return;
   const int lane = threadIdx.x & 63, half = lane >> 5, sub = lane & 31;
   const int64_t stride = (int64_t)gridDim.x * 8;
   for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
     const uint32_t w = simw[t];
     if (!w) continue;
-    const int32_t u = lu[t];
+    const int32_t u = lu[t], mu = tri_mu(a_, u);
     if (lower[u] < mu) continue;
     const int32_t x = oc[t * kTriLine + sub] - 1;
     const bool in = ((w >> sub) & 1u) && lower[x] >= mu;
@@ -977,7 +1002,7 @@ __global__ __launch_bounds__(256) void k_tri_hook(int64_t lines, const int32_t* 
 __global__ __launch_bounds__(256) void k_tri_attach(int64_t lines, const int32_t* __restrict__ lu,
                                                     const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
                                                     const int32_t* __restrict__ lower,
-                                                    const int32_t* __restrict__ idof, int32_t mu, int32_t* parent,
+                                                    const int32_t* __restrict__ idof, TriArgs a, int32_t* parent,
                                                     int32_t* label, const int32_t* __restrict__ flag) {
   if (!*flag) return;
   const int sub = threadIdx.x & 31;
@@ -985,6 +1010,7 @@ __global__ __launch_bounds__(256) void k_tri_attach(int64_t lines, const int32_t
   for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
     if (!((simw[t] >> sub) & 1u)) continue;
     const int32_t u = lu[t], x = oc[t * kTriLine + sub] - 1;
+    const int32_t mu = tri_mu(a, u);
     const bool cu = lower[u] >= mu, cx = lower[x] >= mu;
     if (cu == cx) continue;
     atomicMin(label + idof[cu ? x : u], uf_find(parent, idof[cu ? u : x]));
@@ -992,11 +1018,11 @@ __global__ __launch_bounds__(256) void k_tri_attach(int64_t lines, const int32_t
 }
 
 // Labels of the cores (needed before hub marks, which read every label).
-__global__ void k_tri_core_labels(int32_t n, const int32_t* hof, const int32_t* lower, int32_t mu, int32_t* parent,
+__global__ void k_tri_core_labels(int32_t n, const int32_t* hof, const int32_t* lower, TriArgs a, int32_t* parent,
                                   int32_t* label, int32_t* first) {
   const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= n) return;
-  if (lower[hof[x]] >= mu) label[x] = uf_find(parent, (int32_t)x);
+  if (lower[hof[x]] >= tri_mu(a, x)) label[x] = uf_find(parent, (int32_t)x);
   first[x] = -1;
 }
 
@@ -1023,18 +1049,19 @@ __global__ __launch_bounds__(256) void k_tri_hub(int64_t lines, const int32_t* _
   }
 }
 
-__global__ void k_tri_output(int32_t n, const int32_t* __restrict__ hof, const int32_t* __restrict__ lower, int32_t mu,
-                             int32_t* parent, const int32_t* __restrict__ label, const uint8_t* __restrict__ role,
+__global__ void k_tri_output(int32_t n, const int32_t* __restrict__ hof, const int32_t* __restrict__ lower, TriArgs a,
+                             const int64_t* __restrict__ vtx_off, int32_t* parent, const int32_t* __restrict__ label, const uint8_t* __restrict__ role,
                              int32_t* __restrict__ out_labels, uint8_t* __restrict__ out_roles, int32_t split) {
   const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= n) return;
-  if (lower[hof[x]] >= mu) {
+  const int32_t base = tri_base(a.gid, vtx_off, x);  // labels within the graph
+  if (lower[hof[x]] >= tri_mu(a, x)) {
     out_roles[x] = 1;
-    out_labels[x] = uf_find(parent, (int32_t)x);
+    out_labels[x] = uf_find(parent, (int32_t)x) - base;
     return;
   }
   const int32_t l = label[x];
-  out_labels[x] = l == INT_MAX ? -1 : l;
+  out_labels[x] = l == INT_MAX ? -1 : l - base;
   out_roles[x] = l != INT_MAX ? 2 : split ? (role[x] == ROLE_HUB ? 3 : 4) : 0;
 }
 
@@ -1069,8 +1096,8 @@ uint32_t tri_acc_cap(const TriLayout& T) { return ((uint32_t)T.max_row + 2 + 3) 
 // Dynamic LDS of the block kernel: counters, then the largest table of the graph.
 size_t tri_lds_bytes(const TriLayout& T) {
   const size_t acc = 4 * (size_t)tri_acc_cap(T);
-  size_t b = acc + 2 * ((size_t)std::min(T.n, kTriDirect) + 24);
-  if (T.n > kTriDirect) b = std::max(b, acc + 8 * ((size_t)std::min(T.n, kTriShort) / 32 + 3));
+  size_t b = acc + 2 * ((size_t)std::min(T.span, kTriDirect) + 24);
+  if (T.span > kTriDirect) b = std::max(b, acc + 8 * ((size_t)std::min(T.span, kTriShort) / 32 + 3));
   if (T.max_hash_row > 0) b = std::max(b, 8 * (size_t)tri_hash_slots(T.max_hash_row));
   return (b + 15) & ~(size_t)15;
 }
@@ -1116,7 +1143,7 @@ hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S) {
 }
 
 hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
-                     const int32_t* d_ci, TriLayout* out, int64_t* bucket_edges, int* ok) {
+                     const int32_t* d_ci, const TriGroups* groups, TriLayout* out, int64_t* bucket_edges, int* ok) {
   *ok = 0;
   if (n <= 0 || nnz <= 0 || nnz / 2 >= (int64_t)1 << 31) return hipSuccess;
   TriLayout T;
@@ -1136,23 +1163,36 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
     e = (x);                           \
     if (e != hipSuccess) goto done;    \
   } while (0)
+  T.span = n;
+  if (groups) {
+    T.vtx_off = groups->vtx_off;
+    T.gid = groups->gid;
+    T.span = 0;
+    for (int32_t k = 0; k < groups->count; ++k)
+      T.span = std::max(T.span, (int32_t)(groups->h_vtx_off[k + 1] - groups->h_vtx_off[k]));
+  }
   {
-    // h: counting sort by decreasing degree, ties by id
-    int64_t maxd = 0;
-    for (int32_t v = 0; v < n; ++v) maxd = std::max(maxd, h_rp[v + 1] - h_rp[v]);
-    std::vector<int32_t> first((size_t)maxd + 2, 0), hof((size_t)n), idof((size_t)n);
-    for (int32_t v = 0; v < n; ++v) ++first[(size_t)(h_rp[v + 1] - h_rp[v])];
-    int32_t acc = 0;
-    for (int64_t d = maxd; d >= 0; --d) {
-      const int32_t t = first[(size_t)d];
-      first[(size_t)d] = acc;
-      acc += t;
-      if (d > 2048) nbig = acc;
-    }
-    for (int32_t v = 0; v < n; ++v) {
-      const int32_t h = first[(size_t)(h_rp[v + 1] - h_rp[v])]++;
-      hof[(size_t)v] = h;
-      idof[(size_t)h] = v;
+    // h: counting sort by decreasing degree, ties by id, in every graph
+    std::vector<int32_t> first, hof((size_t)n), idof((size_t)n);
+    const int32_t ng = groups ? groups->count : 1;
+    for (int32_t k = 0; k < ng; ++k) {
+      const int32_t v0 = groups ? (int32_t)groups->h_vtx_off[k] : 0, v1 = groups ? (int32_t)groups->h_vtx_off[k + 1] : n;
+      int64_t maxd = 0;
+      for (int32_t v = v0; v < v1; ++v) maxd = std::max(maxd, h_rp[v + 1] - h_rp[v]);
+      first.assign((size_t)maxd + 1, 0);
+      for (int32_t v = v0; v < v1; ++v) ++first[(size_t)(h_rp[v + 1] - h_rp[v])];
+      int32_t acc = v0;
+      for (int64_t d = maxd; d >= 0; --d) {
+        const int32_t t = first[(size_t)d];
+        first[(size_t)d] = acc;
+        acc += t;
+        if (d > 2048 && !groups) nbig = acc;  // (of a batch, waves take the long rows too)
+      }
+      for (int32_t v = v0; v < v1; ++v) {
+        const int32_t h = first[(size_t)(h_rp[v + 1] - h_rp[v])]++;
+        hof[(size_t)v] = h;
+        idof[(size_t)h] = v;
+      }
     }
     TTRY(dnew(&T.hof, n));
     TTRY(dnew(&T.idof, n));
@@ -1194,8 +1234,8 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   T.lines = tot[0];
   T.words = tot[1];
   T.recs = tot[2];
-  // outside the limits (32-bit byte offsets of entries and bits), or not a symmetric CSR
-  if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 25 || T.words >= (int64_t)1 << 30 ||
+  // outside the limits (32-bit byte offsets of 16-bit entries and of bits), or not a symmetric CSR
+  if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 26 || T.words >= (int64_t)1 << 30 ||
       T.recs >= (int64_t)1 << 32 || (int64_t)h_sums[1 + kNumBuckets] != nnz / 2)
     goto done;
   TTRY(dnew(&T.oline, (int64_t)n + 1));
@@ -1209,8 +1249,9 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (nbig > 0) k_row_fill_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
   if (n > nbig)
     k_row_fill_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
-  k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.oc, T.oc16, T.lu, longer, ctl + 1);
-  k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.oc, T.oc16);
+  k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16, T.lu, longer,
+                                                   ctl + 1);
+  k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16);
   TTRY(hipGetLastError());
   TTRY(dnew(&T.rec, T.recs));
   if (nbig > 0)
@@ -1219,7 +1260,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (n > nbig)
     k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
                                                       T.oc, at2, T.rec, inlen, nin);
-  k_job_counts<<<gv, 256, 0, s>>>(n, T.row, inlen, nin, nline, nword, sums, ctl + 2);
+  k_job_counts<<<gv, 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, inlen, nin, nline, nword, sums, ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
   TTRY(hipGetLastError());
@@ -1261,8 +1302,8 @@ void tri_init(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* l
 
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
   if (T.jobs > 0)
-    k_tri_block<<<(unsigned)T.jobs, kTriBlock, tri_lds_bytes(T), s>>>(T.job, T.rec, T.row, T.oline, T.oc, T.oc16,
-                                                                     S.bits, S.cnt, tri_acc_cap(T));
+    k_tri_block<<<(unsigned)T.jobs, kTriBlock, tri_lds_bytes(T), s>>>(T.job, T.rec, T.row, T.oline, T.gid, T.vtx_off,
+                                                                     T.oc, T.oc16, S.bits, S.cnt, tri_acc_cap(T));
   if (T.wave_rows > 0)
     k_tri_wave<<<grid_for(T.wave_rows, 4), 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc, S.bits, S.cnt);
 }
@@ -1270,7 +1311,7 @@ void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
 void tri_close(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower) {
   if (T.lines <= 0) return;
   const unsigned grid = grid_for(T.lines, 8);
-  if (a.q)
+  if (a.q || a.gq)
     k_tri_close<true><<<grid, 256, 0, s>>>(T.lines, T.lu, T.oline, T.wbase, T.row, T.deg, T.oc, S.bits, S.cnt, a,
                                            S.simw, lower, S.flag);
   else
@@ -1282,32 +1323,32 @@ namespace {
 unsigned line_grid(const TriLayout& T) { return (unsigned)std::min<int64_t>(grid_for(T.lines, 8), 1 << 16); }
 }  // namespace
 
-void tri_hook(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+void tri_hook(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, const int32_t* lower,
               int32_t* parent) {
   if (T.lines <= 0) return;
-  k_tri_link<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, mu, parent, S.flag);
+  k_tri_link<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, a, parent, S.flag);
   k_tri_compress<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, parent, S.flag);
-  k_tri_hook<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, mu, parent, S.flag);
+  k_tri_hook<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, a, parent, S.flag);
 }
 
-void tri_attach(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+void tri_attach(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, const int32_t* lower,
                 int32_t* parent, int32_t* label) {
   if (T.lines > 0)
-    k_tri_attach<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, mu, parent, label, S.flag);
+    k_tri_attach<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, S.simw, lower, T.idof, a, parent, label, S.flag);
 }
 
-void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t mu, const int32_t* lower,
+void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, const int32_t* lower,
                      int32_t* parent, int32_t* label, int32_t* first, uint8_t* role) {
-  k_tri_core_labels<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, T.hof, lower, mu, parent, label, first);
+  k_tri_core_labels<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, T.hof, lower, a, parent, label, first);
   if (T.lines > 0)
     k_tri_hub<<<line_grid(T), 256, 0, s>>>(T.lines, T.lu, T.oc, T.idof, label, first, role, S.flag);
 }
 
-void tri_output(hipStream_t s, const TriLayout& T, int32_t mu, const int32_t* lower, int32_t* parent,
+void tri_output(hipStream_t s, const TriLayout& T, const TriArgs& a, const int32_t* lower, int32_t* parent,
                 const int32_t* label, const uint8_t* role, int32_t* out_labels, uint8_t* out_roles, int32_t split) {
   if (T.n > 0)
-    k_tri_output<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, T.hof, lower, mu, parent, label, role, out_labels, out_roles,
-                                                    split);
+    k_tri_output<<<grid_for(T.n, 256), 256, 0, s>>>(T.n, T.hof, lower, a, T.vtx_off, parent, label, role, out_labels,
+                                                    out_roles, split);
 }
 
 void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, const int64_t* rp, const int32_t* ci,
