@@ -28,7 +28,16 @@ constexpr int kTriWaveRow = 128;  // rows up to this, with few in-edges, go one 
 constexpr int kTriWaveSlots = 256;
 constexpr int64_t kTriWaveWords = 512;  // words of in-edges a wave takes on
 
-// Up to kTriRecLines lines of one in-edge (u, v) of a vertex v: the columns of
+// A line as the close kernel reads it.
+struct TriLineInfo {
+  int32_t u;        // the row's vertex
+  uint32_t wbase;   // first bit word of the row
+  int32_t deg;      // degree of u
+  uint32_t shape;   // row length | column of the line << 16
+};
+
+// Lines of one in-edge (u, v) of a vertex v, up to kTriRecLines for the block
+// kernel, one for the wave kernel: the columns of
 // row u after v's entry are the w to look up in row v.
 struct TriRec {
   uint32_t line;  // first line (of v's entry in row u, or a later one)
@@ -75,6 +84,7 @@ struct TriLayout {
   uint32_t* oline = nullptr;  // [n + 1] first line of a row
   uint32_t* wbase = nullptr;  // [n + 1] first bit word of a row
   int32_t* lu = nullptr;      // [lines] h of the line's row
+  TriLineInfo* li = nullptr;  // [lines]
   int32_t* oc = nullptr;      // [32 lines + pad] h + 1 of the neighbour, or 0
   uint16_t* oc16 = nullptr;   // the same within the graph in 16 bits, 0xFFFF for h >= kTriShort
   TriRec* rec = nullptr;      // [recs] a vertex's records, then unused ones

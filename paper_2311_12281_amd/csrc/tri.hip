@@ -84,47 +84,60 @@ __global__ __launch_bounds__(256) void k_row_len_wave(int32_t h0, int32_t n, con
   }
 }
 
-// In-edge records of (u, v) at most, whatever v's column: kTriRecLines lines each.
-__device__ __forceinline__ int32_t tri_recs_of(int32_t D) {
-  return D < 2 ? 0 : ((int32_t)tri_lines(D) + kTriRecLines - 1) / kTriRecLines;
+// Room for the records of every vertex, from its in-edges' rows (a record's
+// column is not known yet), and whether the wave kernel takes it.
+__device__ __forceinline__ void tri_room(int32_t D, unsigned long long lines, unsigned long long recs, int64_t* nin,
+                                         uint8_t* wave) {
+  const bool w = D <= kTriWaveRow && lines <= kTriWaveWords;
+  *wave = w;
+  *nin = (int64_t)(w ? lines : recs);
 }
 
-__global__ __launch_bounds__(1024) void k_in_bound_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
-                                                         const int32_t* hof, const int32_t* idof, const int32_t* row,
-                                                         int64_t* nin) {
-  __shared__ unsigned long long sum;
+__global__ __launch_bounds__(1024) void k_in_room_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
+                                                        const int32_t* hof, const int32_t* idof, const int32_t* row,
+                                                        int64_t* nin, uint8_t* wcls) {
+  __shared__ unsigned long long sum, sumr;
   const int32_t h = blockIdx.x;
   if (h >= nbig) return;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
-  if (threadIdx.x == 0) sum = 0;
+  if (threadIdx.x == 0) sum = sumr = 0;
   __syncthreads();
-  unsigned long long c = 0;
+  unsigned long long c = 0, r = 0;
   for (int64_t k = b + threadIdx.x; k < e; k += 1024) {
     const int32_t u = hof[ci[k]];
-    if (u > h) c += tri_recs_of(row[u]);
+    const uint32_t W = u > h && row[u] > 1 ? tri_lines(row[u]) : 0;
+    c += W;
+    r += (W + kTriRecLines - 1) / kTriRecLines;
   }
   c = wave_sum(c);
-  if ((threadIdx.x & 63) == 0 && c) atomicAdd(&sum, c);
+  r = wave_sum(r);
+  if ((threadIdx.x & 63) == 0 && c) {
+    atomicAdd(&sum, c);
+    atomicAdd(&sumr, r);
+  }
   __syncthreads();
-  if (threadIdx.x == 0) nin[h] = (int64_t)sum;
+  if (threadIdx.x == 0) tri_room(row[h], sum, sumr, nin + h, wcls + h);
 }
 
-__global__ __launch_bounds__(256) void k_in_bound_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
-                                                       const int32_t* hof, const int32_t* idof, const int32_t* row,
-                                                       int64_t* nin) {
+__global__ __launch_bounds__(256) void k_in_room_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
+                                                      const int32_t* hof, const int32_t* idof, const int32_t* row,
+                                                      int64_t* nin, uint8_t* wcls) {
   const int lane = threadIdx.x & 63;
   const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
   if (h >= n) return;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
-  unsigned long long c = 0;
+  unsigned long long c = 0, r = 0;
   for (int64_t k = b + lane; k < e; k += 64) {
     const int32_t u = hof[ci[k]];
-    if (u > h) c += tri_recs_of(row[u]);
+    const uint32_t W = u > h && row[u] > 1 ? tri_lines(row[u]) : 0;
+    c += W;
+    r += (W + kTriRecLines - 1) / kTriRecLines;
   }
   c = wave_sum(c);
-  if (lane == 0) nin[h] = (int64_t)c;
+  r = wave_sum(r);
+  if (lane == 0) tri_room(row[h], c, r, nin + h, wcls + h);
 }
 
 // Per vertex: lines and bit words of its row; all entries, and the longest row.
@@ -215,8 +228,9 @@ __device__ __forceinline__ uint16_t tri_short(int32_t x, int32_t base) {
 // Rows in decreasing order of h: up to 64 entries in the registers of a wave
 // (bitonic network over the lanes); longer ones are listed for the block kernel.
 __global__ __launch_bounds__(256) void k_row_sort_wave(int32_t n, const uint32_t* oline, const int32_t* row,
-                                                       const int32_t* gid, const int64_t* vtx_off, int32_t* oc,
-                                                       uint16_t* oc16, int32_t* lu, int32_t* longer,
+                                                       const uint32_t* wbase, const int32_t* deg, const int32_t* gid,
+                                                       const int64_t* vtx_off, int32_t* oc, uint16_t* oc16,
+                                                       int32_t* lu, TriLineInfo* li, int32_t* longer,
                                                        int32_t* nlonger) {
   const int lane = threadIdx.x & 63;
   const int64_t h = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
@@ -224,7 +238,10 @@ __global__ __launch_bounds__(256) void k_row_sort_wave(int32_t n, const uint32_t
   const int32_t D = row[h];
   if (D == 0) return;
   const uint32_t W = tri_lines(D), l0 = oline[h];
-  for (uint32_t l = lane; l < W; l += 64) lu[l0 + l] = (int32_t)h;
+  for (uint32_t l = lane; l < W; l += 64) {
+    lu[l0 + l] = (int32_t)h;
+    li[l0 + l] = TriLineInfo{(int32_t)h, wbase[h], deg[h], (uint32_t)D | l << 16};
+  }
   if (D > 64) {
     if (lane == 0) longer[atomicAdd(nlonger, 1)] = (int32_t)h;
     return;
@@ -315,10 +332,10 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x, int lane) {
   return x;
 }
 
-__device__ __forceinline__ void tri_put_recs(TriRec r, TriRec* out, uint32_t p, uint32_t end) {
+__device__ __forceinline__ void tri_put_recs(TriRec r, uint32_t cut, TriRec* out, uint32_t p, uint32_t end) {
   for (; r.nw > 0 && p < end; ++p) {
     TriRec c = r;
-    c.nw = min(r.nw, (uint32_t)kTriRecLines);
+    c.nw = min(r.nw, cut);
     out[p] = c;
     r.line += c.nw;
     r.word += c.nw;
@@ -330,7 +347,7 @@ __device__ __forceinline__ void tri_put_recs(TriRec r, TriRec* out, uint32_t p, 
 __global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
                                                      const int32_t* hof, const int32_t* idof, const uint32_t* oline,
                                                      const uint32_t* wbase, const int32_t* row, const int32_t* oc,
-                                                     const int64_t* inoff, TriRec* rec, uint32_t* inlen,
+                                                     const int64_t* inoff, const uint8_t* wcls, TriRec* rec, uint32_t* inlen,
                                                      int64_t* steps) {
   __shared__ uint32_t at;
   __shared__ unsigned long long sum;
@@ -341,6 +358,7 @@ __global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t
   const int64_t b = rp[x], e = rp[x + 1];
   const uint32_t rn = (uint32_t)(inoff[h + 1] - inoff[h]);
   TriRec* out = rec + inoff[h];
+  const uint32_t cut = wcls[h] ? 1 : kTriRecLines;
   if (threadIdx.x == 0) {
     at = 0;
     sum = 0;
@@ -351,12 +369,12 @@ __global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t
     const int64_t k = k0 + threadIdx.x;
     const int32_t u = k < e ? hof[ci[k]] : -1;
     const TriRec r = u > h ? tri_rec(u, h, oline, wbase, row, oc) : TriRec{};
-    const uint32_t c = (r.nw + kTriRecLines - 1) / kTriRecLines;
+    const uint32_t c = (r.nw + cut - 1) / cut;
     const uint32_t incl = wave_scan(c, lane), all = __shfl(incl, 63, 64);
     uint32_t base = 0;
     if (lane == 0 && all) base = atomicAdd(&at, all);
     base = __shfl(base, 0, 64);
-    tri_put_recs(r, out, base + incl - c, rn);
+    tri_put_recs(r, cut, out, base + incl - c, rn);
     st += r.nw;
   }
   st = wave_sum(st);
@@ -371,7 +389,7 @@ __global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t
 __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                    const int32_t* hof, const int32_t* idof, const uint32_t* oline,
                                                    const uint32_t* wbase, const int32_t* row, const int32_t* oc,
-                                                   const int64_t* inoff, TriRec* rec, uint32_t* inlen,
+                                                   const int64_t* inoff, const uint8_t* wcls, TriRec* rec, uint32_t* inlen,
                                                    int64_t* steps) {
   const int lane = threadIdx.x & 63;
   const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
@@ -380,15 +398,16 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
   const int64_t b = rp[x], e = rp[x + 1];
   const uint32_t rn = (uint32_t)(inoff[h + 1] - inoff[h]);
   TriRec* out = rec + inoff[h];
+  const uint32_t cut = wcls[h] ? 1 : kTriRecLines;
   uint32_t at = 0;
   unsigned long long st = 0;
   for (int64_t k0 = b; k0 < e; k0 += 64) {
     const int64_t k = k0 + lane;
     const int32_t u = k < e ? hof[ci[k]] : -1;
     const TriRec r = u > (int32_t)h ? tri_rec(u, (int32_t)h, oline, wbase, row, oc) : TriRec{};
-    const uint32_t c = (r.nw + kTriRecLines - 1) / kTriRecLines;
+    const uint32_t c = (r.nw + cut - 1) / cut;
     const uint32_t incl = wave_scan(c, lane);
-    tri_put_recs(r, out, at + incl - c, rn);
+    tri_put_recs(r, cut, out, at + incl - c, rn);
     at += __shfl(incl, 63, 64);
     st += r.nw;
   }
@@ -399,21 +418,17 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
   }
 }
 
-__device__ __forceinline__ bool tri_wave_row(int32_t D, uint32_t nin, int64_t steps) {
-  return D <= kTriWaveRow && steps <= kTriWaveWords && nin < (1u << 24);
-}
-
 // Work of every vertex: jobs of the block kernel, or a place in the wave
 // kernel's list; the sum of all words and the longest hash-table row.
 __global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_off, const int32_t* row,
-                             const uint32_t* inlen, const int64_t* steps,
+                             const uint8_t* wcls, const uint32_t* inlen, const int64_t* steps,
                              int64_t* njob, int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t j = 0, w = 0;
   unsigned long long st = 0;
   if (h < n && steps[h] > 0) {
     st = (unsigned long long)steps[h];
-    if (tri_wave_row(row[h], inlen[h], steps[h])) {
+    if (wcls[h]) {
       w = 1;
     } else {
       j = (inlen[h] + kTriJob - 1) / kTriJob;
@@ -689,15 +704,23 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
   }
 }
 
-// Vertices with a short row and few in-edges: one per wave.  Each half of the
-// wave takes every other in-edge, a line of columns a step; the next four lines
-// (of this in-edge or the ones after) are loaded while four are looked up.
+// Vertices with a short row and few in-edges, one per wave; a record is one
+// line, and each half of the wave takes every other one.  Bound by vector
+// instructions (batch of 300 graphs: 0.8 of 1.16 ms when every line's place was
+// worked out here and every lookup could take several probes), so: records of
+// one line, offsets read back from the lane that loaded the record, the bits of
+// four steps stored by eight lanes at once, and for rows up to 40 entries (256
+// slots) a hash that is changed until the row has no collision, after which a
+// lookup is one probe (batch of 300 graphs: 0.77 ms).
+template <typename E>
 __global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* __restrict__ wrow,
-                                                  const TriRec* __restrict__ rec, const int32_t* __restrict__ oc,
-                                                  uint32_t* __restrict__ bits, int32_t* __restrict__ cnt) {
+                                                  const TriRec* __restrict__ rec, const E* __restrict__ cols,
+                                                  int64_t lines, uint32_t* __restrict__ bits,
+                                                  int32_t* __restrict__ cnt) {
   __shared__ __align__(16) int32_t keys[4][kTriWaveSlots];
   __shared__ __align__(16) int32_t hits[4][kTriWaveSlots];
   constexpr uint32_t kMask = kTriWaveSlots - 1;
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
   const int lane = threadIdx.x & 63, half = lane >> 5, sub = lane & 31;
   const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= nrow) return;
@@ -706,100 +729,100 @@ __global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* _
   const TriWave V = wrow[i];
   const uint32_t D = V.shape & 0xFFu, rc = V.shape >> 8;
   const int64_t base = (int64_t)V.line * kTriLine;
-  const int32_t e0 = (uint32_t)lane < D ? oc[base + lane] : 0, e1 = (uint32_t)lane + 64 < D ? oc[base + 64 + lane] : 0;
-  TriRec r = (uint32_t)lane < rc ? rec[V.rbeg + lane] : TriRec{};
-  static_assert(kTriWaveSlots == 256 && kTriWaveRow <= 128, "four slots per lane, two entries per lane");
-  reinterpret_cast<int4*>(key)[lane] = make_int4(-1, -1, -1, -1);
-  reinterpret_cast<int4*>(hit)[lane] = make_int4(0, 0, 0, 0);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  auto insert = [&](int32_t x) -> uint32_t {
-    uint32_t t = tri_hash(x) & kMask;
-    while (atomicCAS(key + t, -1, x) != -1) t = (t + 1) & kMask;
-    return t;
+  const TriRec* recs = rec + V.rbeg;
+  const uint32_t e0 = (uint32_t)lane < D ? cols[base + lane] : 0;
+  const uint32_t e1 = D > 64 && (uint32_t)lane + 64 < D ? cols[base + 64 + lane] : 0;
+  TriRec r = (uint32_t)lane < rc ? recs[lane] : TriRec{kNone, 0, 0, 0};
+  static_assert(kTriWaveSlots == 1 << 8 && kTriWaveRow <= 128, "four slots per lane, two entries per lane");
+  uint32_t shift = 8, t0 = 0, t1 = 0;
+  // one probe per lookup, or (the neighbours of hubs are runs of ids, which the
+  // folded hash would put side by side) a scattering hash with linear probing
+  bool single = D <= 40;
+  auto hash = [&](uint32_t x) -> uint32_t {
+    return single ? (x ^ (x >> shift)) & kMask : x * 0x9E3779B1u >> 24;
   };
-  const uint32_t t0 = e0 ? insert(e0) : 0, t1 = e1 ? insert(e1) : 0;
+  reinterpret_cast<int4*>(hit)[lane] = make_int4(0, 0, 0, 0);
+  for (int attempt = 0;; ++attempt) {
+    reinterpret_cast<int4*>(key)[lane] = make_int4(-1, -1, -1, -1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    t0 = hash(e0);
+    t1 = hash(e1);
+    bool ok = e0 == 0 || atomicCAS(key + t0, -1, (int32_t)e0) == -1;
+    bool ok1 = e1 == 0 || atomicCAS(key + t1, -1, (int32_t)e1) == -1;
+    if (!__ballot(!(ok && ok1))) break;
+    if (single) {
+      shift = attempt == 0 ? 5 : attempt == 1 ? 3 : 10;
+      single = attempt < 3;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      continue;
+    }
+    while (!ok) {
+      t0 = (t0 + 1) & kMask;
+      ok = atomicCAS(key + t0, -1, (int32_t)e0) == -1;
+    }
+    while (!ok1) {
+      t1 = (t1 + 1) & kMask;
+      ok1 = atomicCAS(key + t1, -1, (int32_t)e1) == -1;
+    }
+    break;
+  }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+  struct Group {
+    E x0, x1, x2, x3;
+  };
+  const __amdgpu_buffer_rsrc_t all = buffer_upto(cols, (uint32_t)(lines * kTriLine * 2));  // (16-bit entries)
   for (uint32_t b0 = 0; b0 < rc; b0 += 64) {
-    if (b0) r = b0 + lane < rc ? rec[V.rbeg + b0 + lane] : TriRec{};
+    if (b0) r = b0 + lane < rc ? recs[b0 + lane] : TriRec{kNone, 0, 0, 0};
     const uint32_t nb = min(64u, rc - b0);
-    struct Group {
-      int32_t x0, x1, x2, x3;      // columns (0: none)
-      uint32_t w0, w1, w2, w3;     // words their bits go to (~0: none)
+    // 16-bit entries: the byte offset (past the end for no record); else the line
+    const int where = (int)(sizeof(E) == 2 ? (r.line == kNone ? kNone : r.line * (kTriLine * 2)) : r.line);
+    auto entry = [&](uint32_t k) -> E {
+      const uint32_t o = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((k + half) * 4), where);
+      if (sizeof(E) == 2) return (E)buffer_entry((const uint16_t*)nullptr, all, o == kNone ? o : o + 2 * sub);
+      return o == kNone ? (E)0 : cols[(int64_t)o * kTriLine + sub];
     };
-    uint32_t at = (uint32_t)half, line = 0, word = 0, left = 0;
-    auto fetch = [&]() {  // record `at` of this half (lanes past nb hold empty ones)
-      const int src = (int)min(at, 63u);
-      line = __shfl(r.line, src, 64);
-      word = __shfl(r.word, src, 64);
-      left = __shfl(r.nw, src, 64);
-      if (at >= nb) left = 0;
+    auto load = [&](Group& g, uint32_t k) {
+      g.x0 = entry(k);
+      g.x1 = entry(k + 2);
+      g.x2 = entry(k + 4);
+      g.x3 = entry(k + 6);
     };
-    auto next = [&](int32_t& x, uint32_t& w) {
-      const bool in = left > 0;
-      w = in ? word : ~0u;
-      x = in ? oc[(int64_t)line * kTriLine + sub] : 0;
-      ++line;
-      ++word;
-      if (left > 1) {
-        --left;
-      } else {
-        at += 2;
-        left = 0;
-      }
-      if (__ballot(left == 0)) {
-        const uint32_t l = line, d = word, f = left;
-        fetch();
-        if (f) {
-          line = l;
-          word = d;
-          left = f;
-        }
-      }
-    };
-    auto load = [&](Group& g) {
-      next(g.x0, g.w0);
-      next(g.x1, g.w1);
-      next(g.x2, g.w2);
-      next(g.x3, g.w3);
-    };
-    auto look = [&](int32_t x, uint32_t w) {
-      bool found = false;
-      uint32_t t = tri_hash(x) & kMask;
-      if ((uint32_t)(x - 1) < (uint32_t)V.v) {
-        while (true) {
-          const int32_t y = key[t];
-          if (y == x) {
-            found = true;
-            break;
+    auto look = [&](const Group& g, uint32_t k) {
+      uint32_t w = 0;
+      auto step = [&](E x, auto at) {
+        constexpr int kAt = decltype(at)::value;
+        uint32_t t = hash(x);
+        int32_t y = key[t];
+        if (!single) {
+          while (y != (int32_t)x && y != -1) {
+            t = (t + 1) & kMask;
+            y = key[t];
           }
-          if (y == -1) break;
-          t = (t + 1) & kMask;
         }
-      }
-      if (found) atomicAdd(hit + t, 1);
-      const uint64_t m = __ballot(found);
-      if (sub == 0 && w != ~0u) bits[w] = half ? (uint32_t)(m >> 32) : (uint32_t)m;
-    };
-    auto look4 = [&](const Group& g) {
-      look(g.x0, g.w0);
-      look(g.x1, g.w1);
-      look(g.x2, g.w2);
-      look(g.x3, g.w3);
+        const bool found = y == (int32_t)x;  // 0, no entry, is in no table
+        if (found) atomicAdd(hit + t, 1);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(found);
+        set_lane(w, (uint32_t)m, 2 * kAt);
+        set_lane(w, (uint32_t)(m >> 32), 2 * kAt + 1);
+      };
+      step(g.x0, std::integral_constant<int, 0>{});
+      step(g.x1, std::integral_constant<int, 1>{});
+      step(g.x2, std::integral_constant<int, 2>{});
+      step(g.x3, std::integral_constant<int, 3>{});
+      const uint32_t to = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((k + lane) * 4), (int)r.word);
+      if (lane < 8 && k + lane < nb) bits[to] = w;
     };
     Group g, h;
-    fetch();
-    load(g);
-    while (true) {
-      const bool more = __ballot(at < nb) != 0;
-      if (more) load(h);
-      look4(g);
-      if (!more) break;
-      const bool more2 = __ballot(at < nb) != 0;
-      if (more2) load(g);
-      look4(h);
-      if (!more2) break;
+    load(g, 0);
+    for (uint32_t k = 0; k < nb; k += 16) {
+      if (k + 8 < nb) load(h, k + 8);
+      look(g, k);
+      if (k + 8 >= nb) break;
+      if (k + 16 < nb) load(g, k + 16);
+      look(h, k + 8);
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -828,73 +851,84 @@ __global__ void k_tri_init(int64_t ncnt4, int4* cnt, int32_t n, int32_t* lower, 
 
 __device__ __forceinline__ int32_t tri_mu(const TriArgs& a, int64_t h) { return a.gid ? a.gmu[a.gid[h]] : a.mu; }
 
-// 32 x 32 bits across the lanes of a half wave: lane j's word becomes column j.
-__device__ __forceinline__ uint32_t tri_transpose(uint32_t w, int sub) {
-  uint32_t m = 0x0000FFFFu;
-#pragma unroll
-  for (int s = 16; s >= 1; s >>= 1) {
-    const uint32_t y = (uint32_t)__shfl_xor((int32_t)w, s, 64);
-    w = (sub & s) ? (w & ~m) | ((y & ~m) >> s) : (w & m) | ((y & m) << s);
-    m ^= m << (s >> 1);
+// x of the lane whose number differs by kXor inside the half wave.
+template <int kXor>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+  if constexpr (kXor == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad 1,0,3,2 */, 0xF, 0xF, true);
+  if constexpr (kXor == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad 2,3,0,1 */, 0xF, 0xF, true);
+  if constexpr (kXor == 4) {  // 7 - lane of eight, then 3 - lane of four
+    const int y = __builtin_amdgcn_update_dpp(0, (int)x, 0x141 /* row_half_mirror */, 0xF, 0xF, true);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, y, 0x1B /* quad 3,2,1,0 */, 0xF, 0xF, true);
   }
-  return w;
+  if constexpr (kXor == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128 /* row_ror:8 */, 0xF, 0xF, true);
+  return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x401F /* lane ^ 16 */);
+}
+
+// 32 x 32 bits across the lanes of a half wave: lane j's word becomes column j.
+template <int kStep>
+__device__ __forceinline__ uint32_t tri_exchange(uint32_t w, int sub, uint32_t m) {
+  const uint32_t y = lane_xor<kStep>(w);
+  return (sub & kStep) ? (w & ~m) | ((y & ~m) >> kStep) : (w & m) | ((y & m) << kStep);
+}
+__device__ __forceinline__ uint32_t tri_transpose(uint32_t w, int sub) {
+  w = tri_exchange<16>(w, sub, 0x0000FFFFu);
+  w = tri_exchange<8>(w, sub, 0x00FF00FFu);
+  w = tri_exchange<4>(w, sub, 0x0F0F0F0Fu);
+  w = tri_exchange<2>(w, sub, 0x33333333u);
+  return tri_exchange<1>(w, sub, 0x55555555u);
 }
 
 // One line per half wave: closed counts of its entries, and with eps the
 // similar ones, which are counted on both endpoints.
 template <bool kEps>
-__global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const int32_t* __restrict__ lu,
-                                                   const uint32_t* __restrict__ oline,
-                                                   const uint32_t* __restrict__ wbase,
-                                                   const int32_t* __restrict__ row, const int32_t* __restrict__ deg,
-                                                   const int32_t* __restrict__ oc, const uint32_t* __restrict__ bits,
-                                                   int32_t* __restrict__ cnt, TriArgs a, uint32_t* __restrict__ simw,
-                                                   int32_t* __restrict__ lower, int32_t* __restrict__ flag) {
+__global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const TriLineInfo* __restrict__ li,
+                                                   const int32_t* __restrict__ deg, const int32_t* __restrict__ oc,
+                                                   const uint32_t* __restrict__ bits, int32_t* __restrict__ cnt,
+                                                   TriArgs a, uint32_t* __restrict__ simw,
+                                                   int32_t* __restrict__ lower) {
   const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
   if (t >= lines) return;
   const int sub = threadIdx.x & 31;
-  const int32_t u = lu[t];
-  const uint32_t l0 = oline[u], W = oline[u + 1] - l0, c = (uint32_t)t - l0;
-  const int32_t D = row[u];
-  const uint32_t wb = wbase[u];
+  const TriLineInfo L = li[t];
   const int32_t x = oc[t * kTriLine + sub] - 1;
   int32_t closed = cnt[t * kTriLine + sub] + 2;
+  const int32_t D = (int32_t)(L.shape & 0xFFFFu);
+  const uint32_t W = tri_lines(D), c = L.shape >> 16;
   const int32_t i = (int32_t)(c * kTriLine) + sub;
   // the row's own bits (the last column has none after it and was not written)
-  if (i < D - 1) {
-    const uint32_t* mine = bits + wb + tri_word(W, (uint32_t)i);
-    for (uint32_t k = 0; k < W - c; ++k) closed += __popc(mine[k]);
-  }
+  const uint32_t* mine = bits + L.wbase + tri_word(W, (uint32_t)i);
+  const uint32_t own = i < D - 1 ? *mine : 0;
+  if (i < D - 1)
+    for (uint32_t k = 1; k < W - c; ++k) closed += __popc(mine[k]);
+  const int32_t dx = kEps && x >= 0 ? deg[x] : 0;
   // the bits of its column
-  for (uint32_t b = 0; b <= c; ++b) {
-    const int32_t k = (int32_t)(b * kTriLine) + sub;
-    const uint32_t w = k < D - 1 ? bits[wb + tri_word(W, (uint32_t)k) + (c - b)] : 0;
-    closed += __popc(tri_transpose(w, sub));
+  for (uint32_t b = 0; b < c; ++b) {
+    const uint32_t k = b * kTriLine + sub;
+    closed += __popc(tri_transpose(bits[L.wbase + tri_word(W, k) + (c - b)], sub));
   }
+  closed += __popc(own) + __popc(tri_transpose(own, sub));
   if (!kEps) {
     cnt[t * kTriLine + sub] = closed;
     return;
   }
   if (a.gid) {
-    const int32_t g = a.gid[u];
+    const int32_t g = a.gid[L.u];
     a.p = a.gp[g];
     a.q = a.gq[g];
-    a.mu = a.gmu[g];
   }
   bool sim = false;
   if (x >= 0) {
-    const uint64_t ab = ((uint64_t)deg[u] + 1) * ((uint64_t)deg[x] + 1);
+    const uint64_t ab = ((uint64_t)L.deg + 1) * ((uint64_t)dx + 1);
     const uint64_t cq = (uint64_t)closed * a.q;
     sim = cq * cq >= (a.p * a.p) * ab;
   }
   const uint64_t m = __ballot(sim);
-  const uint32_t mine = (threadIdx.x & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
-  if (sub == 0) simw[t] = mine;
-  if (!m) return;
-  bool core = false;
-  if (sim) core = atomicAdd(lower + x, 1) + 1 >= a.mu;
-  if (sub == 0 && mine) core = (atomicAdd(lower + u, (int32_t)__popc(mine)) + (int32_t)__popc(mine) >= a.mu) || core;
-  if (__ballot(core) && (threadIdx.x & 63) == 0) *flag = 1;
+  const uint32_t word = (threadIdx.x & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
+  if (sub == 0) {
+    simw[t] = word;
+    if (word) atomicAdd(lower + L.u, (int32_t)__popc(word));
+  }
+  if (sim) atomicAdd(lower + x, 1);
 }
 
 // A parent as the caches have it: some ancestor, maybe not the newest.
@@ -904,9 +938,11 @@ __device__ __forceinline__ int32_t ld_near(const int32_t* p) {
 
 // Minimum over a half wave.
 __device__ __forceinline__ int32_t half_min(int32_t x) {
-#pragma unroll
-  for (int d = 16; d >= 1; d >>= 1) x = min(x, __shfl_xor(x, d, 64));
-  return x;
+  x = min(x, (int32_t)lane_xor<16>((uint32_t)x));
+  x = min(x, (int32_t)lane_xor<8>((uint32_t)x));
+  x = min(x, (int32_t)lane_xor<4>((uint32_t)x));
+  x = min(x, (int32_t)lane_xor<2>((uint32_t)x));
+  return min(x, (int32_t)lane_xor<1>((uint32_t)x));
 }
 
 // First step of the clustering: every core points at the least core id that a
@@ -914,25 +950,29 @@ __device__ __forceinline__ int32_t half_min(int32_t x) {
 // a forest, got with one atomicMin per similar entry at most and no retries,
 // and in a dense cluster it leaves few roots for k_tri_hook, where unions of
 // single edges from the start compete for the same roots.
+// Sets the flag that lets the later kernels run: a core has a similar entry.
 __global__ __launch_bounds__(256) void k_tri_link(int64_t lines, const int32_t* __restrict__ lu,
                                                   const int32_t* __restrict__ oc, const uint32_t* __restrict__ simw,
                                                   const int32_t* __restrict__ lower, const int32_t* __restrict__ idof,
-                                                  TriArgs a_, int32_t* parent, const int32_t* __restrict__ flag) {
-  if (!*flag) return;
+                                                  TriArgs a_, int32_t* parent, int32_t* __restrict__ flag) {
   const int sub = threadIdx.x & 31;
   const int64_t stride = (int64_t)gridDim.x * 8;
+  bool cores = false;
   for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
     const uint32_t w = simw[t];
     if (!w) continue;
     const int32_t u = lu[t], mu = tri_mu(a_, u);
-    if (lower[u] < mu) continue;
     const int32_t x = oc[t * kTriLine + sub] - 1;
     const bool in = ((w >> sub) & 1u) && lower[x] >= mu;
+    cores = cores || in;
+    if (lower[u] < mu) continue;
+    cores = true;
     const int32_t a = idof[u], b = in ? idof[x] : a;
     const int32_t least = half_min(min(a, b));
     if (in && least < b && ld_near(parent + b) > least) atomicMin(parent + b, least);
     if (sub == 0 && least < a && ld_near(parent + a) > least) atomicMin(parent + a, least);
   }
+  if (__ballot(cores) && (threadIdx.x & 63) == 0) *flag = 1;
 }
 
 __global__ void k_tri_compress(int32_t n, int32_t* parent, const int32_t* __restrict__ flag) {
@@ -1111,7 +1151,7 @@ hipError_t dnew(T** p, int64_t count) {
 
 uint64_t tri_layout_bytes(const TriLayout& T) {
   const uint64_t n = (uint64_t)T.n, L = (uint64_t)T.lines;
-  return 16 * n + 8 * (n + 1) + 4 * L + 6 * (L * kTriLine + 2 * kTriLine) + sizeof(TriRec) * (uint64_t)T.recs +
+  return 16 * n + 8 * (n + 1) + 20 * L + 6 * (L * kTriLine + 2 * kTriLine) + sizeof(TriRec) * (uint64_t)T.recs +
          sizeof(TriJob) * (uint64_t)T.jobs + sizeof(TriWave) * (uint64_t)T.wave_rows;
 }
 
@@ -1120,7 +1160,7 @@ uint64_t tri_scratch_bytes(const TriLayout& T) {
 }
 
 void tri_release(TriLayout& T) {
-  void* p[] = {T.hof, T.idof, T.deg, T.row, T.oline, T.wbase, T.lu, T.oc, T.oc16, T.rec, T.job, T.wrow};
+  void* p[] = {T.hof, T.idof, T.deg, T.row, T.oline, T.wbase, T.lu, T.li, T.oc, T.oc16, T.rec, T.job, T.wrow};
   for (void* x : p)
     if (x) (void)hipFree(x);
   T = TriLayout();
@@ -1151,6 +1191,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   hipError_t e = hipSuccess;
   int64_t *nline = nullptr, *nword = nullptr, *nin = nullptr, *at0 = nullptr, *at1 = nullptr, *at2 = nullptr;
   uint32_t* inlen = nullptr;
+  uint8_t* wcls = nullptr;
   int32_t *ctl = nullptr, *longer = nullptr;
   unsigned long long* sums = nullptr;
   int64_t tot[3] = {0, 0, 0};
@@ -1216,9 +1257,11 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(dnew(&at1, (int64_t)n + 1));
   TTRY(dnew(&at2, (int64_t)n + 1));
   TTRY(dnew(&inlen, n));
+  TTRY(dnew(&wcls, n));
   k_row_sizes<<<gv, 256, 0, s>>>(n, T.row, nline, nword, sums + 1 + kNumBuckets, ctl);
-  if (nbig > 0) k_in_bound_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.row, nin);
-  if (n > nbig) k_in_bound_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row, nin);
+  if (nbig > 0) k_in_room_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
+  if (n > nbig) 
+    k_in_room_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
   TTRY(hipMemsetAsync(nin + n, 0, 8, s));
   TTRY(hipGetLastError());
   TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1));
@@ -1242,6 +1285,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(dnew(&T.wbase, (int64_t)n + 1));
   k_narrow<<<gv, 256, 0, s>>>(n, at0, at1, T.oline, T.wbase);
   TTRY(dnew(&T.lu, T.lines));
+  TTRY(dnew(&T.li, T.lines));
   // steps of 64 entries may start on a row's last line
   TTRY(dnew(&T.oc, (T.lines + 2) * kTriLine));
   TTRY(dnew(&T.oc16, (T.lines + 2) * kTriLine));
@@ -1249,18 +1293,18 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (nbig > 0) k_row_fill_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
   if (n > nbig)
     k_row_fill_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
-  k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16, T.lu, longer,
-                                                   ctl + 1);
+  k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.wbase, T.deg, T.gid, T.vtx_off, T.oc, T.oc16,
+                                                   T.lu, T.li, longer, ctl + 1);
   k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16);
   TTRY(hipGetLastError());
   TTRY(dnew(&T.rec, T.recs));
   if (nbig > 0)
-    k_recs_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row, T.oc, at2, T.rec,
-                                       inlen, nin);
+    k_recs_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row, T.oc, at2, wcls,
+                                       T.rec, inlen, nin);
   if (n > nbig)
     k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
-                                                      T.oc, at2, T.rec, inlen, nin);
-  k_job_counts<<<gv, 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, inlen, nin, nline, nword, sums, ctl + 2);
+                                                      T.oc, at2, wcls, T.rec, inlen, nin);
+  k_job_counts<<<gv, 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, sums, ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
   TTRY(hipGetLastError());
@@ -1285,7 +1329,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   *ok = 1;
 done:
   (void)hipStreamSynchronize(s);
-  void* tmp[] = {nline, nword, nin, at0, at1, at2, inlen, ctl, longer, sums};
+  void* tmp[] = {nline, nword, nin, at0, at1, at2, inlen, wcls, ctl, longer, sums};
   for (void* x : tmp)
     if (x) (void)hipFree(x);
   if (!*ok) tri_release(T);
@@ -1304,19 +1348,23 @@ void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
   if (T.jobs > 0)
     k_tri_block<<<(unsigned)T.jobs, kTriBlock, tri_lds_bytes(T), s>>>(T.job, T.rec, T.row, T.oline, T.gid, T.vtx_off,
                                                                      T.oc, T.oc16, S.bits, S.cnt, tri_acc_cap(T));
-  if (T.wave_rows > 0)
-    k_tri_wave<<<grid_for(T.wave_rows, 4), 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc, S.bits, S.cnt);
+  if (T.wave_rows > 0) {
+    if (T.span <= kTriShort)
+      k_tri_wave<uint16_t><<<grid_for(T.wave_rows, 4), 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc16, T.lines, S.bits,
+                                                                    S.cnt);
+    else
+      k_tri_wave<uint32_t><<<grid_for(T.wave_rows, 4), 256, 0, s>>>(
+          T.wave_rows, T.wrow, T.rec, reinterpret_cast<const uint32_t*>(T.oc), T.lines, S.bits, S.cnt);
+  }
 }
 
 void tri_close(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower) {
   if (T.lines <= 0) return;
   const unsigned grid = grid_for(T.lines, 8);
   if (a.q || a.gq)
-    k_tri_close<true><<<grid, 256, 0, s>>>(T.lines, T.lu, T.oline, T.wbase, T.row, T.deg, T.oc, S.bits, S.cnt, a,
-                                           S.simw, lower, S.flag);
+    k_tri_close<true><<<grid, 256, 0, s>>>(T.lines, T.li, T.deg, T.oc, S.bits, S.cnt, a, S.simw, lower);
   else
-    k_tri_close<false><<<grid, 256, 0, s>>>(T.lines, T.lu, T.oline, T.wbase, T.row, T.deg, T.oc, S.bits, S.cnt, a,
-                                            S.simw, nullptr, S.flag);
+    k_tri_close<false><<<grid, 256, 0, s>>>(T.lines, T.li, T.deg, T.oc, S.bits, S.cnt, a, S.simw, nullptr);
 }
 
 namespace {
