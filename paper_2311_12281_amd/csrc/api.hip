@@ -257,8 +257,8 @@ uint64_t scan::graph_layout_bytes(const scan_graph* g) {
   const uint64_t n = (uint64_t)g->n, nnz = (uint64_t)g->nnz, m = (uint64_t)g->m;
   const uint64_t b6 = (uint64_t)(g->bucket_off[kNumBuckets] - g->bucket_off[kNumBuckets - 1]);
   if (g->has_tri)
-    return 8 * (n + 1) + 4 * (nnz + kColPad) + 17 * n + tri_layout_bytes(g->tri) + tri_scratch_bytes(g->tri) +
-           (g->tri_na.cnt ? tri_scratch_bytes(g->tri) : 0);
+    return 8 * (n + 1) + 4 * (nnz + kColPad) + 17 * n + tri_layout_bytes(g->tri) + tri_scratch_bytes(g->tri, g->tri_s) +
+           tri_scratch_bytes(g->tri, g->tri_na);
   uint64_t b = 8 * (n + 1) + 4 * (nnz + kColPad) + 8 * m + (g->d_edeg ? 8 * m : 0) + sizeof(HubJob) * (uint64_t)g->hub_jobs + 4 * b6 +
                4 * (uint64_t)g->wtab_entries;
   if (g->d_hci) b += 4 * (nnz + kColPad);

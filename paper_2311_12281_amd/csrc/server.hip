@@ -1,6 +1,9 @@
 // Serving: graphs stay resident with the exact closed count of every edge,
 // and (graph, eps, mu) queries are answered by re-thresholding those counts
-// (no intersection), which needs only streaming passes over the edges.
+// (no intersection), which needs only streaming passes over the edges.  The
+// counts are those of the triangle path, left in its row entries; a server
+// with a device budget keeps the edge list, whose footprint is known before a
+// graph is admitted.
 //
 // Continuous batching: a dispatcher thread admits queued requests onto free
 // slots as soon as slots free up; each slot owns a HIP stream and per-query
@@ -42,6 +45,7 @@ struct ServedGraph {
   int32_t* d_ecount = nullptr;   // resident: closed count per oriented edge
   uint64_t* d_ab = nullptr;      // resident: |N[u]| |N[v]| per oriented edge
   uint64_t bytes = 0;            // device bytes held while resident
+  int64_t state_bytes = 0;       // bytes of Slot::d_state a query needs
   std::vector<int64_t> h_rp;     // non-resident: host copy
   std::vector<int32_t> h_ci;
   int inflight = 0;
@@ -86,7 +90,13 @@ struct Slot {
   std::shared_ptr<Request> req;  // running request, or null
 };
 
-uint64_t slot_bytes(int32_t n, int64_t m) { return 18ull * (uint64_t)n + (uint64_t)m; }
+uint64_t slot_bytes(int32_t n, int64_t state) { return 18ull * (uint64_t)n + (uint64_t)state; }
+
+// d_state of a query on the triangle path's rows: the words of similar entries,
+// the flag, and with hub and outlier roles the first label seen per vertex.
+int64_t tri_state_bytes(const TriLayout& T, bool split) {
+  return 4 * (T.lines + 1) + (split ? 4 * (int64_t)T.n : 0);
+}
 
 // Peak device bytes of adding a graph: the in-memory layout as
 // scan_graph_create builds it (with the degree-ranked copy of the rows where
@@ -163,7 +173,7 @@ struct scan_server {
   int32_t out_total = 0;         // result buffers allocated
   int32_t out_max = 0;           // bound on them
   int32_t slot_n = 0;  // slot scratch capacity
-  int64_t slot_m = 0;
+  int64_t slot_m = 0;  // bytes of d_state
   int64_t completed = 0;
   bool stop = false;
   bool pause_dispatch = false;  // set while slot buffers are being resized
@@ -252,7 +262,7 @@ bool launch_on_slot(scan_server* S, Slot& slot, const std::shared_ptr<Request>& 
   p /= a;
   q /= a;
   scan_graph* g = G->g;
-  if (G->n > slot.cap_n || G->m > slot.cap_m) {
+  if (G->n > slot.cap_n || G->state_bytes > slot.cap_m) {
     r->status = SCAN_E_NOMEM;
     r->error = "slot scratch smaller than the graph";
     return false;
@@ -262,14 +272,36 @@ bool launch_on_slot(scan_server* S, Slot& slot, const std::shared_ptr<Request>& 
     r->error = "no result buffer";
     return false;
   }
-  launch_rethreshold(slot.stream, G->n, G->m, g->d_edges, G->d_ecount, G->d_ab, (uint64_t)p, (uint64_t)q,
-                     r->mu, slot.d_lower, slot.d_role, slot.d_parent, slot.d_label, slot.d_state,
-                     slot.d_out_labels, slot.d_out_roles, S->opts.hub_outlier ? 1 : 0);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && G->n > 0)
-    e = hipMemcpyAsync(slot.out.labels, slot.d_out_labels, 4 * (size_t)G->n, hipMemcpyDeviceToHost, slot.stream);
-  if (e == hipSuccess && G->n > 0)
-    e = hipMemcpyAsync(slot.out.roles, slot.d_out_roles, (size_t)G->n, hipMemcpyDeviceToHost, slot.stream);
+  hipError_t e = hipSuccess;
+  if (g->has_tri) {
+    const TriLayout& T = g->tri;
+    TriScratch Q = g->tri_s;  // the counts; the rest is the slot's
+    Q.simw = reinterpret_cast<uint32_t*>(slot.d_state);
+    Q.flag = reinterpret_cast<int32_t*>(Q.simw + T.lines);
+    TriArgs A;
+    A.p = (uint64_t)p;
+    A.q = (uint64_t)q;
+    A.mu = r->mu;
+    const int32_t split = S->opts.hub_outlier ? 1 : 0;
+    hipStream_t s = slot.stream;
+    tri_init_state(s, T, Q, slot.d_lower, slot.d_parent, slot.d_label, slot.d_role);
+    tri_threshold(s, T, Q, A, slot.d_lower);
+    tri_hook(s, T, Q, A, slot.d_lower, slot.d_parent);
+    tri_attach(s, T, Q, A, slot.d_lower, slot.d_parent, slot.d_label);
+    if (split) tri_hub_outlier(s, T, Q, A, slot.d_lower, slot.d_parent, slot.d_label, Q.flag + 1, slot.d_role);
+    // the results go straight to the pinned buffer
+    tri_output(s, T, A, slot.d_lower, slot.d_parent, slot.d_label, slot.d_role, slot.out.labels, slot.out.roles, split);
+    e = hipGetLastError();
+  } else {
+    launch_rethreshold(slot.stream, G->n, G->m, g->d_edges, G->d_ecount, G->d_ab, (uint64_t)p, (uint64_t)q,
+                       r->mu, slot.d_lower, slot.d_role, slot.d_parent, slot.d_label, slot.d_state,
+                       slot.d_out_labels, slot.d_out_roles, S->opts.hub_outlier ? 1 : 0);
+    e = hipGetLastError();
+    if (e == hipSuccess && G->n > 0)
+      e = hipMemcpyAsync(slot.out.labels, slot.d_out_labels, 4 * (size_t)G->n, hipMemcpyDeviceToHost, slot.stream);
+    if (e == hipSuccess && G->n > 0)
+      e = hipMemcpyAsync(slot.out.roles, slot.d_out_roles, (size_t)G->n, hipMemcpyDeviceToHost, slot.stream);
+  }
   if (e == hipSuccess) e = hipEventRecord(slot.done, slot.stream);
   if (e != hipSuccess) {
     r->status = SCAN_E_DEVICE;
@@ -450,6 +482,8 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
   G->n = n;
   G->nnz = nnz;
   G->m = nnz / 2;
+  G->state_bytes = G->m;
+  bool tri;
   const uint64_t gbytes = graph_bytes(n, nnz, S->opts);
   bool resident;
   {
@@ -460,6 +494,7 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
     const int64_t new_m = G->m > S->slot_m ? G->m : S->slot_m;
     const uint64_t grow = S->slots.size() * (slot_bytes(new_n, new_m) - slot_bytes(S->slot_n, S->slot_m));
     auto fits = [&] { return S->budget == 0 || S->resident_bytes + gbytes + grow <= S->budget; };
+    tri = S->budget == 0;  // (its scratch is known only once it is built)
     resident = fits();
     if (!resident && S->fb.g && !S->fb.busy) {
       fallback_evict(S);
@@ -472,9 +507,13 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
     scan_opts o = S->opts;
     o.device_budget_bytes = 0;
     scan_graph* g = nullptr;
-    int rc = graph_create(n, nnz, row_ptr, col_idx, &o, false, nullptr, &g);
+    int rc = graph_create(n, nnz, row_ptr, col_idx, &o, tri, nullptr, &g);
     G->g = g;
-    if (rc == SCAN_OK && g->m > 0) {
+    if (rc == SCAN_OK && g->has_tri) {
+      std::lock_guard<std::mutex> glk(g->lock);
+      rc = run_counts(g, nullptr, nullptr, g->stream);
+      G->state_bytes = tri_state_bytes(g->tri, S->opts.hub_outlier != 0);
+    } else if (rc == SCAN_OK && g->m > 0) {
       hipError_t e = hipMalloc((void**)&G->d_ecount, sizeof(int32_t) * (size_t)g->m);
       if (e == hipSuccess) e = hipMalloc((void**)&G->d_ab, sizeof(uint64_t) * (size_t)g->m);
       if (e != hipSuccess) {
@@ -494,6 +533,16 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
       // queries never intersect again: the rows renamed by degree rank and
       // the other inputs of the intersections, used only by the counting run,
       // are released
+      if (g->has_tri) {
+        tri_drop_inputs(g->tri);
+        const int32_t* keep = g->tri_s.cnt;
+        TriScratch rest = g->tri_s;
+        rest.cnt = nullptr;
+        tri_release_scratch(rest);
+        tri_release_scratch(g->tri_na);
+        g->tri_s = TriScratch{};
+        g->tri_s.cnt = const_cast<int32_t*>(keep);
+      }
       if (g->d_hci) {
         (void)hipFree(g->d_hci);
         g->d_hci = nullptr;
@@ -506,7 +555,7 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
         (void)hipFree(g->d_edeg);
         g->d_edeg = nullptr;
       }
-      const uint64_t now = graph_device_bytes(g) + 12ull * (uint64_t)g->m;
+      const uint64_t now = graph_device_bytes(g) + (g->has_tri ? 0 : 12ull * (uint64_t)g->m);
       std::lock_guard<std::mutex> lk(S->mu);
       S->resident_bytes -= held;
       S->resident_bytes += now;
@@ -525,9 +574,9 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
     if (nnz > 0) G->h_ci.assign(col_idx, col_idx + nnz);
   }
   std::unique_lock<std::mutex> lk(S->mu);
-  if (resident && (n > S->slot_n || G->m > S->slot_m)) {
+  if (resident && (n > S->slot_n || G->state_bytes > S->slot_m)) {
     const int32_t new_n = n > S->slot_n ? n : S->slot_n;
-    const int64_t new_m = G->m > S->slot_m ? G->m : S->slot_m;
+    const int64_t new_m = G->state_bytes > S->slot_m ? G->state_bytes : S->slot_m;
     drain(S, lk);
     hipError_t e = hipSuccess;
     for (auto& s : S->slots)

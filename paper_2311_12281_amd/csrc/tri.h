@@ -100,9 +100,9 @@ struct TriScratch {
   int32_t* flag = nullptr;    // [1] some vertex is a core
 };
 
-// Device bytes of the layout and of one scratch.
+// Device bytes held by the layout and by one scratch.
 uint64_t tri_layout_bytes(const TriLayout& T);
-uint64_t tri_scratch_bytes(const TriLayout& T);
+uint64_t tri_scratch_bytes(const TriLayout& T, const TriScratch& S);
 
 // Builds the layout from a validated CSR on the device (h_rp: the caller's
 // offsets).  *ok = 0 with hipSuccess when the graph is outside the path's
@@ -124,7 +124,13 @@ struct TriArgs {
   const int32_t* gmu = nullptr;
 };
 
-// Kernel launches of the phases, in this order.
+// Kernel launches of the phases, in this order.  With the counts at hand, a
+// query starts with tri_init_state and tri_threshold instead of the first three.
+void tri_init_state(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* lower, int32_t* parent,
+                    int32_t* label, uint8_t* role);
+void tri_threshold(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower);
+// Frees what only the counting reads.
+void tri_drop_inputs(TriLayout& T);
 void tri_init(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* lower, int32_t* parent,
               int32_t* label, uint8_t* role);
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S);

@@ -878,8 +878,31 @@ __device__ __forceinline__ uint32_t tri_transpose(uint32_t w, int sub) {
   return tri_exchange<1>(w, sub, 0x55555555u);
 }
 
+// Similar entries of line t (half wave), counted on both endpoints.
+__device__ __forceinline__ void tri_mark(int64_t t, int sub, const TriLineInfo& L, int32_t x, int32_t dx,
+                                         int32_t closed, TriArgs& a, uint32_t* simw, int32_t* lower) {
+  if (a.gid) {
+    const int32_t g = a.gid[L.u];
+    a.p = a.gp[g];
+    a.q = a.gq[g];
+  }
+  bool sim = false;
+  if (x >= 0) {
+    const uint64_t ab = ((uint64_t)L.deg + 1) * ((uint64_t)dx + 1);
+    const uint64_t cq = (uint64_t)closed * a.q;
+    sim = cq * cq >= (a.p * a.p) * ab;
+  }
+  const uint64_t m = __ballot(sim);
+  const uint32_t word = (threadIdx.x & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
+  if (sub == 0) {
+    simw[t] = word;
+    if (word) atomicAdd(lower + L.u, (int32_t)__popc(word));
+  }
+  if (sim) atomicAdd(lower + x, 1);
+}
+
 // One line per half wave: closed counts of its entries, and with eps the
-// similar ones, which are counted on both endpoints.
+// similar ones.
 template <bool kEps>
 __global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const TriLineInfo* __restrict__ li,
                                                    const int32_t* __restrict__ deg, const int32_t* __restrict__ oc,
@@ -911,24 +934,20 @@ __global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const TriLineI
     cnt[t * kTriLine + sub] = closed;
     return;
   }
-  if (a.gid) {
-    const int32_t g = a.gid[L.u];
-    a.p = a.gp[g];
-    a.q = a.gq[g];
-  }
-  bool sim = false;
-  if (x >= 0) {
-    const uint64_t ab = ((uint64_t)L.deg + 1) * ((uint64_t)dx + 1);
-    const uint64_t cq = (uint64_t)closed * a.q;
-    sim = cq * cq >= (a.p * a.p) * ab;
-  }
-  const uint64_t m = __ballot(sim);
-  const uint32_t word = (threadIdx.x & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
-  if (sub == 0) {
-    simw[t] = word;
-    if (word) atomicAdd(lower + L.u, (int32_t)__popc(word));
-  }
-  if (sim) atomicAdd(lower + x, 1);
+  tri_mark(t, sub, L, x, dx, closed, a, simw, lower);
+}
+
+// The same from closed counts already in cnt.
+__global__ __launch_bounds__(256) void k_tri_threshold(int64_t lines, const TriLineInfo* __restrict__ li,
+                                                       const int32_t* __restrict__ deg,
+                                                       const int32_t* __restrict__ oc,
+                                                       const int32_t* __restrict__ cnt, TriArgs a,
+                                                       uint32_t* __restrict__ simw, int32_t* __restrict__ lower) {
+  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
+  if (t >= lines) return;
+  const int sub = threadIdx.x & 31;
+  const int32_t x = oc[t * kTriLine + sub] - 1;
+  tri_mark(t, sub, li[t], x, x >= 0 ? deg[x] : 0, cnt[t * kTriLine + sub], a, simw, lower);
 }
 
 // A parent as the caches have it: some ancestor, maybe not the newest.
@@ -1151,12 +1170,24 @@ hipError_t dnew(T** p, int64_t count) {
 
 uint64_t tri_layout_bytes(const TriLayout& T) {
   const uint64_t n = (uint64_t)T.n, L = (uint64_t)T.lines;
-  return 16 * n + 8 * (n + 1) + 20 * L + 6 * (L * kTriLine + 2 * kTriLine) + sizeof(TriRec) * (uint64_t)T.recs +
-         sizeof(TriJob) * (uint64_t)T.jobs + sizeof(TriWave) * (uint64_t)T.wave_rows;
+  return 16 * n + 8 * (n + 1) + 20 * L + 4 * (L + 2) * kTriLine + (T.oc16 ? 2 * (L + 2) * kTriLine : 0) +
+         (T.rec ? sizeof(TriRec) * (uint64_t)T.recs : 0) + (T.job ? sizeof(TriJob) * (uint64_t)T.jobs : 0) +
+         (T.wrow ? sizeof(TriWave) * (uint64_t)T.wave_rows : 0);
 }
 
-uint64_t tri_scratch_bytes(const TriLayout& T) {
-  return 4 * ((uint64_t)T.lines * kTriLine + (uint64_t)T.words + (uint64_t)T.lines + 1);
+uint64_t tri_scratch_bytes(const TriLayout& T, const TriScratch& S) {
+  const uint64_t L = (uint64_t)T.lines;
+  return (S.cnt ? 4 * L * kTriLine : 0) + (S.bits ? 4 * (uint64_t)T.words : 0) + (S.simw ? 4 * L : 0) + (S.flag ? 4 : 0);
+}
+
+void tri_drop_inputs(TriLayout& T) {
+  void* p[] = {T.oc16, T.rec, T.job, T.wrow};
+  for (void* x : p)
+    if (x) (void)hipFree(x);
+  T.oc16 = nullptr;
+  T.rec = nullptr;
+  T.job = nullptr;
+  T.wrow = nullptr;
 }
 
 void tri_release(TriLayout& T) {
@@ -1342,6 +1373,17 @@ void tri_init(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* l
   const int64_t ncnt4 = T.lines * (kTriLine / 4);
   const unsigned grid = (unsigned)std::min<int64_t>(grid_for(std::max<int64_t>(ncnt4, T.n), 256), 8192);
   k_tri_init<<<grid, 256, 0, s>>>(ncnt4, reinterpret_cast<int4*>(S.cnt), T.n, lower, parent, label, role, S.flag);
+}
+
+void tri_init_state(hipStream_t s, const TriLayout& T, const TriScratch& S, int32_t* lower, int32_t* parent,
+                    int32_t* label, uint8_t* role) {
+  const unsigned grid = (unsigned)std::min<int64_t>(grid_for(T.n, 256), 8192);
+  k_tri_init<<<grid, 256, 0, s>>>(0, nullptr, T.n, lower, parent, label, role, S.flag);
+}
+
+void tri_threshold(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower) {
+  if (T.lines > 0)
+    k_tri_threshold<<<grid_for(T.lines, 8), 256, 0, s>>>(T.lines, T.li, T.deg, T.oc, S.cnt, a, S.simw, lower);
 }
 
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
