@@ -620,7 +620,7 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
   if (nnz > 0)
     CTRY(hipMemcpyAsync(g->d_ci, col_idx, sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice, g->stream),
          "copy col_idx");
-  CTRY(check_csr(g->stream, n, nnz, g->d_rp, g->d_ci, g->opts.validate, &d_src, &lay), "layout");
+  CTRY(check_csr(g->stream, n, nnz, g->d_rp, g->d_ci, g->opts.validate, &lay), "layout");
   // The triangle path, unless the options ask for the exhaustive or the
   // binary-search kernels, or bound the device memory (its scratch grows with
   // the pairs of row entries, which scan_graph_footprint cannot know).
@@ -645,8 +645,6 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
     CTRY(e, "triangle layout");
   }
   if (g->has_tri) {
-    (void)hipFree(d_src);
-    d_src = nullptr;
     g->max_degree = lay.max_degree;
     if (g->opts.validate && g->m * 2 != nnz) {
       rc = fail(SCAN_E_GRAPH, "edge count %lld does not match nnz/2", (long long)g->m);
@@ -662,6 +660,7 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
     *out = g;
     return SCAN_OK;
   }
+  CTRY(check_reverse(g->stream, n, nnz, g->d_rp, g->d_ci, g->opts.validate, &d_src, &lay), "layout");
   CTRY(build_layout(g->stream, n, nnz, row_ptr, col_idx, g->d_rp, g->d_ci, d_src, &g->d_edges, &jobs, &lay),
        "layout");
   (void)hipFree(d_src);

@@ -7,6 +7,7 @@
 #include "scan_internal.h"
 
 #include <algorithm>
+#include <cstring>
 #include <thread>
 #include <vector>
 
@@ -27,25 +28,22 @@ enum : int {
 
 __global__ void k_check_offsets(int32_t n, int64_t nnz, const int64_t* rp, int32_t* err,
                                 int32_t* maxdeg) {
-  int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u > n) return;
-  if (u == 0 && rp[0] != 0) atomicOr(err, ERR_OFFSETS);
-  if (u == n && rp[n] != nnz) atomicOr(err, ERR_OFFSETS);
-  if (u < n) {
-    int64_t d = rp[u + 1] - rp[u];
-    if (d < 0 || rp[u] < 0 || rp[u + 1] > nnz) atomicOr(err, ERR_OFFSETS);
-    else if (d > 0) atomicMax(maxdeg, (int32_t)(d > 0x7fffffff ? 0x7fffffff : d));
+  // one atomic per wave of a grid-stride loop: a wave per 64 vertices queued on
+  // the one address
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  int32_t e = 0, most = 0;
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u <= n; u += stride) {
+    if (u == 0 && rp[0] != 0) e |= ERR_OFFSETS;
+    if (u == n && rp[n] != nnz) e |= ERR_OFFSETS;
+    if (u < n) {
+      int64_t d = rp[u + 1] - rp[u];
+      if (d < 0 || rp[u] < 0 || rp[u + 1] > nnz) e |= ERR_OFFSETS;
+      else most = max(most, (int32_t)(d > 0x7fffffff ? 0x7fffffff : d));
+    }
   }
-}
-
-// Row id of every arc (rows are processed one wave per vertex).
-__global__ void k_arc_rows(int32_t n, const int64_t* rp, int32_t* src) {
-  const int lane = threadIdx.x & 63;
-  int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t u = w; u < n; u += nw) {
-    for (int64_t i = rp[u] + lane; i < rp[u + 1]; i += 64) src[i] = (int32_t)u;
-  }
+  for (int d = 32; d >= 1; d >>= 1) most = max(most, __shfl_xor(most, d, 64));
+  if (e) atomicOr(err, e);
+  if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(maxdeg, most);
 }
 
 __device__ inline bool row_contains(const int32_t* row, int64_t len, int32_t x) {
@@ -59,18 +57,70 @@ __device__ inline bool row_contains(const int32_t* row, int64_t len, int32_t x) 
   return lo < len && row[lo] == x;
 }
 
-__global__ void k_check_arcs(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci,
-                             const int32_t* src, int32_t* err, int full) {
+// Adds the sum of c over the block (256 threads, all of them) to *to.
+__device__ __forceinline__ void add_block(unsigned long long c, unsigned long long* to) {
+  __shared__ unsigned long long part[4];
+  for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    c = part[0] + part[1] + part[2] + part[3];
+    if (c) atomicAdd(to, c);
+  }
+}
+
+// Arcs without their rows: ids in range, and the places where an id does not
+// exceed the one before it.  In a sorted CSR these are the row starts that
+// k_check_row_starts counts, so one load per arc does, however long the rows.
+__global__ __launch_bounds__(256) void k_check_values(int32_t n, int64_t nnz, const int32_t* ci, int32_t* err,
+                                                      unsigned long long* descents) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  int32_t e = 0;
+  unsigned long long c = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += stride) {
+    const int32_t v = ci[i];
+    if (v < 0 || v >= n) e |= ERR_RANGE;
+    if (i > 0 && ci[i - 1] >= v) ++c;
+  }
+  if (e) atomicOr(err, e);
+  add_block(c, descents);
+}
+
+// Descents at row starts, and self-loops (looked up: rows are sorted unless the
+// descents tell otherwise).
+__global__ __launch_bounds__(256) void k_check_row_starts(int32_t n, const int64_t* rp, const int32_t* ci, int32_t* err,
+                                                          unsigned long long* starts) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  int32_t e = 0;
+  unsigned long long c = 0;
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
+    const int64_t b = rp[u], len = rp[u + 1] - b;
+    if (len == 0) continue;
+    if (b > 0 && ci[b - 1] >= ci[b]) ++c;
+    if (row_contains(ci + b, len, (int32_t)u)) e |= ERR_SELFLOOP;
+  }
+  if (e) atomicOr(err, e);
+  add_block(c, starts);
+}
+
+// Row id of every arc (rows are processed one wave per vertex).
+__global__ void k_arc_rows(int32_t n, const int64_t* rp, int32_t* src) {
+  const int lane = threadIdx.x & 63;
+  int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  for (int64_t u = w; u < n; u += nw) {
+    for (int64_t i = rp[u] + lane; i < rp[u + 1]; i += 64) src[i] = (int32_t)u;
+  }
+}
+
+// Every arc's reverse arc is there.
+__global__ void k_check_arcs(int64_t nnz, const int64_t* rp, const int32_t* ci, const int32_t* src, int32_t* err) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int32_t e = 0;
   for (; i < nnz; i += stride) {
     const int32_t u = src[i];
     const int32_t v = ci[i];
-    if (v < 0 || v >= n) { e |= ERR_RANGE; continue; }
-    if (!full) continue;
-    if (v == u) e |= ERR_SELFLOOP;
-    if (i > rp[u] && ci[i - 1] >= v) e |= ERR_ORDER;
     if (!row_contains(ci + rp[v], rp[v + 1] - rp[v], u)) e |= ERR_ASYM;
   }
   if (e) atomicOr(err, e);
@@ -296,29 +346,60 @@ hipError_t build_ranked_rows(hipStream_t s, int32_t n, int64_t nnz, const int64_
 
 #define LTRY(x) do { e = (x); if (e != hipSuccess) goto done; } while (0)
 hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
-                     int32_t** d_src_out, LayoutResult* out) {
+                     LayoutResult* out) {
   hipError_t e = hipSuccess;
-  int32_t* d_flags = nullptr;  // [0] = error bits, [1] = max degree
-  int32_t* d_src = nullptr;
-  int32_t h_flags[2] = {0, 0};
-  *d_src_out = nullptr;
+  // [0] = error bits, [1] = max degree, then 64-bit: descents, descents at row starts
+  int32_t* d_flags = nullptr;
+  int32_t h_flags[6] = {0, 0, 0, 0, 0, 0};
+  unsigned long long h_desc[2];
+  unsigned long long* d_desc = nullptr;
   out->error = 0;
   out->max_degree = 0;
-  LTRY(hipMalloc((void**)&d_flags, sizeof(int32_t) * 2));
-  LTRY(hipMemsetAsync(d_flags, 0, sizeof(int32_t) * 2, s));
-  k_check_offsets<<<(unsigned)((n + 1 + 255) / 256), 256, 0, s>>>(n, nnz, d_rp, d_flags, d_flags + 1);
+  LTRY(hipMalloc((void**)&d_flags, sizeof(h_flags)));
+  LTRY(hipMemsetAsync(d_flags, 0, sizeof(h_flags), s));
+  d_desc = reinterpret_cast<unsigned long long*>(d_flags + 2);
+  k_check_offsets<<<(unsigned)std::min<int64_t>(((int64_t)n + 1 + 255) / 256, 512), 256, 0, s>>>(n, nnz, d_rp, d_flags, d_flags + 1);
   LTRY(hipGetLastError());
   LTRY(hipMemcpyAsync(h_flags, d_flags, sizeof(h_flags), hipMemcpyDeviceToHost, s));
   LTRY(hipStreamSynchronize(s));
   out->error = h_flags[0];
   out->max_degree = h_flags[1];
   if (h_flags[0] != 0 || nnz == 0) goto done;  // offsets unusable, or no edges
+  // The id-range check always runs (every later kernel indexes rp by ids);
+  // order is checked when validation is on.
+  k_check_values<<<(unsigned)std::min<int64_t>((nnz + 1023) / 1024, 2048), 256, 0, s>>>(n, nnz, d_ci, d_flags, d_desc);
+  LTRY(hipGetLastError());
+  if (validate) {
+    k_check_row_starts<<<(unsigned)std::min<int64_t>(((int64_t)n + 255) / 256, 1024), 256, 0, s>>>(n, d_rp, d_ci, d_flags,
+                                                                                                  d_desc + 1);
+    LTRY(hipGetLastError());
+  }
+  LTRY(hipMemcpyAsync(h_flags, d_flags, sizeof(h_flags), hipMemcpyDeviceToHost, s));
+  LTRY(hipStreamSynchronize(s));
+  out->error = h_flags[0];
+  memcpy(h_desc, h_flags + 2, sizeof(h_desc));
+  if (!validate) out->error &= ERR_RANGE;
+  else if (h_desc[0] != h_desc[1]) out->error |= ERR_ORDER;
+done:
+  hipStreamSynchronize(s);
+  if (d_flags) hipFree(d_flags);
+  return e;
+}
+
+hipError_t check_reverse(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
+                         int32_t** d_src_out, LayoutResult* out) {
+  hipError_t e = hipSuccess;
+  int32_t* d_flags = nullptr;
+  int32_t* d_src = nullptr;
+  int32_t h_flags[1] = {0};
+  *d_src_out = nullptr;
+  if (out->error || nnz == 0) return hipSuccess;
+  LTRY(hipMalloc((void**)&d_flags, sizeof(int32_t)));
+  LTRY(hipMemsetAsync(d_flags, 0, sizeof(int32_t), s));
   LTRY(hipMalloc((void**)&d_src, sizeof(int32_t) * nnz));
   k_arc_rows<<<4096, 256, 0, s>>>(n, d_rp, d_src);
   LTRY(hipGetLastError());
-  // The id-range check always runs (every later kernel indexes rp by ids);
-  // order and symmetry are checked when validation is on.
-  k_check_arcs<<<8192, 256, 0, s>>>(n, nnz, d_rp, d_ci, d_src, d_flags, validate);
+  if (validate) k_check_arcs<<<8192, 256, 0, s>>>(nnz, d_rp, d_ci, d_src, d_flags);
   LTRY(hipGetLastError());
   LTRY(hipMemcpyAsync(h_flags, d_flags, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   LTRY(hipStreamSynchronize(s));

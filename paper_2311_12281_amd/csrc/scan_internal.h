@@ -274,10 +274,14 @@ struct LayoutResult {
   int32_t max_degree;
   int32_t error;  // 0 or bit mask of validation failures
 };
-// Validates the CSR (out->error, out->max_degree); *d_src: the row of every
-// arc, allocated here (null when the CSR is rejected or has no arcs).
+// Validates the CSR but for the reverse arcs (out->error, out->max_degree).
 hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
-                     int32_t** d_src, LayoutResult* out);
+                     LayoutResult* out);
+// Validates the reverse arcs (the triangle layout finds them while it is built
+// and does without); *d_src: the row of every arc, allocated here (null when
+// the CSR is rejected or has no arcs).
+hipError_t check_reverse(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
+                         int32_t** d_src, LayoutResult* out);
 // Exclusive prefix sum of n int64 on the device (synchronises for more than one block).
 hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n);
 // Builds the oriented, bucketed edge list and the job

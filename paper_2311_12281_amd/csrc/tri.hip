@@ -44,32 +44,42 @@ __host__ __device__ inline uint32_t tri_word(uint32_t W, uint32_t i) {
 
 __device__ __forceinline__ uint64_t lanes_below(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
 
-// deg[h], and the length of every row; one wave per vertex, or (h < nbig, the
-// highest degrees) one block.
-__global__ __launch_bounds__(1024) void k_row_len_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
-                                                        const int32_t* hof, const int32_t* idof, int32_t* deg,
-                                                        int32_t* row) {
+// Rows above kTriBigRow arcs are taken by a block per kTriBigChunk of them, which
+// add up or append through the row's counters (one block per row walked the
+// longest one, 163,089 arcs on R-MAT scale 22, 160 dependent rounds long); the
+// others by a wave.
+struct BigChunk {
+  int32_t h, id;
+  int64_t begin, end;  // arcs
+};
+constexpr int64_t kTriBigRow = 2048;
+constexpr int64_t kTriBigChunk = 2048;
+
+__global__ __launch_bounds__(256) void k_row_len_block(const BigChunk* chunks, const int32_t* ci, const int32_t* hof,
+                                                       int32_t* row) {
   __shared__ int32_t sum;
-  const int32_t h = blockIdx.x;
-  if (h >= nbig) return;
-  const int32_t x = idof[h];
-  const int64_t b = rp[x], e = rp[x + 1];
+  const BigChunk C = chunks[blockIdx.x];
   if (threadIdx.x == 0) sum = 0;
   __syncthreads();
   int32_t c = 0;
-  for (int64_t k = b + threadIdx.x; k < e; k += 1024) c += hof[ci[k]] < h ? 1 : 0;
+  for (int64_t k = C.begin + threadIdx.x; k < C.end; k += 256) c += hof[ci[k]] < C.h ? 1 : 0;
   c = (int32_t)wave_sum((unsigned long long)c);
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(&sum, c);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    deg[h] = (int32_t)(e - b);
-    row[h] = sum;
-  }
+  if (threadIdx.x == 0 && sum) atomicAdd(row + C.h, sum);
+}
+
+// Degrees by h; the length of the rows above kTriBigRow starts at 0.
+__global__ void k_degrees(int32_t n, const int64_t* rp, const int32_t* idof, int32_t* deg, int32_t* row) {
+  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (h >= n) return;
+  const int32_t x = idof[h];
+  deg[h] = (int32_t)(rp[x + 1] - rp[x]);
+  row[h] = 0;
 }
 
 __global__ __launch_bounds__(256) void k_row_len_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
-                                                      const int32_t* hof, const int32_t* idof, int32_t* deg,
-                                                      int32_t* row) {
+                                                      const int32_t* hof, const int32_t* idof, int32_t* row) {
   const int lane = threadIdx.x & 63;
   const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
   if (h >= n) return;
@@ -78,10 +88,7 @@ __global__ __launch_bounds__(256) void k_row_len_wave(int32_t h0, int32_t n, con
   int32_t c = 0;
   for (int64_t k = b + lane; k < e; k += 64) c += hof[ci[k]] < h ? 1 : 0;
   c = (int32_t)wave_sum((unsigned long long)c);
-  if (lane == 0) {
-    deg[h] = (int32_t)(e - b);
-    row[h] = c;
-  }
+  if (lane == 0) row[h] = c;
 }
 
 // Room for the records of every vertex, from its in-edges' rows (a record's
@@ -93,20 +100,16 @@ __device__ __forceinline__ void tri_room(int32_t D, unsigned long long lines, un
   *nin = (int64_t)(w ? lines : recs);
 }
 
-__global__ __launch_bounds__(1024) void k_in_room_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
-                                                        const int32_t* hof, const int32_t* idof, const int32_t* row,
-                                                        int64_t* nin, uint8_t* wcls) {
+__global__ __launch_bounds__(256) void k_in_room_block(const BigChunk* chunks, const int32_t* ci, const int32_t* hof,
+                                                       const int32_t* row, unsigned long long* room) {
   __shared__ unsigned long long sum, sumr;
-  const int32_t h = blockIdx.x;
-  if (h >= nbig) return;
-  const int32_t x = idof[h];
-  const int64_t b = rp[x], e = rp[x + 1];
+  const BigChunk C = chunks[blockIdx.x];
   if (threadIdx.x == 0) sum = sumr = 0;
   __syncthreads();
   unsigned long long c = 0, r = 0;
-  for (int64_t k = b + threadIdx.x; k < e; k += 1024) {
+  for (int64_t k = C.begin + threadIdx.x; k < C.end; k += 256) {
     const int32_t u = hof[ci[k]];
-    const uint32_t W = u > h && row[u] > 1 ? tri_lines(row[u]) : 0;
+    const uint32_t W = u > C.h && row[u] > 1 ? tri_lines(row[u]) : 0;
     c += W;
     r += (W + kTriRecLines - 1) / kTriRecLines;
   }
@@ -117,7 +120,17 @@ __global__ __launch_bounds__(1024) void k_in_room_block(int32_t nbig, const int6
     atomicAdd(&sumr, r);
   }
   __syncthreads();
-  if (threadIdx.x == 0) tri_room(row[h], sum, sumr, nin + h, wcls + h);
+  if (threadIdx.x == 0 && sum) {
+    atomicAdd(room + 2 * C.h, sum);
+    atomicAdd(room + 2 * C.h + 1, sumr);
+  }
+}
+
+// room[2 h], room[2 h + 1]: lines and records of the rows above kTriBigRow.
+__global__ void k_in_room_big(int32_t nbig, const int32_t* row, const unsigned long long* room, int64_t* nin,
+                              uint8_t* wcls) {
+  const int32_t h = blockIdx.x * blockDim.x + threadIdx.x;
+  if (h < nbig) tri_room(row[h], room[2 * h], room[2 * h + 1], nin + h, wcls + h);
 }
 
 __global__ __launch_bounds__(256) void k_in_room_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
@@ -141,20 +154,26 @@ __global__ __launch_bounds__(256) void k_in_room_wave(int32_t h0, int32_t n, con
 }
 
 // Per vertex: lines and bit words of its row; all entries, and the longest row.
+// (A grid-stride loop: one atomic per wave of 64 vertices queued on one address.)
 __global__ void k_row_sizes(int32_t n, const int32_t* row, int64_t* nline, int64_t* nword, unsigned long long* entries,
                             int32_t* max_row) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int32_t D = h < n ? row[h] : 0;
-  const uint32_t W = tri_lines(D);
-  if (h <= n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  unsigned long long all = 0;
+  int32_t m = 0;
+  for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h <= n; h += stride) {
+    const int32_t D = h < n ? row[h] : 0;
+    const uint32_t W = tri_lines(D);
     nline[h] = W;
     nword[h] = D <= kTriMaxRow ? tri_word(W, (uint32_t)D) : 0;
+    all += (unsigned long long)D;
+    m = max(m, D);
   }
-  const unsigned long long all = wave_sum((unsigned long long)D);
-  if ((threadIdx.x & 63) == 0 && all) atomicAdd(entries, all);
-  int32_t m = D;
+  all = wave_sum(all);
   for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d, 64));
-  if ((threadIdx.x & 63) == 0 && m > 0) atomicMax(max_row, m);
+  if ((threadIdx.x & 63) == 0) {
+    if (all) atomicAdd(entries, all);
+    if (m > 0) atomicMax(max_row, m);
+  }
 }
 
 __global__ void k_narrow(int32_t n, const int64_t* a, const int64_t* b, uint32_t* x, uint32_t* y) {
@@ -164,31 +183,34 @@ __global__ void k_narrow(int32_t n, const int64_t* a, const int64_t* b, uint32_t
   y[h] = (uint32_t)b[h];
 }
 
-// Entries of every row, in the order of the CSR (sorted afterwards).
-__global__ __launch_bounds__(1024) void k_row_fill_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
-                                                         const int32_t* hof, const int32_t* idof,
-                                                         const uint32_t* oline, const int32_t* row, int32_t* oc) {
-  __shared__ int32_t at;
-  const int32_t h = blockIdx.x;
-  if (h >= nbig) return;
+// Entries of every row (sorted afterwards); at[h] counts those of the rows above
+// kTriBigRow.
+__global__ __launch_bounds__(256) void k_row_fill_block(const BigChunk* chunks, const int32_t* ci, const int32_t* hof,
+                                                        const uint32_t* oline, const int32_t* row, uint32_t* at,
+                                                        int32_t* oc) {
+  const BigChunk C = chunks[blockIdx.x];
   const int lane = threadIdx.x & 63;
-  const int32_t x = idof[h], D = row[h];
-  const int64_t b = rp[x], e = rp[x + 1];
-  int32_t* out = oc + (int64_t)oline[h] * kTriLine;
-  if (threadIdx.x == 0) at = 0;
-  __syncthreads();
-  for (int64_t k0 = b; k0 < e; k0 += 1024) {
+  const int32_t D = row[C.h];
+  int32_t* out = oc + (int64_t)oline[C.h] * kTriLine;
+  for (int64_t k0 = C.begin; k0 < C.end; k0 += 256) {
     const int64_t k = k0 + threadIdx.x;
-    const int32_t y = k < e ? hof[ci[k]] : INT_MAX;
-    const bool keep = y < h;
+    const int32_t y = k < C.end ? hof[ci[k]] : INT_MAX;
+    const bool keep = y < C.h;
     const uint64_t mask = __ballot(keep);
-    int32_t base = 0;
-    if (lane == 0 && mask) base = atomicAdd(&at, (int32_t)__popcll(mask));
+    uint32_t base = 0;
+    if (lane == 0 && mask) base = atomicAdd(at + C.h, (uint32_t)__popcll(mask));
     base = __shfl(base, 0, 64);
-    const int32_t p = base + (int32_t)__popcll(mask & lanes_below(lane));
+    const int32_t p = (int32_t)(base + (uint32_t)__popcll(mask & lanes_below(lane)));
     if (keep && p < D) out[p] = y + 1;
   }
-  for (int32_t p = D + threadIdx.x; p < (int32_t)tri_lines(D) * kTriLine; p += 1024) out[p] = 0;
+}
+
+// Padding of the rows above kTriBigRow.
+__global__ void k_row_pad(int32_t nbig, const uint32_t* oline, const int32_t* row, int32_t* oc) {
+  const int32_t h = (blockIdx.x * blockDim.x + threadIdx.x) >> 5;
+  if (h >= nbig) return;
+  const int32_t D = row[h], p = D + (int32_t)(threadIdx.x & 31);
+  if (p < (int32_t)tri_lines(D) * kTriLine) oc[(int64_t)oline[h] * kTriLine + p] = 0;
 }
 
 __global__ __launch_bounds__(256) void k_row_fill_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
@@ -310,11 +332,12 @@ __device__ __forceinline__ int32_t tri_find(const int32_t* r, int32_t D, int32_t
 }
 
 __device__ __forceinline__ TriRec tri_rec(int32_t u, int32_t v, const uint32_t* oline, const uint32_t* wbase,
-                                          const int32_t* row, const int32_t* oc) {
+                                          const int32_t* row, const int32_t* oc, bool& missing) {
   TriRec r{};
   const int32_t D = row[u];
   const uint32_t l0 = oline[u];
   const int32_t i = tri_find(oc + (int64_t)l0 * kTriLine, D, v);
+  missing = missing || i < 0;  // no reverse arc
   if (i < 0 || i == D - 1) return r;
   const uint32_t W = tri_lines(D);
   r.line = l0 + ((uint32_t)i >> 5);
@@ -344,53 +367,39 @@ __device__ __forceinline__ void tri_put_recs(TriRec r, uint32_t cut, TriRec* out
 }
 
 // In-edge records of every vertex: their number and the words they hold.
-__global__ __launch_bounds__(1024) void k_recs_block(int32_t nbig, const int64_t* rp, const int32_t* ci,
-                                                     const int32_t* hof, const int32_t* idof, const uint32_t* oline,
-                                                     const uint32_t* wbase, const int32_t* row, const int32_t* oc,
-                                                     const int64_t* inoff, const uint8_t* wcls, TriRec* rec, uint32_t* inlen,
-                                                     int64_t* steps) {
-  __shared__ uint32_t at;
-  __shared__ unsigned long long sum;
-  const int32_t h = blockIdx.x;
-  if (h >= nbig) return;
+__global__ __launch_bounds__(256) void k_recs_block(const BigChunk* chunks, const int32_t* ci, const int32_t* hof,
+                                                    const uint32_t* oline, const uint32_t* wbase, const int32_t* row,
+                                                    const int32_t* oc, const int64_t* inoff, const uint8_t* wcls,
+                                                    TriRec* rec, uint32_t* inlen, int64_t* steps, int32_t* asym) {
+  const BigChunk C = chunks[blockIdx.x];
   const int lane = threadIdx.x & 63;
-  const int32_t x = idof[h];
-  const int64_t b = rp[x], e = rp[x + 1];
-  const uint32_t rn = (uint32_t)(inoff[h + 1] - inoff[h]);
-  TriRec* out = rec + inoff[h];
-  const uint32_t cut = wcls[h] ? 1 : kTriRecLines;
-  if (threadIdx.x == 0) {
-    at = 0;
-    sum = 0;
-  }
-  __syncthreads();
+  const uint32_t rn = (uint32_t)(inoff[C.h + 1] - inoff[C.h]);
+  TriRec* out = rec + inoff[C.h];
+  const uint32_t cut = wcls[C.h] ? 1 : kTriRecLines;
   unsigned long long st = 0;
-  for (int64_t k0 = b; k0 < e; k0 += 1024) {
+  bool missing = false;
+  for (int64_t k0 = C.begin; k0 < C.end; k0 += 256) {
     const int64_t k = k0 + threadIdx.x;
-    const int32_t u = k < e ? hof[ci[k]] : -1;
-    const TriRec r = u > h ? tri_rec(u, h, oline, wbase, row, oc) : TriRec{};
+    const int32_t u = k < C.end ? hof[ci[k]] : -1;
+    const TriRec r = u > C.h ? tri_rec(u, C.h, oline, wbase, row, oc, missing) : TriRec{};
     const uint32_t c = (r.nw + cut - 1) / cut;
     const uint32_t incl = wave_scan(c, lane), all = __shfl(incl, 63, 64);
     uint32_t base = 0;
-    if (lane == 0 && all) base = atomicAdd(&at, all);
+    if (lane == 0 && all) base = atomicAdd(inlen + C.h, all);
     base = __shfl(base, 0, 64);
     tri_put_recs(r, cut, out, base + incl - c, rn);
     st += r.nw;
   }
   st = wave_sum(st);
-  if (lane == 0 && st) atomicAdd(&sum, st);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    inlen[h] = min(at, rn);
-    steps[h] = (int64_t)sum;
-  }
+  if (lane == 0 && st) atomicAdd(reinterpret_cast<unsigned long long*>(steps + C.h), st);
+  if (__ballot(missing) && lane == 0) *asym = 1;
 }
 
 __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                    const int32_t* hof, const int32_t* idof, const uint32_t* oline,
                                                    const uint32_t* wbase, const int32_t* row, const int32_t* oc,
                                                    const int64_t* inoff, const uint8_t* wcls, TriRec* rec, uint32_t* inlen,
-                                                   int64_t* steps) {
+                                                   int64_t* steps, int32_t* asym) {
   const int lane = threadIdx.x & 63;
   const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
   if (h >= n) return;
@@ -400,11 +409,12 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
   TriRec* out = rec + inoff[h];
   const uint32_t cut = wcls[h] ? 1 : kTriRecLines;
   uint32_t at = 0;
+  bool missing = false;
   unsigned long long st = 0;
   for (int64_t k0 = b; k0 < e; k0 += 64) {
     const int64_t k = k0 + lane;
     const int32_t u = k < e ? hof[ci[k]] : -1;
-    const TriRec r = u > (int32_t)h ? tri_rec(u, (int32_t)h, oline, wbase, row, oc) : TriRec{};
+    const TriRec r = u > (int32_t)h ? tri_rec(u, (int32_t)h, oline, wbase, row, oc, missing) : TriRec{};
     const uint32_t c = (r.nw + cut - 1) / cut;
     const uint32_t incl = wave_scan(c, lane);
     tri_put_recs(r, cut, out, at + incl - c, rn);
@@ -416,31 +426,37 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
     inlen[h] = min(at, rn);
     steps[h] = (int64_t)st;
   }
+  if (__ballot(missing) && lane == 0) *asym = 1;
 }
 
 // Work of every vertex: jobs of the block kernel, or a place in the wave
 // kernel's list; the sum of all words and the longest hash-table row.
 __global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_off, const int32_t* row,
-                             const uint8_t* wcls, const uint32_t* inlen, const int64_t* steps,
-                             int64_t* njob, int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t j = 0, w = 0;
+                             const uint8_t* wcls, const uint32_t* inlen, const int64_t* steps, int64_t* njob,
+                             int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   unsigned long long st = 0;
-  if (h < n && steps[h] > 0) {
-    st = (unsigned long long)steps[h];
-    if (wcls[h]) {
-      w = 1;
-    } else {
-      j = (inlen[h] + kTriJob - 1) / kTriJob;
-      if (h - tri_base(gid, vtx_off, h) >= kTriShort) atomicMax(max_hash, row[h]);
+  int32_t most = 0;
+  for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h <= n; h += stride) {
+    int64_t j = 0, w = 0;
+    if (h < n && steps[h] > 0) {
+      st += (unsigned long long)steps[h];
+      if (wcls[h]) {
+        w = 1;
+      } else {
+        j = (inlen[h] + kTriJob - 1) / kTriJob;
+        if (h - tri_base(gid, vtx_off, h) >= kTriShort) most = max(most, row[h]);
+      }
     }
-  }
-  if (h <= n) {
     njob[h] = j;
     nwave[h] = w;
   }
   st = wave_sum(st);
-  if ((threadIdx.x & 63) == 0 && st) atomicAdd(total, st);
+  for (int d = 32; d >= 1; d >>= 1) most = max(most, __shfl_xor(most, d, 64));
+  if ((threadIdx.x & 63) == 0) {
+    if (st) atomicAdd(total, st);
+    if (most > 0) atomicMax(max_hash, most);
+  }
 }
 
 __global__ void k_job_fill(int32_t n, const int64_t* inoff, const uint32_t* inlen, const uint32_t* oline, const int32_t* row,
@@ -1224,6 +1240,10 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   uint32_t* inlen = nullptr;
   uint8_t* wcls = nullptr;
   int32_t *ctl = nullptr, *longer = nullptr;
+  BigChunk* big = nullptr;
+  std::vector<BigChunk> chunks;
+  unsigned long long* room = nullptr;
+  unsigned nchunk = 0;
   unsigned long long* sums = nullptr;
   int64_t tot[3] = {0, 0, 0};
   int32_t h_ctl[4] = {0, 0, 0, 0};
@@ -1258,13 +1278,25 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
         const int32_t t = first[(size_t)d];
         first[(size_t)d] = acc;
         acc += t;
-        if (d > 2048 && !groups) nbig = acc;  // (of a batch, waves take the long rows too)
+        if (d > kTriBigRow && !groups) nbig = acc;  // (of a batch, waves take the long rows too)
       }
       for (int32_t v = v0; v < v1; ++v) {
         const int32_t h = first[(size_t)(h_rp[v + 1] - h_rp[v])]++;
         hof[(size_t)v] = h;
         idof[(size_t)h] = v;
       }
+    }
+    for (int32_t h = 0; h < nbig; ++h) {
+      const int32_t v = idof[(size_t)h];
+      for (int64_t k = h_rp[v]; k < h_rp[v + 1]; k += kTriBigChunk)
+        chunks.push_back(BigChunk{h, v, k, std::min(k + kTriBigChunk, h_rp[v + 1])});
+    }
+    nchunk = (unsigned)chunks.size();
+    if (nchunk) {
+      TTRY(dnew(&big, nchunk));
+      TTRY(hipMemcpyAsync(big, chunks.data(), sizeof(BigChunk) * nchunk, hipMemcpyHostToDevice, s));
+      TTRY(dnew(&room, 2 * (int64_t)nbig));
+      TTRY(hipMemsetAsync(room, 0, 16 * (size_t)nbig, s));
     }
     TTRY(dnew(&T.hof, n));
     TTRY(dnew(&T.idof, n));
@@ -1274,12 +1306,13 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   }
   TTRY(dnew(&T.deg, n));
   TTRY(dnew(&T.row, n));
-  TTRY(dnew(&ctl, 4));   // longest row, rows for the block sort, longest hash row
+  TTRY(dnew(&ctl, 4));   // longest row, rows for the block sort, longest hash row, a reverse arc is missing
   TTRY(dnew(&sums, 2 + kNumBuckets));  // words, edges per bucket, entries
   TTRY(hipMemsetAsync(ctl, 0, 16, s));
   TTRY(hipMemsetAsync(sums, 0, sizeof(h_sums), s));
-  if (nbig > 0) k_row_len_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.deg, T.row);
-  if (n > nbig) k_row_len_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.deg, T.row);
+  k_degrees<<<gv, 256, 0, s>>>(n, d_rp, T.idof, T.deg, T.row);
+  if (nchunk) k_row_len_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.row);
+  if (n > nbig) k_row_len_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row);
   TTRY(hipGetLastError());
   TTRY(dnew(&nline, (int64_t)n + 1));
   TTRY(dnew(&nword, (int64_t)n + 1));
@@ -1289,8 +1322,11 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(dnew(&at2, (int64_t)n + 1));
   TTRY(dnew(&inlen, n));
   TTRY(dnew(&wcls, n));
-  k_row_sizes<<<gv, 256, 0, s>>>(n, T.row, nline, nword, sums + 1 + kNumBuckets, ctl);
-  if (nbig > 0) k_in_room_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
+  k_row_sizes<<<std::min(gv, 512u), 256, 0, s>>>(n, T.row, nline, nword, sums + 1 + kNumBuckets, ctl);
+  if (nchunk) {
+    k_in_room_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.row, room);
+    k_in_room_big<<<grid_for(nbig, 256), 256, 0, s>>>(nbig, T.row, room, nin, wcls);
+  }
   if (n > nbig) 
     k_in_room_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
   TTRY(hipMemsetAsync(nin + n, 0, 8, s));
@@ -1321,7 +1357,11 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(dnew(&T.oc, (T.lines + 2) * kTriLine));
   TTRY(dnew(&T.oc16, (T.lines + 2) * kTriLine));
   TTRY(dnew(&longer, n));
-  if (nbig > 0) k_row_fill_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
+  TTRY(hipMemsetAsync(inlen, 0, 4 * (size_t)n, s));  // here: entries of the big rows so far
+  if (nchunk) {
+    k_row_fill_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.oline, T.row, inlen, T.oc);
+    k_row_pad<<<grid_for(nbig, 8), 256, 0, s>>>(nbig, T.oline, T.row, T.oc);
+  }
   if (n > nbig)
     k_row_fill_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
   k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.wbase, T.deg, T.gid, T.vtx_off, T.oc, T.oc16,
@@ -1329,13 +1369,15 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16);
   TTRY(hipGetLastError());
   TTRY(dnew(&T.rec, T.recs));
-  if (nbig > 0)
-    k_recs_block<<<nbig, 1024, 0, s>>>(nbig, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row, T.oc, at2, wcls,
-                                       T.rec, inlen, nin);
+  TTRY(hipMemsetAsync(inlen, 0, 4 * (size_t)n, s));
+  TTRY(hipMemsetAsync(nin, 0, 8 * (size_t)n, s));  // from here on: words of every vertex's in-edges
+  if (nchunk)
+    k_recs_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.oline, T.wbase, T.row, T.oc, at2, wcls, T.rec, inlen, nin,
+                                        ctl + 3);
   if (n > nbig)
     k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
-                                                      T.oc, at2, wcls, T.rec, inlen, nin);
-  k_job_counts<<<gv, 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, sums, ctl + 2);
+                                                      T.oc, at2, wcls, T.rec, inlen, nin, ctl + 3);
+  k_job_counts<<<std::min(gv, 512u), 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, sums, ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
   TTRY(hipGetLastError());
@@ -1346,6 +1388,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(hipMemcpyAsync(h_ctl, ctl, 16, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(h_sums, sums, sizeof(h_sums), hipMemcpyDeviceToHost, s));
   TTRY(hipStreamSynchronize(s));
+  if (h_ctl[3]) goto done;  // not a symmetric CSR
   T.jobs = tot[0];
   T.wave_rows = tot[1];
   T.max_hash_row = h_ctl[2];
@@ -1360,7 +1403,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   *ok = 1;
 done:
   (void)hipStreamSynchronize(s);
-  void* tmp[] = {nline, nword, nin, at0, at1, at2, inlen, wcls, ctl, longer, sums};
+  void* tmp[] = {nline, nword, nin, at0, at1, at2, inlen, wcls, ctl, longer, sums, big, room};
   for (void* x : tmp)
     if (x) (void)hipFree(x);
   if (!*ok) tri_release(T);
