@@ -234,25 +234,23 @@ __global__ void k_scan_add(int64_t* data, int64_t n, const int64_t* add) {
 
 }  // namespace
 
-hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n) {
+int64_t scan_work_items(int64_t n) {
+  const int64_t nb = (n + kTile - 1) / kTile;
+  return nb <= 1 ? 0 : 2 * nb + scan_work_items(nb);
+}
+
+hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n, int64_t* work) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + kTile - 1) / kTile;
   if (nb == 1) {
     k_scan_block<<<1, kBlock, 0, s>>>(in, out, n, nullptr);
     return hipGetLastError();
   }
-  int64_t* sums = nullptr;
-  hipError_t e = hipMalloc((void**)&sums, sizeof(int64_t) * nb * 2);
+  k_scan_block<<<(unsigned)nb, kBlock, 0, s>>>(in, out, n, work);
+  const hipError_t e = exclusive_scan(s, work, work + nb, nb, work + 2 * nb);
   if (e != hipSuccess) return e;
-  k_scan_block<<<(unsigned)nb, kBlock, 0, s>>>(in, out, n, sums);
-  e = exclusive_scan(s, sums, sums + nb, nb);
-  if (e == hipSuccess) {
-    k_scan_add<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out, n, sums + nb);
-    e = hipGetLastError();
-  }
-  hipError_t f = hipStreamSynchronize(s);
-  hipFree(sums);
-  return e != hipSuccess ? e : f;
+  k_scan_add<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out, n, work + nb);
+  return hipGetLastError();
 }
 
 int64_t hub_windows(const int32_t* row, int64_t dv, std::vector<uint32_t>& out) {
@@ -429,10 +427,10 @@ hipError_t build_layout(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_
   *d_edges_out = nullptr;
   for (int k = 0; k <= kNumBuckets; ++k) out->bucket_off[k] = 0;
   if (out->error || nnz == 0) return hipSuccess;  // rejected by check_csr, or no edges
-  LTRY(hipMalloc((void**)&d_cnt, sizeof(int64_t) * ncnt * 2));
+  LTRY(hipMalloc((void**)&d_cnt, sizeof(int64_t) * (ncnt * 2 + scan_work_items(ncnt))));
   k_bucket_counts<<<(unsigned)nblocks, kBlock, 0, s>>>(nnz, d_rp, d_ci, d_src, nblocks, d_cnt);
   LTRY(hipGetLastError());
-  LTRY(exclusive_scan(s, d_cnt, d_cnt + ncnt, ncnt));
+  LTRY(exclusive_scan(s, d_cnt, d_cnt + ncnt, ncnt, d_cnt + 2 * ncnt));
   for (int k = 0; k < kNumBuckets; ++k)
     LTRY(hipMemcpyAsync(&h_off[k], d_cnt + ncnt + (int64_t)k * nblocks, sizeof(int64_t),
                         hipMemcpyDeviceToHost, s));

@@ -282,8 +282,9 @@ hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp,
 // the CSR is rejected or has no arcs).
 hipError_t check_reverse(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
                          int32_t** d_src, LayoutResult* out);
-// Exclusive prefix sum of n int64 on the device (synchronises for more than one block).
-hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n);
+// Exclusive prefix sum of n int64 on the device; work: scan_work_items(n) int64.
+hipError_t exclusive_scan(hipStream_t s, const int64_t* in, int64_t* out, int64_t n, int64_t* work);
+int64_t scan_work_items(int64_t n);
 // Builds the oriented, bucketed edge list and the job
 // table of the last bucket, both allocated here (caller frees):
 //   *d_edges: bucket_off[kNumBuckets] entries, *d_jobs: hub_jobs entries.

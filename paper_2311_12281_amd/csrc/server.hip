@@ -535,13 +535,8 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
       // are released
       if (g->has_tri) {
         tri_drop_inputs(g->tri);
-        const int32_t* keep = g->tri_s.cnt;
-        TriScratch rest = g->tri_s;
-        rest.cnt = nullptr;
-        tri_release_scratch(rest);
+        tri_drop_work(g->tri_s);
         tri_release_scratch(g->tri_na);
-        g->tri_s = TriScratch{};
-        g->tri_s.cnt = const_cast<int32_t*>(keep);
       }
       if (g->d_hci) {
         (void)hipFree(g->d_hci);

@@ -89,6 +89,7 @@ struct TriLayout {
   uint16_t* oc16 = nullptr;   // the same within the graph in 16 bits, 0xFFFF for h >= kTriShort
   TriRec* rec = nullptr;      // [recs] a vertex's records, then unused ones
   TriJob* job = nullptr;      // [jobs], hubs first
+  void* mem[4] = {};  // per vertex; rows; rows' 16-bit form and records; jobs
   TriWave* wrow = nullptr;    // [wave_rows]
 };
 
@@ -98,6 +99,7 @@ struct TriScratch {
   uint32_t* bits = nullptr;   // [words]
   uint32_t* simw = nullptr;   // [lines] similar entries
   int32_t* flag = nullptr;    // [1] some vertex is a core
+  void* mem = nullptr;        // holds bits, simw and flag
 };
 
 // Device bytes held by the layout and by one scratch.
@@ -112,6 +114,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
 void tri_release(TriLayout& T);
 hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S);
 void tri_release_scratch(TriScratch& S);
+void tri_drop_work(TriScratch& S);  // all but the counts
 
 // eps = p/q and mu of a run, or of every graph of a batch (q == 0 and no gq:
 // only the closed counts, left in S.cnt).

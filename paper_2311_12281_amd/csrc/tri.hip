@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <climits>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 namespace scan {
@@ -1177,10 +1178,30 @@ size_t tri_lds_bytes(const TriLayout& T) {
   return (b + 15) & ~(size_t)15;
 }
 
-template <typename T>
-hipError_t dnew(T** p, int64_t count) {
-  return hipMalloc((void**)p, sizeof(T) * (size_t)(count > 0 ? count : 1));
-}
+// Several arrays in one allocation (allocating and freeing some thirty of them
+// took longer than the kernels that build the layout): take() them, allocate, and
+// their pointers are set.
+class Arena {
+ public:
+  template <typename T>
+  void take(T** p, int64_t count) {
+    slots_.push_back({reinterpret_cast<void**>(p), total_});
+    total_ += (sizeof(T) * (size_t)(count > 0 ? count : 1) + 255) & ~(size_t)255;
+  }
+  hipError_t allocate(void** mem) {
+    const hipError_t e = hipMalloc(mem, total_);
+    if (e != hipSuccess) {
+      *mem = nullptr;
+      return e;
+    }
+    for (const auto& s : slots_) *s.first = static_cast<char*>(*mem) + s.second;
+    return hipSuccess;
+  }
+
+ private:
+  std::vector<std::pair<void**, size_t>> slots_;
+  size_t total_ = 0;
+};
 
 }  // namespace
 
@@ -1197,9 +1218,10 @@ uint64_t tri_scratch_bytes(const TriLayout& T, const TriScratch& S) {
 }
 
 void tri_drop_inputs(TriLayout& T) {
-  void* p[] = {T.oc16, T.rec, T.job, T.wrow};
-  for (void* x : p)
-    if (x) (void)hipFree(x);
+  for (int k = 2; k < 4; ++k) {
+    if (T.mem[k]) (void)hipFree(T.mem[k]);
+    T.mem[k] = nullptr;
+  }
   T.oc16 = nullptr;
   T.rec = nullptr;
   T.job = nullptr;
@@ -1207,25 +1229,36 @@ void tri_drop_inputs(TriLayout& T) {
 }
 
 void tri_release(TriLayout& T) {
-  void* p[] = {T.hof, T.idof, T.deg, T.row, T.oline, T.wbase, T.lu, T.li, T.oc, T.oc16, T.rec, T.job, T.wrow};
-  for (void* x : p)
-    if (x) (void)hipFree(x);
+  for (void* m : T.mem)
+    if (m) (void)hipFree(m);
   T = TriLayout();
 }
 
+void tri_drop_work(TriScratch& S) {
+  if (S.mem) (void)hipFree(S.mem);
+  S.mem = nullptr;
+  S.bits = nullptr;
+  S.simw = nullptr;
+  S.flag = nullptr;
+}
+
 void tri_release_scratch(TriScratch& S) {
-  void* p[] = {S.cnt, S.bits, S.simw, S.flag};
-  for (void* x : p)
-    if (x) (void)hipFree(x);
+  tri_drop_work(S);
+  if (S.cnt) (void)hipFree(S.cnt);
   S = TriScratch();
 }
 
 hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S) {
-  hipError_t e = dnew(&S->cnt, T.lines * kTriLine);
-  if (e == hipSuccess) e = dnew(&S->bits, T.words);
-  if (e == hipSuccess) e = dnew(&S->simw, T.lines);
-  if (e == hipSuccess) e = dnew(&S->flag, 1);
-  if (e != hipSuccess) tri_release_scratch(*S);
+  Arena work;
+  work.take(&S->bits, T.words);
+  work.take(&S->simw, T.lines);
+  work.take(&S->flag, 1);
+  hipError_t e = work.allocate(&S->mem);
+  if (e == hipSuccess) e = hipMalloc((void**)&S->cnt, 4 * (size_t)std::max<int64_t>(T.lines * kTriLine, 1));
+  if (e != hipSuccess) {
+    S->cnt = nullptr;
+    tri_release_scratch(*S);
+  }
   return e;
 }
 
@@ -1237,8 +1270,10 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   T.n = n;
   hipError_t e = hipSuccess;
   int64_t *nline = nullptr, *nword = nullptr, *nin = nullptr, *at0 = nullptr, *at1 = nullptr, *at2 = nullptr;
+  int64_t* work = nullptr;
   uint32_t* inlen = nullptr;
   uint8_t* wcls = nullptr;
+  void* tmp = nullptr;
   int32_t *ctl = nullptr, *longer = nullptr;
   BigChunk* big = nullptr;
   std::vector<BigChunk> chunks;
@@ -1292,36 +1327,38 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
         chunks.push_back(BigChunk{h, v, k, std::min(k + kTriBigChunk, h_rp[v + 1])});
     }
     nchunk = (unsigned)chunks.size();
+    Arena vertex, temp;
+    vertex.take(&T.hof, n);
+    vertex.take(&T.idof, n);
+    vertex.take(&T.deg, n);
+    vertex.take(&T.row, n);
+    vertex.take(&T.oline, (int64_t)n + 1);
+    vertex.take(&T.wbase, (int64_t)n + 1);
+    TTRY(vertex.allocate(&T.mem[0]));
+    for (int64_t** p : {&nline, &nword, &nin, &at0, &at1, &at2}) temp.take(p, (int64_t)n + 1);
+    temp.take(&work, scan_work_items((int64_t)n + 1));
+    temp.take(&inlen, n);
+    temp.take(&wcls, n);
+    temp.take(&longer, n);
+    temp.take(&ctl, 4);  // longest row, rows for the block sort, longest hash row, a reverse arc is missing
+    temp.take(&sums, 2 + kNumBuckets);  // words, edges per bucket, entries
+    temp.take(&big, nchunk);
+    temp.take(&room, 2 * (int64_t)nbig);
+    TTRY(temp.allocate(&tmp));
     if (nchunk) {
-      TTRY(dnew(&big, nchunk));
       TTRY(hipMemcpyAsync(big, chunks.data(), sizeof(BigChunk) * nchunk, hipMemcpyHostToDevice, s));
-      TTRY(dnew(&room, 2 * (int64_t)nbig));
       TTRY(hipMemsetAsync(room, 0, 16 * (size_t)nbig, s));
     }
-    TTRY(dnew(&T.hof, n));
-    TTRY(dnew(&T.idof, n));
     TTRY(hipMemcpyAsync(T.hof, hof.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s));
     TTRY(hipMemcpyAsync(T.idof, idof.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s));
     TTRY(hipStreamSynchronize(s));
   }
-  TTRY(dnew(&T.deg, n));
-  TTRY(dnew(&T.row, n));
-  TTRY(dnew(&ctl, 4));   // longest row, rows for the block sort, longest hash row, a reverse arc is missing
-  TTRY(dnew(&sums, 2 + kNumBuckets));  // words, edges per bucket, entries
   TTRY(hipMemsetAsync(ctl, 0, 16, s));
   TTRY(hipMemsetAsync(sums, 0, sizeof(h_sums), s));
   k_degrees<<<gv, 256, 0, s>>>(n, d_rp, T.idof, T.deg, T.row);
   if (nchunk) k_row_len_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.row);
   if (n > nbig) k_row_len_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row);
   TTRY(hipGetLastError());
-  TTRY(dnew(&nline, (int64_t)n + 1));
-  TTRY(dnew(&nword, (int64_t)n + 1));
-  TTRY(dnew(&nin, (int64_t)n + 1));
-  TTRY(dnew(&at0, (int64_t)n + 1));
-  TTRY(dnew(&at1, (int64_t)n + 1));
-  TTRY(dnew(&at2, (int64_t)n + 1));
-  TTRY(dnew(&inlen, n));
-  TTRY(dnew(&wcls, n));
   k_row_sizes<<<std::min(gv, 512u), 256, 0, s>>>(n, T.row, nline, nword, sums + 1 + kNumBuckets, ctl);
   if (nchunk) {
     k_in_room_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.row, room);
@@ -1331,9 +1368,9 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
     k_in_room_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
   TTRY(hipMemsetAsync(nin + n, 0, 8, s));
   TTRY(hipGetLastError());
-  TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1));
-  TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1));
-  TTRY(exclusive_scan(s, nin, at2, (int64_t)n + 1));
+  TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1, work));
+  TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1, work));
+  TTRY(exclusive_scan(s, nin, at2, (int64_t)n + 1, work));
   TTRY(hipMemcpyAsync(tot + 0, at0 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(tot + 1, at1 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(tot + 2, at2 + n, 8, hipMemcpyDeviceToHost, s));
@@ -1348,15 +1385,18 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 26 || T.words >= (int64_t)1 << 30 ||
       T.recs >= (int64_t)1 << 32 || (int64_t)h_sums[1 + kNumBuckets] != nnz / 2)
     goto done;
-  TTRY(dnew(&T.oline, (int64_t)n + 1));
-  TTRY(dnew(&T.wbase, (int64_t)n + 1));
   k_narrow<<<gv, 256, 0, s>>>(n, at0, at1, T.oline, T.wbase);
-  TTRY(dnew(&T.lu, T.lines));
-  TTRY(dnew(&T.li, T.lines));
-  // steps of 64 entries may start on a row's last line
-  TTRY(dnew(&T.oc, (T.lines + 2) * kTriLine));
-  TTRY(dnew(&T.oc16, (T.lines + 2) * kTriLine));
-  TTRY(dnew(&longer, n));
+  {
+    Arena rows, inputs;
+    rows.take(&T.lu, T.lines);
+    rows.take(&T.li, T.lines);
+    // steps of 64 entries may start on a row's last line
+    rows.take(&T.oc, (T.lines + 2) * kTriLine);
+    TTRY(rows.allocate(&T.mem[1]));
+    inputs.take(&T.oc16, (T.lines + 2) * kTriLine);
+    inputs.take(&T.rec, T.recs);
+    TTRY(inputs.allocate(&T.mem[2]));
+  }
   TTRY(hipMemsetAsync(inlen, 0, 4 * (size_t)n, s));  // here: entries of the big rows so far
   if (nchunk) {
     k_row_fill_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.oline, T.row, inlen, T.oc);
@@ -1368,7 +1408,6 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
                                                    T.lu, T.li, longer, ctl + 1);
   k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16);
   TTRY(hipGetLastError());
-  TTRY(dnew(&T.rec, T.recs));
   TTRY(hipMemsetAsync(inlen, 0, 4 * (size_t)n, s));
   TTRY(hipMemsetAsync(nin, 0, 8 * (size_t)n, s));  // from here on: words of every vertex's in-edges
   if (nchunk)
@@ -1381,8 +1420,8 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
   TTRY(hipGetLastError());
-  TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1));
-  TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1));
+  TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1, work));
+  TTRY(exclusive_scan(s, nword, at1, (int64_t)n + 1, work));
   TTRY(hipMemcpyAsync(tot + 0, at0 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(tot + 1, at1 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(h_ctl, ctl, 16, hipMemcpyDeviceToHost, s));
@@ -1394,8 +1433,12 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   T.max_hash_row = h_ctl[2];
   T.steps = (int64_t)h_sums[0];
   for (int k = 0; k < kNumBuckets; ++k) bucket_edges[k] = (int64_t)h_sums[1 + k];
-  TTRY(dnew(&T.job, T.jobs));
-  TTRY(dnew(&T.wrow, T.wave_rows));
+  {
+    Arena jobs;
+    jobs.take(&T.job, T.jobs);
+    jobs.take(&T.wrow, T.wave_rows);
+    TTRY(jobs.allocate(&T.mem[3]));
+  }
   k_job_fill<<<gv, 256, 0, s>>>(n, at2, inlen, T.oline, T.row, at0, at1, T.job, T.wrow);
   TTRY(hipGetLastError());
   TTRY(hipStreamSynchronize(s));
@@ -1403,9 +1446,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   *ok = 1;
 done:
   (void)hipStreamSynchronize(s);
-  void* tmp[] = {nline, nword, nin, at0, at1, at2, inlen, wcls, ctl, longer, sums, big, room};
-  for (void* x : tmp)
-    if (x) (void)hipFree(x);
+  if (tmp) (void)hipFree(tmp);
   if (!*ok) tri_release(T);
 #undef TTRY
   return e;
