@@ -485,7 +485,7 @@ int scan::run_counts(scan_graph* g, int32_t* d_counts_arc, int32_t* d_counts_edg
     tri_init(s, g->tri, g->tri_s, nullptr, nullptr, nullptr, nullptr);
     tri_count(s, g->tri, g->tri_s);
     tri_close(s, g->tri, g->tri_s, TriArgs{}, nullptr);
-    if (d_counts_arc) tri_arc_counts(s, g->tri, g->tri_s, g->d_rp, g->d_ci, d_counts_arc);
+    if (d_counts_arc) tri_arc_counts(s, g->tri, g->tri_s, g->nnz, g->d_rp, g->d_ci, d_counts_arc);
     if (timing) hipEventRecord(g->ev[1], s);
     turn.enqueued();
     HIP_TRY(hipGetLastError(), "kernel launch");

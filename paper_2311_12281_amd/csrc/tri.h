@@ -148,7 +148,7 @@ void tri_hub_outlier(hipStream_t s, const TriLayout& T, const TriScratch& S, con
 void tri_output(hipStream_t s, const TriLayout& T, const TriArgs& a, const int32_t* lower, int32_t* parent,
                 const int32_t* label, const uint8_t* role, int32_t* out_labels, uint8_t* out_roles, int32_t split);
 // Closed counts of every arc in CSR order from S.cnt (after tri_close).
-void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, const int64_t* rp, const int32_t* ci,
-                    int32_t* counts);
+void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, int64_t nnz, const int64_t* rp,
+                    const int32_t* ci, int32_t* counts);
 
 }  // namespace scan

@@ -1141,24 +1141,40 @@ __global__ void k_tri_output(int32_t n, const int32_t* __restrict__ hof, const i
   out_roles[x] = l != INT_MAX ? 2 : split ? (role[x] == ROLE_HUB ? 3 : 4) : 0;
 }
 
-// Counts in CSR order: one wave per row; the entry of an arc is found in the
-// row of its endpoint with the larger h.
-__global__ __launch_bounds__(256) void k_tri_arcs(int32_t n, const int64_t* __restrict__ rp,
+// Last row that starts at or before arc i, among rows lo .. hi.
+__device__ __forceinline__ int32_t row_of(const int64_t* rp, int32_t lo, int32_t hi, int64_t i) {
+  while (lo < hi) {
+    const int32_t mid = lo + (hi - lo + 1) / 2;
+    if (rp[mid] <= i) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// Counts in CSR order; the entry of an arc is found in the row of its endpoint
+// with the larger h.  A block takes kTriArcs consecutive arcs, whatever their
+// rows (a wave per row left the longest row, some 600 rounds of nine dependent
+// loads on R-MAT scale 19, running alone: 2.2 ms; now 0.58 ms).
+constexpr int kTriArcs = 1024;
+__global__ __launch_bounds__(256) void k_tri_arcs(int32_t n, int64_t nnz, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const int32_t* __restrict__ hof,
                                                   const uint32_t* __restrict__ oline, const int32_t* __restrict__ row,
                                                   const int32_t* __restrict__ oc, const int32_t* __restrict__ cnt,
                                                   int32_t* __restrict__ counts) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nw = ((int64_t)gridDim.x * 256) >> 6;
-  for (int64_t x = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6; x < n; x += nw) {
-    const int32_t hx = hof[x];
-    for (int64_t k = rp[x] + lane; k < rp[x + 1]; k += 64) {
-      const int32_t hy = hof[ci[k]];
-      const int32_t u = max(hx, hy), v = min(hx, hy);
-      const int64_t base = (int64_t)oline[u] * kTriLine;
-      const int32_t j = tri_find(oc + base, row[u], v);
-      if (j >= 0) counts[k] = cnt[base + j];
-    }
+  __shared__ int32_t ends[2];
+  const int64_t a0 = (int64_t)blockIdx.x * kTriArcs, a1 = min(a0 + kTriArcs, nnz);
+  if ((threadIdx.x & 127) == 0) ends[threadIdx.x >> 7] = row_of(rp, 0, n - 1, threadIdx.x ? a1 - 1 : a0);
+  __syncthreads();
+  const int32_t r0 = ends[0], r1 = ends[1];
+#pragma unroll
+  for (int k = 0; k < kTriArcs / 256; ++k) {
+    const int64_t i = a0 + k * 256 + threadIdx.x;
+    if (i >= a1) continue;
+    const int32_t hx = hof[row_of(rp, r0, r1, i)], hy = hof[ci[i]];
+    const int32_t u = max(hx, hy), v = min(hx, hy);
+    const int64_t base = (int64_t)oline[u] * kTriLine;
+    const int32_t j = tri_find(oc + base, row[u], v);
+    if (j >= 0) counts[i] = cnt[base + j];
   }
 }
 
@@ -1525,10 +1541,10 @@ void tri_output(hipStream_t s, const TriLayout& T, const TriArgs& a, const int32
                                                     out_roles, split);
 }
 
-void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, const int64_t* rp, const int32_t* ci,
-                    int32_t* counts) {
-  const unsigned grid = (unsigned)std::min<int64_t>(grid_for(T.n, 4), 1 << 16);
-  k_tri_arcs<<<grid, 256, 0, s>>>(T.n, rp, ci, T.hof, T.oline, T.row, T.oc, S.cnt, counts);
+void tri_arc_counts(hipStream_t s, const TriLayout& T, const TriScratch& S, int64_t nnz, const int64_t* rp,
+                    const int32_t* ci, int32_t* counts) {
+  if (nnz > 0)
+    k_tri_arcs<<<grid_for(nnz, kTriArcs), 256, 0, s>>>(T.n, nnz, rp, ci, T.hof, T.oline, T.row, T.oc, S.cnt, counts);
 }
 
 }  // namespace scan
