@@ -31,6 +31,7 @@
 #include "scan_internal.h"
 #include "device.h"
 
+#include <algorithm>
 #include <climits>
 
 namespace scan {
@@ -444,10 +445,12 @@ struct PassCounts {
 // (T, kWaveSlots int32), and every element of the smaller list is one hash
 // probe; edges with a larger side above that search nbr(v) in global memory.
 // Wave `wave` of `nwaves` takes the chunks wave, wave + nwaves, ... of
-// [begin, end).
+// [begin, end).  A chunk is `per` edges, 64 or fewer: the intersections of a
+// chunk follow one another, so where the bucket has too few edges to fill the
+// chip with chunks of 64 the launch makes them smaller.
 template <int MODE, int G, bool STAGE>
 __device__ __forceinline__ void group_edges(const EdgeArgs& A, int64_t begin, int64_t end, int64_t wave,
-                                            int64_t nwaves, int32_t* T, PassCounts& pc) {
+                                            int64_t nwaves, int32_t* T, PassCounts& pc, int per = 64) {
   static_assert(!STAGE || G == 64, "staging is per wave");
   constexpr int kGroups = 64 / G;
   const int lane = threadIdx.x & 63;
@@ -455,11 +458,11 @@ __device__ __forceinline__ void group_edges(const EdgeArgs& A, int64_t begin, in
   const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << gbase);
   const bool exact = (MODE == MODE_COUNTS) || !A.pruning;
   int32_t staged_v = -1;  // STAGE: the vertex whose list the wave's LDS slot holds
-  for (int64_t base = begin + wave * 64; base < end; base += nwaves * 64) {
+  for (int64_t base = begin + wave * per; base < end; base += nwaves * per) {
     const int64_t e = base + lane;
     EdgeView ev;
     unsigned long long nb = 0;
-    classify<MODE>(A, e, e < end, ev, nb);
+    classify<MODE>(A, e, e < end && lane < per, ev, nb);
     pc.bound += nb;
     bool surv = false;
     if (ev.work == 2) {
@@ -543,16 +546,50 @@ __device__ __forceinline__ void group_edges(const EdgeArgs& A, int64_t begin, in
   }
 }
 
-// One bucket's pass over [A.e_begin, A.e_end), grid-stride over 64-edge chunks.
+// One bucket's pass over [A.e_begin, A.e_end), grid-stride over chunks of `per` edges.
 template <int MODE, int G, bool STAGE = false>
-__global__ __launch_bounds__(kBlock) void k_group(EdgeArgs A) {
+__global__ __launch_bounds__(kBlock) void k_group(EdgeArgs A, int per) {
   if ((MODE == MODE_MERGE || MODE == MODE_ATTACH) && A.ncores && *A.ncores == 0) return;  // no cluster
   __shared__ __align__(16) int32_t stage[STAGE ? (kBlock / 64) * kWaveSlots : 1];
   const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * kBlock) >> 6;
   PassCounts pc;
   group_edges<MODE, G, STAGE>(A, A.e_begin, A.e_end, wave, nwaves, stage + (STAGE ? (threadIdx.x >> 6) * kWaveSlots : 0),
-                              pc);
+                              pc, per);
+  flush_stats_block<kBlock / 64>(A, MODE, pc.eval, pc.bound, pc.probe);
+}
+
+// Buckets 0 to 5 in one launch, the widest first.  The buckets of a partitioned
+// graph's chunk are too small to fill the chip and follow one another's longest
+// chain of loads: five launches of 9 to 54 us a chunk (Chung-Lu, n = 200 thousand,
+// average degree 30, a fifth of its device bytes) against one of 48.
+struct GroupSpans {
+  int64_t begin[kNumBuckets - 1], end[kNumBuckets - 1];
+  uint32_t block[kNumBuckets];  // first block of every span
+  int32_t per[kNumBuckets - 1];
+};
+
+template <int MODE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_groups(EdgeArgs A, GroupSpans S, unsigned long long* zero) {
+  __shared__ __align__(16) int32_t stage[(kBlock / 64) * kWaveSlots];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
+  int k = 0;
+  while (k < kNumBuckets - 2 && blockIdx.x >= S.block[k + 1]) ++k;
+  A.bucket = kNumBuckets - 2 - k;
+  const int64_t wave = ((int64_t)(blockIdx.x - S.block[k]) * kBlock + threadIdx.x) >> 6;
+  const int64_t nwaves = ((int64_t)(S.block[k + 1] - S.block[k]) * kBlock) >> 6;
+  const int64_t begin = S.begin[k], end = S.end[k];
+  const int per = S.per[k];
+  PassCounts pc;
+  switch (A.bucket) {
+    case 0: group_edges<MODE, 4, false>(A, begin, end, wave, nwaves, nullptr, pc, per); break;
+    case 1: group_edges<MODE, 8, false>(A, begin, end, wave, nwaves, nullptr, pc, per); break;
+    case 2: group_edges<MODE, 16, false>(A, begin, end, wave, nwaves, nullptr, pc, per); break;
+    case 3: group_edges<MODE, 32, false>(A, begin, end, wave, nwaves, nullptr, pc, per); break;
+    default:
+      group_edges<MODE, 64, true>(A, begin, end, wave, nwaves, stage + (threadIdx.x >> 6) * kWaveSlots, pc, per);
+      break;
+  }
   flush_stats_block<kBlock / 64>(A, MODE, pc.eval, pc.bound, pc.probe);
 }
 
@@ -1721,19 +1758,32 @@ inline unsigned blocks_for(int64_t items, int64_t per_block, int64_t cap) {
 // lived waves do better; the wider groups keep more waves in flight.
 constexpr int64_t kGroupGridCap[kNumBuckets] = {2048, 2048, 4096, 8192, 8192, 8192, 8192};
 
+// Edges a wave takes at a time: 64, or as few as it takes to have kGroupWaves
+// waves (eight on every SIMD), but no fewer than one per group of the wave.  A
+// partitioned graph's bucket of 30 thousand edges and 64 lanes each ran 470
+// waves of up to 64 intersections in a row: 103 us.
+constexpr int64_t kGroupWaves = 8192;
+inline int group_chunk(int64_t m, int lanes) {
+  int per = 64;
+  while (per > 64 / lanes && m < per * kGroupWaves) per >>= 1;
+  return per;
+}
+
 template <int MODE>
 void launch_edges_mode(hipStream_t s, int bucket, const EdgeArgs& a) {
   const int64_t m = a.e_end - a.e_begin;
   if (m <= 0) return;
-  const unsigned grid = blocks_for(m, kBlock, kGroupGridCap[bucket >= 0 && bucket < kNumBuckets ? bucket : kNumBuckets - 1]);
+  const int per = group_chunk(m, bucket < 4 ? 4 << bucket : 64);
+  const unsigned grid =
+      blocks_for(m, per * (kBlock / 64), kGroupGridCap[bucket >= 0 && bucket < kNumBuckets ? bucket : kNumBuckets - 1]);
   switch (bucket) {
-    case 0: k_group<MODE, 4><<<grid, kBlock, 0, s>>>(a); break;
-    case 1: k_group<MODE, 8><<<grid, kBlock, 0, s>>>(a); break;
-    case 2: k_group<MODE, 16><<<grid, kBlock, 0, s>>>(a); break;
-    case 3: k_group<MODE, 32><<<grid, kBlock, 0, s>>>(a); break;
+    case 0: k_group<MODE, 4><<<grid, kBlock, 0, s>>>(a, per); break;
+    case 1: k_group<MODE, 8><<<grid, kBlock, 0, s>>>(a, per); break;
+    case 2: k_group<MODE, 16><<<grid, kBlock, 0, s>>>(a, per); break;
+    case 3: k_group<MODE, 32><<<grid, kBlock, 0, s>>>(a, per); break;
     case 4:
-    case 5: k_group<MODE, 64, true><<<grid, kBlock, 0, s>>>(a); break;
-    default: k_group<MODE, 64><<<grid, kBlock, 0, s>>>(a); break;
+    case 5: k_group<MODE, 64, true><<<grid, kBlock, 0, s>>>(a, per); break;
+    default: k_group<MODE, 64><<<grid, kBlock, 0, s>>>(a, per); break;
   }
 }
 
@@ -1752,15 +1802,16 @@ template <int MODE>
 void launch_edges_width(hipStream_t s, int lanes, const EdgeArgs& a) {
   const int64_t m = a.e_end - a.e_begin;
   if (m <= 0) return;
-  const unsigned grid = blocks_for(m, kBlock, 8192);
+  const int per = group_chunk(m, lanes);
+  const unsigned grid = blocks_for(m, per * (kBlock / 64), 8192);
   switch (lanes) {
-    case 4: k_group<MODE, 4><<<grid, kBlock, 0, s>>>(a); break;
-    case 8: k_group<MODE, 8><<<grid, kBlock, 0, s>>>(a); break;
-    case 16: k_group<MODE, 16><<<grid, kBlock, 0, s>>>(a); break;
-    case 32: k_group<MODE, 32><<<grid, kBlock, 0, s>>>(a); break;
+    case 4: k_group<MODE, 4><<<grid, kBlock, 0, s>>>(a, per); break;
+    case 8: k_group<MODE, 8><<<grid, kBlock, 0, s>>>(a, per); break;
+    case 16: k_group<MODE, 16><<<grid, kBlock, 0, s>>>(a, per); break;
+    case 32: k_group<MODE, 32><<<grid, kBlock, 0, s>>>(a, per); break;
     default:
-      if (a.bucket == 4 || a.bucket == 5) k_group<MODE, 64, true><<<grid, kBlock, 0, s>>>(a);
-      else k_group<MODE, 64><<<grid, kBlock, 0, s>>>(a);
+      if (a.bucket == 4 || a.bucket == 5) k_group<MODE, 64, true><<<grid, kBlock, 0, s>>>(a, per);
+      else k_group<MODE, 64><<<grid, kBlock, 0, s>>>(a, per);
       break;
   }
 }
@@ -1780,6 +1831,36 @@ void launch_edges(hipStream_t s, int mode, int bucket, const EdgeArgs& a) {
     case MODE_MERGE: launch_edges_mode<MODE_MERGE>(s, bucket, a); break;
     case MODE_ATTACH: launch_edges_mode<MODE_ATTACH>(s, bucket, a); break;
     default: launch_edges_mode<MODE_COUNTS>(s, bucket, a); break;
+  }
+}
+
+void launch_groups(hipStream_t s, int mode, const int64_t* off, const EdgeArgs& a, unsigned long long* zero) {
+  // No more blocks than are resident: each adds its pass counters to the same few
+  // addresses at its end (7500 blocks a launch: 90 us, most of it that; 1536: 48).
+  constexpr int64_t kGroupsGrid = 1536;
+  GroupSpans S;
+  int64_t want[kNumBuckets - 1], all = 0;
+  for (int k = 0; k < kNumBuckets - 1; ++k) {
+    const int b = kNumBuckets - 2 - k;
+    const int64_t m = off[b + 1] - off[b];
+    S.begin[k] = off[b];
+    S.end[k] = off[b + 1];
+    S.per[k] = group_chunk(m, b < 4 ? 4 << b : 64);
+    want[k] = m > 0 ? blocks_for(m, S.per[k] * (kBlock / 64), kGroupGridCap[b]) : 0;
+    all += want[k];
+  }
+  uint32_t blocks = 0;
+  for (int k = 0; k < kNumBuckets - 1; ++k) {
+    S.block[k] = blocks;
+    if (want[k] > 0) blocks += (uint32_t)(all > kGroupsGrid ? std::max<int64_t>(1, want[k] * kGroupsGrid / all) : want[k]);
+  }
+  S.block[kNumBuckets - 1] = blocks;
+  if (blocks == 0) return launch_zero_u64(s, zero, 1);
+  switch (mode) {
+    case MODE_CORES: k_groups<MODE_CORES><<<blocks, kBlock, 0, s>>>(a, S, zero); break;
+    case MODE_MERGE: k_groups<MODE_MERGE><<<blocks, kBlock, 0, s>>>(a, S, zero); break;
+    case MODE_ATTACH: k_groups<MODE_ATTACH><<<blocks, kBlock, 0, s>>>(a, S, zero); break;
+    default: k_groups<MODE_COUNTS><<<blocks, kBlock, 0, s>>>(a, S, zero); break;
   }
 }
 

@@ -216,14 +216,16 @@ int part_create(scan_graph* g, const int64_t* rp, const int32_t* ci, uint64_t bu
   }
   if (nnz > 0) memcpy(P.h_ci, ci, sizeof(int32_t) * (size_t)nnz);
   {
-    // the last bucket of every pair grouped by the larger side, as the LDS-hash jobs need
+    // the buckets whose kernels keep the larger side's row in LDS, grouped by it in
+    // every pair: the last one's jobs need that, and a wave of buckets 4 and 5 loads
+    // its set once per run of edges
     std::vector<std::thread> th;
     for (int t = 0; t < nth; ++t)
       th.emplace_back([&, t]() {
         for (int64_t pi = t; pi < npairs; pi += nth) {
-          int2* b = P.h_edges + off[(size_t)(pi * NB + NB - 1)];
-          int2* e = P.h_edges + off[(size_t)(pi * NB + NB)];
-          std::sort(b, e, [](const int2& x, const int2& y) { return x.y != y.y ? x.y < y.y : x.x < y.x; });
+          for (int k = 4; k < NB; ++k)
+            std::sort(P.h_edges + off[(size_t)(pi * NB + k)], P.h_edges + off[(size_t)(pi * NB + k + 1)],
+                      [](const int2& x, const int2& y) { return x.y != y.y ? x.y < y.y : x.x < y.x; });
         }
       });
     for (auto& x : th) x.join();
@@ -435,16 +437,14 @@ namespace {
 // The kernels of one resident chunk: group kernels for buckets 0-5, the
 // LDS-hash kernel with the chunk's own jobs for the last bucket.
 void launch_chunk(hipStream_t s, int mode, const PartChunk& C, EdgeArgs& A, PartPlan& P) {
-  for (int k = 0; k < kNumBuckets; ++k) {
-    A.e_begin = C.bucket_off[k] - C.begin;
-    A.e_end = C.bucket_off[k + 1] - C.begin;
-    A.bucket = k;
-    if (k < kNumBuckets - 1) {
-      launch_edges(s, mode, k, A);
-    } else if (C.job_cnt > 0) {
-      launch_zero_u64(s, P.d_jobctr, 1);
-      launch_hub(s, mode, A, P.d_jobs + C.job_off, C.job_cnt, P.d_jobctr, P.d_worklist);
-    }
+  int64_t off[kNumBuckets + 1];
+  for (int k = 0; k <= kNumBuckets; ++k) off[k] = C.bucket_off[k] - C.begin;
+  launch_groups(s, mode, off, A, P.d_jobctr);
+  if (C.job_cnt > 0) {
+    A.e_begin = off[kNumBuckets - 1];
+    A.e_end = off[kNumBuckets];
+    A.bucket = kNumBuckets - 1;
+    launch_hub(s, mode, A, P.d_jobs + C.job_off, C.job_cnt, P.d_jobctr, P.d_worklist);
   }
 }
 

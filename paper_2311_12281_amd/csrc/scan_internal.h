@@ -148,7 +148,10 @@ void launch_init(hipStream_t s, int32_t n, const int64_t* rp, int32_t mu, int32_
                  int32_t* upper, uint8_t* role, int32_t* parent, const int32_t* gid = nullptr,
                  const int32_t* gmu = nullptr);
 void launch_edges(hipStream_t s, int mode, int bucket, const EdgeArgs& a);
-// Same with an explicit lane-group width (4, 8, 16, 32 or 64), any bucket.
+// The group kernels of buckets 0 to 5 in one launch: bucket k holds edges
+// off[k] .. off[k + 1].  Zeroes *zero for the launch that follows.
+void launch_groups(hipStream_t s, int mode, const int64_t* off, const EdgeArgs& a, unsigned long long* zero);
+// Same as launch_edges with an explicit lane-group width (4, 8, 16, 32 or 64), any bucket.
 void launch_edges_lanes(hipStream_t s, int mode, int lanes, const EdgeArgs& a);
 // Last bucket through the LDS-hash kernel; counter must be zero on entry,
 // worklist holds one int32 per edge of the bucket.
