@@ -21,7 +21,8 @@ constexpr int kTriLine = 32;
 constexpr int kTriMaxRow = 4096;  // longest row the kernels take
 constexpr int kTriBlock = 512;    // threads of the block kernel
 constexpr int kTriRecLines = 8;   // lines per in-edge record
-constexpr int kTriJob = 1024;     // records per job of the block kernel
+constexpr int kTriBatch = 56;     // records a wave decodes together; up to 7 more are asked for, and are empty
+constexpr int kTriJob = 2 * kTriBatch * (kTriBlock / 64);  // records per job of the block kernel
 constexpr int kTriDirect = 16384; // h below this: table of row positions indexed by h
 constexpr int kTriShort = 65534;  // h below this: 16-bit entries (oc16) and a bitmap table
 constexpr int kTriWaveRow = 128;  // rows up to this, with few in-edges, go one per wave

@@ -54,3 +54,16 @@ def test_rows_above_the_limit():
     keep = np.random.default_rng(7).random(i.size) < 0.995
     g = gg.from_pairs(n, i[keep].astype(np.int32), j[keep].astype(np.int32))
     _check(g, "long rows", [((99, 100), 4000), ((1, 2), 5)])
+
+
+@pytest.mark.parametrize("k", [513, 895, 896, 897, 1008, 1345, 1793])
+def test_in_edge_batches(k):
+    """k vertices joined to the same four: in-edge records of the block kernel
+    around a wave's batch (56) and a job (896), some of several lines."""
+    rng = np.random.default_rng(k)
+    edges = [(a, b) for a in range(4) for b in range(a)]
+    edges += [(a, 4 + i) for i in range(k) for a in range(4)]
+    edges += [(4 + a, 4 + b) for a in range(90) for b in range(a) if rng.random() < 0.9]
+    perm = rng.permutation(4 + k)
+    _check(gg.from_edges(4 + k, [(int(perm[a]), int(perm[b])) for a, b in edges]), f"in-edges {k}",
+           [((1, 2), 2), ((1, 10), 5)])
