@@ -27,6 +27,7 @@ constexpr int kTriDirect = 16384; // h below this: table of row positions indexe
 constexpr int kTriShort = 65534;  // h below this: 16-bit entries (oc16) and a bitmap table
 constexpr int kTriWaveRow = 128;  // rows up to this, with few in-edges, go one per wave
 constexpr int kTriWaveSlots = 256;
+constexpr uint32_t kTriWaveSingle = 1u << 31;  // the wave has all of them: counts are stored, not added
 constexpr int64_t kTriWaveWords = 512;  // words of in-edges a wave takes on
 
 // A line as the close kernel reads it.
@@ -53,11 +54,11 @@ struct TriJob {
   uint32_t single;      // 1: the only job of v (its counts are stored, not added)
 };
 
-// A vertex of the wave kernel.
+// A vertex of the wave kernel, or a part of its records (of one line each).
 struct TriWave {
   int32_t v;
   uint32_t line, rbeg;  // of its row, of its in-edge records
-  uint32_t shape;       // row length | records << 8
+  uint32_t shape;       // row length | records << 8 | kTriWaveSingle
 };
 
 // The graphs of a batch: vertices vtx_off[k] .. vtx_off[k + 1] - 1, and the

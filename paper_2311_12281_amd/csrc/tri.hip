@@ -434,7 +434,7 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
 // kernel's list; the sum of all words and the longest hash-table row.
 __global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_off, const int32_t* row,
                              const uint8_t* wcls, const uint32_t* inlen, const int64_t* steps, int64_t* njob,
-                             int64_t* nwave, unsigned long long* total, int32_t* max_hash) {
+                             int64_t* nwave, uint32_t part, unsigned long long* total, int32_t* max_hash) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   unsigned long long st = 0;
   int32_t most = 0;
@@ -443,7 +443,7 @@ __global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_o
     if (h < n && steps[h] > 0) {
       st += (unsigned long long)steps[h];
       if (wcls[h]) {
-        w = 1;
+        w = (inlen[h] + part - 1) / part;
       } else {
         j = (inlen[h] + kTriJob - 1) / kTriJob;
         if (h - tri_base(gid, vtx_off, h) >= kTriShort) most = max(most, row[h]);
@@ -461,12 +461,16 @@ __global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_o
 }
 
 __global__ void k_job_fill(int32_t n, const int64_t* inoff, const uint32_t* inlen, const uint32_t* oline, const int32_t* row,
-                           const int64_t* job_at, const int64_t* wave_at, TriJob* job, TriWave* wrow) {
+                           const int64_t* job_at, const int64_t* wave_at, uint32_t part, TriJob* job, TriWave* wrow) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (h >= n) return;
   const int64_t j0 = job_at[h], nj = job_at[h + 1] - j0;
   const uint32_t r0 = (uint32_t)inoff[h], r1 = r0 + inlen[h];
-  if (wave_at[h + 1] > wave_at[h]) wrow[wave_at[h]] = TriWave{(int32_t)h, oline[h], r0, (uint32_t)row[h] | (r1 - r0) << 8};
+  const int64_t w0 = wave_at[h], nw = wave_at[h + 1] - w0;
+  for (int64_t j = 0; j < nw; ++j) {
+    const uint32_t beg = r0 + (uint32_t)j * part, cnt = min(part, r1 - beg);
+    wrow[w0 + j] = TriWave{(int32_t)h, oline[h], beg, (uint32_t)row[h] | cnt << 8 | (nw == 1 ? kTriWaveSingle : 0)};
+  }
   for (int64_t j = 0; j < nj; ++j) {
     TriJob J;
     J.v = (int32_t)h;
@@ -752,7 +756,7 @@ __global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* _
   int32_t* key = keys[threadIdx.x >> 6];
   int32_t* hit = hits[threadIdx.x >> 6];
   const TriWave V = wrow[i];
-  const uint32_t D = V.shape & 0xFFu, rc = V.shape >> 8;
+  const uint32_t D = V.shape & 0xFFu, rc = (V.shape & ~kTriWaveSingle) >> 8;
   const int64_t base = (int64_t)V.line * kTriLine;
   const TriRec* recs = rec + V.rbeg;
   const uint32_t e0 = (uint32_t)lane < D ? cols[base + lane] : 0;
@@ -852,8 +856,12 @@ __global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* _
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  if (e0) cnt[base + lane] = hit[t0];
-  if (e1) cnt[base + 64 + lane] = hit[t1];
+  auto put = [&](int64_t at, int32_t c) {
+    if (V.shape & kTriWaveSingle) cnt[at] = c;
+    else if (c) atomicAdd(cnt + at, c);
+  };
+  if (e0) put(base + lane, hit[t0]);
+  if (e1) put(base + 64 + lane, hit[t1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1295,6 +1303,13 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   hipError_t e = hipSuccess;
   int64_t *nline = nullptr, *nword = nullptr, *nin = nullptr, *at0 = nullptr, *at1 = nullptr, *at2 = nullptr;
   int64_t* work = nullptr;
+  // Records per wave of the wave kernel.  A wave goes through its records one
+  // after the other (512 of them: 120 us, all of a small graph's time), but builds
+  // its row's table first.  Kernel, in parts of up to 512, 128, 64 and 32 records:
+  // R-MAT scale 14 (m = 0.2 M) 120, 53, 30, 18 us; scale 17 (1.9 M) 54, 54, 43, 37;
+  // scale 19 (5.9 M) 258, 173, 150, 156; scale 22 (64 M) 490, 490, 496, 526; Chung-Lu
+  // (7.4 M) 250, 217, 220, 229.  300 planted graphs (20 M) 773, 773, 792, 867.
+  const uint32_t part = nnz / 2 < (4 << 20) ? 32 : nnz / 2 < (16 << 20) ? 64 : 128;
   uint32_t* inlen = nullptr;
   uint8_t* wcls = nullptr;
   void* tmp = nullptr;
@@ -1440,7 +1455,8 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (n > nbig)
     k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
                                                       T.oc, at2, wcls, T.rec, inlen, nin, ctl + 3);
-  k_job_counts<<<std::min(gv, 512u), 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, sums, ctl + 2);
+  k_job_counts<<<std::min(gv, 512u), 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, part, sums,
+                                                ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
   TTRY(hipGetLastError());
@@ -1463,7 +1479,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
     jobs.take(&T.wrow, T.wave_rows);
     TTRY(jobs.allocate(&T.mem[3]));
   }
-  k_job_fill<<<gv, 256, 0, s>>>(n, at2, inlen, T.oline, T.row, at0, at1, T.job, T.wrow);
+  k_job_fill<<<gv, 256, 0, s>>>(n, at2, inlen, T.oline, T.row, at0, at1, part, T.job, T.wrow);
   TTRY(hipGetLastError());
   TTRY(hipStreamSynchronize(s));
   *out = T;

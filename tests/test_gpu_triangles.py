@@ -67,3 +67,14 @@ def test_in_edge_batches(k):
     perm = rng.permutation(4 + k)
     _check(gg.from_edges(4 + k, [(int(perm[a]), int(perm[b])) for a, b in edges]), f"in-edges {k}",
            [((1, 2), 2), ((1, 10), 5)])
+
+
+@pytest.mark.parametrize("k", [31, 32, 33, 63, 64, 65, 66, 97, 129, 257, 500])
+def test_wave_parts(k):
+    """k vertices joined to the same three: the in-edges of a wave's row around
+    the parts that waves take (32 records)."""
+    rng = np.random.default_rng(k)
+    edges = [(1, 0), (2, 0), (2, 1)] + [(a, 3 + i) for i in range(k) for a in range(3)]
+    perm = rng.permutation(3 + k)
+    _check(gg.from_edges(3 + k, [(int(perm[a]), int(perm[b])) for a, b in edges]), f"parts {k}",
+           [((1, 2), 2), ((1, 10), 5)])
