@@ -589,6 +589,19 @@ int part_run(scan_graph* g, uint64_t p, uint64_t q, int32_t mu, int32_t* d_label
     }
     const std::vector<int32_t>& list = mode == MODE_CORES ? all : mode == MODE_MERGE ? merge_list : attach_list;
     Streamer st{g, s};
+    // States of chunk k of the list back to the host, on the copy stream: between
+    // the kernels of two chunks the copy and the gaps around it took 30 us.  Queued
+    // behind the upload of the next chunk, so that it holds up only the one after,
+    // which needs the same buffer.
+    auto states_back = [&](int k) -> hipError_t {
+      if (mode == MODE_ATTACH || k < 0) return hipSuccess;
+      const PartChunk& C = P.chunks[(size_t)list[(size_t)k]];
+      hipError_t e = hipStreamWaitEvent(P.copy, P.done[k & 1], 0);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(P.h_state + C.begin, (k & 1) ? P.d_state2 : P.d_state, (size_t)(C.end - C.begin),
+                           hipMemcpyDeviceToHost, P.copy);
+      return e;
+    };
     int idx = 0;
     for (const int32_t ci : list) {
       const PartChunk& C = P.chunks[(size_t)ci];
@@ -607,6 +620,7 @@ int part_run(scan_graph* g, uint64_t p, uint64_t q, int32_t mu, int32_t* d_label
       if (mode != MODE_CORES)
         HIP_TRY(hipMemcpyAsync(ds, P.h_state + C.begin, (size_t)ne, hipMemcpyHostToDevice, P.copy), "state H2D");
       HIP_TRY(hipEventRecord(P.up[b], P.copy), "hipEventRecord");
+      HIP_TRY(states_back(idx - 1), "state D2H");
       P.h2d_bytes += (mode != MODE_CORES ? 9ull : 8ull) * (uint64_t)ne;
       ++P.chunks_streamed;
       HIP_TRY(hipStreamWaitEvent(s, P.up[b], 0), "hipStreamWaitEvent");
@@ -615,11 +629,10 @@ int part_run(scan_graph* g, uint64_t p, uint64_t q, int32_t mu, int32_t* d_label
       if (mode == MODE_CORES) launch_fill_u8(s, ds, ne, SIM_UNK);
       if (mode == MODE_MERGE) launch_hook(s, ne, de, ds, g->d_role, g->d_parent);
       launch_chunk(s, mode, C, A, P);
-      if (mode != MODE_ATTACH)
-        HIP_TRY(hipMemcpyAsync(P.h_state + C.begin, ds, (size_t)ne, hipMemcpyDeviceToHost, s), "state D2H");
       HIP_TRY(hipEventRecord(P.done[b], s), "hipEventRecord");
       ++idx;
     }
+    HIP_TRY(states_back(idx - 1), "state D2H");
     HIP_TRY(st.finish(), "hipEventRecord");
     // the states copied back are read by the next pass's uploads and chunk selection
     HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
