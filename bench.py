@@ -197,8 +197,8 @@ def main():
         launch_ms = sum(st["ms_phase"]["cores"] for st in stats) / launches
         alg_bytes = sum(2.0 * st["probes"]["cores"] + 28.0 * m for st in stats) / launches
         achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
-        dom_kernel = "k_tri_block"
-        dom_name = "k_tri_block, k_tri_wave and k_tri_close: cores phase"
+        dom_kernel = "k_tri_count"
+        dom_name = "k_tri_count and k_tri_close: cores phase"
     traffic = _traffic_from_profile(dom_kernel)
     byte_models = solve_byte_models(g, stats[-len(EPS_SET):], traffic,
                                     float(alg_bytes) if launches else None)

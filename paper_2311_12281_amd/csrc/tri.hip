@@ -627,14 +627,11 @@ __device__ __forceinline__ uint32_t tri_hash(int32_t x) { return (uint32_t)x * 0
 //   h(v) < kTriShort   a bit per h and, per 32 of them, the places before;
 //   above              a hash set of the entries, linear probing, at most half full.
 // The first two read the 16-bit columns.  Block-uniform choice.
-__global__ __launch_bounds__(kTriBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec, const int32_t* __restrict__ row,
-                 const uint32_t* __restrict__ oline, const int32_t* __restrict__ gid,
-                 const int64_t* __restrict__ vtx_off, const int32_t* __restrict__ oc,
-                 const uint16_t* __restrict__ oc16, uint32_t* __restrict__ bits, int32_t* __restrict__ cnt,
-                 uint32_t acc_cap) {
-  extern __shared__ __align__(16) int32_t tri_lds[];
-  const TriJob J = jobs[blockIdx.x];
+__device__ __forceinline__ void tri_job(const TriJob J, int32_t* tri_lds, const TriRec* __restrict__ rec,
+                                        const int32_t* __restrict__ row, const uint32_t* __restrict__ oline,
+                                        const int32_t* __restrict__ gid, const int64_t* __restrict__ vtx_off,
+                                        const int32_t* __restrict__ oc, const uint16_t* __restrict__ oc16,
+                                        uint32_t* __restrict__ bits, int32_t* __restrict__ cnt, uint32_t acc_cap) {
   const int32_t D = row[J.v], h0 = tri_base(gid, vtx_off, J.v), v = J.v - h0;  // v within its graph
   const int64_t base = (int64_t)oline[J.v] * kTriLine;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -733,7 +730,7 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
   }
 }
 
-// Vertices with a short row and few in-edges, one per wave; a record is one
+// Vertices with a short row and few in-edges, a wave each or per part; a record is one
 // line, and each half of the wave takes every other one.  Bound by vector
 // instructions (batch of 300 graphs: 0.8 of 1.16 ms when every line's place was
 // worked out here and every lookup could take several probes), so: records of
@@ -742,20 +739,13 @@ void k_tri_block(const TriJob* __restrict__ jobs, const TriRec* __restrict__ rec
 // slots) a hash that is changed until the row has no collision, after which a
 // lookup is one probe (batch of 300 graphs: 0.77 ms).
 template <typename E>
-__global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* __restrict__ wrow,
-                                                  const TriRec* __restrict__ rec, const E* __restrict__ cols,
-                                                  int64_t lines, uint32_t* __restrict__ bits,
-                                                  int32_t* __restrict__ cnt) {
-  __shared__ __align__(16) int32_t keys[4][kTriWaveSlots];
-  __shared__ __align__(16) int32_t hits[4][kTriWaveSlots];
+__device__ __forceinline__ void tri_row(const TriWave V, int32_t* key, const TriRec* __restrict__ rec,
+                                        const E* __restrict__ cols, int64_t lines, uint32_t* __restrict__ bits,
+                                        int32_t* __restrict__ cnt) {
   constexpr uint32_t kMask = kTriWaveSlots - 1;
   constexpr uint32_t kNone = 0xFFFFFFFFu;
   const int lane = threadIdx.x & 63, half = lane >> 5, sub = lane & 31;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= nrow) return;
-  int32_t* key = keys[threadIdx.x >> 6];
-  int32_t* hit = hits[threadIdx.x >> 6];
-  const TriWave V = wrow[i];
+  int32_t* hit = key + kTriWaveSlots;
   const uint32_t D = V.shape & 0xFFu, rc = (V.shape & ~kTriWaveSingle) >> 8;
   const int64_t base = (int64_t)V.line * kTriLine;
   const TriRec* recs = rec + V.rbeg;
@@ -862,6 +852,45 @@ __global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* _
   };
   if (e0) put(base + lane, hit[t0]);
   if (e1) put(base + 64 + lane, hit[t1]);
+}
+
+// Rows of a graph without jobs, four waves a block (in blocks of eight, as
+// below, 300 planted graphs take 0.81 instead of 0.77 ms).
+template <typename E>
+__global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* __restrict__ wrow,
+                                                  const TriRec* __restrict__ rec, const E* __restrict__ cols,
+                                                  int64_t lines, uint32_t* __restrict__ bits,
+                                                  int32_t* __restrict__ cnt) {
+  __shared__ __align__(16) int32_t sets[4][2 * kTriWaveSlots];
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i < nrow) tri_row(wrow[i], sets[threadIdx.x >> 6], rec, cols, lines, bits, cnt);
+}
+
+// Jobs and waves' rows in one launch, spread evenly over it: `ratio` is the
+// share of the blocks that take a job, in 2^-32.  The jobs wait for memory and
+// the rows for vector instructions, so they run well side by side, and on a small
+// graph neither fills the chip (R-MAT scale 14: 21 and 18 us one after the other,
+// 24 together; scale 17: 79 and 37, 109; scale 22 the same within 1 %).
+template <typename E>
+__global__ __launch_bounds__(kTriBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void k_tri_count(uint64_t ratio, const TriJob* __restrict__ jobs, int64_t nrow, const TriWave* __restrict__ wrow,
+                 const TriRec* __restrict__ rec, const int32_t* __restrict__ row, const uint32_t* __restrict__ oline,
+                 const int32_t* __restrict__ gid, const int64_t* __restrict__ vtx_off,
+                 const int32_t* __restrict__ oc, const uint16_t* __restrict__ oc16, int64_t lines,
+                 uint32_t* __restrict__ bits, int32_t* __restrict__ cnt, uint32_t acc_cap) {
+  extern __shared__ __align__(16) int32_t tri_lds[];
+  const uint32_t before = (uint32_t)((uint64_t)blockIdx.x * ratio >> 32);  // blocks before this one with a job
+  if ((uint32_t)(((uint64_t)blockIdx.x + 1) * ratio >> 32) > before) {
+    tri_job(jobs[before], tri_lds, rec, row, oline, gid, vtx_off, oc, oc16, bits, cnt, acc_cap);
+    return;
+  }
+  const uint32_t wave = threadIdx.x >> 6;
+  const int64_t i = (int64_t)(blockIdx.x - before) * (kTriBlock / 64) + wave;
+  if (i >= nrow) return;
+  if constexpr (sizeof(E) == 2)
+    tri_row(wrow[i], tri_lds + wave * 2 * kTriWaveSlots, rec, oc16, lines, bits, cnt);
+  else
+    tri_row(wrow[i], tri_lds + wave * 2 * kTriWaveSlots, rec, reinterpret_cast<const uint32_t*>(oc), lines, bits, cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -1201,13 +1230,15 @@ inline unsigned grid_for(int64_t items, int64_t per_block) {
 
 uint32_t tri_acc_cap(const TriLayout& T) { return ((uint32_t)T.max_row + 2 + 3) & ~3u; }
 
-// Dynamic LDS of the block kernel: counters, then the largest table of the graph.
+// Dynamic LDS of the counting kernel: of a job, counters, then the largest table
+// of the graph; of waves' rows, a hash set and counters each.
 size_t tri_lds_bytes(const TriLayout& T) {
+  const size_t rows = 8 * kTriWaveSlots * (kTriBlock / 64);
   const size_t acc = 4 * (size_t)tri_acc_cap(T);
   size_t b = acc + 2 * ((size_t)std::min(T.span, kTriDirect) + 24);
   if (T.span > kTriDirect) b = std::max(b, acc + 8 * ((size_t)std::min(T.span, kTriShort) / 32 + 3));
   if (T.max_hash_row > 0) b = std::max(b, 8 * (size_t)tri_hash_slots(T.max_hash_row));
-  return (b + 15) & ~(size_t)15;
+  return std::max((b + 15) & ~(size_t)15, rows);
 }
 
 // Several arrays in one allocation (allocating and freeing some thirty of them
@@ -1511,17 +1542,23 @@ void tri_threshold(hipStream_t s, const TriLayout& T, const TriScratch& S, const
 }
 
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
-  if (T.jobs > 0)
-    k_tri_block<<<(unsigned)T.jobs, kTriBlock, tri_lds_bytes(T), s>>>(T.job, T.rec, T.row, T.oline, T.gid, T.vtx_off,
-                                                                     T.oc, T.oc16, S.bits, S.cnt, tri_acc_cap(T));
-  if (T.wave_rows > 0) {
+  if (T.jobs == 0) {
+    if (T.wave_rows == 0) return;
+    const unsigned grid = grid_for(T.wave_rows, 4);
     if (T.span <= kTriShort)
-      k_tri_wave<uint16_t><<<grid_for(T.wave_rows, 4), 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc16, T.lines, S.bits,
-                                                                    S.cnt);
+      k_tri_wave<<<grid, 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc16, T.lines, S.bits, S.cnt);
     else
-      k_tri_wave<uint32_t><<<grid_for(T.wave_rows, 4), 256, 0, s>>>(
-          T.wave_rows, T.wrow, T.rec, reinterpret_cast<const uint32_t*>(T.oc), T.lines, S.bits, S.cnt);
+      k_tri_wave<<<grid, 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, reinterpret_cast<const uint32_t*>(T.oc), T.lines,
+                                      S.bits, S.cnt);
+    return;
   }
+  const uint64_t blocks = (uint64_t)T.jobs + (uint64_t)(T.wave_rows + kTriBlock / 64 - 1) / (kTriBlock / 64);
+  // rounded up: exactly T.jobs of the products blocks * ratio step over a whole number
+  const uint64_t ratio = (((uint64_t)T.jobs << 32) + blocks - 1) / blocks;
+  const auto launch = T.span <= kTriShort ? k_tri_count<uint16_t> : k_tri_count<uint32_t>;
+  launch<<<(unsigned)blocks, kTriBlock, tri_lds_bytes(T), s>>>(ratio, T.job, T.wave_rows, T.wrow, T.rec, T.row, T.oline,
+                                                               T.gid, T.vtx_off, T.oc, T.oc16, T.lines, S.bits, S.cnt,
+                                                               tri_acc_cap(T));
 }
 
 void tri_close(hipStream_t s, const TriLayout& T, const TriScratch& S, const TriArgs& a, int32_t* lower) {
