@@ -963,6 +963,16 @@ __device__ __forceinline__ void tri_mark(int64_t t, int sub, const TriLineInfo& 
   if (sim) atomicAdd(lower + x, 1);
 }
 
+// Block of lines that block b of nb takes.  In a batch the blocks of an XCD (every
+// eighth) take consecutive ones, so that a graph's vertices are read through one
+// L2 (300 graphs: k_tri_close 380 -> 358 us, k_tri_hook 237 -> 166; k_tri_link and
+// k_tri_attach, which wait for atomics, and k_tri_wave got slower).  Of a single
+// graph that would put all the long rows on the first XCD.
+__device__ __forceinline__ int64_t line_block(int64_t b, int64_t nb, const TriArgs& a) {
+  const int64_t per = nb >> 3;
+  return a.gid && b < per * 8 ? (b & 7) * per + (b >> 3) : b;
+}
+
 // One line per half wave: closed counts of its entries, and with eps the
 // similar ones.
 template <bool kEps>
@@ -971,7 +981,7 @@ __global__ __launch_bounds__(256) void k_tri_close(int64_t lines, const TriLineI
                                                    const uint32_t* __restrict__ bits, int32_t* __restrict__ cnt,
                                                    TriArgs a, uint32_t* __restrict__ simw,
                                                    int32_t* __restrict__ lower) {
-  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
+  const int64_t t = line_block(blockIdx.x, gridDim.x, a) * 8 + (threadIdx.x >> 5);
   if (t >= lines) return;
   const int sub = threadIdx.x & 31;
   const TriLineInfo L = li[t];
@@ -1074,9 +1084,10 @@ __global__ __launch_bounds__(256) void k_tri_hook(int64_t lines, const int32_t* 
                                                   TriArgs a_, int32_t* parent, const int32_t* __restrict__ flag) {
   if (!*flag) return;
   const int lane = threadIdx.x & 63, half = lane >> 5, sub = lane & 31;
-  const int64_t stride = (int64_t)gridDim.x * 8;
-  for (int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5; t < lines; t += stride) {
-    const uint32_t w = simw[t];
+  const int64_t blocks = (lines + 7) >> 3;
+  for (int64_t k = blockIdx.x; k < blocks; k += gridDim.x) {
+    const int64_t t = line_block(k, blocks, a_) * 8 + (threadIdx.x >> 5);
+    const uint32_t w = t < lines ? simw[t] : 0;
     if (!w) continue;
     const int32_t u = lu[t], mu = tri_mu(a_, u);
     if (lower[u] < mu) continue;
