@@ -317,7 +317,7 @@ bool launch_on_slot(scan_server* S, Slot& slot, const std::shared_ptr<Request>& 
 bool out_available(const scan_server* S) { return !S->out_free.empty() || S->out_total < S->out_max; }
 
 // Gives the slot a result buffer of the current capacity if it has none
-// (server lock held); false when the pool is exhausted.
+// (server lock held); false when none is free.
 bool acquire_out(scan_server* S, Slot& slot) {
   if (slot.out.labels && slot.out.cap >= S->slot_n) return true;
   if (slot.out.labels) {  // too small since the capacity grew
@@ -334,19 +334,28 @@ bool acquire_out(scan_server* S, Slot& slot) {
     free_out(b);
     --S->out_total;
   }
+  return false;
+}
+
+// Adds a result buffer to the pool; the lock is not held meanwhile (0.3 ms of
+// page pinning, in which clients may return buffers and slots go on).
+bool grow_out(scan_server* S, std::unique_lock<std::mutex>& lk) {
   if (S->out_total >= S->out_max) return false;
-  const size_t N = (size_t)(S->slot_n > 0 ? S->slot_n : 1);
+  ++S->out_total;
   OutBuf b;
-  if (hipHostMalloc((void**)&b.labels, 4 * N, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&b.roles, N, hipHostMallocDefault) != hipSuccess) {
+  b.cap = S->slot_n;
+  const size_t N = (size_t)(b.cap > 0 ? b.cap : 1);
+  lk.unlock();
+  const bool ok = hipHostMalloc((void**)&b.labels, 4 * N, hipHostMallocDefault) == hipSuccess &&
+                  hipHostMalloc((void**)&b.roles, N, hipHostMallocDefault) == hipSuccess;
+  if (!ok) {
     (void)hipGetLastError();
     free_out(b);
-    return false;
   }
-  b.cap = S->slot_n;
-  slot.out = b;
-  ++S->out_total;
-  return true;
+  lk.lock();
+  if (ok) S->out_free.push_back(b);
+  else --S->out_total;
+  return ok;
 }
 
 void worker_loop(scan_server* S) {
@@ -400,7 +409,12 @@ void worker_loop(scan_server* S) {
           ++it;
           continue;
         }
-        if (!acquire_out(S, *free_slot)) break;  // every result buffer awaits collection
+        if (!acquire_out(S, *free_slot)) {
+          // every result buffer awaits collection, or one more may be had (the
+          // lists may have changed meanwhile: start over)
+          progress = grow_out(S, lk) || progress;
+          break;
+        }
         if (!launch_on_slot(S, *free_slot, r, G)) finish(S, r);
       }
       it = S->pending.erase(it);
@@ -588,6 +602,13 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
     S->resident_bytes += S->slots.size() * (slot_bytes(new_n, new_m) - slot_bytes(S->slot_n, S->slot_m));
     S->slot_n = new_n;
     S->slot_m = new_m;
+    // a result buffer of the new capacity per slot, so that the first queries
+    // do not wait for them (failing that, they are allocated as needed)
+    for (auto& b : S->out_free) free_out(b);
+    S->out_total -= (int32_t)S->out_free.size();
+    S->out_free.clear();
+    while (S->out_free.size() < S->slots.size() && grow_out(S, lk)) {
+    }
     S->pause_dispatch = false;
     S->cv_work.notify_one();
   }
