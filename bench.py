@@ -197,7 +197,7 @@ def main():
         launch_ms = sum(st["ms_phase"]["cores"] for st in stats) / launches
         alg_bytes = sum(2.0 * st["probes"]["cores"] + 28.0 * m for st in stats) / launches
         achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
-        dom_kernel = "k_tri_count"
+        dom_kernel = "k_tri_count+k_tri_close"
         dom_name = "k_tri_count and k_tri_close: cores phase"
     traffic = _traffic_from_profile(dom_kernel)
     byte_models = solve_byte_models(g, stats[-len(EPS_SET):], traffic,
@@ -380,13 +380,13 @@ def _cpu_model():
     return {"model": info.get("Model name"), "cpus": info.get("CPU(s)"), "nproc": os.cpu_count()}
 
 
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_k_hub_cores_rmat22.md")
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_k_tri_rmat22.md")
 # counter passes beside the traffic ones (each within one pass's per-block limits)
 LDS_COUNTERS = ["SQ_LDS_BANK_CONFLICT", "SQ_LDS_IDX_ACTIVE", "SQ_INSTS_LDS", "SQ_INSTS_VALU", "SQ_INSTS_VMEM_RD",
                 "SQ_WAVE_CYCLES", "SQ_BUSY_CYCLES", "SQ_WAIT_ANY"]
 ATOMIC_COUNTERS = ["TCC_ATOMIC_sum", "TCC_EA0_ATOMIC_sum", "TCP_TCC_ATOMIC_WITH_RET_REQ_sum",
                    "TCP_TCC_ATOMIC_WITHOUT_RET_REQ_sum"]
-KERNEL_SOURCES = ["kernels.hip", "layout.hip", "api.hip", "scan_internal.h"]
+KERNEL_SOURCES = ["kernels.hip", "layout.hip", "api.hip", "scan_internal.h", "tri.hip", "tri.h", "device.h"]
 
 
 def _kernel_source_hash():
@@ -447,11 +447,17 @@ def summarize_pmc(args):
         rows += _pmc_rows(d)
     is_copy = lambda nm: "k_copy16" in nm  # noqa: E731
     want = args.pmc_kernel
-    is_k = lambda nm: want in nm  # noqa: E731
     got = {}
+
+    def of_want(c):  # "a+b": a dispatch of each
+        vals = [_per_dispatch_mean(rows, c, lambda nm, part=part: part in nm) for part in want.split("+")]
+        if any(v is None for v, _ in vals):
+            return None, 0
+        return sum(v for v, _ in vals), min(n for _, n in vals)
+
     for c in ("FETCH_SIZE", "WRITE_SIZE", "TCC_EA0_RDREQ_32B_sum", "TCC_EA0_RDREQ_64B_sum",
               "TCC_EA0_RDREQ_128B_sum", "TCC_EA0_RDREQ_sum", "TCC_EA0_RDREQ_DRAM_sum"):
-        got[c] = (_per_dispatch_mean(rows, c, is_copy), _per_dispatch_mean(rows, c, is_k))
+        got[c] = (_per_dispatch_mean(rows, c, is_copy), of_want(c))
     (cf, ncf), (kf, nkf) = got["FETCH_SIZE"]
     (cw, ncw), (kw, nkw) = got["WRITE_SIZE"]
     if None in (cf, cw, kf, kw):
@@ -476,7 +482,7 @@ def summarize_pmc(args):
         vals = [got[c][which][0] for c in ("TCC_EA0_RDREQ_32B_sum", "TCC_EA0_RDREQ_64B_sum", "TCC_EA0_RDREQ_128B_sum",
                                             "TCC_EA0_RDREQ_sum", "TCC_EA0_RDREQ_DRAM_sum")]
         size_rows += "| " + label + " | " + " | ".join("-" if v is None else f"{v:.4g}" for v in vals) + " |\n"
-    print(f"""# HBM traffic of {want} (cores pass, LDS-hash bucket), R-MAT scale 22
+    print(f"""# HBM traffic of {want} (cores pass), R-MAT scale 22
 
 Commands (from the repository root on the MI355X host, each its own run):
 
@@ -515,7 +521,7 @@ those that went to DRAM:
     # any further counters of the runs (LDS, atomics, instructions): per-dispatch means for the kernel
     known = {"FETCH_SIZE", "WRITE_SIZE", "TCC_EA0_RDREQ_32B_sum", "TCC_EA0_RDREQ_64B_sum", "TCC_EA0_RDREQ_128B_sum",
              "TCC_EA0_RDREQ_sum", "TCC_EA0_RDREQ_DRAM_sum"}
-    extra = sorted({c for _, nm, c, _ in rows if c not in known and is_k(nm)})
+    extra = sorted({c for _, nm, c, _ in rows if c not in known and any(part in nm for part in want.split("+"))})
     if extra:
         print("Further counters of the kernel (per dispatch, mean over dispatches; SQ counters are sums over\n"
               "the shader engines, LDS cycle counters in the units rocprofv3 reports):\n")
@@ -523,7 +529,9 @@ those that went to DRAM:
         print("|---|---|")
         vals = {}
         for c in extra:
-            v, nd = _per_dispatch_mean(rows, c, is_k)
+            v, nd = of_want(c)
+            if v is None:
+                continue
             vals[c] = v
             print(f"| {c} | {v:.4g} ({nd} dispatches) |")
         if vals.get("SQ_LDS_IDX_ACTIVE") and "SQ_LDS_BANK_CONFLICT" in vals:
@@ -533,6 +541,8 @@ those that went to DRAM:
             print(f"- VALU instructions per LDS instruction: {vals['SQ_INSTS_VALU'] / vals['SQ_INSTS_LDS']:.2f}")
         print()
     bt = _bucket_traffic(rows, sf, sw)
+    if not any(nd for nd, _, _ in bt.values()):
+        return
     print("Every cores-pass kernel, by degree bucket (scaled FETCH_SIZE and WRITE_SIZE per dispatch, GB;")
     print("dispatches are those of the FETCH and WRITE runs together):\n")
     print("| bucket | kernel | dispatches | read GB | written GB |")

@@ -34,7 +34,9 @@
  * plus 5 n of output staging for scan_run), on its own stream or the
  * caller's.  The sets are
  * allocated at the first overlap that needs them and kept for later calls
- * until scan_graph_destroy (scan_graph_device_bytes counts them).  A call
+ * until scan_graph_destroy (scan_graph_device_bytes counts them).  A graph that
+ * counts triangles (see scan_graph_create) has the edge counts once: there
+ * overlapping calls take turns on the device, in the order they came.  A call
  * waits for the graph's own buffers instead when the graph was created with
  * device_budget_bytes and another set would exceed it (the graph's own
  * output and count staging counted as allocated).  Calls on a
@@ -107,7 +109,11 @@ void scan_opts_default(scan_opts* opts);
  * (GPUSCAN++ Section 5): the CSR stays in pinned host memory, only row_ptr and
  * the per-vertex state reside on the device, and every run streams blocks of
  * rows and their edges through buffers that fit the budget.  Results are
- * identical on both paths.
+ * identical on both paths.  A graph created without a budget, with strategy 0
+ * and pruning 1, instead keeps every edge once in the row of the endpoint of
+ * the lower degree and counts all triangles in one pass (the same results);
+ * graphs that this layout does not take (a row above 4096 entries, or too
+ * little device memory) keep the edge list.
  *   n        number of vertices, n >= 0
  *   nnz      number of arcs (= 2 |E|)
  *   row_ptr  host int64[n+1], row_ptr[0] = 0, row_ptr[n] = nnz, non-decreasing
@@ -177,6 +183,7 @@ int scan_run_device(scan_graph* g, int64_t eps_num, int64_t eps_den, int32_t mu,
  * The run needs about 17 bytes per vertex, 1 byte per edge and 4 bytes per
  * edge of the LDS-hash bucket, each part rounded up to 256 bytes; a graph that
  * needs more than the 64 MiB is refused with SCAN_E_NOMEM (nothing is run).
+ * (A graph that counts triangles holds the scratch of its counts itself.)
  * All calls on one device share its array and each call leaves its contents
  * there: calls that overlap on one device race and must be serialised by the
  * caller.  Only kernels are enqueued (no memset, copy or event).  With
@@ -219,12 +226,13 @@ enum { SCAN_NUM_BUCKETS = 7 };
 typedef struct scan_stats {
   double ms_total;                        /* device time of the whole call */
   double ms_phase[SCAN_NUM_PHASES];       /* device time per phase */
-  double ms_cores_bucket[SCAN_NUM_BUCKETS]; /* similarity/core kernel, per degree bucket */
+  double ms_cores_bucket[SCAN_NUM_BUCKETS]; /* similarity/core kernel, per degree bucket
+                                               (0 where the buckets share a launch) */
   int64_t edges;                          /* undirected edges m */
   int64_t bucket_edges[SCAN_NUM_BUCKETS]; /* edges per degree bucket */
   int64_t evaluated[SCAN_NUM_PHASES];     /* edges intersected, per phase */
   int64_t bounded[SCAN_NUM_PHASES];       /* edges decided dissimilar by |N[u]&N[v]| <= min(a,b) */
-  int64_t probes[SCAN_NUM_PHASES];        /* smaller-list elements consumed by intersections */
+  int64_t probes[SCAN_NUM_PHASES];        /* list elements looked up by intersections */
   int64_t cores_bucket_evaluated[SCAN_NUM_BUCKETS];
   int64_t cores_bucket_probes[SCAN_NUM_BUCKETS];
   int64_t h2d_bytes;                      /* partitioned path: bytes streamed to the device */
@@ -303,7 +311,10 @@ int scan_server_destroy(scan_server* s);
  * the intersection (4 to 64 lanes per edge, or a wave with an LDS hash set for
  * the two buckets whose smaller side has more than 32 neighbours), and the
  * edges per tile; SCAN_AUTOTUNE_CACHE names an optional file that caches the
- * choice by batch shape.
+ * choice by batch shape.  That kernel serves batches created with
+ * SCAN_BATCH_WATCHDOG_US set and those that the triangle layout does not take;
+ * all others run the kernels of a single graph on the union, captured in the
+ * same way, and have nothing to tune.
  */
 typedef struct scan_batch {
   int32_t num_graphs;       /* G >= 0 */
