@@ -507,9 +507,14 @@ __global__ __launch_bounds__(256) void k_tri_buckets(int64_t lines, const int32_
 // ---------------------------------------------------------------------------
 // Counting
 
-// w of lane `to` = x (x and `to` uniform).
+// w of lane `to` = x (x and `to` uniform).  The write-lane instruction has no
+// builtin, so its intrinsic is declared by name.  Not an asm statement: x comes
+// from a compare, and a vector instruction may read a compare's scalar result
+// only two wait states later, which the compiler sees to only for instructions
+// that it can see (as asm it directly followed the compare in 24 places).
+__device__ int32_t write_lane(int32_t x, int32_t to, int32_t old) __asm("llvm.amdgcn.writelane.i32");
 __device__ __forceinline__ void set_lane(uint32_t& w, uint32_t x, const int to) {
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(w) : "s"(x), "i"(to));
+  w = (uint32_t)write_lane((int32_t)x, to, (int32_t)w);
 }
 
 // Accesses through a buffer descriptor that ends where the record ends: loads
