@@ -1245,6 +1245,14 @@ inline unsigned grid_for(int64_t items, int64_t per_block) {
   return (unsigned)(b < 1 ? 1 : b);
 }
 
+// HIP launches fewer than 2^32 threads at once.
+inline bool launchable(int64_t blocks, int64_t threads) { return blocks * threads < (int64_t)1 << 32; }
+
+// Blocks of the counting kernel: its jobs' and its waves' rows'.
+int64_t count_blocks(const TriLayout& T) {
+  return T.jobs == 0 ? (T.wave_rows + 3) / 4 : T.jobs + (T.wave_rows + kTriBlock / 64 - 1) / (kTriBlock / 64);
+}
+
 uint32_t tri_acc_cap(const TriLayout& T) { return ((uint32_t)T.max_row + 2 + 3) & ~3u; }
 
 // Dynamic LDS of the counting kernel: of a job, counters, then the largest table
@@ -1346,6 +1354,9 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
                      const int32_t* d_ci, const TriGroups* groups, TriLayout* out, int64_t* bucket_edges, int* ok) {
   *ok = 0;
   if (n <= 0 || nnz <= 0 || nnz / 2 >= (int64_t)1 << 31) return hipSuccess;
+  // The kernels below take a wave per vertex: up to 67,108,860 vertices (more than
+  // that seldom fit the limit on lines either, one per vertex and up).
+  if (!launchable(grid_for(n, 4), 256)) return hipSuccess;
   TriLayout T;
   T.n = n;
   hipError_t e = hipSuccess;
@@ -1520,6 +1531,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   T.wave_rows = tot[1];
   T.max_hash_row = h_ctl[2];
   T.steps = (int64_t)h_sums[0];
+  if (!launchable(count_blocks(T), T.jobs == 0 ? 256 : kTriBlock)) goto done;
   for (int k = 0; k < kNumBuckets; ++k) bucket_edges[k] = (int64_t)h_sums[1 + k];
   {
     Arena jobs;
@@ -1561,7 +1573,7 @@ void tri_threshold(hipStream_t s, const TriLayout& T, const TriScratch& S, const
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
   if (T.jobs == 0) {
     if (T.wave_rows == 0) return;
-    const unsigned grid = grid_for(T.wave_rows, 4);
+    const unsigned grid = (unsigned)count_blocks(T);
     if (T.span <= kTriShort)
       k_tri_wave<<<grid, 256, 0, s>>>(T.wave_rows, T.wrow, T.rec, T.oc16, T.lines, S.bits, S.cnt);
     else
@@ -1569,7 +1581,7 @@ void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
                                       S.bits, S.cnt);
     return;
   }
-  const uint64_t blocks = (uint64_t)T.jobs + (uint64_t)(T.wave_rows + kTriBlock / 64 - 1) / (kTriBlock / 64);
+  const uint64_t blocks = (uint64_t)count_blocks(T);
   // rounded up: exactly T.jobs of the products blocks * ratio step over a whole number
   const uint64_t ratio = (((uint64_t)T.jobs << 32) + blocks - 1) / blocks;
   const auto launch = T.span <= kTriShort ? k_tri_count<uint16_t> : k_tri_count<uint32_t>;

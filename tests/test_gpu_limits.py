@@ -1,0 +1,54 @@
+"""Sizes around the limits of the triangle layout: beyond them a graph keeps the
+edge list, with the same results."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+import paper_2311_12281_amd as S
+from gpu_helpers import assert_same, note
+
+pytestmark = pytest.mark.gpu
+
+
+def _spread(n):
+    """Few edges over n vertices: a small graph whose vertices are moved, in order, to ids from one end
+    to the other.  The graph, the ids and the small graph."""
+    small = gg.planted(400, 8, 0.5, 0.01, 5)
+    ids = np.linspace(0, n - 1, small.n).astype(np.int64)
+    row_ptr = np.zeros(n + 1, np.int64)
+    row_ptr[ids + 1] = small.degrees()
+    np.cumsum(row_ptr, out=row_ptr)
+    return gg.CSR(n, row_ptr, ids[small.col_idx].astype(np.int32)), ids, small
+
+
+def _check(labels, roles, ids, small, p, q, mu, ctx):
+    ol, orr = oracle.scan(small, p, q, mu)
+    assert_same(labels[ids], roles[ids], np.where(ol < 0, -1, ids[ol]).astype(np.int32), orr, ctx)
+    assert np.count_nonzero(roles) == np.count_nonzero(orr) and np.count_nonzero(labels >= 0) == np.count_nonzero(ol >= 0)
+
+
+@pytest.mark.parametrize("n", [67_108_860, 67_108_861])
+def test_vertex_limit(n):
+    """A wave per vertex is 2^32 threads from 67,108,861 vertices on, more than a launch takes."""
+    g, ids, small = _spread(n)
+    note("vertices", n)
+    with S.Graph.from_csr(g) as G:
+        assert np.array_equal(G.similarity(), oracle.counts(small))
+        for (p, q), mu in [((1, 2), 3), ((1, 5), 5)]:
+            _check(*G.run(p, q, mu), ids, small, p, q, mu, f"n={n} eps={p}/{q}")
+
+
+def test_vertex_limit_in_a_batch_and_a_server():
+    g, ids, small = _spread(67_108_700)
+    note("batch of", g.n + small.n, "vertices")
+    with S.Batch([g, small], [(1, 2), (1, 5)], [3, 5]) as B:
+        labels, roles = B.run()
+        (l0, l1), (r0, r1) = B.split(labels), B.split(roles)
+        _check(l0, r0, ids, small, 1, 2, 3, "batch, first")
+        assert_same(l1, r1, *oracle.scan(small, 1, 5, 5), "batch, second")
+    g, ids, small = _spread(67_108_861)
+    note("server", g.n)
+    with S.Server(num_slots=1) as srv:
+        gid = srv.add(g)
+        _check(*srv.wait(srv.submit(gid, 1, 2, 3), gid)[:2], ids, small, 1, 2, 3, "server")
