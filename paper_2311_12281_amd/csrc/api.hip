@@ -59,7 +59,7 @@ void release(scan_graph* g) {
   tri_release(g->tri);
   tri_release_scratch(g->tri_s);
   tri_release_scratch(g->tri_na);
-  if (g->tri_ev) hipEventDestroy(g->tri_ev);
+  if (g->tri_turn.ev) hipEventDestroy(g->tri_turn.ev);
   if (g->state_mem) {
     hipFree(g->state_mem);
     g->d_lower = g->d_upper = g->d_parent = g->d_label = nullptr;
@@ -290,46 +290,21 @@ int scan::check_params(const scan_graph* g, int64_t& p, int64_t& q, int32_t mu) 
 
 namespace {
 
-// The graph's triangle scratch on stream s for the life of this object: work
-// enqueued on s meanwhile starts after the work of the calls that hold it now.
-// (A call waits for its stream before it lets go, so that without overlapping
-// calls nothing is recorded or waited for.)
-class TriTurn {
- public:
-  TriTurn(scan_graph* g, hipStream_t s) : g_(g), lk_(g->tri_lock) {
-    if (g->tri_inflight > 0 && g->tri_stream != s) {
-      err_ = hipEventRecord(g->tri_ev, g->tri_stream);
-      if (err_ == hipSuccess) err_ = hipStreamWaitEvent(s, g->tri_ev, 0);
-    }
-    g->tri_stream = s;
-    ++g->tri_inflight;
-  }
-  hipError_t error() const { return err_; }
-  void enqueued() { lk_.unlock(); }  // everything is on the stream
-  ~TriTurn() {
-    if (!lk_.owns_lock()) lk_.lock();
-    --g_->tri_inflight;
-  }
-
- private:
-  scan_graph* g_;
-  std::unique_lock<std::mutex> lk_;
-  hipError_t err_ = hipSuccess;
-};
-
 // One clustering through the triangle path, in R, waited for.
 int run_tri(scan_graph* g, int64_t p, int64_t q, int32_t mu, int32_t* d_labels, uint8_t* d_roles, hipStream_t s,
             const RunState& R, hipEvent_t* ev) {
   const bool timing = g->opts.timing != 0;
-  TriTurn turn(g, s);
-  if (turn.error() != hipSuccess) return fail_hip(turn.error(), "wait for an overlapping call");
+  Turn turn(g->tri_turn, s, true);
+  HIP_TRY(turn.error(), "wait for an overlapping call");
   TriArgs a;
   a.p = (uint64_t)p;
   a.q = (uint64_t)q;
   a.mu = mu;
   enqueue_tri(g, g->tri_s, a, d_labels, d_roles, s, R, timing ? ev : nullptr);
-  turn.enqueued();
-  return collect_stats(g, s, timing, R, ev);
+  HIP_TRY(turn.enqueued(), "hipEventRecord");
+  const int rc = collect_stats(g, s, timing, R, ev);
+  if (rc == SCAN_OK) turn.done();
+  return rc;
 }
 
 // Validates eps and mu and runs the in-memory or partitioned clustering.
@@ -479,18 +454,19 @@ hipError_t scan::copy_out(void* dst, const void* src, size_t bytes, hipStream_t 
 int scan::run_counts(scan_graph* g, int32_t* d_counts_arc, int32_t* d_counts_edge, hipStream_t s, int32_t* h_counts) {
   const bool timing = g->opts.timing != 0;
   if (g->has_tri) {
-    TriTurn turn(g, s);
-    if (turn.error() != hipSuccess) return fail_hip(turn.error(), "wait for an overlapping call");
+    Turn turn(g->tri_turn, s, false);
+    HIP_TRY(turn.error(), "wait for an overlapping call");
     if (timing) hipEventRecord(g->ev[0], s);
     tri_init(s, g->tri, g->tri_s, nullptr, nullptr, nullptr, nullptr);
     tri_count(s, g->tri, g->tri_s);
     tri_close(s, g->tri, g->tri_s, TriArgs{}, nullptr);
     if (d_counts_arc) tri_arc_counts(s, g->tri, g->tri_s, g->nnz, g->d_rp, g->d_ci, d_counts_arc);
     if (timing) hipEventRecord(g->ev[1], s);
-    turn.enqueued();
+    HIP_TRY(turn.enqueued(), "hipEventRecord");
     HIP_TRY(hipGetLastError(), "kernel launch");
     if (h_counts) HIP_TRY(copy_out(h_counts, d_counts_arc, sizeof(int32_t) * (size_t)g->nnz, s), "copy counts");
     HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    turn.done();
     scan_stats L;
     memset(&L, 0, sizeof(L));
     L.edges = L.evaluated[SCAN_PHASE_CORES] = g->m;
@@ -683,7 +659,7 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
     }
     if (g->opts.timing)
       for (auto& ev : g->ev) CTRY(hipEventCreate(&ev), "hipEventCreate");
-    CTRY(hipEventCreateWithFlags(&g->tri_ev, hipEventDisableTiming), "hipEventCreate");
+    CTRY(hipEventCreateWithFlags(&g->tri_turn.ev, hipEventDisableTiming), "hipEventCreate");
     *out = g;
     return SCAN_OK;
   }

@@ -4,6 +4,7 @@
 
 #include "scan_internal.h"
 #include "tri.h"
+#include "turn.h"
 #include "../../include/scan.h"
 
 #include <atomic>
@@ -134,10 +135,7 @@ struct scan_graph {
   TriLayout tri;
   TriScratch tri_s;                 // of the calls on the graph's own and pooled buffer sets, in turn
   TriScratch tri_na;                // of scan_run_device_noalloc
-  std::mutex tri_lock;              // the three below
-  int tri_inflight = 0;             // calls using tri_s
-  hipStream_t tri_stream = nullptr; // stream of the last of them
-  hipEvent_t tri_ev = nullptr;
+  TurnState tri_turn;               // of tri_s
   hipEvent_t ev[SCAN_NUM_PHASES + kNumBuckets + 2] = {};
   std::mutex lock;  // the graph's own per-run buffers, staging and events (one call at a time)
   // buffer sets of calls that find the graph's own ones in use
