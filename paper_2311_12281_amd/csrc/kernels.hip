@@ -1758,14 +1758,20 @@ inline unsigned blocks_for(int64_t items, int64_t per_block, int64_t cap) {
 // lived waves do better; the wider groups keep more waves in flight.
 constexpr int64_t kGroupGridCap[kNumBuckets] = {2048, 2048, 4096, 8192, 8192, 8192, 8192};
 
-// Edges a wave takes at a time: 64, or as few as it takes to have kGroupWaves
-// waves (eight on every SIMD), but no fewer than one per group of the wave.  A
-// partitioned graph's bucket of 30 thousand edges and 64 lanes each ran 470
-// waves of up to 64 intersections in a row: 103 us.
-constexpr int64_t kGroupWaves = 8192;
-inline int group_chunk(int64_t m, int lanes) {
+// Edges a wave takes at a time: 64, or as few as it takes to have `waves` waves,
+// but no fewer than one per group of the wave.  A partitioned graph's bucket of
+// 30 thousand edges and 64 lanes each ran 470 waves of up to 64 intersections in
+// a row: 103 us.  In the launch that all its buckets share (and which bounds its
+// blocks) 8192 waves, eight on every SIMD, did best.  A bucket launched alone gets
+// two on every SIMD: at high thresholds nearly all edges are settled by their
+// degrees, and then more blocks only add their pass counters to the same few
+// addresses (planted, n = 10 thousand, eps 4/5, in chunks of 64 edges 192 us, for
+// 8192 waves 234, for 2048 163; R-MAT 15 315 / 404 / 276, R-MAT 17 474 / 578 / 484;
+// at eps 1/5 381 / 393 / 328, 964 / 838 / 759, 1167 / 1203 / 1155).
+constexpr int64_t kGroupWavesShared = 8192, kGroupWavesAlone = 2048;
+inline int group_chunk(int64_t m, int lanes, int64_t waves) {
   int per = 64;
-  while (per > 64 / lanes && m < per * kGroupWaves) per >>= 1;
+  while (per > 64 / lanes && m < per * waves) per >>= 1;
   return per;
 }
 
@@ -1773,7 +1779,7 @@ template <int MODE>
 void launch_edges_mode(hipStream_t s, int bucket, const EdgeArgs& a) {
   const int64_t m = a.e_end - a.e_begin;
   if (m <= 0) return;
-  const int per = group_chunk(m, bucket < 4 ? 4 << bucket : 64);
+  const int per = group_chunk(m, bucket < 4 ? 4 << bucket : 64, kGroupWavesAlone);
   const unsigned grid =
       blocks_for(m, per * (kBlock / 64), kGroupGridCap[bucket >= 0 && bucket < kNumBuckets ? bucket : kNumBuckets - 1]);
   switch (bucket) {
@@ -1802,7 +1808,7 @@ template <int MODE>
 void launch_edges_width(hipStream_t s, int lanes, const EdgeArgs& a) {
   const int64_t m = a.e_end - a.e_begin;
   if (m <= 0) return;
-  const int per = group_chunk(m, lanes);
+  const int per = group_chunk(m, lanes, kGroupWavesAlone);
   const unsigned grid = blocks_for(m, per * (kBlock / 64), 8192);
   switch (lanes) {
     case 4: k_group<MODE, 4><<<grid, kBlock, 0, s>>>(a, per); break;
@@ -1845,7 +1851,7 @@ void launch_groups(hipStream_t s, int mode, const int64_t* off, const EdgeArgs& 
     const int64_t m = off[b + 1] - off[b];
     S.begin[k] = off[b];
     S.end[k] = off[b + 1];
-    S.per[k] = group_chunk(m, b < 4 ? 4 << b : 64);
+    S.per[k] = group_chunk(m, b < 4 ? 4 << b : 64, kGroupWavesShared);
     want[k] = m > 0 ? blocks_for(m, S.per[k] * (kBlock / 64), kGroupGridCap[b]) : 0;
     all += want[k];
   }
