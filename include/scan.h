@@ -111,9 +111,10 @@ void scan_opts_default(scan_opts* opts);
  * rows and their edges through buffers that fit the budget.  Results are
  * identical on both paths.  A graph created without a budget, with strategy 0
  * and pruning 1, instead keeps every edge once in the row of the endpoint of
- * the lower degree and counts all triangles in one pass (the same results);
- * graphs that this layout does not take (a row above 4096 entries, or too
- * little device memory) keep the edge list.
+ * the lower degree and counts all triangles in one pass (the same results).
+ * Its device memory stays within five times scan_graph_footprint plus 512 MiB;
+ * graphs that it does not take (more memory than that or than the device has, a
+ * row above 4096 entries, 67,108,861 vertices and more) keep the edge list.
  *   n        number of vertices, n >= 0
  *   nnz      number of arcs (= 2 |E|)
  *   row_ptr  host int64[n+1], row_ptr[0] = 0, row_ptr[n] = nnz, non-decreasing
@@ -129,13 +130,17 @@ int scan_graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int3
 /* Releases every device and host resource of the graph.  NULL is accepted. */
 int scan_graph_destroy(scan_graph* g);
 
-/* Upper bound of the device bytes scan_graph_create allocates for an in-memory
- * graph of n vertices and nnz arcs under opts (NULL = defaults): row offsets,
+/* Upper bound of the device bytes that the edge list of an in-memory graph of n
+ * vertices and nnz arcs takes under opts (NULL = defaults): row offsets,
  * neighbour ids (and their degree-ranked copy when opts->hub_ranked is set and
  * n > 2^19) with every 32nd id sampled, the oriented edge list with the degrees of both ends of each
  * edge, its worklist and edge states, per-vertex
  * state and output staging, plus 1 MiB for small tables.  A graph created with
- * device_budget_bytes below this value takes the partition-based path. */
+ * device_budget_bytes of this value or more holds no more than that; below it,
+ * the graph takes the partition-based path.  A graph created without a budget may
+ * count triangles instead (see above) and then holds more: up to five times this
+ * value plus 512 MiB, with host outputs and counts taken and no overlapping calls
+ * (scan_graph_device_bytes tells). */
 int scan_graph_footprint(int32_t n, int64_t nnz, const scan_opts* opts, uint64_t* bytes);
 
 /* Sizes of a created graph: vertices, arcs, undirected edges, maximum degree. */

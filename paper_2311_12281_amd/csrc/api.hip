@@ -619,11 +619,25 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
   CTRY(check_csr(g->stream, n, nnz, g->d_rp, g->d_ci, g->opts.validate, &lay), "layout");
   // The triangle path, unless the options ask for the exhaustive or the
   // binary-search kernels, or bound the device memory (its scratch grows with
-  // the pairs of row entries, which scan_graph_footprint cannot know).
+  // the pairs of row entries, which scan_graph_footprint cannot know).  Nor where it
+  // would hold more than five footprints and 512 MiB, the bound that scan.h states
+  // for graphs without a budget: the graphs beyond it are those whose rows have
+  // about a thousand entries and more, or fewer than one on average over millions
+  // of vertices.  Dense ones were also slower on it at low thresholds: 4,000 vertices,
+  // each pair an edge with probability 0.9, 6.0 ms at every threshold and 3.6 GB
+  // against 0.7 to 2.6 ms and 0.27 GB on the edge list; 10,000 vertices of degree
+  // 2,000 (20 words of bits an edge) 4.4 against 2.3 to 2.6 ms up to eps 1/2, 3.6
+  // against 5.2 to 8.6 above; of degree 1,000 (11 words), which stay, 2.8 and 2.1
+  // against 2.5 and 4.  (A clique of 4,000 takes 3.6 to 15.9 instead of 7.4 ms, and 0.3 GB
+  // instead of 4.4.)
   if (tri && !lay.error && g->opts.pruning && g->opts.strategy == 0 && !g->opts.device_budget_bytes) {
     int64_t be[kNumBuckets];
     int ok = 0;
-    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, groups, &g->tri, be, &ok);
+    const uint64_t most = 5 * inmemory_footprint(n, nnz, g->opts.hub_ranked != 0) + (512ull << 20);
+    const uint64_t rest = 8 * ((uint64_t)n + 1) + 8 * ((uint64_t)nnz + kColPad) + 22 * (uint64_t)n;  // rows, state, staging
+    // whether a second scratch may be allocated below
+    const bool may_noalloc = !groups && 17 * (uint64_t)n + (uint64_t)nnz / 2 <= kNoallocScratch;
+    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, groups, may_noalloc ? 2 : 1, most - rest, &g->tri, be, &ok);
     if (e == hipSuccess && ok) e = tri_alloc_scratch(g->tri, &g->tri_s);
     if (e == hipSuccess && ok) {
       g->has_tri = true;

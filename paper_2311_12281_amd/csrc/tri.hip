@@ -1293,12 +1293,27 @@ class Arena {
 
 }  // namespace
 
-uint64_t tri_layout_bytes(const TriLayout& T) {
+namespace {
+
+uint64_t row_bytes(const TriLayout& T) {  // per vertex and per line
   const uint64_t n = (uint64_t)T.n, L = (uint64_t)T.lines;
-  return 16 * n + 8 * (n + 1) + 20 * L + 4 * (L + 2) * kTriLine + (T.oc16 ? 2 * (L + 2) * kTriLine : 0) +
-         (T.rec ? sizeof(TriRec) * (uint64_t)T.recs : 0) + (T.job ? sizeof(TriJob) * (uint64_t)T.jobs : 0) +
-         (T.wrow ? sizeof(TriWave) * (uint64_t)T.wave_rows : 0);
+  return 16 * n + 8 * (n + 1) + 20 * L + 4 * (L + 2) * kTriLine;
 }
+
+uint64_t input_bytes(const TriLayout& T) {  // what tri_drop_inputs frees
+  return 2 * ((uint64_t)T.lines + 2) * kTriLine + sizeof(TriRec) * (uint64_t)T.recs + sizeof(TriJob) * (uint64_t)T.jobs +
+         sizeof(TriWave) * (uint64_t)T.wave_rows;
+}
+
+// A layout of T's sizes and its scratches.
+uint64_t tri_bytes(const TriLayout& T, int scratches) {
+  const uint64_t L = (uint64_t)T.lines;
+  return row_bytes(T) + input_bytes(T) + (uint64_t)scratches * (4 * L * kTriLine + 4 * (uint64_t)T.words + 4 * L + 4);
+}
+
+}  // namespace
+
+uint64_t tri_layout_bytes(const TriLayout& T) { return row_bytes(T) + (T.oc16 ? input_bytes(T) : 0); }
 
 uint64_t tri_scratch_bytes(const TriLayout& T, const TriScratch& S) {
   const uint64_t L = (uint64_t)T.lines;
@@ -1351,7 +1366,8 @@ hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S) {
 }
 
 hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
-                     const int32_t* d_ci, const TriGroups* groups, TriLayout* out, int64_t* bucket_edges, int* ok) {
+                     const int32_t* d_ci, const TriGroups* groups, int scratches, uint64_t max_bytes, TriLayout* out,
+                     int64_t* bucket_edges, int* ok) {
   *ok = 0;
   if (n <= 0 || nnz <= 0 || nnz / 2 >= (int64_t)1 << 31) return hipSuccess;
   // The kernels below take a wave per vertex: up to 67,108,860 vertices (more than
@@ -1483,6 +1499,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 26 || T.words >= (int64_t)1 << 30 ||
       T.recs >= (int64_t)1 << 32 || (int64_t)h_sums[1 + kNumBuckets] != nnz / 2)
     goto done;
+  if (tri_bytes(T, scratches) > max_bytes) goto done;
   k_narrow<<<gv, 256, 0, s>>>(n, at0, at1, T.oline, T.wbase);
   {
     Arena rows, inputs;
@@ -1531,6 +1548,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   T.wave_rows = tot[1];
   T.max_hash_row = h_ctl[2];
   T.steps = (int64_t)h_sums[0];
+  if (tri_bytes(T, scratches) > max_bytes) goto done;  // with the jobs
   if (!launchable(count_blocks(T), T.jobs == 0 ? 256 : kTriBlock)) goto done;
   for (int k = 0; k < kNumBuckets; ++k) bucket_edges[k] = (int64_t)h_sums[1 + k];
   {
