@@ -573,6 +573,7 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
   std::vector<uint32_t> wtab;
   std::vector<int32_t> ranked;
   int32_t* d_src = nullptr;
+  const size_t stride = ((size_t)n + 63) & ~(size_t)63;  // of the arrays in state_mem
 #define CTRY(call, what)                         \
   do {                                           \
     e = (call);                                  \
@@ -639,6 +640,7 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
     const bool may_noalloc = !groups && 17 * (uint64_t)n + (uint64_t)nnz / 2 <= kNoallocScratch;
     e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, groups, may_noalloc ? 2 : 1, most - rest, &g->tri, be, &ok);
     if (e == hipSuccess && ok) e = tri_alloc_scratch(g->tri, &g->tri_s);
+    if (e == hipSuccess && ok) e = hipMalloc(&g->state_mem, 17 * stride);
     if (e == hipSuccess && ok) {
       g->has_tri = true;
       for (int k = 0; k < kNumBuckets; ++k) g->bucket_off[k + 1] = g->bucket_off[k] + be[k];
@@ -649,6 +651,8 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
       (void)hipGetLastError();
       tri_release(g->tri);
       tri_release_scratch(g->tri_s);
+      if (g->state_mem) (void)hipFree(g->state_mem);
+      g->state_mem = nullptr;
       g->has_tri = false;
       e = hipSuccess;
     }
@@ -660,17 +664,12 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
       rc = fail(SCAN_E_GRAPH, "edge count %lld does not match nnz/2", (long long)g->m);
       goto error;
     }
-    {
-      const size_t stride = ((size_t)n + 63) & ~(size_t)63;
-      int32_t* p = nullptr;
-      CTRY(hipMalloc(&g->state_mem, 17 * stride), "hipMalloc");
-      p = static_cast<int32_t*>(g->state_mem);
-      g->d_lower = p;
-      g->d_upper = p + stride;
-      g->d_parent = p + 2 * stride;
-      g->d_label = p + 3 * stride;
-      g->d_role = reinterpret_cast<uint8_t*>(p + 4 * stride);
-    }
+    int32_t* const p = static_cast<int32_t*>(g->state_mem);
+    g->d_lower = p;
+    g->d_upper = p + stride;
+    g->d_parent = p + 2 * stride;
+    g->d_label = p + 3 * stride;
+    g->d_role = reinterpret_cast<uint8_t*>(p + 4 * stride);
     if (g->opts.timing)
       for (auto& ev : g->ev) CTRY(hipEventCreate(&ev), "hipEventCreate");
     CTRY(hipEventCreateWithFlags(&g->tri_turn.ev, hipEventDisableTiming), "hipEventCreate");

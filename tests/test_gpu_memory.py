@@ -51,3 +51,4 @@ def test_within_the_stated_bound(name):
         held = G.device_bytes()
         note(f"{held / 1e6:.0f} MB of {most / 1e6:.0f}")
         assert held <= most
+
