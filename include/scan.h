@@ -188,7 +188,8 @@ int scan_run_device(scan_graph* g, int64_t eps_num, int64_t eps_den, int32_t mu,
  * The run needs about 17 bytes per vertex, 1 byte per edge and 4 bytes per
  * edge of the LDS-hash bucket, each part rounded up to 256 bytes; a graph that
  * needs more than the 64 MiB is refused with SCAN_E_NOMEM (nothing is run).
- * (A graph that counts triangles holds the scratch of its counts itself.)
+ * (A graph that counts triangles has the scratch of its counts in the array too
+ * where it fits beside those, and else holds one itself.)
  * All calls on one device share its array and each call leaves its contents
  * there: calls that overlap on one device race and must be serialised by the
  * caller.  Only kernels are enqueued (no memset, copy or event).  With

@@ -645,7 +645,8 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
       g->has_tri = true;
       for (int k = 0; k < kNumBuckets; ++k) g->bucket_off[k + 1] = g->bucket_off[k] + be[k];
       g->m = g->bucket_off[kNumBuckets];
-      if (!groups && noalloc_bytes(g) <= kNoallocScratch) e = tri_alloc_scratch(g->tri, &g->tri_na);
+      if (!groups && noalloc_bytes(g) <= kNoallocScratch && !noalloc_holds_scratch(g))
+        e = tri_alloc_scratch(g->tri, &g->tri_na);
     }
     if (e == hipErrorOutOfMemory) {  // no room: the edge list takes less
       (void)hipGetLastError();

@@ -134,7 +134,7 @@ struct scan_graph {
   void* state_mem = nullptr;        // holds d_lower .. d_label of a triangle-path graph
   TriLayout tri;
   TriScratch tri_s;                 // of the calls on the graph's own and pooled buffer sets, in turn
-  TriScratch tri_na;                // of scan_run_device_noalloc
+  TriScratch tri_na;                // of scan_run_device_noalloc, where its static array does not hold one
   TurnState tri_turn;               // of tri_s
   hipEvent_t ev[SCAN_NUM_PHASES + kNumBuckets + 2] = {};
   std::mutex lock;  // the graph's own per-run buffers, staging and events (one call at a time)
@@ -183,6 +183,8 @@ int graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* 
 // Device bytes a noalloc call's per-run buffers take in the static scratch.
 uint64_t noalloc_bytes(const scan_graph* g);
 constexpr uint64_t kNoallocScratch = 64ull << 20;
+// Whether the static scratch holds the triangle path's scratch too.
+bool noalloc_holds_scratch(const scan_graph* g);
 // Checks eps = p/q and mu against the graph (Def 2.3, Def 2.4, the 64-bit
 // range of the test) and reduces p/q; SCAN_OK or the error code.
 int check_params(const scan_graph* g, int64_t& p, int64_t& q, int32_t mu);

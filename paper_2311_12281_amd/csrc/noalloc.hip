@@ -47,8 +47,8 @@ int scratch_address(int device, unsigned char** out) {
 constexpr uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
 
 // Bytes of the scratch a run on g needs, and the run state laid out from base
-// (base may be null to size only).
-uint64_t layout_state(const scan_graph* g, unsigned char* base, RunState* R) {
+// (base may be null to size only).  *vertices: where the per-vertex buffers end.
+uint64_t layout_state(const scan_graph* g, unsigned char* base, RunState* R, uint64_t* vertices = nullptr) {
   const uint64_t n = (uint64_t)(g->n > 0 ? g->n : 1);
   const uint64_t m = (uint64_t)(g->m > 0 ? g->m : 1);
   const int64_t w = g->bucket_off[kNumBuckets] - g->bucket_off[kNumBuckets - 1];
@@ -67,6 +67,7 @@ uint64_t layout_state(const scan_graph* g, unsigned char* base, RunState* R) {
   r.parent = reinterpret_cast<int32_t*>(take(4 * n));
   r.label = reinterpret_cast<int32_t*>(take(4 * n));
   r.role = take(n);
+  if (vertices) *vertices = off;
   r.state = take(m);
   r.worklist = reinterpret_cast<int32_t*>(take(4 * wl));
   if (R) *R = r;
@@ -76,6 +77,13 @@ uint64_t layout_state(const scan_graph* g, unsigned char* base, RunState* R) {
 }  // namespace
 
 uint64_t scan::noalloc_bytes(const scan_graph* g) { return layout_state(g, nullptr, nullptr); }
+
+// (The triangle path has no edge states and no worklist: its scratch takes their place.)
+bool scan::noalloc_holds_scratch(const scan_graph* g) {
+  uint64_t at = 0;
+  layout_state(g, nullptr, nullptr, &at);
+  return at + tri_place_scratch(g->tri, nullptr, nullptr) <= kScratchBytes;
+}
 
 extern "C" {
 
@@ -101,14 +109,17 @@ int scan_run_device_noalloc(scan_graph* g, int64_t eps_num, int64_t eps_den, int
   rc = scratch_address(dev, &base);
   if (rc != SCAN_OK) return rc;
   RunState R{};
-  layout_state(g, base, &R);
+  uint64_t at = 0;
+  layout_state(g, base, &R, &at);
   hipStream_t s = stream ? (hipStream_t)stream : g->stream;
   if (g->has_tri) {
     TriArgs a;
     a.p = (uint64_t)p;
     a.q = (uint64_t)q;
     a.mu = mu;
-    enqueue_tri(g, g->tri_na, a, d_labels, d_roles, s, R, nullptr);
+    TriScratch T = g->tri_na;
+    if (!T.cnt) tri_place_scratch(g->tri, base + at, &T);
+    enqueue_tri(g, T, a, d_labels, d_roles, s, R, nullptr);
   } else {
     EdgeArgs A{};
     A.p = (uint64_t)p;

@@ -117,6 +117,9 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
                      int64_t* bucket_edges, int* ok);
 void tri_release(TriLayout& T);
 hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S);
+// Lays a scratch out at base (256-byte aligned; S null: to size only), which stays
+// the caller's; its bytes.
+uint64_t tri_place_scratch(const TriLayout& T, unsigned char* base, TriScratch* S);
 void tri_release_scratch(TriScratch& S);
 void tri_drop_work(TriScratch& S);  // all but the counts
 

@@ -1351,6 +1351,21 @@ void tri_release_scratch(TriScratch& S) {
   S = TriScratch();
 }
 
+uint64_t tri_place_scratch(const TriLayout& T, unsigned char* base, TriScratch* S) {
+  // (no container here: a no-alloc call must not allocate on the host either)
+  const uint64_t bytes[4] = {4 * (uint64_t)T.lines * kTriLine, 4 * (uint64_t)T.words, 4 * (uint64_t)T.lines, 4};
+  uint64_t at[5] = {0};
+  for (int k = 0; k < 4; ++k) at[k + 1] = at[k] + ((bytes[k] + 255) & ~255ull);
+  if (S) {
+    *S = TriScratch();
+    S->cnt = reinterpret_cast<int32_t*>(base);
+    S->bits = reinterpret_cast<uint32_t*>(base + at[1]);
+    S->simw = reinterpret_cast<uint32_t*>(base + at[2]);
+    S->flag = reinterpret_cast<int32_t*>(base + at[3]);
+  }
+  return at[4];
+}
+
 hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S) {
   Arena work;
   work.take(&S->bits, T.words);
