@@ -600,17 +600,21 @@ int scan_server_add_graph(scan_server* S, int32_t n, int64_t nnz, const int64_t*
       return fail_hip(e, "slot scratch");
     }
     S->resident_bytes += S->slots.size() * (slot_bytes(new_n, new_m) - slot_bytes(S->slot_n, S->slot_m));
+    const bool wider = new_n > S->slot_n;
     S->slot_n = new_n;
     S->slot_m = new_m;
-    // a result buffer of the new capacity per slot, so that the first queries
-    // do not wait for them (failing that, they are allocated as needed)
-    for (auto& b : S->out_free) free_out(b);
-    S->out_total -= (int32_t)S->out_free.size();
-    S->out_free.clear();
-    while (S->out_free.size() < S->slots.size() && grow_out(S, lk)) {
+    if (wider) {
+      for (auto& b : S->out_free) free_out(b);
+      S->out_total -= (int32_t)S->out_free.size();
+      S->out_free.clear();
     }
     S->pause_dispatch = false;
     S->cv_work.notify_one();
+    // a result buffer of the new capacity per slot, so that the first queries
+    // do not wait for them (failing that, they are allocated as needed); the
+    // graphs that are there already are served meanwhile
+    while (wider && S->out_free.size() < S->slots.size() && grow_out(S, lk)) {
+    }
   }
   const int32_t gid = S->next_gid++;
   S->graphs[gid] = std::move(G);

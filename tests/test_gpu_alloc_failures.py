@@ -3,14 +3,9 @@ to fail (in a process of its own, where hipMalloc is counted on its way to the
 runtime).  A graph whose triangle layout cannot be had keeps the edge list, with
 the same results; only what every graph needs makes creation fail, and nothing
 stays allocated."""
-import os
-import shutil
-import subprocess
-import sys
-
 import pytest
 
-from paper_2311_12281_amd import build as B
+from hip_shim import run_child
 
 pytestmark = pytest.mark.gpu
 
@@ -85,14 +80,4 @@ print("OK")
 
 
 def test_each_allocation_fails_once(tmp_path):
-    cxx = shutil.which("g++")
-    if not cxx:
-        pytest.skip("no host compiler")
-    src, so, child = tmp_path / "shim.cpp", tmp_path / "shim.so", tmp_path / "child.py"
-    src.write_text(SHIM)
-    child.write_text(CHILD)
-    subprocess.run([cxx, "-O1", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
-    env = dict(os.environ, PYTHONPATH=B.ROOT + os.pathsep + os.environ.get("PYTHONPATH", ""))
-    r = subprocess.run([sys.executable, "-u", str(child), str(so)], cwd=B.ROOT, env=env, capture_output=True, text=True,
-                       timeout=100)
-    assert r.returncode == 0 and r.stdout.endswith("OK\n"), r.stdout[-1000:] + r.stderr[-2000:]
+    run_child(tmp_path, SHIM, CHILD)
