@@ -52,3 +52,31 @@ def test_vertex_limit_in_a_batch_and_a_server():
     with S.Server(num_slots=1) as srv:
         gid = srv.add(g)
         _check(*srv.wait(srv.submit(gid, 1, 2, 3), gid)[:2], ids, small, 1, 2, 3, "server")
+
+
+@pytest.mark.parametrize("n", [262_143, 262_144, 262_147])
+@pytest.mark.parametrize("hub", [2_048, 2_049, 70_000])
+def test_renaming_by_host_threads(n, hub):
+    """From 2^18 vertices on, host threads rename the vertices by degree (fewer where the largest degree
+    is high); rows above 2,048 arcs are laid out in chunks."""
+    rng = np.random.default_rng(n + hub)
+    src = [np.arange(n - 2), np.arange(n - 2), np.zeros(hub, np.int64) + 17]
+    dst = [np.arange(1, n - 1), np.arange(2, n), rng.choice(n, hub, replace=False)]
+    g = gg.from_pairs(n, np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32))
+    oc = oracle.counts(g, threads=oracle.max_threads())
+    note("renaming", n, hub)
+    with S.Graph.from_csr(g) as G:
+        assert np.array_equal(G.similarity(), oc)
+        for (p, q), mu in [((3, 5), 3), ((1, 4), 4)]:
+            assert_same(*G.run(p, q, mu), *oracle.cluster(g, oc, p, q, mu), f"n={n} hub={hub} eps={p}/{q}")
+
+
+def test_renaming_of_a_large_batch():
+    graphs = [gg.rmat(9 + k % 6, 8, seed=80 + k) for k in range(90)] + [gg.from_edges(0, []), gg.from_edges(3, [(0, 2)])]
+    assert sum(g.n for g in graphs) > 1 << 18
+    eps, mus = [(1 + k % 5, 8) for k in range(len(graphs))], [2 + k % 4 for k in range(len(graphs))]
+    note("renaming of a batch")
+    with S.Batch(graphs, eps, mus) as B:
+        labels, roles = B.run()
+        for k, (g, (p, q), mu, l, r) in enumerate(zip(graphs, eps, mus, B.split(labels), B.split(roles))):
+            assert_same(l, r, *oracle.scan(g, p, q, mu), f"graph {k} eps={p}/{q} mu={mu}")
