@@ -12,8 +12,8 @@ compared with the CPU oracle and the line reports whether all match exactly.
 
 roofline: the cores phase (the count and close kernels of the triangle path),
 which is nearly all of a solve; its algorithmic bytes are 2 per row entry
-looked up and, per edge, 16 of in-edge record, 4 of count, written and read,
-and 4 of neighbour, divided by its duration measured with HIP events on the
+looked up and 28 per edge (16 of in-edge record, 4 of count written and 4 read,
+4 of neighbour), divided by its duration measured with HIP events on the
 library's stream, against 8 TB/s.  A graph outside that path reports the
 edge-list kernel of the degree bucket with the most device time: 4 bytes per
 smaller-list element consumed and 9 per intersected edge.
@@ -195,7 +195,7 @@ def main():
     dom_name = f"{dom_kernel}: cores pass, degree bucket {dom}"
     if ms_b.sum() == 0:  # no pass per bucket: the triangle path
         launch_ms = sum(st["ms_phase"]["cores"] for st in stats) / launches
-        alg_bytes = sum(2.0 * st["probes"]["cores"] + 28.0 * m for st in stats) / launches
+        alg_bytes = sum(triangle_bytes(st, m) for st in stats) / launches
         achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
         dom_kernel = "k_tri_count+k_tri_close"
         dom_name = "k_tri_count and k_tri_close: cores phase"
@@ -206,8 +206,8 @@ def main():
     # every bucket's kernel against the same roofline, and the whole cores pass
     # (the intersection bytes above, and beside them the same plus the classification stream:
     # 8 bytes of endpoints, 8 of degrees and 1 of edge state for every edge of the bucket)
-    buckets = []
-    for b in range(nb):
+    buckets = []  # (of the triangle path: none, its kernels take all edges together)
+    for b in range(nb if ms_b.sum() else 0):
         ms_l = ms_b[b] / launches
         alg_l = bytes_b[b] / launches
         eb = int(stats[0]["bucket_edges"][b])
@@ -338,9 +338,14 @@ def main():
     print(json.dumps(line), flush=True)
 
 
+def triangle_bytes(stats, m):
+    """Algorithmic bytes of the triangle path's cores phase: 2 per row entry looked up and 28 per edge."""
+    return 2.0 * stats["probes"]["cores"] + 28.0 * m
+
+
 def solve_byte_models(g, stats_per_eps, traffic=None, alg_per_launch=None):
     """Byte models of a whole solve: the measured intersections (4 bytes per element consumed + 9 per
-    intersected edge, every bucket) plus each row read once as the probe side (4 nnz), the offsets
+    intersected edge, every bucket; on the triangle path, which reports no buckets, triangle_bytes) plus each row read once as the probe side (4 nnz), the offsets
     (8 (n + 1)) and the per-vertex state (17 n), one figure per run in stats_per_eps (their
     cores_bucket_probes and cores_bucket_evaluated); beside them, for a solve that evaluates every edge
     without pruning, whole smaller lists (4 sum_e min(d_u, d_v) + 9 m) and both lists (the merge model,
@@ -355,10 +360,14 @@ def solve_byte_models(g, stats_per_eps, traffic=None, alg_per_launch=None):
     sum_min = int(np.minimum(deg[src[own]], deg[dst[own]]).sum())
     sum_both = int((deg * deg).sum())
     fixed = 4.0 * int(g.nnz) + 8.0 * (n + 1) + 17.0 * n
+
+    def cores_bytes(st):
+        if not np.sum(st["cores_bucket_probes"]) and st.get("probes", {}).get("cores"):
+            return triangle_bytes(st, m)
+        return 4.0 * np.sum(st["cores_bucket_probes"]) + 9.0 * np.sum(st["cores_bucket_evaluated"])
+
     return {
-        "per_eps_probe_model_bytes": [
-            float(4.0 * np.sum(s_["cores_bucket_probes"]) + 9.0 * np.sum(s_["cores_bucket_evaluated"]) + fixed)
-            for s_ in stats_per_eps],
+        "per_eps_probe_model_bytes": [float(cores_bytes(st) + fixed) for st in stats_per_eps],
         "full_evaluation_min_model_bytes": 4.0 * sum_min + 9.0 * m + fixed,
         "full_evaluation_merge_model_bytes": 4.0 * sum_both,
         "dominant_kernel_traffic_over_alg": (traffic / alg_per_launch) if traffic and alg_per_launch else None,
@@ -386,6 +395,8 @@ LDS_COUNTERS = ["SQ_LDS_BANK_CONFLICT", "SQ_LDS_IDX_ACTIVE", "SQ_INSTS_LDS", "SQ
                 "SQ_WAVE_CYCLES", "SQ_BUSY_CYCLES", "SQ_WAIT_ANY"]
 ATOMIC_COUNTERS = ["TCC_ATOMIC_sum", "TCC_EA0_ATOMIC_sum", "TCP_TCC_ATOMIC_WITH_RET_REQ_sum",
                    "TCP_TCC_ATOMIC_WITHOUT_RET_REQ_sum"]
+HIT_COUNTERS = ["TCC_HIT_sum", "TCC_MISS_sum", "TCC_REQ_sum"]
+CLOCK_COUNTERS = ["GRBM_GUI_ACTIVE"]
 KERNEL_SOURCES = ["kernels.hip", "layout.hip", "api.hip", "scan_internal.h", "tri.hip", "tri.h", "device.h"]
 
 
@@ -493,6 +504,8 @@ rocprofv3 --pmc TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_64B_sum TCC_EA0_RDREQ_128B_s
 rocprofv3 --pmc TCC_EA0_RDREQ_DRAM_sum TCC_EA0_RDREQ_sum --output-format csv -d gpurun_out/pmc_dram -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
 rocprofv3 --pmc {' '.join(LDS_COUNTERS)} --output-format csv -d gpurun_out/pmc_lds -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
 rocprofv3 --pmc {' '.join(ATOMIC_COUNTERS)} --output-format csv -d gpurun_out/pmc_atomic -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc {' '.join(HIT_COUNTERS)} --output-format csv -d gpurun_out/pmc_hit -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc {' '.join(CLOCK_COUNTERS)} --output-format csv -d gpurun_out/pmc_clock -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
 {cmd}
 ```
 
@@ -539,6 +552,16 @@ those that went to DRAM:
             print(f"\n- LDS bank-conflict cycles per conflict-free LDS cycle: {bc / max(act - bc, 1.0):.3f}")
         if vals.get("SQ_INSTS_LDS") and vals.get("SQ_INSTS_VALU"):
             print(f"- VALU instructions per LDS instruction: {vals['SQ_INSTS_VALU'] / vals['SQ_INSTS_LDS']:.2f}")
+        if vals.get("TCC_HIT_sum") and vals.get("TCC_MISS_sum"):
+            print(f"- L2 hits: {vals['TCC_HIT_sum'] / (vals['TCC_HIT_sum'] + vals['TCC_MISS_sum']):.3f} of the requests")
+        if vals.get("GRBM_GUI_ACTIVE"):
+            # the counter is summed over the 8 dies, each of 32 compute units with 4 vector units
+            cycles = vals["GRBM_GUI_ACTIVE"] / 8
+            if vals.get("SQ_INSTS_VALU"):
+                print(f"- vector units busy: {vals['SQ_INSTS_VALU'] * 4 / (cycles * 256 * 4):.3f} of the cycles "
+                      "(4 per instruction of 64 lanes)")
+            if vals.get("SQ_LDS_IDX_ACTIVE"):
+                print(f"- LDS busy: {vals['SQ_LDS_IDX_ACTIVE'] / (cycles * 256):.3f} of the cycles")
         print()
     bt = _bucket_traffic(rows, sf, sw)
     if not any(nd for nd, _, _ in bt.values()):

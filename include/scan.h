@@ -94,7 +94,8 @@ typedef struct scan_opts {
                                    vertex is renamed to its rank by increasing degree
                                    (4 more device bytes per arc, built on the host when the
                                    graph is created); 0: the rows as given.  Results are
-                                   identical either way. */
+                                   identical either way; a graph that counts triangles
+                                   has no such copy. */
   void* hip_stream;             /* hipStream_t to run on; NULL = a library-owned stream */
 } scan_opts;
 
@@ -261,7 +262,10 @@ int scan_last_stats(const scan_graph* g, scan_stats* out);
  * plus 12 bytes per edge for the cached counts and closed-size products) plus
  * what the slots' scratch would grow by (18 bytes per vertex and 1 per edge of
  * the largest resident graph, per slot) fit opts->device_budget_bytes (0 = no
- * cap).  Otherwise it stays in host memory and its queries run on a fallback
+ * cap: such a server's graphs count triangles where they can, within the bound
+ * that scan_graph_create states, and keep the row entries and their counts; a
+ * slot then holds 18 bytes per vertex, 4 per line of 32 entries, and with hub and
+ * outlier roles 4 more per vertex).  Otherwise it stays in host memory and its queries run on a fallback
  * thread with its own stream, through a partition-based graph built with the
  * budget left over (kept, and counted as held, until a query of another
  * non-resident graph or an admission needs the memory); resident queries keep
@@ -351,9 +355,9 @@ int scan_batch_set_params(scan_batch_graph* bg, const int64_t* eps_num, const in
 /* Clusters every graph of the batch: labels[vtx_off[G]] receive graph-local
  * labels (minimum core id within the graph, -1 if unclassified) and roles the
  * roles, both host, caller-owned, packed like the vertices.  replay = 1 runs
- * the captured HIP graph, 0 launches the same two kernels directly.  A run in
- * which a block waits more than 20 s for a work item is abandoned and
- * reported as SCAN_E_DEVICE. */
+ * the captured HIP graph, 0 launches the same kernels directly.  A run of the
+ * queue kernel in which a block waits more than 20 s for a work item is abandoned
+ * and reported as SCAN_E_DEVICE. */
 int scan_batch_run(scan_batch_graph* bg, int32_t replay, int32_t* labels, uint8_t* roles);
 
 /* Chosen configuration: lanes[SCAN_NUM_BUCKETS] lane-group widths per degree

@@ -3,7 +3,9 @@
 // roles, union-find parents, labels, edge states, statistics and job
 // counters, the LDS-hash kernel's worklist) is carved out of one file-scope
 // device array, `scratch`, of kScratchBytes bytes.  Each device the library
-// runs on holds its own copy of the array for the life of the process.
+// runs on holds its own copy of the array for the life of the process.  On the
+// triangle path its scratch takes the place of the edge states and the worklist;
+// where it does not fit there, the graph has allocated one for these calls.
 //
 // Host code never passes `scratch` itself to a kernel: in host code that name
 // is only a stand-in for the symbol.  The device address of each device's copy

@@ -551,7 +551,7 @@ using LdsCounter = __attribute__((address_space(3))) int32_t;
 // scale 17: 95 and 80 us); all four loads are always issued, since a load under a
 // branch would make the compiler wait for every load in flight.  At scale 22
 // 22.8 GB are then read past the L2s (13 % hits) and 3.2 written, 3.9 TB/s of the
-// 4.9 of a large copy, with the vector units busy 58 % of the time and the LDS 35 %.
+// 4.9 of a large copy, with the vector units busy 59 % of the cycles and the LDS 36 %.
 // Columns up to v's own are in no table of v (h(w) >= h(v)) and need no mask.
 template <typename E, typename F>
 __device__ __forceinline__ void tri_stream(const E* __restrict__ cols, const TriRec* __restrict__ rec, uint32_t cnt,
