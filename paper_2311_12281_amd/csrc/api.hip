@@ -638,7 +638,7 @@ int scan::graph_create(int32_t n, int64_t nnz, const int64_t* row_ptr, const int
     const uint64_t rest = 8 * ((uint64_t)n + 1) + 8 * ((uint64_t)nnz + kColPad) + 22 * (uint64_t)n;  // rows, state, staging
     // whether a second scratch may be allocated below
     const bool may_noalloc = !groups && 17 * (uint64_t)n + (uint64_t)nnz / 2 <= kNoallocScratch;
-    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, lay.max_degree, groups, may_noalloc ? 2 : 1, most - rest,
+    e = tri_build(g->stream, n, nnz, row_ptr, g->d_rp, g->d_ci, lay, groups, may_noalloc ? 2 : 1, most - rest,
                   &g->tri, be, &ok);
     if (e == hipSuccess && ok) e = tri_alloc_scratch(g->tri, &g->tri_s);
     if (e == hipSuccess && ok) e = hipMalloc(&g->state_mem, 17 * stride);

@@ -27,11 +27,11 @@ enum : int {
 };
 
 __global__ void k_check_offsets(int32_t n, int64_t nnz, const int64_t* rp, int32_t* err,
-                                int32_t* maxdeg) {
+                                int32_t* maxdeg, int32_t* long_rows) {
   // one atomic per wave of a grid-stride loop: a wave per 64 vertices queued on
   // the one address
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  int32_t e = 0, most = 0;
+  int32_t e = 0, most = 0, lng = 0;
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u <= n; u += stride) {
     if (u == 0 && rp[0] != 0) e |= ERR_OFFSETS;
     if (u == n && rp[n] != nnz) e |= ERR_OFFSETS;
@@ -39,11 +39,18 @@ __global__ void k_check_offsets(int32_t n, int64_t nnz, const int64_t* rp, int32
       int64_t d = rp[u + 1] - rp[u];
       if (d < 0 || rp[u] < 0 || rp[u + 1] > nnz) e |= ERR_OFFSETS;
       else most = max(most, (int32_t)(d > 0x7fffffff ? 0x7fffffff : d));
+      lng += d > kLongRow ? 1 : 0;
     }
   }
-  for (int d = 32; d >= 1; d >>= 1) most = max(most, __shfl_xor(most, d, 64));
+  for (int d = 32; d >= 1; d >>= 1) {
+    most = max(most, __shfl_xor(most, d, 64));
+    lng += __shfl_xor(lng, d, 64);
+  }
   if (e) atomicOr(err, e);
-  if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(maxdeg, most);
+  if ((threadIdx.x & 63) == 0) {
+    if (most > 0) atomicMax(maxdeg, most);
+    if (lng > 0) atomicAdd(long_rows, lng);
+  }
 }
 
 __device__ inline bool row_contains(const int32_t* row, int64_t len, int32_t x) {
@@ -346,22 +353,24 @@ hipError_t build_ranked_rows(hipStream_t s, int32_t n, int64_t nnz, const int64_
 hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
                      LayoutResult* out) {
   hipError_t e = hipSuccess;
-  // [0] = error bits, [1] = max degree, then 64-bit: descents, descents at row starts
+  // [0] = error bits, [1] = max degree, then 64-bit: descents, descents at row starts; [6] = long rows
   int32_t* d_flags = nullptr;
-  int32_t h_flags[6] = {0, 0, 0, 0, 0, 0};
+  int32_t h_flags[7] = {0, 0, 0, 0, 0, 0, 0};
   unsigned long long h_desc[2];
   unsigned long long* d_desc = nullptr;
   out->error = 0;
-  out->max_degree = 0;
+  out->max_degree = out->long_rows = 0;
   LTRY(hipMalloc((void**)&d_flags, sizeof(h_flags)));
   LTRY(hipMemsetAsync(d_flags, 0, sizeof(h_flags), s));
   d_desc = reinterpret_cast<unsigned long long*>(d_flags + 2);
-  k_check_offsets<<<(unsigned)std::min<int64_t>(((int64_t)n + 1 + 255) / 256, 512), 256, 0, s>>>(n, nnz, d_rp, d_flags, d_flags + 1);
+  k_check_offsets<<<(unsigned)std::min<int64_t>(((int64_t)n + 1 + 255) / 256, 512), 256, 0, s>>>(n, nnz, d_rp, d_flags,
+                                                                                                  d_flags + 1, d_flags + 6);
   LTRY(hipGetLastError());
   LTRY(hipMemcpyAsync(h_flags, d_flags, sizeof(h_flags), hipMemcpyDeviceToHost, s));
   LTRY(hipStreamSynchronize(s));
   out->error = h_flags[0];
   out->max_degree = h_flags[1];
+  out->long_rows = h_flags[6];
   if (h_flags[0] != 0 || nnz == 0) goto done;  // offsets unusable, or no edges
   // The id-range check always runs (every later kernel indexes rp by ids);
   // order is checked when validation is on.

@@ -109,11 +109,11 @@ uint64_t tri_layout_bytes(const TriLayout& T);
 uint64_t tri_scratch_bytes(const TriLayout& T, const TriScratch& S);
 
 // Builds the layout from a validated CSR on the device (h_rp: the caller's
-// offsets).  *ok = 0 with hipSuccess when the graph is outside the path's
+// offsets; csr: what check_csr found).  *ok = 0 with hipSuccess when the graph is outside the path's
 // limits, or the layout and `scratches` scratches would take more than max_bytes
 // (nothing stays allocated).  bucket_edges: edges per degree bucket.
 hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
-                     const int32_t* d_ci, int32_t max_degree, const TriGroups* groups, int scratches,
+                     const int32_t* d_ci, const LayoutResult& csr, const TriGroups* groups, int scratches,
                      uint64_t max_bytes, TriLayout* T, int64_t* bucket_edges, int* ok);
 void tri_release(TriLayout& T);
 hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S);

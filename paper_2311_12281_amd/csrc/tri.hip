@@ -24,9 +24,6 @@
 
 #include <algorithm>
 #include <climits>
-#include <memory>
-#include <new>
-#include <thread>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -56,7 +53,7 @@ struct BigChunk {
   int32_t h, id;
   int64_t begin, end;  // arcs
 };
-constexpr int64_t kTriBigRow = 2048;
+constexpr int64_t kTriBigRow = kLongRow;
 constexpr int64_t kTriBigChunk = 2048;
 
 __global__ __launch_bounds__(256) void k_row_len_block(const BigChunk* chunks, const int32_t* ci, const int32_t* hof,
@@ -71,6 +68,129 @@ __global__ __launch_bounds__(256) void k_row_len_block(const BigChunk* chunks, c
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(&sum, c);
   __syncthreads();
   if (threadIdx.x == 0 && sum) atomicAdd(row + C.h, sum);
+}
+
+// Renaming: a stable sort of the vertices by max degree - degree, 8 bits a pass
+// (one pass up to degree 255, three for any R-MAT), a block per kSortTile
+// consecutive ones.  (On one host thread, faulting the arrays in and two passes
+// over the vertices took most of the creation of a large sparse graph: a road-like
+// grid of 4 million vertices 22.5 ms, now 11.9; R-MAT scale 22 55 and 43.  Host
+// threads came to 17.4 and 45, and made a process's first creation 3 ms longer.)
+constexpr int kSortTile = 4096;
+inline int64_t sort_blocks(int32_t n) { return ((int64_t)n + kSortTile - 1) / kSortTile; }
+inline int64_t sort_counts(int32_t n) { return 256 * sort_blocks(n); }
+
+// Vertex i of the pass: of the input, or of the graph.
+__device__ __forceinline__ int2 sort_item(int64_t i, const int2* in, const int64_t* rp, int32_t max_degree) {
+  return in ? in[i] : make_int2(max_degree - (int32_t)(rp[i + 1] - rp[i]), (int32_t)i);
+}
+
+// cnt[256 digits][blocks]
+__global__ __launch_bounds__(256) void k_sort_count(int32_t n, int shift, const int64_t* rp, int32_t max_degree,
+                                                    const int2* in, int64_t* cnt) {
+  __shared__ uint32_t c[256];
+  c[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t b = (int64_t)blockIdx.x * kSortTile, e = min(b + kSortTile, (int64_t)n);
+  for (int64_t i = b + threadIdx.x; i < e; i += 256) atomicAdd(&c[sort_item(i, in, rp, max_degree).x >> shift & 255], 1u);
+  __syncthreads();
+  cnt[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = c[threadIdx.x];
+}
+
+// Lanes of the wave whose valid digit is this lane's.
+__device__ __forceinline__ uint64_t same_digit(uint32_t d, bool valid) {
+  uint64_t m = __ballot(valid);
+  for (int b = 0; b < 8; ++b) {
+    const bool on = (d >> b) & 1u;
+    const uint64_t v = __ballot(on);
+    m &= on ? v : ~v;
+  }
+  return m;
+}
+
+// A wave places a quarter of the tile, 64 vertices at a time, behind the waves
+// before it (off: the scanned counts); the last pass (out null) writes the names.
+__global__ __launch_bounds__(256) void k_sort_place(int32_t n, int shift, const int64_t* rp, int32_t max_degree,
+                                                    const int2* in, const int64_t* off, int2* out, int32_t* hof,
+                                                    int32_t* idof) {
+  __shared__ uint32_t at[4][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int w = 0; w < 4; ++w) at[w][threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t b = (int64_t)blockIdx.x * kSortTile + wave * (kSortTile / 4);
+  for (int r = 0; r < kSortTile / 256; ++r) {
+    const int64_t i = b + r * 64 + lane;
+    const bool valid = i < n;
+    const uint32_t d = valid ? (uint32_t)(sort_item(i, in, rp, max_degree).x >> shift) & 255u : 0;
+    const uint64_t m = same_digit(d, valid);
+    if (valid && (m & lanes_below(lane)) == 0) at[wave][d] += (uint32_t)__popcll(m);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  {
+    uint32_t to = (uint32_t)off[(int64_t)threadIdx.x * gridDim.x + blockIdx.x];
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t c = at[w][threadIdx.x];
+      at[w][threadIdx.x] = to;
+      to += c;
+    }
+  }
+  __syncthreads();
+  for (int r = 0; r < kSortTile / 256; ++r) {
+    const int64_t i = b + r * 64 + lane;
+    const bool valid = i < n;
+    const int2 x = valid ? sort_item(i, in, rp, max_degree) : make_int2(0, 0);
+    const uint32_t d = (uint32_t)(x.x >> shift) & 255u;
+    const uint64_t m = same_digit(d, valid);
+    const uint32_t to = at[wave][d] + (uint32_t)__popcll(m & lanes_below(lane));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid && (m & lanes_below(lane)) == 0) at[wave][d] += (uint32_t)__popcll(m);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (!valid) continue;
+    if (out) {
+      out[to] = x;
+    } else {
+      hof[x.y] = (int32_t)to;
+      idof[to] = x.y;
+    }
+  }
+}
+
+// a, b: n items each; digits: 2 sort_counts(n); work: of their scan.
+hipError_t sort_by_degree(hipStream_t s, int32_t n, const int64_t* rp, int32_t max_degree, int2* a, int2* b,
+                          int64_t* digits, int64_t* work, int32_t* hof, int32_t* idof) {
+  const unsigned grid = (unsigned)sort_blocks(n);
+  int64_t* off = digits + sort_counts(n);
+  const int2* in = nullptr;
+  for (int shift = 0; shift == 0 || max_degree >> shift > 0; shift += 8) {
+    const bool last = max_degree >> shift < 256;
+    k_sort_count<<<grid, 256, 0, s>>>(n, shift, rp, max_degree, in, digits);
+    const hipError_t e = exclusive_scan(s, digits, off, sort_counts(n), work);
+    if (e != hipSuccess) return e;
+    int2* out = last ? nullptr : in == a ? b : a;
+    k_sort_place<<<grid, 256, 0, s>>>(n, shift, rp, max_degree, in, off, out, hof, idof);
+    if (last) break;
+    in = out;
+  }
+  return hipGetLastError();
+}
+
+// The same inside every graph of a batch, on the host.
+void rename_groups(const int64_t* rp, const TriGroups& G, int32_t* hof) {
+  std::vector<int32_t> first;
+  for (int32_t k = 0; k < G.count; ++k) {
+    const int32_t v0 = (int32_t)G.h_vtx_off[k], v1 = (int32_t)G.h_vtx_off[k + 1];
+    int64_t most = 0;
+    for (int32_t v = v0; v < v1; ++v) most = std::max(most, rp[v + 1] - rp[v]);
+    first.assign((size_t)most + 1, 0);
+    for (int32_t v = v0; v < v1; ++v) ++first[(size_t)(rp[v + 1] - rp[v])];
+    int32_t acc = v0;
+    for (int64_t d = most; d >= 0; --d) acc += std::exchange(first[(size_t)d], acc);
+    for (int32_t v = v0; v < v1; ++v) hof[v] = first[(size_t)(rp[v + 1] - rp[v])]++;
+  }
 }
 
 __global__ void k_inverse(int32_t n, const int32_t* hof, int32_t* idof) {
@@ -1388,73 +1508,9 @@ hipError_t tri_alloc_scratch(const TriLayout& T, TriScratch* S) {
   return e;
 }
 
-namespace {
-
-// h of every vertex: a counting sort by decreasing degree, ties by id, in every
-// graph; and the vertices of more than kTriBigRow neighbours by h (none of a batch,
-// where waves take the long rows too).  On host threads, as many as the counts of
-// all degrees allow: on one, faulting the new arrays in and two passes over the
-// vertices took most of the creation of a large sparse graph (a road-like grid of 4
-// million vertices 22.9 ms, now 17.4; R-MAT 22 55 and 45).
-bool tri_rename(int32_t n, const int64_t* rp, int32_t max_degree, const TriGroups* groups, int32_t* hof,
-                std::vector<int32_t>* long_rows) {
-  constexpr int32_t kWorth = 1 << 18;  // vertices from which on threads pay
-  const int64_t degrees = (int64_t)max_degree + 1;
-  int nt = n < kWorth ? 1 : (int)std::min(16u, std::max(1u, std::thread::hardware_concurrency()));
-  if (!groups) nt = (int)std::max<int64_t>(1, std::min<int64_t>(nt, n / (4 * degrees)));
-  std::unique_ptr<int32_t[]> place(new (std::nothrow) int32_t[(size_t)(nt * degrees)]);
-  if (!place) return false;
-  auto run = [&](auto body) {
-    std::vector<std::thread> th;
-    for (int t = 1; t < nt; ++t) th.emplace_back(body, t);
-    body(0);
-    for (auto& x : th) x.join();
-  };
-  auto degree = [&](int32_t v) { return rp[v + 1] - rp[v]; };
-  auto part = [&](int32_t lo, int32_t hi, int t) { return lo + (int32_t)((int64_t)(hi - lo) * t / nt); };
-  if (groups) {
-    run([&](int t) {  // whole graphs, whose degrees stay below their sizes
-      int32_t* at = place.get() + t * degrees;
-      for (int32_t k = part(0, groups->count, t), end = part(0, groups->count, t + 1); k < end; ++k) {
-        const int32_t v0 = (int32_t)groups->h_vtx_off[k], v1 = (int32_t)groups->h_vtx_off[k + 1];
-        int64_t most = 0;
-        for (int32_t v = v0; v < v1; ++v) most = std::max(most, degree(v));
-        std::fill(at, at + most + 1, 0);
-        for (int32_t v = v0; v < v1; ++v) ++at[degree(v)];
-        int32_t acc = v0;
-        for (int64_t d = most; d >= 0; --d) acc += std::exchange(at[d], acc);
-        for (int32_t v = v0; v < v1; ++v) hof[v] = at[degree(v)]++;
-      }
-    });
-    return true;
-  }
-  run([&](int t) {
-    int32_t* at = place.get() + t * degrees;
-    std::fill(at, at + degrees, 0);
-    for (int32_t v = part(0, n, t), end = part(0, n, t + 1); v < end; ++v) ++at[degree(v)];
-  });
-  int32_t acc = 0, big = 0;
-  for (int64_t d = degrees - 1; d >= 0; --d) {
-    for (int t = 0; t < nt; ++t) acc += std::exchange(place[(size_t)(t * degrees + d)], acc);
-    if (d > kTriBigRow) big = acc;
-  }
-  long_rows->resize((size_t)big);
-  run([&](int t) {
-    int32_t* at = place.get() + t * degrees;
-    for (int32_t v = part(0, n, t), end = part(0, n, t + 1); v < end; ++v) {
-      hof[v] = at[degree(v)]++;
-      if (hof[v] < big) (*long_rows)[(size_t)hof[v]] = v;
-    }
-  });
-  return true;
-}
-
-}  // namespace
-
 hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp, const int64_t* d_rp,
-                     const int32_t* d_ci, int32_t max_degree, const TriGroups* groups, int scratches,
-                     uint64_t max_bytes, TriLayout* out,
-                     int64_t* bucket_edges, int* ok) {
+                     const int32_t* d_ci, const LayoutResult& csr, const TriGroups* groups, int scratches,
+                     uint64_t max_bytes, TriLayout* out, int64_t* bucket_edges, int* ok) {
   *ok = 0;
   if (n <= 0 || nnz <= 0 || nnz / 2 >= (int64_t)1 << 31) return hipSuccess;
   // The kernels below take a wave per vertex: up to 67,108,860 vertices (more than
@@ -1485,7 +1541,8 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   int32_t h_ctl[4] = {0, 0, 0, 0};
   unsigned long long h_sums[2 + kNumBuckets] = {0};
   const unsigned gv = grid_for((int64_t)n + 1, 256);
-  int32_t nbig = 0;
+  const int32_t nbig = groups ? 0 : csr.long_rows;  // (of a batch, waves take the long rows too)
+  int64_t* digits = nullptr;
 #define TTRY(x)                        \
   do {                                 \
     e = (x);                           \
@@ -1500,16 +1557,6 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
       T.span = std::max(T.span, (int32_t)(groups->h_vtx_off[k + 1] - groups->h_vtx_off[k]));
   }
   {
-    std::unique_ptr<int32_t[]> hof(new (std::nothrow) int32_t[(size_t)n]);
-    std::vector<int32_t> long_rows;
-    if (!hof || !tri_rename(n, h_rp, max_degree, groups, hof.get(), &long_rows)) TTRY(hipErrorOutOfMemory);
-    nbig = (int32_t)long_rows.size();
-    for (int32_t h = 0; h < nbig; ++h) {
-      const int32_t v = long_rows[(size_t)h];
-      for (int64_t k = h_rp[v]; k < h_rp[v + 1]; k += kTriBigChunk)
-        chunks.push_back(BigChunk{h, v, k, std::min(k + kTriBigChunk, h_rp[v + 1])});
-    }
-    nchunk = (unsigned)chunks.size();
     Arena vertex, temp;
     vertex.take(&T.hof, n);
     vertex.take(&T.idof, n);
@@ -1519,23 +1566,40 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
     vertex.take(&T.wbase, (int64_t)n + 1);
     TTRY(vertex.allocate(&T.mem[0]));
     for (int64_t** p : {&nline, &nword, &nin, &at0, &at1, &at2}) temp.take(p, (int64_t)n + 1);
-    temp.take(&work, scan_work_items((int64_t)n + 1));
+    temp.take(&digits, 2 * sort_counts(n));
+    temp.take(&work, scan_work_items(std::max((int64_t)n + 1, sort_counts(n))));
     temp.take(&inlen, n);
     temp.take(&wcls, n);
     temp.take(&longer, n);
     temp.take(&ctl, 4);  // longest row, rows for the block sort, longest hash row, a reverse arc is missing
     temp.take(&sums, 2 + kNumBuckets);  // words, edges per bucket, entries
-    temp.take(&big, nchunk);
+    temp.take(&big, nbig + nnz / kTriBigChunk);
     temp.take(&room, 2 * (int64_t)nbig);
     TTRY(temp.allocate(&tmp));
-    if (nchunk) {
-      TTRY(hipMemcpyAsync(big, chunks.data(), sizeof(BigChunk) * nchunk, hipMemcpyHostToDevice, s));
-      TTRY(hipMemsetAsync(room, 0, 16 * (size_t)nbig, s));
-    }
-    TTRY(hipMemcpyAsync(T.hof, hof.get(), 4 * (size_t)n, hipMemcpyHostToDevice, s));
+  }
+  if (groups) {
+    std::vector<int32_t> hof((size_t)n);
+    rename_groups(h_rp, *groups, hof.data());
+    TTRY(hipMemcpyAsync(T.hof, hof.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s));
     k_inverse<<<gv, 256, 0, s>>>(n, T.hof, T.idof);
     TTRY(hipGetLastError());
     TTRY(hipStreamSynchronize(s));
+  } else {
+    TTRY(sort_by_degree(s, n, d_rp, csr.max_degree, reinterpret_cast<int2*>(nline), reinterpret_cast<int2*>(nword),
+                        digits, work, T.hof, T.idof));
+  }
+  if (nbig > 0) {
+    std::vector<int32_t> ids((size_t)nbig);
+    TTRY(hipMemcpyAsync(ids.data(), T.idof, 4 * (size_t)nbig, hipMemcpyDeviceToHost, s));
+    TTRY(hipStreamSynchronize(s));
+    for (int32_t h = 0; h < nbig; ++h) {
+      const int32_t v = ids[(size_t)h];
+      for (int64_t k = h_rp[v]; k < h_rp[v + 1]; k += kTriBigChunk)
+        chunks.push_back(BigChunk{h, v, k, std::min(k + kTriBigChunk, h_rp[v + 1])});
+    }
+    nchunk = (unsigned)chunks.size();
+    TTRY(hipMemcpyAsync(big, chunks.data(), sizeof(BigChunk) * nchunk, hipMemcpyHostToDevice, s));
+    TTRY(hipMemsetAsync(room, 0, 16 * (size_t)nbig, s));
   }
   TTRY(hipMemsetAsync(ctl, 0, 16, s));
   TTRY(hipMemsetAsync(sums, 0, sizeof(h_sums), s));

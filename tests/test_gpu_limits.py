@@ -54,15 +54,16 @@ def test_vertex_limit_in_a_batch_and_a_server():
         _check(*srv.wait(srv.submit(gid, 1, 2, 3), gid)[:2], ids, small, 1, 2, 3, "server")
 
 
-@pytest.mark.parametrize("n", [262_143, 262_144, 262_147])
-@pytest.mark.parametrize("hub", [2_048, 2_049, 70_000])
-def test_renaming_by_host_threads(n, hub):
-    """From 2^18 vertices on, host threads rename the vertices by degree (fewer where the largest degree
-    is high); rows above 2,048 arcs are laid out in chunks."""
+@pytest.mark.parametrize("n,hub", [(63, 40), (4_095, 251), (4_096, 252), (4_097, 253), (8_193, 2_044), (8_192, 2_045),
+                                   (262_147, 65_531), (262_144, 65_532), (300_001, 70_000)])
+def test_renaming(n, hub):
+    """The sort by degree: vertices around its tiles of 4,096, largest degrees around one, two and three
+    passes of 8 bits; and around 2,048 neighbours, above which a row is laid out in chunks."""
     rng = np.random.default_rng(n + hub)
     src = [np.arange(n - 2), np.arange(n - 2), np.zeros(hub, np.int64) + 17]
-    dst = [np.arange(1, n - 1), np.arange(2, n), rng.choice(n, hub, replace=False)]
+    dst = [np.arange(1, n - 1), np.arange(2, n), rng.choice(np.setdiff1d(np.arange(n), np.arange(15, 20)), hub, replace=False)]
     g = gg.from_pairs(n, np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32))
+    assert g.degrees().max() == hub + 4
     oc = oracle.counts(g, threads=oracle.max_threads())
     note("renaming", n, hub)
     with S.Graph.from_csr(g) as G:
