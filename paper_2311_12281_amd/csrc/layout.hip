@@ -27,11 +27,11 @@ enum : int {
 };
 
 __global__ void k_check_offsets(int32_t n, int64_t nnz, const int64_t* rp, int32_t* err,
-                                int32_t* maxdeg, int32_t* long_rows) {
+                                int32_t* maxdeg, int32_t* rows) {
   // one atomic per wave of a grid-stride loop: a wave per 64 vertices queued on
   // the one address
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  int32_t e = 0, most = 0, lng = 0;
+  int32_t e = 0, most = 0, lng = 0, wide = 0;
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u <= n; u += stride) {
     if (u == 0 && rp[0] != 0) e |= ERR_OFFSETS;
     if (u == n && rp[n] != nnz) e |= ERR_OFFSETS;
@@ -40,16 +40,19 @@ __global__ void k_check_offsets(int32_t n, int64_t nnz, const int64_t* rp, int32
       if (d < 0 || rp[u] < 0 || rp[u + 1] > nnz) e |= ERR_OFFSETS;
       else most = max(most, (int32_t)(d > 0x7fffffff ? 0x7fffffff : d));
       lng += d > kLongRow ? 1 : 0;
+      wide += d > kNarrowRow ? 1 : 0;
     }
   }
   for (int d = 32; d >= 1; d >>= 1) {
     most = max(most, __shfl_xor(most, d, 64));
     lng += __shfl_xor(lng, d, 64);
+    wide += __shfl_xor(wide, d, 64);
   }
   if (e) atomicOr(err, e);
   if ((threadIdx.x & 63) == 0) {
     if (most > 0) atomicMax(maxdeg, most);
-    if (lng > 0) atomicAdd(long_rows, lng);
+    if (lng > 0) atomicAdd(rows, lng);
+    if (wide > 0) atomicAdd(rows + 1, wide);
   }
 }
 
@@ -353,13 +356,14 @@ hipError_t build_ranked_rows(hipStream_t s, int32_t n, int64_t nnz, const int64_
 hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
                      LayoutResult* out) {
   hipError_t e = hipSuccess;
-  // [0] = error bits, [1] = max degree, then 64-bit: descents, descents at row starts; [6] = long rows
+  // [0] = error bits, [1] = max degree, then 64-bit: descents, descents at row starts; [6], [7] = long and
+  // wide rows
   int32_t* d_flags = nullptr;
-  int32_t h_flags[7] = {0, 0, 0, 0, 0, 0, 0};
+  int32_t h_flags[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   unsigned long long h_desc[2];
   unsigned long long* d_desc = nullptr;
   out->error = 0;
-  out->max_degree = out->long_rows = 0;
+  out->max_degree = out->long_rows = out->wide_rows = 0;
   LTRY(hipMalloc((void**)&d_flags, sizeof(h_flags)));
   LTRY(hipMemsetAsync(d_flags, 0, sizeof(h_flags), s));
   d_desc = reinterpret_cast<unsigned long long*>(d_flags + 2);
@@ -371,6 +375,7 @@ hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp,
   out->error = h_flags[0];
   out->max_degree = h_flags[1];
   out->long_rows = h_flags[6];
+  out->wide_rows = h_flags[7];
   if (h_flags[0] != 0 || nnz == 0) goto done;  // offsets unusable, or no edges
   // The id-range check always runs (every later kernel indexes rp by ids);
   // order is checked when validation is on.

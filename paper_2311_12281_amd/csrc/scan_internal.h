@@ -276,10 +276,12 @@ struct LayoutResult {
   int64_t hub_jobs;
   int32_t max_degree;
   int32_t long_rows;  // vertices of more than kLongRow neighbours
+  int32_t wide_rows;  // vertices of more than kNarrowRow
   int32_t error;  // 0 or bit mask of validation failures
 };
-constexpr int64_t kLongRow = 2048;
-// Validates the CSR but for the reverse arcs (out->error, out->max_degree, out->long_rows).
+constexpr int64_t kLongRow = 2048, kNarrowRow = 8;
+// Validates the CSR but for the reverse arcs (out->error, out->max_degree,
+// out->long_rows, out->wide_rows).
 hipError_t check_csr(hipStream_t s, int32_t n, int64_t nnz, const int64_t* d_rp, const int32_t* d_ci, int validate,
                      LayoutResult* out);
 // Validates the reverse arcs (the triangle layout finds them while it is built

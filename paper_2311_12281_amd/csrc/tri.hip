@@ -207,16 +207,44 @@ __global__ void k_degrees(int32_t n, const int64_t* rp, const int32_t* idof, int
   row[h] = 0;
 }
 
+// The kernels below take G lanes per vertex: 64, or 8 for the vertices of at most
+// kNarrowRow neighbours, which follow the others, where there are kNarrowWorth of
+// them (a wave each, with 61 lanes idle, made each of the five kernels take 2.4 to
+// 5.8 ms on a triangulated grid of 9 million vertices, all of degree 6, and its
+// creation 32 ms, now 16; of a road-like grid of 4 million 11.9 and 6.3).
+constexpr int32_t kNarrowWorth = 1 << 16;
+
+// Vertex and lane of a thread.
+template <int G>
+__device__ __forceinline__ int64_t group_vertex(int32_t h0) {
+  return h0 + ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+}
+
+template <int G, typename T>
+__device__ __forceinline__ T group_sum(T x) {
+  for (int d = G / 2; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+  return x;
+}
+
+// The group's part of a ballot.
+template <int G>
+__device__ __forceinline__ uint64_t group_ballot(bool p) {
+  const uint64_t m = __ballot(p);
+  if constexpr (G == 64) return m;
+  return (m >> (threadIdx.x & 63 & ~(G - 1))) & ((1ull << (G & 63)) - 1);
+}
+
+template <int G>
 __global__ __launch_bounds__(256) void k_row_len_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                       const int32_t* hof, const int32_t* idof, int32_t* row) {
-  const int lane = threadIdx.x & 63;
-  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t h = group_vertex<G>(h0);
   if (h >= n) return;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
   int32_t c = 0;
-  for (int64_t k = b + lane; k < e; k += 64) c += hof[ci[k]] < h ? 1 : 0;
-  c = (int32_t)wave_sum((unsigned long long)c);
+  for (int64_t k = b + lane; k < e; k += G) c += hof[ci[k]] < h ? 1 : 0;
+  c = group_sum<G>(c);
   if (lane == 0) row[h] = c;
 }
 
@@ -262,23 +290,24 @@ __global__ void k_in_room_big(int32_t nbig, const int32_t* row, const unsigned l
   if (h < nbig) tri_room(row[h], room[2 * h], room[2 * h + 1], nin + h, wcls + h);
 }
 
+template <int G>
 __global__ __launch_bounds__(256) void k_in_room_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                       const int32_t* hof, const int32_t* idof, const int32_t* row,
                                                       int64_t* nin, uint8_t* wcls) {
-  const int lane = threadIdx.x & 63;
-  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t h = group_vertex<G>(h0);
   if (h >= n) return;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
   unsigned long long c = 0, r = 0;
-  for (int64_t k = b + lane; k < e; k += 64) {
+  for (int64_t k = b + lane; k < e; k += G) {
     const int32_t u = hof[ci[k]];
     const uint32_t W = u > h && row[u] > 1 ? tri_lines(row[u]) : 0;
     c += W;
     r += (W + kTriRecLines - 1) / kTriRecLines;
   }
-  c = wave_sum(c);
-  r = wave_sum(r);
+  c = group_sum<G>(c);
+  r = group_sum<G>(r);
   if (lane == 0) tri_room(row[h], c, r, nin + h, wcls + h);
 }
 
@@ -342,11 +371,12 @@ __global__ void k_row_pad(int32_t nbig, const uint32_t* oline, const int32_t* ro
   if (p < (int32_t)tri_lines(D) * kTriLine) oc[(int64_t)oline[h] * kTriLine + p] = 0;
 }
 
+template <int G>
 __global__ __launch_bounds__(256) void k_row_fill_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                        const int32_t* hof, const int32_t* idof,
                                                        const uint32_t* oline, const int32_t* row, int32_t* oc) {
-  const int lane = threadIdx.x & 63;
-  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t h = group_vertex<G>(h0);
   if (h >= n) return;
   const int32_t D = row[h];
   if (D == 0) return;
@@ -354,16 +384,16 @@ __global__ __launch_bounds__(256) void k_row_fill_wave(int32_t h0, int32_t n, co
   const int64_t b = rp[x], e = rp[x + 1];
   int32_t* out = oc + (int64_t)oline[h] * kTriLine;
   int32_t at = 0;
-  for (int64_t k0 = b; k0 < e; k0 += 64) {
+  for (int64_t k0 = b; k0 < e; k0 += G) {
     const int64_t k = k0 + lane;
     const int32_t y = k < e ? hof[ci[k]] : INT_MAX;
     const bool keep = y < h;
-    const uint64_t mask = __ballot(keep);
+    const uint64_t mask = group_ballot<G>(keep);
     const int32_t p = at + (int32_t)__popcll(mask & lanes_below(lane));
     if (keep && p < D) out[p] = y + 1;
     at += (int32_t)__popcll(mask);
   }
-  for (int32_t p = D + lane; p < (int32_t)tri_lines(D) * kTriLine; p += 64) out[p] = 0;
+  for (int32_t p = D + lane; p < (int32_t)tri_lines(D) * kTriLine; p += G) out[p] = 0;
 }
 
 // First h of the graph of h.
@@ -376,41 +406,44 @@ __device__ __forceinline__ uint16_t tri_short(int32_t x, int32_t base) {
   return x == 0 ? (uint16_t)0 : x - base <= kTriShort ? (uint16_t)(x - base) : (uint16_t)0xFFFF;
 }
 
-// Rows in decreasing order of h: up to 64 entries in the registers of a wave
+// Rows in decreasing order of h: up to G entries in the registers of a group
 // (bitonic network over the lanes); longer ones are listed for the block kernel.
-__global__ __launch_bounds__(256) void k_row_sort_wave(int32_t n, const uint32_t* oline, const int32_t* row,
+template <int G>
+__global__ __launch_bounds__(256) void k_row_sort_wave(int32_t h0, int32_t n, const uint32_t* oline, const int32_t* row,
                                                        const uint32_t* wbase, const int32_t* deg, const int32_t* gid,
                                                        const int64_t* vtx_off, int32_t* oc, uint16_t* oc16,
                                                        int32_t* lu, TriLineInfo* li, int32_t* longer,
                                                        int32_t* nlonger) {
-  const int lane = threadIdx.x & 63;
-  const int64_t h = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t h = group_vertex<G>(h0);
   if (h >= n) return;
   const int32_t D = row[h];
   if (D == 0) return;
   const uint32_t W = tri_lines(D), l0 = oline[h];
-  for (uint32_t l = lane; l < W; l += 64) {
+  for (uint32_t l = lane; l < W; l += G) {
     lu[l0 + l] = (int32_t)h;
     li[l0 + l] = TriLineInfo{(int32_t)h, wbase[h], deg[h], (uint32_t)D | l << 16};
   }
-  if (D > 64) {
+  if (D > G) {
     if (lane == 0) longer[atomicAdd(nlonger, 1)] = (int32_t)h;
     return;
   }
   int32_t* out = oc + (int64_t)l0 * kTriLine;
   const bool in = lane < (int)(W * kTriLine);
   int32_t x = in ? out[lane] : 0;
-  for (int k = 2; k <= 64; k <<= 1)
+  for (int k = 2; k <= G; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
       const int32_t y = __shfl_xor(x, j, 64);
       const bool up = (lane & k) != 0;            // ascending part
       const bool low = (lane & j) == 0;
       x = (low != up) ? max(x, y) : min(x, y);
     }
+  uint16_t* out16 = oc16 + (int64_t)l0 * kTriLine;
   if (in) {
     out[lane] = x;
-    oc16[(int64_t)l0 * kTriLine + lane] = tri_short(x, tri_base(gid, vtx_off, h));
+    out16[lane] = tri_short(x, tri_base(gid, vtx_off, h));
   }
+  for (int p = lane + G; p < kTriLine; p += G) out16[p] = 0;  // (of a group narrower than a line)
 }
 
 __global__ __launch_bounds__(256) void k_row_sort_block(const int32_t* longer, const int32_t* nlonger,
@@ -475,9 +508,10 @@ __device__ __forceinline__ TriRec tri_rec(int32_t u, int32_t v, const uint32_t* 
   return r;
 }
 
-// Inclusive prefix sum over the wave.
+// Inclusive prefix sum over G lanes.
+template <int G = 64>
 __device__ __forceinline__ uint32_t wave_scan(uint32_t x, int lane) {
-  for (int d = 1; d < 64; d <<= 1) {
+  for (int d = 1; d < G; d <<= 1) {
     const uint32_t y = __shfl_up(x, d, 64);
     if (lane >= d) x += y;
   }
@@ -524,13 +558,14 @@ __global__ __launch_bounds__(256) void k_recs_block(const BigChunk* chunks, cons
   if (__ballot(missing) && lane == 0) *asym = 1;
 }
 
+template <int G>
 __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const int64_t* rp, const int32_t* ci,
                                                    const int32_t* hof, const int32_t* idof, const uint32_t* oline,
                                                    const uint32_t* wbase, const int32_t* row, const int32_t* oc,
                                                    const int64_t* inoff, const uint8_t* wcls, TriRec* rec, uint32_t* inlen,
                                                    int64_t* steps, int32_t* asym) {
-  const int lane = threadIdx.x & 63;
-  const int64_t h = h0 + (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t h = group_vertex<G>(h0);
   if (h >= n) return;
   const int32_t x = idof[h];
   const int64_t b = rp[x], e = rp[x + 1];
@@ -540,22 +575,22 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
   uint32_t at = 0;
   bool missing = false;
   unsigned long long st = 0;
-  for (int64_t k0 = b; k0 < e; k0 += 64) {
+  for (int64_t k0 = b; k0 < e; k0 += G) {
     const int64_t k = k0 + lane;
     const int32_t u = k < e ? hof[ci[k]] : -1;
     const TriRec r = u > (int32_t)h ? tri_rec(u, (int32_t)h, oline, wbase, row, oc, missing) : TriRec{};
     const uint32_t c = (r.nw + cut - 1) / cut;
-    const uint32_t incl = wave_scan(c, lane);
+    const uint32_t incl = wave_scan<G>(c, lane);
     tri_put_recs(r, cut, out, at + incl - c, rn);
-    at += __shfl(incl, 63, 64);
+    at += __shfl(incl, (threadIdx.x & 63) | (G - 1), 64);
     st += r.nw;
   }
-  st = wave_sum(st);
+  st = group_sum<G>(st);
   if (lane == 0) {
     inlen[h] = min(at, rn);
     steps[h] = (int64_t)st;
   }
-  if (__ballot(missing) && lane == 0) *asym = 1;
+  if (missing) *asym = 1;
 }
 
 // Work of every vertex: jobs of the block kernel, or a place in the wave
@@ -1542,6 +1577,8 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   unsigned long long h_sums[2 + kNumBuckets] = {0};
   const unsigned gv = grid_for((int64_t)n + 1, 256);
   const int32_t nbig = groups ? 0 : csr.long_rows;  // (of a batch, waves take the long rows too)
+  // vertices from here on have few neighbours, and go eight to a wave
+  const int32_t narrow = !groups && n - csr.wide_rows >= kNarrowWorth ? csr.wide_rows : n;
   int64_t* digits = nullptr;
 #define TTRY(x)                        \
   do {                                 \
@@ -1605,15 +1642,21 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(hipMemsetAsync(sums, 0, sizeof(h_sums), s));
   k_degrees<<<gv, 256, 0, s>>>(n, d_rp, T.idof, T.deg, T.row);
   if (nchunk) k_row_len_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.row);
-  if (n > nbig) k_row_len_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row);
+  if (narrow > nbig)
+    k_row_len_wave<64><<<grid_for(narrow - nbig, 4), 256, 0, s>>>(nbig, narrow, d_rp, d_ci, T.hof, T.idof, T.row);
+  if (n > narrow)
+    k_row_len_wave<8><<<grid_for(n - narrow, 32), 256, 0, s>>>(narrow, n, d_rp, d_ci, T.hof, T.idof, T.row);
   TTRY(hipGetLastError());
   k_row_sizes<<<std::min(gv, 512u), 256, 0, s>>>(n, T.row, nline, nword, sums + 1 + kNumBuckets, ctl);
   if (nchunk) {
     k_in_room_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.row, room);
     k_in_room_big<<<grid_for(nbig, 256), 256, 0, s>>>(nbig, T.row, room, nin, wcls);
   }
-  if (n > nbig) 
-    k_in_room_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
+  if (narrow > nbig)
+    k_in_room_wave<64><<<grid_for(narrow - nbig, 4), 256, 0, s>>>(nbig, narrow, d_rp, d_ci, T.hof, T.idof, T.row, nin,
+                                                                  wcls);
+  if (n > narrow)
+    k_in_room_wave<8><<<grid_for(n - narrow, 32), 256, 0, s>>>(narrow, n, d_rp, d_ci, T.hof, T.idof, T.row, nin, wcls);
   TTRY(hipMemsetAsync(nin + n, 0, 8, s));
   TTRY(hipGetLastError());
   TTRY(exclusive_scan(s, nline, at0, (int64_t)n + 1, work));
@@ -1651,10 +1694,18 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
     k_row_fill_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.oline, T.row, inlen, T.oc);
     k_row_pad<<<grid_for(nbig, 8), 256, 0, s>>>(nbig, T.oline, T.row, T.oc);
   }
-  if (n > nbig)
-    k_row_fill_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.row, T.oc);
-  k_row_sort_wave<<<grid_for(n, 4), 256, 0, s>>>(n, T.oline, T.row, T.wbase, T.deg, T.gid, T.vtx_off, T.oc, T.oc16,
-                                                   T.lu, T.li, longer, ctl + 1);
+  if (narrow > nbig)
+    k_row_fill_wave<64><<<grid_for(narrow - nbig, 4), 256, 0, s>>>(nbig, narrow, d_rp, d_ci, T.hof, T.idof, T.oline,
+                                                                   T.row, T.oc);
+  if (n > narrow)
+    k_row_fill_wave<8><<<grid_for(n - narrow, 32), 256, 0, s>>>(narrow, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.row,
+                                                                T.oc);
+  if (narrow > 0)
+    k_row_sort_wave<64><<<grid_for(narrow, 4), 256, 0, s>>>(0, narrow, T.oline, T.row, T.wbase, T.deg, T.gid, T.vtx_off,
+                                                            T.oc, T.oc16, T.lu, T.li, longer, ctl + 1);
+  if (n > narrow)
+    k_row_sort_wave<8><<<grid_for(n - narrow, 32), 256, 0, s>>>(narrow, n, T.oline, T.row, T.wbase, T.deg, T.gid,
+                                                                T.vtx_off, T.oc, T.oc16, T.lu, T.li, longer, ctl + 1);
   k_row_sort_block<<<4096, 256, 0, s>>>(longer, ctl + 1, T.oline, T.row, T.gid, T.vtx_off, T.oc, T.oc16);
   TTRY(hipGetLastError());
   TTRY(hipMemsetAsync(inlen, 0, 4 * (size_t)n, s));
@@ -1662,9 +1713,12 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (nchunk)
     k_recs_block<<<nchunk, 256, 0, s>>>(big, d_ci, T.hof, T.oline, T.wbase, T.row, T.oc, at2, wcls, T.rec, inlen, nin,
                                         ctl + 3);
-  if (n > nbig)
-    k_recs_wave<<<grid_for(n - nbig, 4), 256, 0, s>>>(nbig, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase, T.row,
-                                                      T.oc, at2, wcls, T.rec, inlen, nin, ctl + 3);
+  if (narrow > nbig)
+    k_recs_wave<64><<<grid_for(narrow - nbig, 4), 256, 0, s>>>(nbig, narrow, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase,
+                                                               T.row, T.oc, at2, wcls, T.rec, inlen, nin, ctl + 3);
+  if (n > narrow)
+    k_recs_wave<8><<<grid_for(n - narrow, 32), 256, 0, s>>>(narrow, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase,
+                                                            T.row, T.oc, at2, wcls, T.rec, inlen, nin, ctl + 3);
   k_job_counts<<<std::min(gv, 512u), 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, part, sums,
                                                 ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,

@@ -81,3 +81,43 @@ def test_renaming_of_a_large_batch():
         labels, roles = B.run()
         for k, (g, (p, q), mu, l, r) in enumerate(zip(graphs, eps, mus, B.split(labels), B.split(roles))):
             assert_same(l, r, *oracle.scan(g, p, q, mu), f"graph {k} eps={p}/{q} mu={mu}")
+
+
+def _rings(parts, seed=None):
+    """Disjoint rings (vertices, neighbours on each side), ids shuffled if a seed is given."""
+    src, dst, at = [], [], 0
+    for n, k in parts:
+        i = np.arange(n)
+        for d in range(1, k + 1):
+            src.append(at + i)
+            dst.append(at + (i + d) % n)
+        at += n
+    p = np.arange(at) if seed is None else np.random.default_rng(seed).permutation(at)
+    return gg.from_pairs(at, p[np.concatenate(src)].astype(np.int32), p[np.concatenate(dst)].astype(np.int32))
+
+
+@pytest.mark.parametrize("parts", [
+    [(65_535, 4)], [(65_536, 4)], [(65_537, 4), (100, 5)], [(1_001, 40), (65_600, 3)], [(70_001, 1), (33, 2)],
+    [(30_000, 2), (30_000, 4), (6_007, 1), (5_000, 5)]], ids=str)
+@pytest.mark.parametrize("seed", [None, 5])
+def test_vertices_of_few_neighbours(parts, seed):
+    """From 65,536 vertices of at most 8 neighbours on, eight of them share a wave while the rows are laid out."""
+    g = _rings(parts, seed)
+    oc = oracle.counts(g, threads=oracle.max_threads())
+    note("few neighbours", parts, seed)
+    with S.Graph.from_csr(g) as G:
+        assert np.array_equal(G.similarity(), oc)
+        for (p, q), mu in [((1, 2), 3), ((7, 10), 2), ((4, 5), 5)]:
+            assert_same(*G.run(p, q, mu), *oracle.cluster(g, oc, p, q, mu), f"{parts} eps={p}/{q}")
+
+
+def test_a_missing_reverse_arc_among_them():
+    g = _rings([(70_000, 2)])
+    ci = g.col_idx.copy()
+    u = 43_210  # its last neighbour becomes one that does not name it back
+    assert ci[g.row_ptr[u + 1] - 1] == u + 2
+    ci[g.row_ptr[u + 1] - 1] = u + 3
+    note("missing reverse arc")
+    with pytest.raises(S.ScanError) as ei:
+        S.scan_graph_create(g.n, g.nnz, g.row_ptr, ci)
+    assert ei.value.code == S.SCAN_E_GRAPH
