@@ -45,7 +45,7 @@ struct TriRec {
   uint32_t line;  // first line (of v's entry in row u, or a later one)
   uint32_t word;  // bit word of that line
   uint32_t nw;    // lines
-  uint32_t pad;
+  int32_t v;      // the vertex (read by k_tri_few only)
 };
 
 struct TriJob {
@@ -78,6 +78,7 @@ struct TriLayout {
   const int32_t* gid = nullptr;
   int64_t lines = 0, words = 0, recs = 0, steps = 0;
   int64_t jobs = 0, wave_rows = 0;
+  int64_t few_at = 0, few = 0;  // records of the vertices of at most kNarrowRow neighbours, unused ones among them
   int32_t max_row = 0, max_hash_row = 0;
   int32_t* hof = nullptr;     // [n] id -> h
   int32_t* idof = nullptr;    // [n] h -> id

@@ -505,6 +505,7 @@ __device__ __forceinline__ TriRec tri_rec(int32_t u, int32_t v, const uint32_t* 
   r.line = l0 + ((uint32_t)i >> 5);
   r.word = wbase[u] + tri_word(W, (uint32_t)i);
   r.nw = W - ((uint32_t)i >> 5);
+  r.v = v;
   return r;
 }
 
@@ -590,12 +591,15 @@ __global__ __launch_bounds__(256) void k_recs_wave(int32_t h0, int32_t n, const 
     inlen[h] = min(at, rn);
     steps[h] = (int64_t)st;
   }
+  if (G < 64)  // k_tri_few goes through all of them
+    for (uint32_t p = at + lane; p < rn; p += G) out[p] = TriRec{};
   if (missing) *asym = 1;
 }
 
 // Work of every vertex: jobs of the block kernel, or a place in the wave
-// kernel's list; the sum of all words and the longest hash-table row.
-__global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_off, const int32_t* row,
+// kernel's list (from `few` on, none); the sum of all words and the longest
+// hash-table row.
+__global__ void k_job_counts(int32_t n, int32_t few, const int32_t* gid, const int64_t* vtx_off, const int32_t* row,
                              const uint8_t* wcls, const uint32_t* inlen, const int64_t* steps, int64_t* njob,
                              int64_t* nwave, uint32_t part, unsigned long long* total, int32_t* max_hash) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -605,7 +609,8 @@ __global__ void k_job_counts(int32_t n, const int32_t* gid, const int64_t* vtx_o
     int64_t j = 0, w = 0;
     if (h < n && steps[h] > 0) {
       st += (unsigned long long)steps[h];
-      if (wcls[h]) {
+      if (h >= few) {
+      } else if (wcls[h]) {
         w = (inlen[h] + part - 1) / part;
       } else {
         j = (inlen[h] + kTriJob - 1) / kTriJob;
@@ -1033,6 +1038,41 @@ __global__ __launch_bounds__(256) void k_tri_wave(int64_t nrow, const TriWave* _
   __shared__ __align__(16) int32_t sets[4][2 * kTriWaveSlots];
   const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i < nrow) tri_row(wrow[i], sets[threadIdx.x >> 6], rec, cols, lines, bits, cnt);
+}
+
+// Records of vertices of at most kNarrowRow neighbours, one per thread: row u
+// and row v have a line and at most 8 entries each.  In a wave per vertex nearly
+// all lanes were idle or on padding, and one chain of loads was under way: 3.05 ms
+// on a triangulated grid of 9 million vertices (26 million records), now 0.88, at
+// 3.7 TB/s for the 128 bytes a record reads and writes; 0.62 and 0.16 on a
+// road-like grid of 4 million.
+static_assert(kNarrowRow == 8, "two loads of four entries");
+__global__ __launch_bounds__(256) void k_tri_few(int64_t few, const TriRec* __restrict__ rec,
+                                                 const int32_t* __restrict__ row, const uint32_t* __restrict__ oline,
+                                                 const int32_t* __restrict__ oc, uint32_t* __restrict__ bits,
+                                                 int32_t* __restrict__ cnt) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= few) return;
+  const TriRec r = rec[i];
+  if (r.nw == 0) return;
+  const int32_t D = row[r.v];
+  const int64_t base = (int64_t)oline[r.v] * kTriLine;
+  const int4* mine = reinterpret_cast<const int4*>(oc + base);
+  const int4* theirs = reinterpret_cast<const int4*>(oc + (int64_t)r.line * kTriLine);
+  const int4 none = make_int4(0, 0, 0, 0);
+  const int4 a0 = theirs[0], a1 = theirs[1], b0 = D > 0 ? mine[0] : none, b1 = D > 4 ? mine[1] : none;
+  const int32_t b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+  uint32_t w = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (b[j] == 0) continue;  // no entry
+    const uint32_t hit = (a0.x == b[j] ? 1u : 0u) | (a0.y == b[j] ? 2u : 0u) | (a0.z == b[j] ? 4u : 0u) |
+                         (a0.w == b[j] ? 8u : 0u) | (a1.x == b[j] ? 16u : 0u) | (a1.y == b[j] ? 32u : 0u) |
+                         (a1.z == b[j] ? 64u : 0u) | (a1.w == b[j] ? 128u : 0u);
+    if (hit) atomicAdd(cnt + base + j, 1);
+    w |= hit;
+  }
+  bits[r.word] = w;
 }
 
 // Jobs and waves' rows in one launch, spread evenly over it: `ratio` is the
@@ -1572,13 +1612,14 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   unsigned long long* room = nullptr;
   unsigned nchunk = 0;
   unsigned long long* sums = nullptr;
-  int64_t tot[3] = {0, 0, 0};
+  int64_t tot[4] = {0, 0, 0, 0};
   int32_t h_ctl[4] = {0, 0, 0, 0};
   unsigned long long h_sums[2 + kNumBuckets] = {0};
   const unsigned gv = grid_for((int64_t)n + 1, 256);
   const int32_t nbig = groups ? 0 : csr.long_rows;  // (of a batch, waves take the long rows too)
   // vertices from here on have few neighbours, and go eight to a wave
   const int32_t narrow = !groups && n - csr.wide_rows >= kNarrowWorth ? csr.wide_rows : n;
+  int32_t few = n;  // vertices from here on are left to k_tri_few
   int64_t* digits = nullptr;
 #define TTRY(x)                        \
   do {                                 \
@@ -1665,6 +1706,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   TTRY(hipMemcpyAsync(tot + 0, at0 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(tot + 1, at1 + n, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(tot + 2, at2 + n, 8, hipMemcpyDeviceToHost, s));
+  if (narrow < n) TTRY(hipMemcpyAsync(tot + 3, at2 + narrow, 8, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(h_ctl, ctl, 16, hipMemcpyDeviceToHost, s));
   TTRY(hipMemcpyAsync(h_sums, sums, sizeof(h_sums), hipMemcpyDeviceToHost, s));
   TTRY(hipStreamSynchronize(s));
@@ -1672,6 +1714,13 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   T.lines = tot[0];
   T.words = tot[1];
   T.recs = tot[2];
+  // Where most records are those of vertices of few neighbours, k_tri_few takes
+  // them.  (Elsewhere they stay with the waves: taken out of R-MAT scale 22, where
+  // they are few and k_tri_few needs 10 us, the blocks left in k_tri_count went from
+  // 6.9 to 8.1 ms.)
+  few = narrow < n && T.recs - tot[3] >= T.recs / 2 ? narrow : n;
+  T.few_at = few < n ? tot[3] : T.recs;
+  T.few = T.recs - T.few_at;
   // outside the limits (32-bit byte offsets of 16-bit entries and of bits), or not a symmetric CSR
   if (T.max_row > kTriMaxRow || T.lines >= (int64_t)1 << 26 || T.words >= (int64_t)1 << 30 ||
       T.recs >= (int64_t)1 << 32 || (int64_t)h_sums[1 + kNumBuckets] != nnz / 2)
@@ -1719,7 +1768,7 @@ hipError_t tri_build(hipStream_t s, int32_t n, int64_t nnz, const int64_t* h_rp,
   if (n > narrow)
     k_recs_wave<8><<<grid_for(n - narrow, 32), 256, 0, s>>>(narrow, n, d_rp, d_ci, T.hof, T.idof, T.oline, T.wbase,
                                                             T.row, T.oc, at2, wcls, T.rec, inlen, nin, ctl + 3);
-  k_job_counts<<<std::min(gv, 512u), 256, 0, s>>>(n, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, part, sums,
+  k_job_counts<<<std::min(gv, 512u), 256, 0, s>>>(n, few, T.gid, T.vtx_off, T.row, wcls, inlen, nin, nline, nword, part, sums,
                                                 ctl + 2);
   k_tri_buckets<<<grid_for(std::min<int64_t>(T.lines * kTriLine, 1 << 22), 1024), 256, 0, s>>>(T.lines, T.lu, T.oc,
                                                                                                T.deg, sums + 1);
@@ -1777,6 +1826,8 @@ void tri_threshold(hipStream_t s, const TriLayout& T, const TriScratch& S, const
 }
 
 void tri_count(hipStream_t s, const TriLayout& T, const TriScratch& S) {
+  if (T.few > 0)
+    k_tri_few<<<grid_for(T.few, 256), 256, 0, s>>>(T.few, T.rec + T.few_at, T.row, T.oline, T.oc, S.bits, S.cnt);
   if (T.jobs == 0) {
     if (T.wave_rows == 0) return;
     const unsigned grid = (unsigned)count_blocks(T);

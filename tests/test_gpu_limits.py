@@ -7,6 +7,7 @@ import graphgen as gg
 import oracle
 import paper_2311_12281_amd as S
 from gpu_helpers import assert_same, note
+from test_zz_no_alloc import _device_result
 
 pytestmark = pytest.mark.gpu
 
@@ -98,10 +99,11 @@ def _rings(parts, seed=None):
 
 @pytest.mark.parametrize("parts", [
     [(65_535, 4)], [(65_536, 4)], [(65_537, 4), (100, 5)], [(1_001, 40), (65_600, 3)], [(70_001, 1), (33, 2)],
-    [(30_000, 2), (30_000, 4), (6_007, 1), (5_000, 5)]], ids=str)
+    [(30_000, 2), (30_000, 4), (6_007, 1), (5_000, 5)], [(400, 150), (70_001, 4)], [(3_000, 300), (66_001, 2)]], ids=str)
 @pytest.mark.parametrize("seed", [None, 5])
 def test_vertices_of_few_neighbours(parts, seed):
-    """From 65,536 vertices of at most 8 neighbours on, eight of them share a wave while the rows are laid out."""
+    """From 65,536 vertices of at most 8 neighbours on, eight of them share a wave while the rows are laid
+    out, and k_tri_few counts for them unless the others have more records."""
     g = _rings(parts, seed)
     oc = oracle.counts(g, threads=oracle.max_threads())
     note("few neighbours", parts, seed)
@@ -109,6 +111,19 @@ def test_vertices_of_few_neighbours(parts, seed):
         assert np.array_equal(G.similarity(), oc)
         for (p, q), mu in [((1, 2), 3), ((7, 10), 2), ((4, 5), 5)]:
             assert_same(*G.run(p, q, mu), *oracle.cluster(g, oc, p, q, mu), f"{parts} eps={p}/{q}")
+
+
+def test_few_neighbours_served_and_without_allocations():
+    g = _rings([(500, 60), (66_000, 4), (300, 2)], 9)
+    p, q, mu = 3, 5, 4
+    ol, orr = oracle.scan(g, p, q, mu, threads=oracle.max_threads())
+    note("few neighbours, no-alloc and served")
+    with S.Graph.from_csr(g) as G:
+        for _ in range(2):
+            assert_same(*_device_result(G, g.n, G.run_device_noalloc, p, q, mu), ol, orr, "no-alloc")
+    with S.Server(num_slots=2) as srv:
+        gid = srv.add(g)
+        assert_same(*srv.wait(srv.submit(gid, p, q, mu), gid)[:2], ol, orr, "served")
 
 
 def test_a_missing_reverse_arc_among_them():
