@@ -499,14 +499,14 @@ def summarize_pmc(args):
 Commands (from the repository root on the MI355X host, each its own run):
 
 ```
-rocprofv3 --pmc FETCH_SIZE --output-format csv -d gpurun_out/pmc_fetch -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc WRITE_SIZE --output-format csv -d gpurun_out/pmc_write -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_64B_sum TCC_EA0_RDREQ_128B_sum TCC_EA0_RDREQ_sum --output-format csv -d gpurun_out/pmc_rdreq -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc TCC_EA0_RDREQ_DRAM_sum TCC_EA0_RDREQ_sum --output-format csv -d gpurun_out/pmc_dram -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc {' '.join(LDS_COUNTERS)} --output-format csv -d gpurun_out/pmc_lds -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc {' '.join(ATOMIC_COUNTERS)} --output-format csv -d gpurun_out/pmc_atomic -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc {' '.join(HIT_COUNTERS)} --output-format csv -d gpurun_out/pmc_hit -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
-rocprofv3 --pmc {' '.join(CLOCK_COUNTERS)} --output-format csv -d gpurun_out/pmc_clock -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc FETCH_SIZE --output-format csv -d prof/pmc_fetch -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc WRITE_SIZE --output-format csv -d prof/pmc_write -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_64B_sum TCC_EA0_RDREQ_128B_sum TCC_EA0_RDREQ_sum --output-format csv -d prof/pmc_rdreq -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc TCC_EA0_RDREQ_DRAM_sum TCC_EA0_RDREQ_sum --output-format csv -d prof/pmc_dram -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc {' '.join(LDS_COUNTERS)} --output-format csv -d prof/pmc_lds -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc {' '.join(ATOMIC_COUNTERS)} --output-format csv -d prof/pmc_atomic -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc {' '.join(HIT_COUNTERS)} --output-format csv -d prof/pmc_hit -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
+rocprofv3 --pmc {' '.join(CLOCK_COUNTERS)} --output-format csv -d prof/pmc_clock -o bench -- python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-verify --no-eps10
 {cmd}
 ```
 
